@@ -183,7 +183,7 @@ int run_batch(rbffd_ctx ctx, const std::vector<rbw::Job>& jobs, const std::vecto
         if (items[b].empty()) continue;
         const int nitems = (int)items[b].size();
         const int grid = std::max(1, std::min(nitems, tuning[b].groups_per_cu * cus));
-        rc = weights_launch_batched(ctx, kernel, b == 0 ? 1 : 2, djobs, ditems[b], nitems, cursors + 32 * b, grid);
+        rc = weights_launch_batched(ctx, kernel, b == 0 ? 64 : 128, djobs, ditems[b], nitems, cursors + 32 * b, grid);
         if (rc) return rc;
     }
     if (t1) HIP_TRY(ctx, hipEventRecord(t1, ctx->stream));

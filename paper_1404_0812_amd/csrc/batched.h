@@ -12,11 +12,11 @@ struct WorkItem {
 };
 
 namespace rbw {
-// Kernel launchers, one specialisation per (radial kernel K, tiling NB),
+// Kernel launchers, one specialisation per (radial kernel K, tiling MM),
 // each defined in its own build of weights_kernels.hip.
-template <int K, int NB>
+template <int K, int MM>
 void launch_weights(hipStream_t st, const Job& J);
-template <int K, int NB>
+template <int K, int MM>
 void launch_weights_batched(hipStream_t st, const Job* jobs, const WorkItem* items, int nitems, int* cursor,
                             int grid);
 }  // namespace rbw
@@ -24,6 +24,6 @@ void launch_weights_batched(hipStream_t st, const Job* jobs, const WorkItem* ite
 // Validates opts for a set of N nodes and fills o (returns an RBFFD_E_* code).
 int weights_check_opts(rbffd_ctx ctx, int64_t N, const rbffd_weight_opts* opts, rbw::WOpts& o);
 // Persistent launch over `nitems` items (device arrays) with `grid` workgroups
-// of four wavefronts; nb = 1 for m <= 64, 2 for m <= 128.  *cursor must be 0.
-int weights_launch_batched(rbffd_ctx ctx, int kernel, int nb, const rbw::Job* jobs, const WorkItem* items,
+// of four wavefronts; mm = 64 for m <= 64, 128 for m <= 128.  *cursor must be 0.
+int weights_launch_batched(rbffd_ctx ctx, int kernel, int mm, const rbw::Job* jobs, const WorkItem* items,
                            int nitems, int* cursor, int grid);

@@ -13,14 +13,14 @@
 // Bisection on eps toward kappa_target, or a given/learned eps checked
 // against a kappa band.
 //
-// How, on gfx950: the m x m matrix lives in registers.  NB = 1 (m <= 64): one
-// wavefront per stencil, lane i holding column i.  NB = 2 (m <= 128): four
+// How, on gfx950: the m x m matrix lives in registers.  m <= 64: one
+// wavefront per stencil, lane i holding column i.  m <= 128: four
 // wavefronts per stencil, wave (rb, cb) holding rows 64 rb .. 64 rb + 63 of
 // columns 64 cb + lane.  A~ is reduced to tridiagonal form T = Q^T A~ Q by
-// Householder reflections; the pivot column of each step is published to LDS
-// during the previous step's rank-2 update (row k+1, by symmetry), so no
-// register is indexed dynamically, and each reflector is kept in the
-// registers of the row it annihilated.  kappa_2 comes from Sturm counts of T
+// Householder reflections; the pivot column of each step is row k+1 after the
+// previous step's rank-2 update (by symmetry), no register is indexed
+// dynamically, and each reflector is kept in the registers of the row it
+// annihilated.  kappa_2 comes from Sturm counts of T
 // evaluated at 32 shifts per wave at once (multisection); the solves use
 // A~^{-1} = Q T^{-1} Q^T with a pivoted tridiagonal factorisation and one step
 // of iterative refinement (the residual re-evaluated from the nodes).  All
@@ -77,18 +77,18 @@ int check_opts(rbffd_ctx ctx, int64_t N, const rbffd_weight_opts* opts, WOpts& o
     return RBFFD_OK;
 }
 
-template <int NB>
+template <int MM>
 void launch_plain(hipStream_t st, const Job& J) {
     switch (J.o.kernel) {
-        case RBFFD_KERNEL_MQ: launch_weights<RBFFD_KERNEL_MQ, NB>(st, J); break;
-        case RBFFD_KERNEL_IMQ: launch_weights<RBFFD_KERNEL_IMQ, NB>(st, J); break;
-        default: launch_weights<RBFFD_KERNEL_GA, NB>(st, J); break;
+        case RBFFD_KERNEL_MQ: launch_weights<RBFFD_KERNEL_MQ, MM>(st, J); break;
+        case RBFFD_KERNEL_IMQ: launch_weights<RBFFD_KERNEL_IMQ, MM>(st, J); break;
+        default: launch_weights<RBFFD_KERNEL_GA, MM>(st, J); break;
     }
 }
 
 int dispatch(rbffd_ctx ctx, const Job& J) {
-    if (J.o.n + border_cols(J.o.degree) <= 64) launch_plain<1>(ctx->stream, J);
-    else launch_plain<2>(ctx->stream, J);
+    if (J.o.n + border_cols(J.o.degree) <= 64) launch_plain<64>(ctx->stream, J);
+    else launch_plain<128>(ctx->stream, J);
     HIP_TRY(ctx, hipGetLastError());
     return RBFFD_OK;
 }
@@ -101,22 +101,22 @@ int weights_check_opts(rbffd_ctx ctx, int64_t N, const rbffd_weight_opts* opts, 
 
 namespace {
 
-template <int NB>
-void launch_batched_nb(hipStream_t st, int kernel, const Job* jobs, const WorkItem* items, int nitems, int* cursor,
+template <int MM>
+void launch_batched_mm(hipStream_t st, int kernel, const Job* jobs, const WorkItem* items, int nitems, int* cursor,
                        int grid) {
     switch (kernel) {
-        case RBFFD_KERNEL_MQ: launch_weights_batched<RBFFD_KERNEL_MQ, NB>(st, jobs, items, nitems, cursor, grid); break;
-        case RBFFD_KERNEL_IMQ: launch_weights_batched<RBFFD_KERNEL_IMQ, NB>(st, jobs, items, nitems, cursor, grid); break;
-        default: launch_weights_batched<RBFFD_KERNEL_GA, NB>(st, jobs, items, nitems, cursor, grid); break;
+        case RBFFD_KERNEL_MQ: launch_weights_batched<RBFFD_KERNEL_MQ, MM>(st, jobs, items, nitems, cursor, grid); break;
+        case RBFFD_KERNEL_IMQ: launch_weights_batched<RBFFD_KERNEL_IMQ, MM>(st, jobs, items, nitems, cursor, grid); break;
+        default: launch_weights_batched<RBFFD_KERNEL_GA, MM>(st, jobs, items, nitems, cursor, grid); break;
     }
 }
 
 }  // namespace
 
-int weights_launch_batched(rbffd_ctx ctx, int kernel, int nb, const Job* jobs, const WorkItem* items, int nitems,
+int weights_launch_batched(rbffd_ctx ctx, int kernel, int mm, const Job* jobs, const WorkItem* items, int nitems,
                            int* cursor, int grid) {
-    if (nb == 1) launch_batched_nb<1>(ctx->stream, kernel, jobs, items, nitems, cursor, grid);
-    else launch_batched_nb<2>(ctx->stream, kernel, jobs, items, nitems, cursor, grid);
+    if (mm == 64) launch_batched_mm<64>(ctx->stream, kernel, jobs, items, nitems, cursor, grid);
+    else launch_batched_mm<128>(ctx->stream, kernel, jobs, items, nitems, cursor, grid);
     HIP_TRY(ctx, hipGetLastError());
     return RBFFD_OK;
 }

@@ -5,16 +5,20 @@
 #include "weights_job.h"
 
 #include <cmath>
+#include <type_traits>
 
 namespace rbw {
 
 constexpr int RMAX = RBW_RMAX;  // border columns (degree-2 monomials in R^3)
-// Rows per guarded chunk in the tridiagonalisation loops (one wave / four
-// waves per stencil): a chunk is skipped once all its rows are reduced, and a
-// longer chunk lets its LDS reads be issued together (measured: 8 and 16 are
-// 6-11% faster than 4; a single chunk of 64 is 40% slower).
-template <int NB>
-constexpr int chunk_rows() { return NB == 1 ? 8 : 16; }
+
+// Tilings, named by the largest m they hold: 64 (one wavefront per stencil,
+// lane = column) and 128 (four wavefronts, wave (rb, cb) holding rows
+// 64 rb .. 64 rb + 63 of columns 64 cb + lane).
+template <int MM>
+struct Lay {
+    static constexpr int NB = MM == 128 ? 2 : 1;  // row and column blocks
+    static constexpr int R = 64;                  // matrix rows held by a thread
+};
 
 // ------------------------------------------------------------ reductions ----
 // Wavefront reductions with DPP (within rows of 16 lanes) and the row swaps
@@ -62,6 +66,16 @@ __device__ __forceinline__ double rows_total(double v) {
     return a + b;
 }
 __device__ __forceinline__ double wave_sum(double v) { return rows_total(row_sum16(v)); }
+// Sum of the products x y: the first step pairs one lane's rounded product
+// with the other lane's through an FMA, so the two lanes of a pair differ in
+// the last bit and only one lane's total (lane 0, or the caller's own) counts.
+__device__ __forceinline__ double wave_dot(double x, double y) {
+    double v = fma(x, y, dpp64<0xB1>(x * y));
+    v += dpp64<0x4E>(v);
+    v += dpp64<0x141>(v);
+    v += dpp64<0x140>(v);
+    return rows_total(v);
+}
 // The same swaps with two different operands x (vdst) and y (vsrc):
 // permlane32_swap leaves x = [x lanes 0-31, y lanes 0-31] and
 // y = [x lanes 32-63, y lanes 32-63], so their sum folds x into lanes 0-31
@@ -163,26 +177,40 @@ __device__ __forceinline__ double rbf_psi(double e2, double r2) {
     return -2.0 * e2 * exp(-e);
 }
 
-// LDS of one stencil
-template <int NB>
+// LDS of one stencil.  The arrays of the eigenvalue search and those of the
+// solves are never live together and share their space.
+template <int MM>
 struct Shared {
-    static constexpr int MM = 64 * NB;
+    static constexpr bool ONE = MM <= 64;
     double x[MM], y[MM], z[MM];  // stencil node coordinates
     double U[MM * RMAX];         // border basis values U[j*RMAX + k]
     double T[RMAX * RMAX];       // monomial coefficients of the border basis T[l*RMAX + k]
-    double col[MM], vv[MM], ww[MM], vb[MM];
-    double pp[NB][MM];           // matvec partial sums per row block
     double red[16];              // cross-wave partial sums, two sets of 8
-    double d[MM], e[MM], e2[MM], tau[MM];
+    double d[MM], e[MM], tau[MM];
+    double2 de[MM];              // (d_i, e_{i-1}^2): one 16-byte read per Sturm step
+    double col[MM], ww[MM];      // next pivot column
+    double vr[ONE ? 1 : 4][64], wr[ONE ? 1 : 4][64];  // v and w of a wave's row block
+    double vb[ONE ? 1 : MM];
+    double pp[ONE ? 1 : 2][MM];  // matvec partial sums per row block
     double fd[MM], fdu[MM], fdl[MM], ffact[MM];  // pivoted tridiagonal factors (fd: 1/pivot)
     int fswap[MM];
     double rhs[3][MM];
-    double zb[3][MM];
+    double zb[MM];
     double hx[MM], hy[MM], hz[MM];
-    double G[NB == 1 ? 96 : 1];  // Gram entries of the reflectors in blocks of four (one wave)
+    double G[ONE ? 96 : 1];  // Gram entries of the reflectors in blocks of four (one wave)
     double nrm0[3];
     int m, r, n, fact_ok;
 };
+
+// m and n as scalars (the same for the whole stencil, so for the wavefront).
+template <int MM>
+__device__ __forceinline__ int stencil_m(const Shared<MM>& S) {
+    return __builtin_amdgcn_readfirstlane(S.m);
+}
+template <int MM>
+__device__ __forceinline__ int stencil_n(const Shared<MM>& S) {
+    return __builtin_amdgcn_readfirstlane(S.n);
+}
 
 // Position of a thread in the stencil's work group.
 struct Tid {
@@ -190,75 +218,79 @@ struct Tid {
     int rb;    // row block (rows 64 rb + jj held in registers)
     int cb;    // column block
     int c;     // column index 64 cb + lane
-    int tid;   // 0 .. 64 NB^2 - 1 within the stencil's threads
+    int tid;   // 0 .. 63 (255 with four waves) within the stencil's threads
+    int l15;   // lane within its row of 16
     mutable int rot = 0;  // reductions done so far (selects the slot set)
 };
 
-template <int NB>
+// One wavefront: order LDS accesses and keep the compiler from moving them.
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+template <int MM>
 __device__ __forceinline__ void bsync() {
-    if constexpr (NB == 1) {
-        // one wavefront: order LDS accesses and keep the compiler from moving them
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if constexpr (MM <= 64) {
+        wave_order();
     } else {
         __syncthreads();
     }
 }
 
-// Cross-wave partial sums (NB = 2) go through one of two slot sets, taken in
+// Cross-wave partial sums (four waves) go through one of two slot sets, taken in
 // turn by successive reductions; every reduction has one barrier between its
 // writes and its reads, so by the time a set is written again every thread
 // has read it, and no second barrier is needed.
 __device__ __forceinline__ double* red_set(double* red, const Tid& t) { return red + 8 * (t.rot++ & 1); }
 
-// Sum over the columns (lane-distributed; each column is held by NB threads).
-template <int NB>
-__device__ __forceinline__ double sum_cols(double v, Shared<NB>& S, const Tid& t) {
+// Sum over the columns (lane-distributed; each column is held by Lay::NB threads).
+template <int MM>
+__device__ __forceinline__ double sum_cols(double v, Shared<MM>& S, const Tid& t) {
     const double w = wave_sum(v);
-    if constexpr (NB == 1) {
+    if constexpr (MM <= 64) {
         return w;
     } else {
         double* red = red_set(S.red, t);
         if (t.rb == 0 && t.lane == 0) red[t.cb] = w;
-        bsync<NB>();
+        bsync<MM>();
         return red[0] + red[1];
     }
 }
-template <int NB>
-__device__ __forceinline__ void sum_cols3(double& a, double& b, double& c, Shared<NB>& S, const Tid& t) {
+template <int MM>
+__device__ __forceinline__ void sum_cols3(double& a, double& b, double& c, Shared<MM>& S, const Tid& t) {
     wave_sum3(a, b, c);
-    if constexpr (NB == 2) {
+    if constexpr (MM == 128) {
         double* red = red_set(S.red, t);
         if (t.rb == 0 && t.lane == 0) {
             red[t.cb] = a;
             red[2 + t.cb] = b;
             red[4 + t.cb] = c;
         }
-        bsync<NB>();
+        bsync<MM>();
         a = red[0] + red[1];
         b = red[2] + red[3];
         c = red[4] + red[5];
     }
 }
 // Sum over the rows held by lanes (row 64 rb + lane; cb == 0 waves count).
-template <int NB>
-__device__ __forceinline__ double sum_rows(double v, Shared<NB>& S, const Tid& t) {
+template <int MM>
+__device__ __forceinline__ double sum_rows(double v, Shared<MM>& S, const Tid& t) {
     const double w = wave_sum(v);
-    if constexpr (NB == 1) {
+    if constexpr (MM <= 64) {
         return w;
     } else {
         double* red = red_set(S.red, t);
         if (t.cb == 0 && t.lane == 0) red[6 + t.rb] = w;
-        bsync<NB>();
+        bsync<MM>();
         return red[6] + red[7];
     }
 }
 // Four sums over the rows held by lanes at once (see sum_rows).
-template <int NB>
-__device__ __forceinline__ void sum_rows4(double& a, double& b, double& c, double& d, Shared<NB>& S, const Tid& t) {
+template <int MM>
+__device__ __forceinline__ void sum_rows4(double& a, double& b, double& c, double& d, Shared<MM>& S, const Tid& t) {
     wave_sum4(a, b, c, d);
-    if constexpr (NB == 2) {
+    if constexpr (MM == 128) {
         double* red = red_set(S.red, t);
         if (t.cb == 0 && t.lane == 0) {
             red[4 * t.rb] = a;
@@ -266,31 +298,31 @@ __device__ __forceinline__ void sum_rows4(double& a, double& b, double& c, doubl
             red[4 * t.rb + 2] = c;
             red[4 * t.rb + 3] = d;
         }
-        bsync<NB>();
+        bsync<MM>();
         a = red[0] + red[4];
         b = red[1] + red[5];
         c = red[2] + red[6];
         d = red[3] + red[7];
     }
 }
-template <int NB>
-__device__ __forceinline__ double max_cols(double v, Shared<NB>& S, const Tid& t) {
+template <int MM>
+__device__ __forceinline__ double max_cols(double v, Shared<MM>& S, const Tid& t) {
     const double w = wave_max(v);
-    if constexpr (NB == 1) {
+    if constexpr (MM <= 64) {
         return w;
     } else {
         double* red = red_set(S.red, t);
         if (t.rb == 0 && t.lane == 0) red[t.cb] = w;
-        bsync<NB>();
+        bsync<MM>();
         return fmax(red[0], red[1]);
     }
 }
 
 // ----------------------------------------------------------- local matrix ----
 // Column t.c, rows 64 rb .. 64 rb + 63 of A~(eps).
-template <int K, int NB>
-__device__ __forceinline__ void build_matrix(double (&a)[64], const Shared<NB>& S, const Tid& t, double e2) {
-    const int n = S.n, m = S.m, c = t.c;
+template <int K, int MM>
+__device__ __forceinline__ void build_matrix(double (&a)[Lay<MM>::R], const Shared<MM>& S, const Tid& t, double e2) {
+    const int n = stencil_n<MM>(S), m = stencil_m<MM>(S), c = t.c;
     const int cc = c < n ? c : 0;
     const double xi = S.x[cc], yi = S.y[cc], zi = S.z[cc];
     const int r0 = 64 * t.rb;
@@ -313,106 +345,271 @@ __device__ __forceinline__ void build_matrix(double (&a)[64], const Shared<NB>& 
     }
 }
 
+// Row broadcasts.  v holds 16 consecutive entries of a vector, the same 16 in
+// each of the wavefront's four rows of lanes (lane l: entry l % 16), and
+// entry O + i multiplies the registers of matrix row i through the DPP row
+// broadcast of v_fmac_f64 -- no LDS read and no extra instruction per row.
+// s_nop: two wait states between a vector write of v and its DPP read (the
+// compiler does not look for that hazard inside an asm block).  Reading v and
+// w per row from LDS instead (a broadcast read of two rows at a time) kept the
+// LDS busy 44% and the waves waiting 47% of the time; bisection of 250k
+// 50-node stencils went from 48% to 65% VALU issue, the learned pass over
+// them from 28.9 to 24.0 ms, 16 surfaces of 31 to 101 nodes from 189 to
+// 133 ms (28 to 12.6 ms in the one-wave tiling, 157 to 117 in the four-wave).
+//   dot8:  p0 += sum over even i of v_i a_i, p1 over odd i, in row order
+//   rank2: a_i = fma(-v_i, wi, fma(-w_i, vi, a_i)) with nv = -vi, nw = -wi
+#define RBW_BC(i) " row_newbcast:%" #i " row_mask:0xf bank_mask:0xf\n\t"
+template <int O>
+__device__ __forceinline__ void dot8(double& p0, double& p1, double v, double a0, double a1, double a2, double a3,
+                                     double a4, double a5, double a6, double a7) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %2, %3" RBW_BC(11) "v_fmac_f64_dpp %1, %2, %4" RBW_BC(12)
+        "v_fmac_f64_dpp %0, %2, %5" RBW_BC(13) "v_fmac_f64_dpp %1, %2, %6" RBW_BC(14)
+        "v_fmac_f64_dpp %0, %2, %7" RBW_BC(15) "v_fmac_f64_dpp %1, %2, %8" RBW_BC(16)
+        "v_fmac_f64_dpp %0, %2, %9" RBW_BC(17) "v_fmac_f64_dpp %1, %2, %10" RBW_BC(18)
+        : "+&v"(p0), "+&v"(p1)
+        : "v"(v), "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(a4), "v"(a5), "v"(a6), "v"(a7), "n"(O), "n"(O + 1),
+          "n"(O + 2), "n"(O + 3), "n"(O + 4), "n"(O + 5), "n"(O + 6), "n"(O + 7));
+}
+template <int O>
+__device__ __forceinline__ void rank2(double v, double w, double nv, double nw, double& a0, double& a1, double& a2,
+                                      double& a3, double& a4, double& a5, double& a6, double& a7) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %9, %10" RBW_BC(12) "v_fmac_f64_dpp %1, %9, %10" RBW_BC(13)
+        "v_fmac_f64_dpp %2, %9, %10" RBW_BC(14) "v_fmac_f64_dpp %3, %9, %10" RBW_BC(15)
+        "v_fmac_f64_dpp %4, %9, %10" RBW_BC(16) "v_fmac_f64_dpp %5, %9, %10" RBW_BC(17)
+        "v_fmac_f64_dpp %6, %9, %10" RBW_BC(18) "v_fmac_f64_dpp %7, %9, %10" RBW_BC(19)
+        "v_fmac_f64_dpp %0, %8, %11" RBW_BC(12) "v_fmac_f64_dpp %1, %8, %11" RBW_BC(13)
+        "v_fmac_f64_dpp %2, %8, %11" RBW_BC(14) "v_fmac_f64_dpp %3, %8, %11" RBW_BC(15)
+        "v_fmac_f64_dpp %4, %8, %11" RBW_BC(16) "v_fmac_f64_dpp %5, %8, %11" RBW_BC(17)
+        "v_fmac_f64_dpp %6, %8, %11" RBW_BC(18) "v_fmac_f64_dpp %7, %8, %11" RBW_BC(19)
+        : "+&v"(a0), "+&v"(a1), "+&v"(a2), "+&v"(a3), "+&v"(a4), "+&v"(a5), "+&v"(a6), "+&v"(a7)
+        : "v"(v), "v"(w), "v"(nv), "v"(nw), "n"(O), "n"(O + 1), "n"(O + 2), "n"(O + 3), "n"(O + 4), "n"(O + 5),
+          "n"(O + 6), "n"(O + 7));
+}
+#undef RBW_BC
+// Rows 8 j .. 8 j + 7 (j a constant after unrolling); v, w: the 16-entry groups.
+template <int R>
+__device__ __forceinline__ void dot_rows(const double (&a)[R], int j, const double* v, double& p0, double& p1) {
+    if (j & 1)
+        dot8<8>(p0, p1, v[j >> 1], a[8 * j], a[8 * j + 1], a[8 * j + 2], a[8 * j + 3], a[8 * j + 4], a[8 * j + 5],
+                a[8 * j + 6], a[8 * j + 7]);
+    else
+        dot8<0>(p0, p1, v[j >> 1], a[8 * j], a[8 * j + 1], a[8 * j + 2], a[8 * j + 3], a[8 * j + 4], a[8 * j + 5],
+                a[8 * j + 6], a[8 * j + 7]);
+}
+template <int R>
+__device__ __forceinline__ void rank2_rows(double (&a)[R], int j, const double* v, const double* w, double nv,
+                                           double nw) {
+    if (j & 1)
+        rank2<8>(v[j >> 1], w[j >> 1], nv, nw, a[8 * j], a[8 * j + 1], a[8 * j + 2], a[8 * j + 3], a[8 * j + 4],
+                 a[8 * j + 5], a[8 * j + 6], a[8 * j + 7]);
+    else
+        rank2<0>(v[j >> 1], w[j >> 1], nv, nw, a[8 * j], a[8 * j + 1], a[8 * j + 2], a[8 * j + 3], a[8 * j + 4],
+                 a[8 * j + 5], a[8 * j + 6], a[8 * j + 7]);
+}
+
+// f(i) for the one constant i in [LO, HI) that equals the wave-uniform k: a
+// binary tree of scalar branches.
+template <int LO, int HI, typename F>
+__device__ __forceinline__ void at_row(int k, F&& f) {
+    if constexpr (HI - LO == 1) {
+        f(std::integral_constant<int, LO>{});
+        // keeps the branches apart: merged, they would index the array dynamically
+        asm volatile("; row %0" ::"n"(LO));
+    } else {
+        constexpr int MID = (LO + HI) / 2;
+        if (k < MID) at_row<LO, MID>(k, f);
+        else at_row<MID, HI>(k, f);
+    }
+}
+
+// Scalars of one reflector H = I - tau v v^T that maps the pivot column's
+// tail (squared norm xnorm2 below alpha) to beta e_1; v = (1, scal * tail).
+struct Reflector {
+    double tau, beta, scal;
+};
+__device__ __forceinline__ Reflector reflector(double alpha, double xnorm2) {
+    Reflector h{0.0, alpha, 0.0};
+    if (xnorm2 > 0.0) {
+        h.beta = -copysign(sqrt(alpha * alpha + xnorm2), alpha);
+        // reciprocals instead of divisions: an ulp or so in tau and in the
+        // scale of v, a perturbation of each reflector's orthogonality of
+        // the size its own rounding already leaves
+        h.tau = (h.beta - alpha) * recip(h.beta);
+        h.scal = recip(alpha - h.beta);
+    }
+    return h;
+}
+
 // Householder tridiagonalisation of the m x m leading block (lane = column).
-// On return: S.d[0..m-1], S.e[0..m-2] (and e^2), S.tau[0..m-3], and row k of
+// On return: S.d[0..m-1], S.e[0..m-2], S.de, S.tau[0..m-3], and row k of
 // the register matrix holds the reflector v_k (v_k[k+1] = 1).
-template <int NB>
-__device__ __forceinline__ void tridiagonalise(double (&a)[64], Shared<NB>& S, const Tid& t) {
-    constexpr int CH = chunk_rows<NB>();
-    const int m = S.m, c = t.c, r0 = 64 * t.rb;
-    if (t.rb == 0) S.col[c] = a[0];
-    bsync<NB>();
-    for (int k = 0; k < m - 2; ++k) {
-        const double xi = S.col[c];
-        const double alpha = S.col[k + 1];
-        const double dk = S.col[k];
-        const bool tail = c > k + 1 && c < m;
-        const double xnorm2 = sum_cols<NB>(tail ? xi * xi : 0.0, S, t);
-        double tau = 0.0, beta = alpha, scal = 0.0;
-        if (xnorm2 > 0.0) {
-            beta = -copysign(sqrt(alpha * alpha + xnorm2), alpha);
-            // reciprocals instead of divisions: an ulp or so in tau and in the
-            // scale of v, a perturbation of each reflector's orthogonality of
-            // the size its own rounding already leaves
-            tau = (beta - alpha) * recip(beta);
-            scal = recip(alpha - beta);
-        }
-        const double vi = (c == k + 1) ? 1.0 : (tail ? xi * scal : 0.0);
+//
+// One wave: steps k = 8 B .. 8 B + 7 run the code of block B, which holds only
+// the rows from 8 B on.  xi: the pivot column (row k of the symmetric matrix).
+template <int MM, int B>
+__device__ __forceinline__ void tridiag_block(double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t, int m, int cl,
+                                              double& xi) {
+    constexpr int R = Lay<MM>::R;
+    const int c = t.c;
+    const int kend = m - 2 < 8 * B + 8 ? m - 2 : 8 * B + 8;
+#pragma unroll 1
+    for (int k = 8 * B; k < kend; ++k) {
+        const double alpha = S.col[k + 1], dk = S.col[k];
+        const bool tail = cl > k + 1;
+        const double xnorm2 = wave_sum(tail ? xi * xi : 0.0);
+        const Reflector h = reflector(alpha, xnorm2);
+        const double vi = (c == k + 1) ? 1.0 : (tail ? xi * h.scal : 0.0);
+        S.vr[0][c] = vi;
         if (t.tid == 0) {
             S.d[k] = dk;
-            S.e[k] = beta;
-            S.e2[k] = beta * beta;
-            S.tau[k] = tau;
+            S.e[k] = h.beta;
+            S.de[k].x = dk;
+            S.de[k + 1].y = h.beta * h.beta;
+            S.tau[k] = h.tau;
         }
-        if (t.rb == 0) S.vv[c] = vi;
-        bsync<NB>();
-        // p = A v over this thread's rows (rows <= k hold zero weight in v)
+        bsync<MM>();
+        double v[R / 16], w[R / 16];
+#pragma unroll
+        for (int g = 0; g < R / 16; ++g) v[g] = g >= B / 2 ? S.vr[0][16 * g + t.l15] : 0.0;
+        // p = A v (entries of v up to row k are zero)
         double p0 = 0.0, p1 = 0.0;
 #pragma unroll
-        for (int j0 = 0; j0 < 64; j0 += CH) {
-            if (r0 + j0 + CH > k + 1 && r0 + j0 < m) {
+        for (int j = 0; j < R / 8; ++j)
+            if (j >= B && (j <= B + 1 || 8 * j < m)) dot_rows<R>(a, j, v, p0, p1);
+        double wi = cl > k ? h.tau * (p0 + p1) : 0.0;
+        const double s = wave_dot(wi, vi);
+        wi = fma(-0.5 * h.tau * s, vi, wi);
+        S.wr[0][c] = wi;
+        bsync<MM>();
 #pragma unroll
-                for (int q = 0; q < CH; q += 2) {
-                    p0 = fma(a[j0 + q], S.vv[r0 + j0 + q], p0);
-                    p1 = fma(a[j0 + q + 1], S.vv[r0 + j0 + q + 1], p1);
-                }
-            }
-        }
-        double p = p0 + p1;
-        if constexpr (NB == 2) {
-            S.pp[t.rb][c] = p;
-            bsync<NB>();
-            p = S.pp[0][c] + S.pp[1][c];
-        }
-        double wi = (c > k && c < m) ? tau * p : 0.0;
-        const double s = sum_cols<NB>(wi * vi, S, t);
-        wi = fma(-0.5 * tau * s, vi, wi);
-        if (t.rb == 0) S.ww[c] = wi;
-        bsync<NB>();
-        // A -= v w^T + w v^T; store v in row k; publish row k+1 as the next pivot column
+        for (int g = 0; g < R / 16; ++g) w[g] = g >= B / 2 ? S.wr[0][16 * g + t.l15] : 0.0;
+        // A -= v w^T + w v^T
+        const double nv = -vi, nw = -wi;
 #pragma unroll
-        for (int j0 = 0; j0 < 64; j0 += CH) {
-            if (r0 + j0 + CH > k + 1 && r0 + j0 < m) {
-#pragma unroll
-                for (int q = 0; q < CH; ++q)
-                    a[j0 + q] = fma(-S.vv[r0 + j0 + q], wi, fma(-S.ww[r0 + j0 + q], vi, a[j0 + q]));
-            }
-            if (r0 + j0 <= k + 1 && k < r0 + j0 + CH) {  // this chunk holds row k or row k + 1
-#pragma unroll
-                for (int q = 0; q < CH; ++q) {
-                    if (r0 + j0 + q == k) a[j0 + q] = vi;
-                    if (r0 + j0 + q == k + 1) S.col[c] = a[j0 + q];
-                }
-            }
-        }
-        bsync<NB>();
+        for (int j = 0; j < R / 8; ++j)
+            if (j >= B && (j <= B + 1 || 8 * j < m)) rank2_rows<R>(a, j, v, w, nv, nw);
+        // row k keeps v, row k + 1 is the next pivot column
+        at_row<0, 8>(k - 8 * B, [&](auto q) __attribute__((always_inline)) {
+            constexpr int row = 8 * B + decltype(q)::value;
+            a[row] = vi;
+            if constexpr (row + 1 < R) xi = a[row + 1];
+        });
+        S.col[c] = xi;
+        bsync<MM>();
     }
-    // trailing 2 x 2 block
+    if constexpr (B + 1 < R / 8) tridiag_block<MM, B + 1>(a, S, t, m, cl, xi);
+}
+
+template <int MM>
+__device__ __forceinline__ void tridiag_one(double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t, int m) {
+    double xi = a[0];
+    S.col[t.c] = xi;
+    bsync<MM>();
+    tridiag_block<MM, 0>(a, S, t, m, t.c < m ? t.c : -1, xi);
+    // trailing 2 x 2 block: row m - 1
+    at_row<0, Lay<MM>::R>(m - 1, [&](auto q) __attribute__((always_inline)) {
+        S.ww[t.c] = a[decltype(q)::value];
+    });
+}
+
+// Four waves.  Every wave forms the reflector and both halves of p and w
+// itself (the sums over a column block are the same bits wherever they are
+// formed), so a step needs two barriers: after the row-block partial sums of
+// p and after the next pivot column.
+template <int MM>
+__device__ __forceinline__ void tridiag_four(double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t, int m) {
+    constexpr int R = Lay<MM>::R;
+    const int c = t.c, o = c ^ 64, r0 = 64 * t.rb, wv = 2 * t.rb + t.cb;
+    const bool own = t.rb == t.cb;  // this wave's rows are its columns' block
+    const int cl = c < m ? c : -1, ol = o < m ? o : -1;
+    if (t.rb == 0) S.col[c] = a[0];
+    bsync<MM>();
+#pragma unroll 1
+    for (int k = 0; k < m - 2; ++k) {
+        const double xc = S.col[c], xo = S.col[o];
+        const double alpha = S.col[k + 1], dk = S.col[k];
+        const bool tc = cl > k + 1, to = ol > k + 1;
+        const double xnorm2 = wave_sum(tc ? xc * xc : 0.0) + wave_sum(to ? xo * xo : 0.0);
+        const Reflector h = reflector(alpha, xnorm2);
+        const double vc = (c == k + 1) ? 1.0 : (tc ? xc * h.scal : 0.0);
+        const double vo = (o == k + 1) ? 1.0 : (to ? xo * h.scal : 0.0);
+        S.vr[wv][t.lane] = own ? vc : vo;
+        if (t.tid == 0) {
+            S.d[k] = dk;
+            S.e[k] = h.beta;
+            S.de[k].x = dk;
+            S.de[k + 1].y = h.beta * h.beta;
+            S.tau[k] = h.tau;
+        }
+        wave_order();
+        double v[R / 16], w[R / 16];
 #pragma unroll
-    for (int jj = 0; jj < 64; ++jj)
-        if (r0 + jj == m - 1) S.ww[c] = a[jj];
-    bsync<NB>();
+        for (int g = 0; g < R / 16; ++g) v[g] = S.vr[wv][16 * g + t.l15];
+        double p0 = 0.0, p1 = 0.0;
+#pragma unroll
+        for (int j = 0; j < R / 8; ++j)
+            if (r0 + 8 * j + 8 > k + 1 && r0 + 8 * j < m) dot_rows<R>(a, j, v, p0, p1);
+        S.pp[t.rb][c] = p0 + p1;
+        bsync<MM>();
+        const double pc = S.pp[0][c] + S.pp[1][c], po = S.pp[0][o] + S.pp[1][o];
+        double wc = cl > k ? h.tau * pc : 0.0, wo = ol > k ? h.tau * po : 0.0;
+        const double s = readlane64(wave_dot(wc, vc), 0) + readlane64(wave_dot(wo, vo), 0);
+        wc = fma(-0.5 * h.tau * s, vc, wc);
+        wo = fma(-0.5 * h.tau * s, vo, wo);
+        S.wr[wv][t.lane] = own ? wc : wo;
+        wave_order();
+#pragma unroll
+        for (int g = 0; g < R / 16; ++g) w[g] = S.wr[wv][16 * g + t.l15];
+        const double nv = -vc, nw = -wc;
+#pragma unroll
+        for (int j = 0; j < R / 8; ++j)
+            if (r0 + 8 * j + 8 > k + 1 && r0 + 8 * j < m) rank2_rows<R>(a, j, v, w, nv, nw);
+        if (t.rb == k >> 6)
+            at_row<0, R>(k & 63, [&](auto q) __attribute__((always_inline)) {
+                    a[decltype(q)::value] = vc;
+            });
+        if (t.rb == (k + 1) >> 6)
+            at_row<0, R>((k + 1) & 63, [&](auto q) __attribute__((always_inline)) {
+                    S.col[c] = a[decltype(q)::value];
+            });
+        bsync<MM>();
+    }
+    if (t.rb == (m - 1) >> 6)
+        at_row<0, R>((m - 1) & 63, [&](auto q) __attribute__((always_inline)) {
+            S.ww[c] = a[decltype(q)::value];
+        });
+}
+
+template <int MM>
+__device__ __forceinline__ void tridiagonalise(double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t, int m) {
+    if constexpr (MM <= 64) tridiag_one<MM>(a, S, t, m);
+    else tridiag_four<MM>(a, S, t, m);
+    bsync<MM>();
     if (t.tid == 0) {
         if (m >= 2) {
-            S.d[m - 2] = S.col[m - 2];
+            S.d[m - 2] = S.de[m - 2].x = S.col[m - 2];
             S.e[m - 2] = S.col[m - 1];
-            S.e2[m - 2] = S.col[m - 1] * S.col[m - 1];
+            S.de[m - 1].y = S.col[m - 1] * S.col[m - 1];
         }
-        S.d[m - 1] = S.ww[m - 1];
+        S.d[m - 1] = S.de[m - 1].x = S.ww[m - 1];
     }
-    bsync<NB>();
+    bsync<MM>();
 }
 
 // ------------------------------------------------------------ Sturm counts ----
 // Number of eigenvalues of T below sigma.  Wave-local: every wave of a
 // stencil may evaluate these (they read only S.d, S.e2).
-template <int NB>
-__device__ __forceinline__ int sturm(const Shared<NB>& S, int m, double sigma, double pivmin) {
+template <int MM>
+__device__ __forceinline__ int sturm(const Shared<MM>& S, int m, double sigma, double pivmin) {
     double q = S.d[0] - sigma;
     if (fabs(q) < pivmin) q = -pivmin;
     int c = q < 0.0 ? 1 : 0;
+#pragma unroll 4
     for (int i = 1; i < m; ++i) {
-        q = fma(-S.e2[i - 1], recip(q), S.d[i] - sigma);
+        const double2 de = S.de[i];
+        q = fma(-de.y, recip(q), de.x - sigma);
         if (fabs(q) < pivmin) q = -pivmin;
         c += q < 0.0 ? 1 : 0;
     }
@@ -440,10 +637,10 @@ __device__ __forceinline__ void amax_bounds(const Spectrum& sp, double& alo, dou
 // all 64 lanes split the other's bracket 65 ways.  With rel > 0 the rounds
 // stop as soon as the bracket of max |lambda| is within 2 rel of its midpoint
 // (midpoint error <= rel relative).  sp.amax is that midpoint.
-template <int NB>
-__device__ __forceinline__ void spectrum_refine(const Shared<NB>& S, int lane, Spectrum& sp, int rounds,
+template <int MM>
+__device__ __forceinline__ void spectrum_refine(const Shared<MM>& S, int lane, Spectrum& sp, int rounds,
                                                 double rel = 0.0) {
-    const int m = S.m;
+    const int m = stencil_m<MM>(S);
     double lo1 = sp.lo1, hi1 = sp.hi1, lo2 = sp.lo2, hi2 = sp.hi2;
     for (int rd = 0; rd < rounds; ++rd) {
         // all conditions below are wave-uniform: the brackets are
@@ -456,7 +653,7 @@ __device__ __forceinline__ void spectrum_refine(const Shared<NB>& S, int lane, S
             const double lo = g ? lo2 : lo1, hi = g ? hi2 : hi1;
             const double sig = lo + (hi - lo) * (double)(tt + 1) / 33.0;
             const int kidx = g ? m : 1;
-            const bool below = sturm<NB>(S, m, sig, sp.pivmin) < kidx;  // eigenvalue kidx lies above sig
+            const bool below = sturm<MM>(S, m, sig, sp.pivmin) < kidx;  // eigenvalue kidx lies above sig
             const uint64_t bal = __ballot(below);
             const int nb1 = __popcll(bal & 0xffffffffull);
             const int nb2 = __popcll(bal >> 32);
@@ -468,7 +665,7 @@ __device__ __forceinline__ void spectrum_refine(const Shared<NB>& S, int lane, S
         } else {
             const double lo = need2 ? lo2 : lo1, hi = need2 ? hi2 : hi1;
             const double sig = lo + (hi - lo) * (double)(lane + 1) / 65.0;
-            const bool below = sturm<NB>(S, m, sig, sp.pivmin) < (need2 ? m : 1);
+            const bool below = sturm<MM>(S, m, sig, sp.pivmin) < (need2 ? m : 1);
             const int nb = __popcll(__ballot(below));
             const double n_lo = nb > 0 ? lo + (hi - lo) * (double)nb / 65.0 : lo;
             const double n_hi = nb < 64 ? lo + (hi - lo) * (double)(nb + 1) / 65.0 : hi;
@@ -487,9 +684,9 @@ __device__ __forceinline__ void spectrum_refine(const Shared<NB>& S, int lane, S
 
 // Largest |lambda| of T to ~33^-rounds of the Gershgorin width (see
 // spectrum_refine for rel).
-template <int NB>
-__device__ __forceinline__ Spectrum spectrum_max(const Shared<NB>& S, int lane, int rounds, double rel = 0.0) {
-    const int m = S.m;
+template <int MM>
+__device__ __forceinline__ Spectrum spectrum_max(const Shared<MM>& S, int lane, int rounds, double rel = 0.0) {
+    const int m = stencil_m<MM>(S);
     Spectrum sp;
     // Gershgorin interval of T: each lane takes rows lane, lane + 64, then
     // wavefront min/max (exact, so the same bits as a serial scan)
@@ -503,7 +700,7 @@ __device__ __forceinline__ Spectrum spectrum_max(const Shared<NB>& S, int lane, 
         gu = fmax(gu, S.d[i] + off);
         dmax = fmax(dmax, S.d[i]);
         ndmin = fmax(ndmin, -S.d[i]);
-        if (i < m - 1) emax2 = fmax(emax2, S.e2[i]);
+        if (i < m - 1) emax2 = fmax(emax2, S.de[i + 1].y);
         fin = fin && isfinite(S.d[i]) && (i == m - 1 || isfinite(S.e[i]));
     }
     double gl = -wave_max(ngl);
@@ -526,21 +723,21 @@ __device__ __forceinline__ Spectrum spectrum_max(const Shared<NB>& S, int lane, 
         sp.amax = NAN;
         return sp;
     }
-    spectrum_refine<NB>(S, lane, sp, rounds, rel);
+    spectrum_refine<MM>(S, lane, sp, rounds, rel);
     return sp;
 }
 
 // #eigenvalues with |lambda| < tau for two thresholds (lanes 0-1 and 2-3)
-template <int NB>
-__device__ __forceinline__ void small_counts(const Shared<NB>& S, int lane, const Spectrum& sp, double tau_a,
+template <int MM>
+__device__ __forceinline__ void small_counts(const Shared<MM>& S, int lane, const Spectrum& sp, double tau_a,
                                              double tau_b, int& ca, int& cb) {
-    const int m = S.m;
+    const int m = stencil_m<MM>(S);
     double sig = 0.0;
     if (lane == 0) sig = -tau_a;
     if (lane == 1) sig = tau_a;
     if (lane == 2) sig = -tau_b;
     if (lane == 3) sig = tau_b;
-    const int c = lane < 4 ? sturm<NB>(S, m, sig, sp.pivmin) : 0;
+    const int c = lane < 4 ? sturm<MM>(S, m, sig, sp.pivmin) : 0;
     const int c0 = __shfl(c, 0, 64), c1 = __shfl(c, 1, 64), c2 = __shfl(c, 2, 64), c3 = __shfl(c, 3, 64);
     ca = c1 - c0;
     cb = c3 - c2;
@@ -553,10 +750,10 @@ __device__ __forceinline__ void small_counts(const Shared<NB>& S, int lane, cons
 // exist), all 64 lanes split the other's 65 ways.  Rounds continue until the
 // log bracket of min |lambda| is 2 rel wide (midpoint error <= rel relative),
 // at most `rounds`.
-template <int NB>
-__device__ __forceinline__ double min_abs_refine(const Shared<NB>& S, int lane, const Spectrum& sp, int nu, double lp,
+template <int MM>
+__device__ __forceinline__ double min_abs_refine(const Shared<MM>& S, int lane, const Spectrum& sp, int nu, double lp,
                                                  double hp, double ln_, double hn, int rounds, double rel) {
-    const int m = S.m;
+    const int m = stencil_m<MM>(S);
     const bool has_pos = nu < m, has_neg = nu > 0;
     for (int rd = 0; rd < rounds; ++rd) {
         // wave-uniform: the brackets are
@@ -570,8 +767,8 @@ __device__ __forceinline__ double min_abs_refine(const Shared<NB>& S, int lane, 
             const double lo = g ? ln_ : lp, hi = g ? hn : hp;
             const double sig = exp(lo + (hi - lo) * (double)(tt + 1) / 33.0);
             bool above;  // target magnitude lies above sig
-            if (g == 0) above = sturm<NB>(S, m, sig, sp.pivmin) <= nu;   // lambda_{nu+1} > sig
-            else above = sturm<NB>(S, m, -sig, sp.pivmin) >= nu;         // lambda_nu < -sig
+            if (g == 0) above = sturm<MM>(S, m, sig, sp.pivmin) <= nu;   // lambda_{nu+1} > sig
+            else above = sturm<MM>(S, m, -sig, sp.pivmin) >= nu;         // lambda_nu < -sig
             const uint64_t bal = __ballot(above);
             const int nb1 = __popcll(bal & 0xffffffffull);
             const int nb2 = __popcll(bal >> 32);
@@ -584,7 +781,7 @@ __device__ __forceinline__ double min_abs_refine(const Shared<NB>& S, int lane, 
         } else {
             const double lo = need_p ? lp : ln_, hi = need_p ? hp : hn;
             const double sig = exp(lo + (hi - lo) * (double)(lane + 1) / 65.0);
-            const bool above = need_p ? sturm<NB>(S, m, sig, sp.pivmin) <= nu : sturm<NB>(S, m, -sig, sp.pivmin) >= nu;
+            const bool above = need_p ? sturm<MM>(S, m, sig, sp.pivmin) <= nu : sturm<MM>(S, m, -sig, sp.pivmin) >= nu;
             const int nb = __popcll(__ballot(above));
             const double a1 = lo + (hi - lo) * (double)nb / 65.0, b1 = lo + (hi - lo) * (double)(nb + 1) / 65.0;
             const double n_lo = nb > 0 ? a1 : lo, n_hi = nb < 64 ? b1 : hi;
@@ -602,10 +799,10 @@ __device__ __forceinline__ double min_abs_refine(const Shared<NB>& S, int lane, 
     return fmin(pos, neg);
 }
 
-template <int NB>
-__device__ __forceinline__ double spectrum_min_abs_in(const Shared<NB>& S, int lane, const Spectrum& sp, int nu,
+template <int MM>
+__device__ __forceinline__ double spectrum_min_abs_in(const Shared<MM>& S, int lane, const Spectrum& sp, int nu,
                                                       double L, double H, int rounds, double rel) {
-    return min_abs_refine<NB>(S, lane, sp, nu, log(L), log(H), log(L), log(H), rounds, rel);
+    return min_abs_refine<MM>(S, lane, sp, nu, log(L), log(H), log(L), log(H), rounds, rel);
 }
 
 // The band test of a learned proposal and the first round of its min |lambda|
@@ -615,11 +812,11 @@ __device__ __forceinline__ double spectrum_min_abs_in(const Shared<NB>& S, int l
 // side.  If the proposal is kept (ca > 0, cb == 0), min |lambda| lies in
 // [tau_b, tau_a), and the returned log brackets (lp, hp) and (ln_, hn) are
 // those after that first round.
-template <int NB>
-__device__ __forceinline__ void band_counts_min(const Shared<NB>& S, int lane, const Spectrum& sp, double tau_a,
+template <int MM>
+__device__ __forceinline__ void band_counts_min(const Shared<MM>& S, int lane, const Spectrum& sp, double tau_a,
                                                 double tau_b, int& ca, int& cb, int& nu, double& lp, double& hp,
                                                 double& ln_, double& hn) {
-    const int m = S.m;
+    const int m = stencil_m<MM>(S);
     const double l0 = log(tau_b), l1 = log(tau_a);
     double sig = 0.0;
     if (lane == 0) sig = -tau_a;
@@ -629,7 +826,7 @@ __device__ __forceinline__ void band_counts_min(const Shared<NB>& S, int lane, c
     const bool pos_lane = lane >= 8 && lane < 36, neg_lane = lane >= 36;
     if (pos_lane) sig = exp(l0 + (l1 - l0) * (double)(lane - 8 + 1) / 29.0);
     if (neg_lane) sig = -exp(l0 + (l1 - l0) * (double)(lane - 36 + 1) / 29.0);
-    const int c = (lane < 5 || lane >= 8) ? sturm<NB>(S, m, sig, sp.pivmin) : 0;
+    const int c = (lane < 5 || lane >= 8) ? sturm<MM>(S, m, sig, sp.pivmin) : 0;
     const int c0 = __shfl(c, 0, 64), c1 = __shfl(c, 1, 64), c2 = __shfl(c, 2, 64), c3 = __shfl(c, 3, 64);
     ca = c1 - c0;
     cb = c3 - c2;
@@ -647,10 +844,10 @@ __device__ __forceinline__ void band_counts_min(const Shared<NB>& S, int lane, c
 }
 
 // Smallest |lambda| with no prior bracket: [1e-30, 1] x max |lambda|, 7 rounds.
-template <int NB>
-__device__ __forceinline__ double spectrum_min_abs(const Shared<NB>& S, int lane, const Spectrum& sp) {
-    const int nu = sturm<NB>(S, S.m, 0.0, sp.pivmin);  // eigenvalues below zero (uniform)
-    return spectrum_min_abs_in<NB>(S, lane, sp, nu, sp.amax * 1e-30 + sp.pivmin,
+template <int MM>
+__device__ __forceinline__ double spectrum_min_abs(const Shared<MM>& S, int lane, const Spectrum& sp) {
+    const int nu = sturm<MM>(S, stencil_m<MM>(S), 0.0, sp.pivmin);  // eigenvalues below zero (uniform)
+    return spectrum_min_abs_in<MM>(S, lane, sp, nu, sp.amax * 1e-30 + sp.pivmin,
                                    sp.amax * (1.0 + 1e-12) + sp.pivmin, 7, 0.0);
 }
 
@@ -659,9 +856,9 @@ __device__ __forceinline__ double spectrum_min_abs(const Shared<NB>& S, int lane
 // zero pivot.  The diagonal and super-diagonal of the row being eliminated are
 // carried in registers, so each step reads LDS only for inputs that do not
 // depend on the previous step.
-template <int NB>
-__device__ __forceinline__ bool tri_factor(Shared<NB>& S) {
-    const int m = S.m;
+template <int MM>
+__device__ __forceinline__ bool tri_factor(Shared<MM>& S) {
+    const int m = stencil_m<MM>(S);
     double dcur = S.d[0];                      // pivot-row diagonal (after earlier steps)
     double ucur = m > 1 ? S.e[0] : 0.0;        // its super-diagonal
     for (int i = 0; i < m - 1; ++i) {
@@ -702,9 +899,9 @@ __device__ __forceinline__ bool tri_factor(Shared<NB>& S) {
 
 // b <- T^{-1} b with the factors of tri_factor (one thread); the running
 // entries of b are carried in registers.
-template <int NB>
-__device__ __forceinline__ void tri_solve(const Shared<NB>& S, double* b) {
-    const int m = S.m;
+template <int MM>
+__device__ __forceinline__ void tri_solve(const Shared<MM>& S, double* b) {
+    const int m = stencil_m<MM>(S);
     double bi = b[0];
     for (int i = 0; i < m - 1; ++i) {
         const double f = S.ffact[i];
@@ -732,50 +929,49 @@ __device__ __forceinline__ void tri_solve(const Shared<NB>& S, double* b) {
 }
 
 // y <- Q^T y (FWD) or y <- Q y, for NV = 1 or 3 vectors (thread holds component
-// t.c).  The reflector v_k is register row k (NB = 1) or is published through
-// LDS by the row block that holds row k (NB = 2).
-template <int NB, int NV, bool FWD>
-__device__ __forceinline__ void apply_q(const double (&a)[64], Shared<NB>& S, const Tid& t, double (&y)[3]) {
-    const int m = S.m;
-    constexpr int MM = 64 * NB;
-#pragma unroll
+// t.c).  The reflector v_k is register row k (one wave) or is published through
+// LDS by the row block that holds row k (four waves).
+template <int MM, int NV, bool FWD>
+__device__ __forceinline__ void apply_q(const double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t, double (&y)[3]) {
+    const int m = stencil_m<MM>(S);
+    #pragma unroll
     for (int kk = 0; kk < MM - 2; ++kk) {
         const int k = FWD ? kk : MM - 3 - kk;  // a compile-time constant after unrolling
         if (k < m - 2) {
             double v;
-            if constexpr (NB == 1) {
+            if constexpr (MM <= 64) {
                 v = a[k];
             } else {
                 if (t.rb == k / 64) S.vb[t.c] = a[k % 64];
-                bsync<NB>();
+                bsync<MM>();
                 v = S.vb[t.c];
             }
             if constexpr (NV == 3) {
                 double s0 = v * y[0], s1 = v * y[1], s2 = v * y[2];
-                sum_cols3<NB>(s0, s1, s2, S, t);  // ends with a barrier when NB = 2
+                sum_cols3<MM>(s0, s1, s2, S, t);  // ends with a barrier with four waves
                 const double ta = S.tau[k];
                 y[0] = fma(-ta * s0, v, y[0]);
                 y[1] = fma(-ta * s1, v, y[1]);
                 y[2] = fma(-ta * s2, v, y[2]);
             } else {
-                const double s0 = sum_cols<NB>(v * y[0], S, t);
+                const double s0 = sum_cols<MM>(v * y[0], S, t);
                 y[0] = fma(-S.tau[k] * s0, v, y[0]);
             }
         }
     }
 }
 
-// One wave (NB = 1), NV vectors: Q^T y (FWD) or Q y four reflectors at a time.
+// One wave, NV vectors: Q^T y (FWD) or Q y four reflectors at a time.
 // For a block H_{k0} .. H_{k0+3} the four products d_i = v_i . y of a vector
 // are reduced together, and the coupling of successive reflectors inside the
 // block comes from their Gram entries G_ij = v_i . v_j (S.G, six per block,
 // from reflector_gram): applying H_{k0} first, s_i = d_i - sum_{j<i} tau_j s_j G_ij
 // and y -= sum_i tau_i s_i v_i (the reverse order for Q y).  Rows past the last
 // reflector enter with v = 0 and tau = 0.
-template <int NB, int NV, bool FWD>
-__device__ __forceinline__ void apply_q_blocked(const double (&a)[64], Shared<NB>& S, double (&y)[3]) {
-    static_assert(NB == 1, "one-wave tiling only");
-    const int p = S.m - 2;
+template <int MM, int NV, bool FWD>
+__device__ __forceinline__ void apply_q_blocked(const double (&a)[Lay<MM>::R], Shared<MM>& S, double (&y)[3]) {
+    static_assert(MM <= 64, "one-wave tiling only");
+    const int p = stencil_m<MM>(S) - 2;
 #pragma unroll
     for (int bb = 0; bb < 16; ++bb) {
         const int b = FWD ? bb : 15 - bb;
@@ -818,10 +1014,10 @@ __device__ __forceinline__ void apply_q_blocked(const double (&a)[64], Shared<NB
 }
 
 // S.G for apply_q_blocked (one wave, after the final tridiagonalisation).
-template <int NB>
-__device__ __forceinline__ void reflector_gram(const double (&a)[64], Shared<NB>& S, const Tid& t) {
-    static_assert(NB == 1, "one-wave tiling only");
-    const int p = S.m - 2;
+template <int MM>
+__device__ __forceinline__ void reflector_gram(const double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t) {
+    static_assert(MM <= 64, "one-wave tiling only");
+    const int p = stencil_m<MM>(S) - 2;
 #pragma unroll
     for (int b = 0; b < 16; ++b) {
         const int k0 = 4 * b;
@@ -838,33 +1034,33 @@ __device__ __forceinline__ void reflector_gram(const double (&a)[64], Shared<NB>
             }
         }
     }
-    bsync<NB>();
+    bsync<MM>();
 }
 
 // y <- A~^{-1} y via Q T^{-1} Q^T
-template <int NB, int NV>
-__device__ __forceinline__ void solve(const double (&a)[64], Shared<NB>& S, const Tid& t, double (&y)[3]) {
-    const int m = S.m;
-    if constexpr (NB == 1) apply_q_blocked<NB, NV, true>(a, S, y);
-    else apply_q<NB, NV, true>(a, S, t, y);
+template <int MM, int NV>
+__device__ __forceinline__ void solve(const double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t, double (&y)[3]) {
+    const int m = stencil_m<MM>(S);
+    if constexpr (MM <= 64) apply_q_blocked<MM, NV, true>(a, S, y);
+    else apply_q<MM, NV, true>(a, S, t, y);
     if (t.rb == 0) {
 #pragma unroll
         for (int v = 0; v < NV; ++v) S.rhs[v][t.c] = y[v];
     }
-    bsync<NB>();
-    if (t.tid < NV) tri_solve<NB>(S, S.rhs[t.tid]);
-    bsync<NB>();
+    bsync<MM>();
+    if (t.tid < NV) tri_solve<MM>(S, S.rhs[t.tid]);
+    bsync<MM>();
 #pragma unroll
     for (int v = 0; v < NV; ++v) y[v] = t.c < m ? S.rhs[v][t.c] : 0.0;
-    bsync<NB>();
-    if constexpr (NB == 1) apply_q_blocked<NB, NV, false>(a, S, y);
-    else apply_q<NB, NV, false>(a, S, t, y);
+    bsync<MM>();
+    if constexpr (MM <= 64) apply_q_blocked<MM, NV, false>(a, S, y);
+    else apply_q<MM, NV, false>(a, S, t, y);
 }
 
 // (A~ z) row t.c for NV vectors read from S.zb; A~ re-evaluated from the nodes
-template <int K, int NB, int NV>
-__device__ __forceinline__ void matvec_lds(const Shared<NB>& S, const Tid& t, double e2, double (&out)[3]) {
-    const int n = S.n, m = S.m, r = S.r, c = t.c;
+template <int K, int MM, int NV>
+__device__ __forceinline__ void matvec_lds(const Shared<MM>& S, const Tid& t, double e2, double (&out)[3]) {
+    const int n = stencil_n<MM>(S), m = stencil_m<MM>(S), r = S.r, c = t.c;
     out[0] = out[1] = out[2] = 0.0;
     if (c < n) {
         const double xi = S.x[c], yi = S.y[c], zi = S.z[c];
@@ -872,19 +1068,19 @@ __device__ __forceinline__ void matvec_lds(const Shared<NB>& S, const Tid& t, do
             const double dx = xi - S.x[j], dy = yi - S.y[j], dz = zi - S.z[j];
             const double av = rbf_phi<K>(e2, (dx * dx + dy * dy) + dz * dz);
 #pragma unroll
-            for (int v = 0; v < NV; ++v) out[v] = fma(av, S.zb[v][j], out[v]);
+            for (int v = 0; v < NV; ++v) out[v] = fma(av, S.zb[j], out[v]);
         }
         for (int k = 0; k < r; ++k) {
             const double u = S.U[c * RMAX + k];
 #pragma unroll
-            for (int v = 0; v < NV; ++v) out[v] = fma(u, S.zb[v][n + k], out[v]);
+            for (int v = 0; v < NV; ++v) out[v] = fma(u, S.zb[n + k], out[v]);
         }
     } else if (c < m) {
         const int k = c - n;
         for (int j = 0; j < n; ++j) {
             const double u = S.U[j * RMAX + k];
 #pragma unroll
-            for (int v = 0; v < NV; ++v) out[v] = fma(u, S.zb[v][j], out[v]);
+            for (int v = 0; v < NV; ++v) out[v] = fma(u, S.zb[j], out[v]);
         }
     }
 }
@@ -893,23 +1089,23 @@ __device__ __forceinline__ void matvec_lds(const Shared<NB>& S, const Tid& t, do
 // The Householder route alone leaves an error several times that of LU with
 // partial pivoting on these ill-conditioned saddle systems; one step brings it
 // to that level.
-template <int K, int NB, int NV>
-__device__ __forceinline__ void solve_refined(const double (&a)[64], Shared<NB>& S, const Tid& t, double e2,
+template <int K, int MM, int NV>
+__device__ __forceinline__ void solve_refined(const double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t, double e2,
                                               double (&y)[3]) {
     const double b[3] = {y[0], y[1], y[2]};
-    solve<NB, NV>(a, S, t, y);
+    solve<MM, NV>(a, S, t, y);
     if (t.rb == 0) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) S.zb[v][t.c] = y[v];
+        for (int v = 0; v < NV; ++v) S.zb[t.c] = y[v];
     }
-    bsync<NB>();
+    bsync<MM>();
     double az[3];
-    matvec_lds<K, NB, NV>(S, t, e2, az);
-    bsync<NB>();
+    matvec_lds<K, MM, NV>(S, t, e2, az);
+    bsync<MM>();
     double r[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-    for (int v = 0; v < NV; ++v) r[v] = t.c < S.m ? b[v] - az[v] : 0.0;
-    solve<NB, NV>(a, S, t, r);
+    for (int v = 0; v < NV; ++v) r[v] = t.c < stencil_m<MM>(S) ? b[v] - az[v] : 0.0;
+    solve<MM, NV>(a, S, t, r);
 #pragma unroll
     for (int v = 0; v < NV; ++v) y[v] += r[v];
 }
@@ -926,16 +1122,16 @@ __device__ __forceinline__ void solve_refined(const double (&a)[64], Shared<NB>&
 // own norm would miss an exact dependency among small columns: at the poles
 // of a fine sphere the z^2 column, of norm ~1e-4 sqrt n, keeps a rounding
 // residual of 4e-10 of its norm.)  Degree 0 is the plain column of ones.
-template <int NB>
-__device__ __forceinline__ void build_border(Shared<NB>& S, const Tid& t, int degree, double rank_tol, double xr, double yr,
+template <int MM>
+__device__ __forceinline__ void build_border(Shared<MM>& S, const Tid& t, int degree, double rank_tol, double xr, double yr,
                              double zr) {
-    const int n = S.n;
+    const int n = stencil_n<MM>(S);
     const int jr = 64 * t.rb + t.lane;
     if (degree == 0) {
         if (t.cb == 0 && jr < n) S.U[jr * RMAX] = 1.0;
         if (t.tid < RMAX) S.T[t.tid * RMAX] = t.tid == 0 ? 1.0 : 0.0;
         if (t.tid == 0) S.r = 1;
-        bsync<NB>();
+        bsync<MM>();
         return;
     }
     const int M = degree == 1 ? 4 : 10;
@@ -964,7 +1160,7 @@ __device__ __forceinline__ void build_border(Shared<NB>& S, const Tid& t, int de
                     double g[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) g[i] = (q0 + i < l && keep[q0 + i]) ? u[q0 + i] * u[l] : 0.0;
-                    sum_rows4<NB>(g[0], g[1], g[2], g[3], S, t);
+                    sum_rows4<MM>(g[0], g[1], g[2], g[3], S, t);
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         if (q0 + i < l) cq[q0 + i] = g[i];
@@ -975,7 +1171,7 @@ __device__ __forceinline__ void build_border(Shared<NB>& S, const Tid& t, int de
                     tc[l] = fma(-cq[q], tc[q], tc[l]);
                 }
             }
-            const double n2 = sum_rows<NB>(u[l] * u[l], S, t);
+            const double n2 = sum_rows<MM>(u[l] * u[l], S, t);
             if (n2 > rank_tol * rank_tol * (double)n && n2 > 0.0) {
                 const double inv = 1.0 / sqrt(n2);
                 u[l] *= inv;
@@ -988,16 +1184,16 @@ __device__ __forceinline__ void build_border(Shared<NB>& S, const Tid& t, int de
         }
     }
     if (t.tid == 0) S.r = r;
-    bsync<NB>();
+    bsync<MM>();
 }
 
 // ------------------------------------------------------ kappa evaluations ----
-template <int K, int NB>
-__device__ __forceinline__ Spectrum eval_spectrum(double (&a)[64], Shared<NB>& S, const Tid& t, double eps,
+template <int K, int MM>
+__device__ __forceinline__ Spectrum eval_spectrum(double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t, double eps,
                                                   int rounds, double rel = 0.0) {
-    build_matrix<K, NB>(a, S, t, eps * eps);
-    tridiagonalise<NB>(a, S, t);
-    return spectrum_max<NB>(S, t.lane, rounds, rel);
+    build_matrix<K, MM>(a, S, t, eps * eps);
+    tridiagonalise<MM>(a, S, t, stencil_m<MM>(S));
+    return spectrum_max<MM>(S, t.lane, rounds, rel);
 }
 
 // kappa_2(T) > target ?  (non-finite counts as above, like an infinite kappa)
@@ -1007,28 +1203,28 @@ __device__ __forceinline__ Spectrum eval_spectrum(double (&a)[64], Shared<NB>& S
 // the two counts differ is max |lambda| refined (two multisection rounds at a
 // time), so every decision is the one the Sturm counts of T give at the exact
 // max |lambda|, up to a bracket of a few ulps.  sp's brackets are refined in place.
-template <int NB>
-__device__ __forceinline__ bool kappa_above(const Shared<NB>& S, int lane, Spectrum& sp, double target) {
+template <int MM>
+__device__ __forceinline__ bool kappa_above(const Shared<MM>& S, int lane, Spectrum& sp, double target) {
     if (!sp.finite || !(sp.amax > 0.0)) return true;
     for (int it = 0; it < 12; ++it) {
         double alo, ahi;
         amax_bounds(sp, alo, ahi);
         int ca, cb;
-        small_counts<NB>(S, lane, sp, alo / target, ahi / target, ca, cb);
+        small_counts<MM>(S, lane, sp, alo / target, ahi / target, ca, cb);
         if (ca > 0) return true;
         if (cb == 0) return false;
         if (ahi - alo <= 8.0 * 2.2e-16 * ahi) break;  // bracket at FP64 resolution
-        spectrum_refine<NB>(S, lane, sp, 2);
+        spectrum_refine<MM>(S, lane, sp, 2);
     }
     int ca, cb;
-    small_counts<NB>(S, lane, sp, sp.amax / target, sp.amax / target, ca, cb);
+    small_counts<MM>(S, lane, sp, sp.amax / target, sp.amax / target, ca, cb);
     return ca > 0;
 }
 
 // --------------------------------------------------------------- stencil ----
-// The whole computation for stencil s of job J by the NB^2 waves of one stencil.
-template <int K, int NB>
-__device__ __forceinline__ void process_stencil(const Job& J, int64_t s, Shared<NB>& S, const Tid& t) {
+// The whole computation for stencil s of job J by the waves of one stencil.
+template <int K, int MM>
+__device__ __forceinline__ void process_stencil(const Job& J, int64_t s, Shared<MM>& S, const Tid& t) {
     const WOpts& o = J.o;
     const int n = o.n;
     const int c = t.c;
@@ -1062,14 +1258,14 @@ __device__ __forceinline__ void process_stencil(const Job& J, int64_t s, Shared<
         S.nrm0[0] = nx; S.nrm0[1] = ny; S.nrm0[2] = nz;
         S.n = n;
     }
-    bsync<NB>();
+    bsync<MM>();
     // ---- stencil radius, scaled offsets of the thread's column node and row node
     const double dx0 = px - S.x[0], dy0 = py - S.y[0], dz0 = pz - S.z[0];
     const double r20 = c < n ? (dx0 * dx0 + dy0 * dy0) + dz0 * dz0 : 0.0;
     // 3: an index out of range somewhere in the stencil; 2: a zero or
     // non-finite normal; 1: two nodes coincide
     const double flagf =
-        max_cols<NB>(bad ? 3.0 : (badn ? 2.0 : ((c > 0 && c < n && r20 == 0.0) ? 1.0 : 0.0)), S, t);
+        max_cols<MM>(bad ? 3.0 : (badn ? 2.0 : ((c > 0 && c < n && r20 == 0.0) ? 1.0 : 0.0)), S, t);
     if (flagf >= 2.0) {
         if (t.tid == 0) {
             if (J.eps) J.eps[s] = NAN;
@@ -1078,11 +1274,11 @@ __device__ __forceinline__ void process_stencil(const Job& J, int64_t s, Shared<
             if (J.status) J.status[s] = flagf >= 3.0 ? RBFFD_ST_BAD_INDEX : RBFFD_ST_BAD_NORMAL;
         }
         if (!J.kappa_only && c < n && t.rb == 0) J.w[s * n + c] = NAN;
-        bsync<NB>();
+        bsync<MM>();
         return;
     }
     const double dupf = flagf;
-    const double rho = sqrt(max_cols<NB>(r20, S, t));
+    const double rho = sqrt(max_cols<MM>(r20, S, t));
     const double irho = 1.0 / rho;
     const double xi = dx0 / rho, yi = dy0 / rho, zi = dz0 / rho;
     const int jr = 64 * t.rb + t.lane;
@@ -1092,101 +1288,108 @@ __device__ __forceinline__ void process_stencil(const Job& J, int64_t s, Shared<
         yr = (S.y[jr] - S.y[0]) / rho;
         zr = (S.z[jr] - S.z[0]) / rho;
     }
-    build_border<NB>(S, t, o.degree, o.rank_tol, xr, yr, zr);
+    build_border<MM>(S, t, o.degree, o.rank_tol, xr, yr, zr);
     if (t.tid == 0) S.m = n + S.r;
-    bsync<NB>();
+    bsync<MM>();
     int status = RBFFD_ST_OK;
     int evals = 0;
-    double a[64];
+    double a[Lay<MM>::R];
     double eps;
     if (dupf > 0.0) status = RBFFD_ST_DUPLICATE;
 
-    // ---- shape parameter
-    bool have_final = false;  // registers / S hold the tridiagonal form at eps
+    // ---- shape parameter: one evaluation (matrix, tridiagonal form, max |lambda|)
+    // per turn of the loop, so that its code is in the kernel once
+    enum Phase { LEARN, LOW, HIGH, MID, FINAL };
     double amin_known = 0.0;  // min |lambda| if already found
-    Spectrum sp;
+    double lo = 0.0, hi = 0.0;
+    int ph = FINAL, q = 0;
     if (o.mode == RBFFD_EPS_FIXED) {
         eps = o.eps_fixed;
     } else if (o.mode == RBFFD_EPS_GIVEN) {
         eps = J.eps_in[s];
     } else {
-        bool need_bisect = true;
+        lo = o.br_lo / rho;
+        hi = o.br_hi / rho;
+        eps = lo;
+        ph = LOW;
         if (o.mode == RBFFD_EPS_LEARNED) {
-            eps = J.eps_in[s];
-            if (isfinite(eps) && eps > 0.0) {
-                // max |lambda| to band_rel: also the reported kappa's if kept
-                sp = eval_spectrum<K, NB>(a, S, t, eps, 8, o.band_rel);
-                ++evals;
-                if (sp.finite && sp.amax > 0.0) {
-                    int c_lo, c_hi, nu;  // |lambda| below amax/band_lo and below amax/band_hi
-                    const double tau_lo = sp.amax / o.band_lo, tau_hi = sp.amax / o.band_hi;
-                    double lp, hp, ln_, hn;
-                    band_counts_min<NB>(S, t.lane, sp, tau_lo, tau_hi, c_lo, c_hi, nu, lp, hp, ln_, hn);
-                    if (c_lo > 0 && c_hi == 0) {  // band_lo < kappa <= band_hi
-                        need_bisect = false;
-                        have_final = true;
-                        // min |lambda| lies in [tau_hi, tau_lo): its first round is done
-                        amin_known = min_abs_refine<NB>(S, t.lane, sp, nu, lp, hp, ln_, hn, 6, o.band_rel);
-                    }
-                }
+            const double e = J.eps_in[s];
+            if (isfinite(e) && e > 0.0) {
+                eps = e;
+                ph = LEARN;
+            } else if (status == RBFFD_ST_OK) {
+                status = RBFFD_ST_FALLBACK;
             }
-            if (need_bisect && status == RBFFD_ST_OK) status = RBFFD_ST_FALLBACK;
-        }
-        if (need_bisect) {
-            double lo = o.br_lo / rho, hi = o.br_hi / rho;
-            sp = eval_spectrum<K, NB>(a, S, t, lo, 2);
-            ++evals;
-            bool ab = kappa_above<NB>(S, t.lane, sp, o.kappa_target);
-            for (int q = 0; !ab && q < o.max_expand; ++q) {
-                lo *= 0.5;
-                sp = eval_spectrum<K, NB>(a, S, t, lo, 2);
-                ++evals;
-                ab = kappa_above<NB>(S, t.lane, sp, o.kappa_target);
-            }
-            bool ok = ab;
-            sp = eval_spectrum<K, NB>(a, S, t, hi, 2);
-            ++evals;
-            ab = kappa_above<NB>(S, t.lane, sp, o.kappa_target);
-            for (int q = 0; ab && q < o.max_expand; ++q) {
-                hi *= 2.0;
-                sp = eval_spectrum<K, NB>(a, S, t, hi, 2);
-                ++evals;
-                ab = kappa_above<NB>(S, t.lane, sp, o.kappa_target);
-            }
-            ok = ok && !ab;
-            if (!ok && status == RBFFD_ST_OK) status = RBFFD_ST_NO_BRACKET;
-            bool stop = false;
-            while (hi - lo > o.eps_tol && !stop) {
-                const double mid = 0.5 * (lo + hi);
-                sp = eval_spectrum<K, NB>(a, S, t, mid, 2);
-                ++evals;
-                if (o.band_stop && sp.finite && sp.amax > 0.0) {
-                    int c_lo, c_hi;
-                    small_counts<NB>(S, t.lane, sp, sp.amax / o.band_lo, sp.amax / o.band_hi, c_lo, c_hi);
-                    if (c_lo > 0 && c_hi == 0) {
-                        eps = mid;
-                        stop = true;
-                        have_final = true;
-                        // six more rounds: the same brackets as eight from the start,
-                        // full precision for the reported kappa
-                        spectrum_refine<NB>(S, t.lane, sp, 6);
-                        break;
-                    }
-                }
-                if (kappa_above<NB>(S, t.lane, sp, o.kappa_target)) lo = mid;
-                else hi = mid;
-            }
-            if (!stop) eps = 0.5 * (lo + hi);
         }
     }
-    if (!have_final) {
-        sp = eval_spectrum<K, NB>(a, S, t, eps, 8);
+    Spectrum sp;
+    for (;;) {
+        // max |lambda| of a proposal to band_rel: also the reported kappa's if kept
+        sp = eval_spectrum<K, MM>(a, S, t, eps, ph == FINAL || ph == LEARN ? 8 : 2, ph == LEARN ? o.band_rel : 0.0);
         ++evals;
+        if (ph == FINAL) break;
+        const bool good = sp.finite && sp.amax > 0.0;
+        if (ph == LEARN) {
+            if (good) {
+                int c_lo, c_hi, nu;  // |lambda| below amax/band_lo and below amax/band_hi
+                const double tau_lo = sp.amax / o.band_lo, tau_hi = sp.amax / o.band_hi;
+                double lp, hp, ln_, hn;
+                band_counts_min<MM>(S, t.lane, sp, tau_lo, tau_hi, c_lo, c_hi, nu, lp, hp, ln_, hn);
+                if (c_lo > 0 && c_hi == 0) {  // band_lo < kappa <= band_hi
+                    // min |lambda| lies in [tau_hi, tau_lo): its first round is done
+                    amin_known = min_abs_refine<MM>(S, t.lane, sp, nu, lp, hp, ln_, hn, 6, o.band_rel);
+                    break;
+                }
+            }
+            if (status == RBFFD_ST_OK) status = RBFFD_ST_FALLBACK;
+            eps = lo;
+            ph = LOW;
+            continue;
+        }
+        if (ph == MID && o.band_stop && good) {
+            int c_lo, c_hi;
+            small_counts<MM>(S, t.lane, sp, sp.amax / o.band_lo, sp.amax / o.band_hi, c_lo, c_hi);
+            if (c_lo > 0 && c_hi == 0) {
+                // six more rounds: the same brackets as eight from the start,
+                // full precision for the reported kappa
+                spectrum_refine<MM>(S, t.lane, sp, 6);
+                break;
+            }
+        }
+        const bool above = kappa_above<MM>(S, t.lane, sp, o.kappa_target);
+        if (ph == LOW) {
+            if (!above && q < o.max_expand) {
+                ++q;
+                lo *= 0.5;
+                eps = lo;
+                continue;
+            }
+            if (!above && status == RBFFD_ST_OK) status = RBFFD_ST_NO_BRACKET;
+            q = 0;
+            eps = hi;
+            ph = HIGH;
+            continue;
+        }
+        if (ph == HIGH) {
+            if (above && q < o.max_expand) {
+                ++q;
+                hi *= 2.0;
+                eps = hi;
+                continue;
+            }
+            if (above && status == RBFFD_ST_OK) status = RBFFD_ST_NO_BRACKET;
+        } else if (above) {
+            lo = eps;
+        } else {
+            hi = eps;
+        }
+        ph = hi - lo > o.eps_tol ? MID : FINAL;
+        eps = 0.5 * (lo + hi);
     }
     // ---- kappa_2 at the final eps
     double kappa = NAN;
     if (sp.finite && sp.amax > 0.0) {
-        const double amin = amin_known > 0.0 ? amin_known : spectrum_min_abs<NB>(S, t.lane, sp);
+        const double amin = amin_known > 0.0 ? amin_known : spectrum_min_abs<MM>(S, t.lane, sp);
         kappa = sp.amax / amin;
     } else if (status == RBFFD_ST_OK) {
         status = RBFFD_ST_NONFINITE;
@@ -1199,19 +1402,19 @@ __device__ __forceinline__ void process_stencil(const Job& J, int64_t s, Shared<
     }
     if (J.kappa_only) {
         if (t.tid == 0 && J.status) J.status[s] = status;
-        bsync<NB>();
+        bsync<MM>();
         return;
     }
 
     // ---- weights: w = (A~^{-1} r)[:n], r = sum_d (B^d)^T g_d, g_d = (A~^{-1} b_d)[:n]
-    if (t.tid == 0) S.fact_ok = sp.finite ? (int)tri_factor<NB>(S) : 0;
-    bsync<NB>();
-    const int m = S.m;
+    if (t.tid == 0) S.fact_ok = sp.finite ? (int)tri_factor<MM>(S) : 0;
+    bsync<MM>();
+    const int m = stencil_m<MM>(S);
     if (!S.fact_ok) {
         if (status == RBFFD_ST_OK) status = sp.finite ? RBFFD_ST_SINGULAR : RBFFD_ST_NONFINITE;
         if (t.tid == 0 && J.status) J.status[s] = status;
         if (c < n && t.rb == 0) J.w[s * n + c] = NAN;
-        bsync<NB>();
+        bsync<MM>();
         return;
     }
     const double e2 = eps * eps;
@@ -1234,12 +1437,12 @@ __device__ __forceinline__ void process_stencil(const Job& J, int64_t s, Shared<
         b[1] = gy - n0y * dn;
         b[2] = gz - n0z * dn;
     }
-    if constexpr (NB == 1) reflector_gram<NB>(a, S, t);
+    if constexpr (MM <= 64) reflector_gram<MM>(a, S, t);
     // g_d: plain solve.  Refining this solve as well as the final one does not
     // lower the error of w (measured against 60-digit weights: both ways
     // 0.02-0.07 kappa u at kappa_T = 1e10 and 1e12; without any refinement
     // 0.1-0.28 kappa u), so only the final solve is refined.
-    solve<NB, 3>(a, S, t, b);
+    solve<MM, 3>(a, S, t, b);
     // h_i = Pi_i g_i
     double hx = 0, hy = 0, hz = 0;
     if (c < n) {
@@ -1253,7 +1456,7 @@ __device__ __forceinline__ void process_stencil(const Job& J, int64_t s, Shared<
         S.hy[c] = hy;
         S.hz[c] = hz;
     }
-    bsync<NB>();
+    bsync<MM>();
     // r_j = sum_i psi(r_ij) (x_i - x_j) . h_i   (j = c < n)
     double rj = 0.0;
     if (c < n) {
@@ -1282,15 +1485,15 @@ __device__ __forceinline__ void process_stencil(const Job& J, int64_t s, Shared<
                 }
                 cv = (gx * hx + gy * hy + gz * hz) * irho;
             }
-            cv = sum_cols<NB>(cv, S, t);
+            cv = sum_cols<MM>(cv, S, t);
             if (c == n + k) rj = cv;
         }
     }
     double wv[3] = {rj, 0.0, 0.0};
-    solve_refined<K, NB, 1>(a, S, t, e2, wv);
+    solve_refined<K, MM, 1>(a, S, t, e2, wv);
     if (c < n && t.rb == 0) J.w[s * n + c] = wv[0];
     if (t.tid == 0 && J.status) J.status[s] = status;
-    bsync<NB>();
+    bsync<MM>();
 }
 
 }  // namespace rbw
