@@ -167,8 +167,8 @@ int rbffd_kappa(rbffd_ctx ctx, int64_t N, const double* xyz, const rbffd_weight_
 /* ------------------------------------------------------------------------
  * Batched weights (Secs. 4 and 5 applied to many node sets at once).  The
  * stencils of nsurf surfaces, each with its own N and n, are computed by
- * persistent launches -- one for the surfaces with n + border <= 64 (one
- * wavefront per stencil), one for 64 < n + border <= 128 (four wavefronts per
+ * persistent launches -- one per register tiling: for n + border <= 48 and
+ * <= 64 (one wavefront per stencil) and <= 128 (four wavefronts per
  * stencil) -- whose workgroups take work items (runs of consecutive stencils
  * of one surface) from an atomic counter until none are left.  Every output
  * is bit-identical to rbffd_build_weights on that surface with the same opts
@@ -203,7 +203,8 @@ typedef struct {
 
 /* surf: HOST array of nsurf descriptors (device pointers inside).  tuning:
  * HOST array of RBFFD_BUCKETS schedules, or NULL for the built-in default
- * (16 stencils per item in bucket 0, 2 in bucket 1, 2 groups per CU, order 0).
+ * (16 stencils per item in bucket 0, 2 in bucket 1 -- fewer in small batches,
+ * so that every workgroup gets several items -- 2 groups per CU, order 0).
  * The call first drains the context's stream (the host waits for work
  * enqueued earlier) and then uploads the work list; the weights themselves
  * are enqueued asynchronously as usual.

@@ -18,10 +18,10 @@ LIB = os.path.join(HERE, "librbffd.so")
 ARCH = os.environ.get("RBFFD_ARCH", "gfx950")
 
 # (source, object name, defines); the weights kernels are built once per
-# (radial kernel, tiling) so that the six large variants compile in parallel.
+# (radial kernel, tiling) so that the large variants compile in parallel.
 # Longest first.
 SOURCES = [("weights_kernels.hip", f"weights_k{k}_mm{mm}", [f"-DRBW_K={k}", f"-DRBW_MM={mm}"])
-           for mm in (128, 64) for k in (0, 1, 2)]
+           for mm in (128, 64, 48, 32) for k in (0, 1, 2)]
 SOURCES += [("weights_dd.hip", "weights_dd", []), ("mlp.hip", "mlp", []), ("step.hip", "step", []), ("grid_knn.hip", "grid_knn", []),
             ("context.cpp", "context", []), ("batched.cpp", "batched", []), ("weights.cpp", "weights", [])]
 

@@ -2,8 +2,9 @@
 // schedule autotuner with its JSON cache.
 //
 // Each surface is one weights job (Secs. 4 and 5 with that surface's N and n).
-// Jobs fall into two buckets by the register tiling their local system needs
-// (m = n + border <= 64: one wavefront per stencil; m <= 128: four).  A
+// Jobs fall into two buckets (m = n + border <= 64: at most one wavefront per
+// stencil; m <= 128: four), each with one schedule; inside the first bucket
+// every register tiling (m <= 48, 64) is a launch of its own.  A
 // bucket's stencils are cut into work items of `stencils_per_item`
 // consecutive stencils of one surface; a persistent grid of
 // groups_per_cu x (compute units) workgroups takes items from an atomic
@@ -35,6 +36,21 @@ rbffd_batch_tuning default_tuning(int bucket) {
     t.stencils_per_item = bucket == 0 ? 16 : 2;
     t.groups_per_cu = 2;
     t.order = 0;
+    return t;
+}
+
+// The default schedule for one bucket's stencils: items small enough that
+// every resident workgroup of the bucket's smallest launch gets several (a
+// batch of 6000 31-node stencils in items of 16 filled 375 of 512 workgroups).
+rbffd_batch_tuning default_tuning(const std::vector<rbw::Job>& jobs, const Bucket& b, int bucket, int cus) {
+    rbffd_batch_tuning t = default_tuning(bucket);
+    std::map<int, int64_t> count;  // stencils per tiling
+    for (int s : b.jobs) count[rbw::batch_tiling(jobs[s].o)] += jobs[s].N;
+    int64_t least = INT64_MAX;
+    for (const auto& kv : count) least = std::min(least, kv.second);
+    const int floor_spi = bucket == 0 ? 4 : 1;  // one stencil per wavefront (group of four)
+    while (t.stencils_per_item > floor_spi && least / t.stencils_per_item < 4LL * t.groups_per_cu * cus)
+        t.stencils_per_item /= 2;
     return t;
 }
 
@@ -111,6 +127,9 @@ void make_items(const std::vector<rbw::Job>& jobs, const Bucket& b, const rbffd_
     std::vector<int> order = b.jobs;
     if (t.order == 0)
         std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return jobs[a].o.n > jobs[c].o.n; });
+    // the surfaces of one tiling together, the largest first (three tilings at most: run_batch's cursors)
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int a, int c) { return rbw::batch_tiling(jobs[a].o) > rbw::batch_tiling(jobs[c].o); });
     for (int s : order) {
         const int64_t N = limit ? std::min<int64_t>((*limit)[s], jobs[s].N) : jobs[s].N;
         for (int64_t st = 0; st < N; st += t.stencils_per_item) {
@@ -160,7 +179,7 @@ int run_batch(rbffd_ctx ctx, const std::vector<rbw::Job>& jobs, const std::vecto
     const size_t jbytes = align256(jobs.size() * sizeof(rbw::Job));
     const size_t ibytes0 = align256(items[0].size() * sizeof(WorkItem));
     const size_t ibytes1 = align256(items[1].size() * sizeof(WorkItem));
-    const size_t cbytes = 256;
+    const size_t cbytes = 512;
     rc = ensure_batch(ctx, jbytes + ibytes0 + ibytes1 + cbytes);
     if (rc) return rc;
     char* base = (char*)ctx->batch;
@@ -178,13 +197,18 @@ int run_batch(rbffd_ctx ctx, const std::vector<rbw::Job>& jobs, const std::vecto
     HIP_TRY(ctx, hipMemsetAsync(cursors, 0, cbytes, ctx->stream));
     const int kernel = jobs.empty() ? 0 : jobs[0].o.kernel;
     if (t0) HIP_TRY(ctx, hipEventRecord(t0, ctx->stream));
-    // bucket 1 (the costlier stencils) first
+    // bucket 1 (the costlier stencils) first; one launch per run of items of one tiling
+    int launches = 0;
     for (int b = RBFFD_BUCKETS - 1; b >= 0; --b) {
-        if (items[b].empty()) continue;
-        const int nitems = (int)items[b].size();
-        const int grid = std::max(1, std::min(nitems, tuning[b].groups_per_cu * cus));
-        rc = weights_launch_batched(ctx, kernel, b == 0 ? 64 : 128, djobs, ditems[b], nitems, cursors + 32 * b, grid);
-        if (rc) return rc;
+        for (size_t i = 0; i < items[b].size();) {
+            const int mm = rbw::batch_tiling(jobs[items[b][i].job].o);
+            size_t e = i + 1;
+            while (e < items[b].size() && rbw::batch_tiling(jobs[items[b][e].job].o) == mm) ++e;
+            rc = weights_launch_batched(ctx, kernel, mm, djobs, ditems[b] + i, (int)(e - i), cursors + 32 * launches++,
+                                        tuning[b].groups_per_cu * cus);
+            if (rc) return rc;
+            i = e;
+        }
     }
     if (t1) HIP_TRY(ctx, hipEventRecord(t1, ctx->stream));
     return RBFFD_OK;
@@ -281,17 +305,19 @@ int time_candidate(rbffd_ctx ctx, const std::vector<rbw::Job>& jobs, const Bucke
 extern "C" int rbffd_build_weights_batched(rbffd_ctx ctx, int32_t nsurf, const rbffd_surface* surf,
                                            const rbffd_weight_opts* opts, const rbffd_batch_tuning* tuning) {
     if (!ctx) return RBFFD_E_ARG;
-    rbffd_batch_tuning tun[RBFFD_BUCKETS];
-    for (int b = 0; b < RBFFD_BUCKETS; ++b) {
-        tun[b] = tuning ? tuning[b] : default_tuning(b);
-        int rc = check_tuning(ctx, tun[b]);
+    for (int b = 0; tuning && b < RBFFD_BUCKETS; ++b) {
+        int rc = check_tuning(ctx, tuning[b]);
         if (rc) return rc;
     }
     std::vector<rbw::Job> jobs;
+    int cus = 0;
     int rc = prepare_jobs(ctx, nsurf, surf, opts, jobs);
+    if (!rc) rc = compute_units(ctx, cus);
     if (rc) return rc;
     Bucket bk[RBFFD_BUCKETS];
     split_buckets(jobs, bk);
+    rbffd_batch_tuning tun[RBFFD_BUCKETS];
+    for (int b = 0; b < RBFFD_BUCKETS; ++b) tun[b] = tuning ? tuning[b] : default_tuning(jobs, bk[b], b, cus);
     std::vector<WorkItem> items[RBFFD_BUCKETS];
     for (int b = 0; b < RBFFD_BUCKETS; ++b) make_items(jobs, bk[b], tun[b], nullptr, items[b]);
     if (items[0].empty() && items[1].empty()) return RBFFD_OK;

@@ -24,6 +24,6 @@ void launch_weights_batched(hipStream_t st, const Job* jobs, const WorkItem* ite
 // Validates opts for a set of N nodes and fills o (returns an RBFFD_E_* code).
 int weights_check_opts(rbffd_ctx ctx, int64_t N, const rbffd_weight_opts* opts, rbw::WOpts& o);
 // Persistent launch over `nitems` items (device arrays) with `grid` workgroups
-// of four wavefronts; mm = 64 for m <= 64, 128 for m <= 128.  *cursor must be 0.
+// of four wavefronts; mm: batch_tiling of every item.  *cursor must be 0.
 int weights_launch_batched(rbffd_ctx ctx, int kernel, int mm, const rbw::Job* jobs, const WorkItem* items,
                            int nitems, int* cursor, int grid);

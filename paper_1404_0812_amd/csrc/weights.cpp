@@ -14,7 +14,7 @@
 // against a kappa band.
 //
 // How, on gfx950: the m x m matrix lives in registers.  m <= 64: one
-// wavefront per stencil, lane i holding column i.  m <= 128: four
+// wavefront per stencil, lane i holding column i (m <= 32: half a wavefront).  m <= 128: four
 // wavefronts per stencil, wave (rb, cb) holding rows 64 rb .. 64 rb + 63 of
 // columns 64 cb + lane.  A~ is reduced to tridiagonal form T = Q^T A~ Q by
 // Householder reflections; the pivot column of each step is row k+1 after the
@@ -87,8 +87,12 @@ void launch_plain(hipStream_t st, const Job& J) {
 }
 
 int dispatch(rbffd_ctx ctx, const Job& J) {
-    if (J.o.n + border_cols(J.o.degree) <= 64) launch_plain<64>(ctx->stream, J);
-    else launch_plain<128>(ctx->stream, J);
+    switch (tiling(J.o)) {
+        case 32: launch_plain<32>(ctx->stream, J); break;
+        case 48: launch_plain<48>(ctx->stream, J); break;
+        case 64: launch_plain<64>(ctx->stream, J); break;
+        default: launch_plain<128>(ctx->stream, J); break;
+    }
     HIP_TRY(ctx, hipGetLastError());
     return RBFFD_OK;
 }
@@ -115,8 +119,11 @@ void launch_batched_mm(hipStream_t st, int kernel, const Job* jobs, const WorkIt
 
 int weights_launch_batched(rbffd_ctx ctx, int kernel, int mm, const Job* jobs, const WorkItem* items, int nitems,
                            int* cursor, int grid) {
-    if (mm == 64) launch_batched_mm<64>(ctx->stream, kernel, jobs, items, nitems, cursor, grid);
-    else launch_batched_mm<128>(ctx->stream, kernel, jobs, items, nitems, cursor, grid);
+    switch (mm) {
+        case 48: launch_batched_mm<48>(ctx->stream, kernel, jobs, items, nitems, cursor, grid); break;
+        case 64: launch_batched_mm<64>(ctx->stream, kernel, jobs, items, nitems, cursor, grid); break;
+        default: launch_batched_mm<128>(ctx->stream, kernel, jobs, items, nitems, cursor, grid); break;
+    }
     HIP_TRY(ctx, hipGetLastError());
     return RBFFD_OK;
 }

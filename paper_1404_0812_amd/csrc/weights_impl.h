@@ -11,13 +11,35 @@ namespace rbw {
 
 constexpr int RMAX = RBW_RMAX;  // border columns (degree-2 monomials in R^3)
 
-// Tilings, named by the largest m they hold: 64 (one wavefront per stencil,
-// lane = column) and 128 (four wavefronts, wave (rb, cb) holding rows
-// 64 rb .. 64 rb + 63 of columns 64 cb + lane).
+// Tilings, named by the largest m they hold: 32 (two stencils per wavefront,
+// one in each half, lane of the half = column), 48 and 64 (one wavefront per
+// stencil, lane = column) and 128 (four wavefronts, wave (rb, cb) holding
+// rows 64 rb .. 64 rb + 63 of columns 64 cb + lane).  The same operations in
+// the same order whatever the tiling: lanes and rows past m hold zeros, and a
+// sum over 32 lanes equals the sum over 64 whose upper half is zero.
+//
+// The two halves of a wavefront run different stencils, so whatever depends
+// on the stencil (brackets, counts, the phase of the search) may diverge
+// between them; nothing below moves data across the halves, and m is made
+// wave-uniform before it bounds a loop (see process_stencil).
+//
+// Why these lines: at m = 32 (the paper's n = 31 with the constant border) one
+// stencil per wavefront leaves half the lanes idle (10242 stencils by
+// bisection: 6.35 ms; two per wavefront: 3.27 ms); 48 rows instead of 64 let
+// three wavefronts share a SIMD (2500 stencils of 31 nodes, degree 2, one
+// eps: 462 -> 408 us).  Past 64 the matrix needs more than one wavefront's
+// registers.
 template <int MM>
 struct Lay {
-    static constexpr int NB = MM == 128 ? 2 : 1;  // row and column blocks
-    static constexpr int R = 64;                  // matrix rows held by a thread
+    static constexpr int NB = MM == 128 ? 2 : 1;   // row and column blocks
+    static constexpr int R = MM < 64 ? MM : 64;    // matrix rows held by a thread
+    static constexpr int SPW = MM == 32 ? 2 : 1;   // stencils per wavefront
+    static constexpr int LW = 64 / SPW;            // lanes of a stencil in a wavefront
+    static constexpr int LA = MM > LW ? MM : LW;   // entries of a lane-indexed array
+    static constexpr int OCC = MM <= 48 ? 3 : 2;   // wavefronts per SIMD
+    // border basis entries: n + M <= MM with M = 1, 4 or 10 columns
+    static constexpr int UN = MM == 32 ? 220 : 10 * (MM - 10);
+    static constexpr int WAVES = NB * NB;          // wavefronts per stencil
 };
 
 // ------------------------------------------------------------ reductions ----
@@ -59,23 +81,34 @@ __device__ __forceinline__ void swap32(double v, double& a, double& b) {
     a = __hiloint2double((int)h[0], (int)l[0]);
     b = __hiloint2double((int)h[1], (int)l[1]);
 }
+template <int MM>
 __device__ __forceinline__ double rows_total(double v) {
     double a, b;
     swap16(v, a, b);
+    if constexpr (MM == 32) return a + b;
     swap32(a + b, a, b);
     return a + b;
 }
-__device__ __forceinline__ double wave_sum(double v) { return rows_total(row_sum16(v)); }
+template <int MM>
+__device__ __forceinline__ double wave_sum(double v) {
+    return rows_total<MM>(row_sum16(v));
+}
 // Sum of the products x y: the first step pairs one lane's rounded product
 // with the other lane's through an FMA, so the two lanes of a pair differ in
 // the last bit and only one lane's total (lane 0, or the caller's own) counts.
+template <int MM>
 __device__ __forceinline__ double wave_dot(double x, double y) {
     double v = fma(x, y, dpp64<0xB1>(x * y));
     v += dpp64<0x4E>(v);
     v += dpp64<0x141>(v);
     v += dpp64<0x140>(v);
-    return rows_total(v);
+    return rows_total<MM>(v);
 }
+// wave_dot(x0, y0) + wave_dot(x1, y1), whole wavefront, the same in every
+// lane: the row totals of the two products share the cross-row steps (row 0
+// and 2 finish the first, row 1 and 3 the second), and the lanes 0 of the two
+// hand over the totals.
+__device__ __forceinline__ double wave_dot_pair(double x0, double y0, double x1, double y1);
 // The same swaps with two different operands x (vdst) and y (vsrc):
 // permlane32_swap leaves x = [x lanes 0-31, y lanes 0-31] and
 // y = [x lanes 32-63, y lanes 32-63], so their sum folds x into lanes 0-31
@@ -99,8 +132,31 @@ __device__ __forceinline__ double readlane64(double v, int lane) {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
                             __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
-// Four wavefront sums at once: the folds put a, c, b, d in rows 0..3.
+__device__ __forceinline__ double wave_dot_pair(double x0, double y0, double x1, double y1) {
+    double u = fma(x0, y0, dpp64<0xB1>(x0 * y0));
+    double v = fma(x1, y1, dpp64<0xB1>(x1 * y1));
+    u += dpp64<0x4E>(u);
+    v += dpp64<0x4E>(v);
+    u += dpp64<0x141>(u);
+    v += dpp64<0x141>(v);
+    u += dpp64<0x140>(u);
+    v += dpp64<0x140>(v);
+    double a, b;
+    swap32(fold16(u, v), a, b);
+    a += b;
+    return readlane64(a, 0) + readlane64(a, 16);
+}
+// Four wavefront sums at once: the folds put a, c, b, d in rows 0..3 (two
+// stencils per wavefront: a, b and c, d in the two rows of each half).
+template <int MM>
 __device__ __forceinline__ void wave_sum4(double& a, double& b, double& c, double& d) {
+    if constexpr (MM == 32) {
+        const double s = row_sum16(fold16(a, b));
+        const double t = row_sum16(fold16(c, d));
+        swap16(s, a, b);
+        swap16(t, c, d);
+        return;
+    }
     const double s = fold32(a, b);
     const double t = fold32(c, d);
     const double u = row_sum16(fold16(s, t));
@@ -113,7 +169,7 @@ __device__ __forceinline__ void wave_sum4(double& a, double& b, double& c, doubl
 // b in 32-63), c is folded with itself, the second fold puts a, c, b, c in
 // rows 0..3, one row sum finishes all three, and lanes 0, 32, 16 hand them
 // to every lane.  About a third of the instructions of three wave_sum calls.
-__device__ __forceinline__ void wave_sum3(double& a, double& b, double& c) {
+__device__ __forceinline__ void wave_sum3(double& a, double& b, double& c) {  // whole wavefront
     const double s = fold32(a, b);
     const double t = fold32(c, c);
     const double u = row_sum16(fold16(s, t));
@@ -121,6 +177,7 @@ __device__ __forceinline__ void wave_sum3(double& a, double& b, double& c) {
     c = readlane64(u, 16);
     b = readlane64(u, 32);
 }
+template <int MM>
 __device__ __forceinline__ double wave_max(double v) {
     v = fmax(v, dpp64<0xB1>(v));
     v = fmax(v, dpp64<0x4E>(v));
@@ -128,6 +185,7 @@ __device__ __forceinline__ double wave_max(double v) {
     v = fmax(v, dpp64<0x140>(v));
     double a, b;
     swap16(v, a, b);
+    if constexpr (MM == 32) return fmax(a, b);
     swap32(fmax(a, b), a, b);
     return fmax(a, b);
 }
@@ -182,24 +240,42 @@ __device__ __forceinline__ double rbf_psi(double e2, double r2) {
 template <int MM>
 struct Shared {
     static constexpr bool ONE = MM <= 64;
+    static constexpr int LA = Lay<MM>::LA, LW = Lay<MM>::LW;
+    struct Search {
+        double2 de[MM];  // (d_i, e_{i-1}^2): one 16-byte read per Sturm step
+        double col[LA];  // next pivot column
+        double ww[LA];
+        double vr[Lay<MM>::WAVES][LW], wr[Lay<MM>::WAVES][LW];  // v and w of a wave's row block
+        double pp[ONE ? 1 : 2][ONE ? 1 : MM];                   // matvec partial sums per row block
+        double nrm2[ONE ? 1 : 2];                               // squared norm of the pivot column's tail
+    };
+    struct Solve {
+        double fd[MM], fdu[MM], fdl[MM], ffact[MM];  // pivoted tridiagonal factors (fd: 1/pivot)
+        double rhs[3][LA];
+        double zb[LA];
+        double hx[ONE ? 1 : MM], hy[ONE ? 1 : MM], hz[ONE ? 1 : MM];
+        double vb[ONE ? 1 : MM];
+        double G[ONE ? 6 * (Lay<MM>::R / 4) : 1];  // Gram entries of the reflectors in blocks of four
+        int fswap[MM];
+    };
+    union {
+        Search f;
+        Solve g;
+    };
     double x[MM], y[MM], z[MM];  // stencil node coordinates
-    double U[MM * RMAX];         // border basis values U[j*RMAX + k]
+    double U[Lay<MM>::UN];       // border basis values U[j * us + k], us = border_cols(degree)
     double T[RMAX * RMAX];       // monomial coefficients of the border basis T[l*RMAX + k]
-    double red[16];              // cross-wave partial sums, two sets of 8
+    double red[ONE ? 1 : 16];    // cross-wave partial sums, two sets of 8
     double d[MM], e[MM], tau[MM];
-    double2 de[MM];              // (d_i, e_{i-1}^2): one 16-byte read per Sturm step
-    double col[MM], ww[MM];      // next pivot column
-    double vr[ONE ? 1 : 4][64], wr[ONE ? 1 : 4][64];  // v and w of a wave's row block
-    double vb[ONE ? 1 : MM];
-    double pp[ONE ? 1 : 2][MM];  // matvec partial sums per row block
-    double fd[MM], fdu[MM], fdl[MM], ffact[MM];  // pivoted tridiagonal factors (fd: 1/pivot)
-    int fswap[MM];
-    double rhs[3][MM];
-    double zb[MM];
-    double hx[MM], hy[MM], hz[MM];
-    double G[ONE ? 96 : 1];  // Gram entries of the reflectors in blocks of four (one wave)
     double nrm0[3];
+    double eps;  // the next evaluation's, and whether there is none (four waves)
+    int done;
     int m, r, n, fact_ok;
+    // h = Pi g: its three components take the place of the solved right-hand sides (one wave)
+    __device__ double* h(int i) {
+        if constexpr (ONE) return g.rhs[i];
+        else return i == 0 ? g.hx : (i == 1 ? g.hy : g.hz);
+    }
 };
 
 // m and n as scalars (the same for the whole stencil, so for the wavefront).
@@ -247,7 +323,7 @@ __device__ __forceinline__ double* red_set(double* red, const Tid& t) { return r
 // Sum over the columns (lane-distributed; each column is held by Lay::NB threads).
 template <int MM>
 __device__ __forceinline__ double sum_cols(double v, Shared<MM>& S, const Tid& t) {
-    const double w = wave_sum(v);
+    const double w = wave_sum<MM>(v);
     if constexpr (MM <= 64) {
         return w;
     } else {
@@ -276,7 +352,7 @@ __device__ __forceinline__ void sum_cols3(double& a, double& b, double& c, Share
 // Sum over the rows held by lanes (row 64 rb + lane; cb == 0 waves count).
 template <int MM>
 __device__ __forceinline__ double sum_rows(double v, Shared<MM>& S, const Tid& t) {
-    const double w = wave_sum(v);
+    const double w = wave_sum<MM>(v);
     if constexpr (MM <= 64) {
         return w;
     } else {
@@ -289,7 +365,7 @@ __device__ __forceinline__ double sum_rows(double v, Shared<MM>& S, const Tid& t
 // Four sums over the rows held by lanes at once (see sum_rows).
 template <int MM>
 __device__ __forceinline__ void sum_rows4(double& a, double& b, double& c, double& d, Shared<MM>& S, const Tid& t) {
-    wave_sum4(a, b, c, d);
+    wave_sum4<MM>(a, b, c, d);
     if constexpr (MM == 128) {
         double* red = red_set(S.red, t);
         if (t.cb == 0 && t.lane == 0) {
@@ -307,7 +383,7 @@ __device__ __forceinline__ void sum_rows4(double& a, double& b, double& c, doubl
 }
 template <int MM>
 __device__ __forceinline__ double max_cols(double v, Shared<MM>& S, const Tid& t) {
-    const double w = wave_max(v);
+    const double w = wave_max<MM>(v);
     if constexpr (MM <= 64) {
         return w;
     } else {
@@ -321,13 +397,13 @@ __device__ __forceinline__ double max_cols(double v, Shared<MM>& S, const Tid& t
 // ----------------------------------------------------------- local matrix ----
 // Column t.c, rows 64 rb .. 64 rb + 63 of A~(eps).
 template <int K, int MM>
-__device__ __forceinline__ void build_matrix(double (&a)[Lay<MM>::R], const Shared<MM>& S, const Tid& t, double e2) {
+__device__ __forceinline__ void build_matrix(double (&a)[Lay<MM>::R], const Shared<MM>& S, const Tid& t, double e2, int us) {
     const int n = stencil_n<MM>(S), m = stencil_m<MM>(S), c = t.c;
     const int cc = c < n ? c : 0;
     const double xi = S.x[cc], yi = S.y[cc], zi = S.z[cc];
     const int r0 = 64 * t.rb;
 #pragma unroll
-    for (int jj = 0; jj < 64; ++jj) {
+    for (int jj = 0; jj < Lay<MM>::R; ++jj) {
         const int j = r0 + jj;
         double v = 0.0;
         if (j < n) {
@@ -336,10 +412,10 @@ __device__ __forceinline__ void build_matrix(double (&a)[Lay<MM>::R], const Shar
                 const double r2 = (dx * dx + dy * dy) + dz * dz;
                 v = rbf_phi<K>(e2, r2);
             } else if (c < m) {
-                v = S.U[j * RMAX + (c - n)];
+                v = S.U[j * us + (c - n)];
             }
         } else if (j < m) {
-            if (c < n) v = S.U[c * RMAX + (j - n)];
+            if (c < n) v = S.U[c * us + (j - n)];
         }
         a[jj] = v;
     }
@@ -456,35 +532,35 @@ __device__ __forceinline__ void tridiag_block(double (&a)[Lay<MM>::R], Shared<MM
     const int kend = m - 2 < 8 * B + 8 ? m - 2 : 8 * B + 8;
 #pragma unroll 1
     for (int k = 8 * B; k < kend; ++k) {
-        const double alpha = S.col[k + 1], dk = S.col[k];
+        const double alpha = S.f.col[k + 1], dk = S.f.col[k];
         const bool tail = cl > k + 1;
-        const double xnorm2 = wave_sum(tail ? xi * xi : 0.0);
+        const double xnorm2 = wave_sum<MM>(tail ? xi * xi : 0.0);
         const Reflector h = reflector(alpha, xnorm2);
         const double vi = (c == k + 1) ? 1.0 : (tail ? xi * h.scal : 0.0);
-        S.vr[0][c] = vi;
+        S.f.vr[0][c] = vi;
         if (t.tid == 0) {
             S.d[k] = dk;
             S.e[k] = h.beta;
-            S.de[k].x = dk;
-            S.de[k + 1].y = h.beta * h.beta;
+            S.f.de[k].x = dk;
+            S.f.de[k + 1].y = h.beta * h.beta;
             S.tau[k] = h.tau;
         }
         bsync<MM>();
         double v[R / 16], w[R / 16];
 #pragma unroll
-        for (int g = 0; g < R / 16; ++g) v[g] = g >= B / 2 ? S.vr[0][16 * g + t.l15] : 0.0;
+        for (int g = 0; g < R / 16; ++g) v[g] = g >= B / 2 ? S.f.vr[0][16 * g + t.l15] : 0.0;
         // p = A v (entries of v up to row k are zero)
         double p0 = 0.0, p1 = 0.0;
 #pragma unroll
         for (int j = 0; j < R / 8; ++j)
             if (j >= B && (j <= B + 1 || 8 * j < m)) dot_rows<R>(a, j, v, p0, p1);
         double wi = cl > k ? h.tau * (p0 + p1) : 0.0;
-        const double s = wave_dot(wi, vi);
+        const double s = wave_dot<MM>(wi, vi);
         wi = fma(-0.5 * h.tau * s, vi, wi);
-        S.wr[0][c] = wi;
+        S.f.wr[0][c] = wi;
         bsync<MM>();
 #pragma unroll
-        for (int g = 0; g < R / 16; ++g) w[g] = g >= B / 2 ? S.wr[0][16 * g + t.l15] : 0.0;
+        for (int g = 0; g < R / 16; ++g) w[g] = g >= B / 2 ? S.f.wr[0][16 * g + t.l15] : 0.0;
         // A -= v w^T + w v^T
         const double nv = -vi, nw = -wi;
 #pragma unroll
@@ -496,7 +572,7 @@ __device__ __forceinline__ void tridiag_block(double (&a)[Lay<MM>::R], Shared<MM
             a[row] = vi;
             if constexpr (row + 1 < R) xi = a[row + 1];
         });
-        S.col[c] = xi;
+        S.f.col[c] = xi;
         bsync<MM>();
     }
     if constexpr (B + 1 < R / 8) tridiag_block<MM, B + 1>(a, S, t, m, cl, xi);
@@ -505,16 +581,17 @@ __device__ __forceinline__ void tridiag_block(double (&a)[Lay<MM>::R], Shared<MM
 template <int MM>
 __device__ __forceinline__ void tridiag_one(double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t, int m) {
     double xi = a[0];
-    S.col[t.c] = xi;
+    S.f.col[t.c] = xi;
     bsync<MM>();
     tridiag_block<MM, 0>(a, S, t, m, t.c < m ? t.c : -1, xi);
     // trailing 2 x 2 block: row m - 1
     at_row<0, Lay<MM>::R>(m - 1, [&](auto q) __attribute__((always_inline)) {
-        S.ww[t.c] = a[decltype(q)::value];
+        S.f.ww[t.c] = a[decltype(q)::value];
     });
 }
 
-// Four waves.  Every wave forms the reflector and both halves of p and w
+// Four waves.  The two waves that hold row k + 1 publish it with the sums of
+// its squares; every wave then forms the reflector and both halves of p and w
 // itself (the sums over a column block are the same bits wherever they are
 // formed), so a step needs two barriers: after the row-block partial sums of
 // p and after the next pivot column.
@@ -524,61 +601,70 @@ __device__ __forceinline__ void tridiag_four(double (&a)[Lay<MM>::R], Shared<MM>
     const int c = t.c, o = c ^ 64, r0 = 64 * t.rb, wv = 2 * t.rb + t.cb;
     const bool own = t.rb == t.cb;  // this wave's rows are its columns' block
     const int cl = c < m ? c : -1, ol = o < m ? o : -1;
-    if (t.rb == 0) S.col[c] = a[0];
+    // row k (held by this wave) as pivot column k: its entries and their tail's squared norm
+    auto publish = [&](double x, int k) {
+        S.f.col[c] = x;
+        const double n2 = wave_sum<MM>(cl > k + 1 ? x * x : 0.0);
+        if (t.lane == 0) S.f.nrm2[t.cb] = n2;
+    };
+    if (t.rb == 0) publish(a[0], 0);
     bsync<MM>();
 #pragma unroll 1
     for (int k = 0; k < m - 2; ++k) {
-        const double xc = S.col[c], xo = S.col[o];
-        const double alpha = S.col[k + 1], dk = S.col[k];
+        const double xc = S.f.col[c], xo = S.f.col[o];
+        const double alpha = S.f.col[k + 1], dk = S.f.col[k];
         const bool tc = cl > k + 1, to = ol > k + 1;
-        const double xnorm2 = wave_sum(tc ? xc * xc : 0.0) + wave_sum(to ? xo * xo : 0.0);
+        // columns up to k are done with: past k = 62 the whole first block
+        const bool live = t.cb == 1 || k < 63;
+        const double xnorm2 = S.f.nrm2[0] + S.f.nrm2[1];
         const Reflector h = reflector(alpha, xnorm2);
         const double vc = (c == k + 1) ? 1.0 : (tc ? xc * h.scal : 0.0);
         const double vo = (o == k + 1) ? 1.0 : (to ? xo * h.scal : 0.0);
-        S.vr[wv][t.lane] = own ? vc : vo;
+        S.f.vr[wv][t.lane] = own ? vc : vo;
         if (t.tid == 0) {
             S.d[k] = dk;
             S.e[k] = h.beta;
-            S.de[k].x = dk;
-            S.de[k + 1].y = h.beta * h.beta;
+            S.f.de[k].x = dk;
+            S.f.de[k + 1].y = h.beta * h.beta;
             S.tau[k] = h.tau;
         }
         wave_order();
         double v[R / 16], w[R / 16];
 #pragma unroll
-        for (int g = 0; g < R / 16; ++g) v[g] = S.vr[wv][16 * g + t.l15];
+        for (int g = 0; g < R / 16; ++g) v[g] = S.f.vr[wv][16 * g + t.l15];
         double p0 = 0.0, p1 = 0.0;
 #pragma unroll
         for (int j = 0; j < R / 8; ++j)
-            if (r0 + 8 * j + 8 > k + 1 && r0 + 8 * j < m) dot_rows<R>(a, j, v, p0, p1);
-        S.pp[t.rb][c] = p0 + p1;
+            if (r0 + 8 * j + 8 > k + 1 && r0 + 8 * j < m && live) dot_rows<R>(a, j, v, p0, p1);
+        S.f.pp[t.rb][c] = p0 + p1;
         bsync<MM>();
-        const double pc = S.pp[0][c] + S.pp[1][c], po = S.pp[0][o] + S.pp[1][o];
+        const double pc = S.f.pp[0][c] + S.f.pp[1][c], po = S.f.pp[0][o] + S.f.pp[1][o];
         double wc = cl > k ? h.tau * pc : 0.0, wo = ol > k ? h.tau * po : 0.0;
-        const double s = readlane64(wave_dot(wc, vc), 0) + readlane64(wave_dot(wo, vo), 0);
+        const double s = wave_dot_pair(wc, vc, wo, vo);
         wc = fma(-0.5 * h.tau * s, vc, wc);
         wo = fma(-0.5 * h.tau * s, vo, wo);
-        S.wr[wv][t.lane] = own ? wc : wo;
+        S.f.wr[wv][t.lane] = own ? wc : wo;
         wave_order();
 #pragma unroll
-        for (int g = 0; g < R / 16; ++g) w[g] = S.wr[wv][16 * g + t.l15];
+        for (int g = 0; g < R / 16; ++g) w[g] = S.f.wr[wv][16 * g + t.l15];
         const double nv = -vc, nw = -wc;
 #pragma unroll
         for (int j = 0; j < R / 8; ++j)
-            if (r0 + 8 * j + 8 > k + 1 && r0 + 8 * j < m) rank2_rows<R>(a, j, v, w, nv, nw);
+            if (r0 + 8 * j + 8 > k + 1 && r0 + 8 * j < m && live) rank2_rows<R>(a, j, v, w, nv, nw);
         if (t.rb == k >> 6)
             at_row<0, R>(k & 63, [&](auto q) __attribute__((always_inline)) {
                     a[decltype(q)::value] = vc;
             });
-        if (t.rb == (k + 1) >> 6)
-            at_row<0, R>((k + 1) & 63, [&](auto q) __attribute__((always_inline)) {
-                    S.col[c] = a[decltype(q)::value];
-            });
+        if (t.rb == (k + 1) >> 6) {
+            double x = 0.0;
+            at_row<0, R>((k + 1) & 63, [&](auto q) __attribute__((always_inline)) { x = a[decltype(q)::value]; });
+            publish(x, k + 1);
+        }
         bsync<MM>();
     }
     if (t.rb == (m - 1) >> 6)
         at_row<0, R>((m - 1) & 63, [&](auto q) __attribute__((always_inline)) {
-            S.ww[c] = a[decltype(q)::value];
+            S.f.ww[c] = a[decltype(q)::value];
         });
 }
 
@@ -589,18 +675,17 @@ __device__ __forceinline__ void tridiagonalise(double (&a)[Lay<MM>::R], Shared<M
     bsync<MM>();
     if (t.tid == 0) {
         if (m >= 2) {
-            S.d[m - 2] = S.de[m - 2].x = S.col[m - 2];
-            S.e[m - 2] = S.col[m - 1];
-            S.de[m - 1].y = S.col[m - 1] * S.col[m - 1];
+            S.d[m - 2] = S.f.de[m - 2].x = S.f.col[m - 2];
+            S.e[m - 2] = S.f.col[m - 1];
+            S.f.de[m - 1].y = S.f.col[m - 1] * S.f.col[m - 1];
         }
-        S.d[m - 1] = S.de[m - 1].x = S.ww[m - 1];
+        S.d[m - 1] = S.f.de[m - 1].x = S.f.ww[m - 1];
     }
     bsync<MM>();
 }
 
 // ------------------------------------------------------------ Sturm counts ----
-// Number of eigenvalues of T below sigma.  Wave-local: every wave of a
-// stencil may evaluate these (they read only S.d, S.e2).
+// Number of eigenvalues of T below sigma (wave-local).
 template <int MM>
 __device__ __forceinline__ int sturm(const Shared<MM>& S, int m, double sigma, double pivmin) {
     double q = S.d[0] - sigma;
@@ -608,12 +693,61 @@ __device__ __forceinline__ int sturm(const Shared<MM>& S, int m, double sigma, d
     int c = q < 0.0 ? 1 : 0;
 #pragma unroll 4
     for (int i = 1; i < m; ++i) {
-        const double2 de = S.de[i];
+        const double2 de = S.f.de[i];
         q = fma(-de.y, recip(q), de.x - sigma);
         if (fabs(q) < pivmin) q = -pivmin;
         c += q < 0.0 ? 1 : 0;
     }
     return c;
+}
+
+// Two shifts per lane.
+template <int MM>
+__device__ __forceinline__ void sturm2(const Shared<MM>& S, int m, double sa, double sb, double pivmin, int& ca,
+                                       int& cb) {
+    const double d0 = S.d[0];
+    double qa = d0 - sa, qb = d0 - sb;
+    if (fabs(qa) < pivmin) qa = -pivmin;
+    if (fabs(qb) < pivmin) qb = -pivmin;
+    ca = qa < 0.0 ? 1 : 0;
+    cb = qb < 0.0 ? 1 : 0;
+#pragma unroll 2
+    for (int i = 1; i < m; ++i) {
+        const double2 de = S.f.de[i];
+        qa = fma(-de.y, recip(qa), de.x - sa);
+        qb = fma(-de.y, recip(qb), de.x - sb);
+        if (fabs(qa) < pivmin) qa = -pivmin;
+        if (fabs(qb) < pivmin) qb = -pivmin;
+        ca += qa < 0.0 ? 1 : 0;
+        cb += qb < 0.0 ? 1 : 0;
+    }
+}
+
+// One multisection round: shift sig(l) and its test pass(l, count) for
+// l = 0..63; bit l of the result is the test's.  Each lane takes one l, or
+// two (lane and lane + 32) where a stencil has half a wavefront.
+template <int MM, typename F, typename P>
+__device__ __forceinline__ uint64_t sturm64(const Shared<MM>& S, int m, int lane, double pivmin, F&& sig, P&& pass) {
+    if constexpr (Lay<MM>::SPW == 1) {
+        return __ballot(pass(lane, sturm<MM>(S, m, sig(lane), pivmin)));
+    } else {
+        int c0, c1;
+        sturm2<MM>(S, m, sig(lane), sig(lane + 32), pivmin, c0, c1);
+        const int half = threadIdx.x & 32;
+        const uint64_t b0 = __ballot(pass(lane, c0)) >> half, b1 = __ballot(pass(lane + 32, c1)) >> half;
+        return (b0 & 0xffffffffull) | (b1 << 32);
+    }
+}
+// Lanes of the stencil for which p holds.
+template <int MM>
+__device__ __forceinline__ uint64_t stencil_ballot(bool p) {
+    const uint64_t b = __ballot(p);
+    return MM == 32 ? (b >> (threadIdx.x & 32)) & 0xffffffffull : b;
+}
+// Value of lane `l` (< 32) of the stencil's lanes in this wavefront.
+template <int MM>
+__device__ __forceinline__ int from_lane(int v, int l) {
+    return __shfl(v, l, Lay<MM>::LW);
 }
 
 struct Spectrum {
@@ -649,12 +783,13 @@ __device__ __forceinline__ void spectrum_refine(const Shared<MM>& S, int lane, S
         const bool need1 = !(lo2 > -lo1);  // lambda_1 can still be the largest in magnitude
         const bool need2 = !(-hi1 > hi2);  // lambda_m can
         if (need1 && need2) {
-            const int g = lane >> 5, tt = lane & 31;
-            const double lo = g ? lo2 : lo1, hi = g ? hi2 : hi1;
-            const double sig = lo + (hi - lo) * (double)(tt + 1) / 33.0;
-            const int kidx = g ? m : 1;
-            const bool below = sturm<MM>(S, m, sig, sp.pivmin) < kidx;  // eigenvalue kidx lies above sig
-            const uint64_t bal = __ballot(below);
+            const uint64_t bal = sturm64<MM>(
+                S, m, lane, sp.pivmin,
+                [&](int l) {
+                    const double lo = l >> 5 ? lo2 : lo1, hi = l >> 5 ? hi2 : hi1;
+                    return lo + (hi - lo) * (double)((l & 31) + 1) / 33.0;
+                },
+                [&](int l, int cnt) { return cnt < (l >> 5 ? m : 1); });  // the eigenvalue lies above the shift
             const int nb1 = __popcll(bal & 0xffffffffull);
             const int nb2 = __popcll(bal >> 32);
             const double n_lo1 = nb1 > 0 ? lo1 + (hi1 - lo1) * (double)nb1 / 33.0 : lo1;
@@ -664,9 +799,9 @@ __device__ __forceinline__ void spectrum_refine(const Shared<MM>& S, int lane, S
             lo1 = n_lo1; hi1 = n_hi1; lo2 = n_lo2; hi2 = n_hi2;
         } else {
             const double lo = need2 ? lo2 : lo1, hi = need2 ? hi2 : hi1;
-            const double sig = lo + (hi - lo) * (double)(lane + 1) / 65.0;
-            const bool below = sturm<MM>(S, m, sig, sp.pivmin) < (need2 ? m : 1);
-            const int nb = __popcll(__ballot(below));
+            const int nb = __popcll(sturm64<MM>(
+                S, m, lane, sp.pivmin, [&](int l) { return lo + (hi - lo) * (double)(l + 1) / 65.0; },
+                [&](int, int cnt) { return cnt < (need2 ? m : 1); }));
             const double n_lo = nb > 0 ? lo + (hi - lo) * (double)nb / 65.0 : lo;
             const double n_hi = nb < 64 ? lo + (hi - lo) * (double)(nb + 1) / 65.0 : hi;
             if (need2) {
@@ -694,21 +829,21 @@ __device__ __forceinline__ Spectrum spectrum_max(const Shared<MM>& S, int lane, 
     // lambda_1 <= min d_i and lambda_m >= max d_i
     double ngl = -INFINITY, gu = -INFINITY, emax2 = 0.0, dmax = -INFINITY, ndmin = -INFINITY;
     bool fin = true;
-    for (int i = lane; i < m; i += 64) {
+    for (int i = lane; i < m; i += Lay<MM>::LW) {
         const double off = (i > 0 ? fabs(S.e[i - 1]) : 0.0) + (i < m - 1 ? fabs(S.e[i]) : 0.0);
         ngl = fmax(ngl, off - S.d[i]);
         gu = fmax(gu, S.d[i] + off);
         dmax = fmax(dmax, S.d[i]);
         ndmin = fmax(ndmin, -S.d[i]);
-        if (i < m - 1) emax2 = fmax(emax2, S.de[i + 1].y);
+        if (i < m - 1) emax2 = fmax(emax2, S.f.de[i + 1].y);
         fin = fin && isfinite(S.d[i]) && (i == m - 1 || isfinite(S.e[i]));
     }
-    double gl = -wave_max(ngl);
-    gu = wave_max(gu);
-    dmax = wave_max(dmax);
-    const double dmin = -wave_max(ndmin);
-    emax2 = wave_max(emax2);
-    fin = __ballot(!fin) == 0;
+    double gl = -wave_max<MM>(ngl);
+    gu = wave_max<MM>(gu);
+    dmax = wave_max<MM>(dmax);
+    const double dmin = -wave_max<MM>(ndmin);
+    emax2 = wave_max<MM>(emax2);
+    fin = stencil_ballot<MM>(!fin) == 0;
     sp.finite = fin;
     sp.pivmin = 2.2250738585072014e-308 * fmax(1.0, emax2);
     const double w = gu - gl;
@@ -738,7 +873,7 @@ __device__ __forceinline__ void small_counts(const Shared<MM>& S, int lane, cons
     if (lane == 2) sig = -tau_b;
     if (lane == 3) sig = tau_b;
     const int c = lane < 4 ? sturm<MM>(S, m, sig, sp.pivmin) : 0;
-    const int c0 = __shfl(c, 0, 64), c1 = __shfl(c, 1, 64), c2 = __shfl(c, 2, 64), c3 = __shfl(c, 3, 64);
+    const int c0 = from_lane<MM>(c, 0), c1 = from_lane<MM>(c, 1), c2 = from_lane<MM>(c, 2), c3 = from_lane<MM>(c, 3);
     ca = c1 - c0;
     cb = c3 - c2;
 }
@@ -763,13 +898,15 @@ __device__ __forceinline__ double min_abs_refine(const Shared<MM>& S, int lane, 
         const double bhi = need_p ? (need_n ? fmin(hp, hn) : hp) : hn;
         if (!(bhi - blo > 2.0 * rel)) break;
         if (need_p && need_n) {
-            const int g = lane >> 5, tt = lane & 31;
-            const double lo = g ? ln_ : lp, hi = g ? hn : hp;
-            const double sig = exp(lo + (hi - lo) * (double)(tt + 1) / 33.0);
-            bool above;  // target magnitude lies above sig
-            if (g == 0) above = sturm<MM>(S, m, sig, sp.pivmin) <= nu;   // lambda_{nu+1} > sig
-            else above = sturm<MM>(S, m, -sig, sp.pivmin) >= nu;         // lambda_nu < -sig
-            const uint64_t bal = __ballot(above);
+            const uint64_t bal = sturm64<MM>(
+                S, m, lane, sp.pivmin,
+                [&](int l) {
+                    const double lo = l >> 5 ? ln_ : lp, hi = l >> 5 ? hn : hp;
+                    const double sig = exp(lo + (hi - lo) * (double)((l & 31) + 1) / 33.0);
+                    return l >> 5 ? -sig : sig;
+                },
+                // the target's magnitude lies above: lambda_{nu+1} > sig, or lambda_nu < -sig
+                [&](int l, int cnt) { return l >> 5 ? cnt >= nu : cnt <= nu; });
             const int nb1 = __popcll(bal & 0xffffffffull);
             const int nb2 = __popcll(bal >> 32);
             const double a1 = lp + (hp - lp) * (double)nb1 / 33.0, b1 = lp + (hp - lp) * (double)(nb1 + 1) / 33.0;
@@ -780,9 +917,13 @@ __device__ __forceinline__ double min_abs_refine(const Shared<MM>& S, int lane, 
             if (nb2 < 32) hn = b2;
         } else {
             const double lo = need_p ? lp : ln_, hi = need_p ? hp : hn;
-            const double sig = exp(lo + (hi - lo) * (double)(lane + 1) / 65.0);
-            const bool above = need_p ? sturm<MM>(S, m, sig, sp.pivmin) <= nu : sturm<MM>(S, m, -sig, sp.pivmin) >= nu;
-            const int nb = __popcll(__ballot(above));
+            const int nb = __popcll(sturm64<MM>(
+                S, m, lane, sp.pivmin,
+                [&](int l) {
+                    const double sig = exp(lo + (hi - lo) * (double)(l + 1) / 65.0);
+                    return need_p ? sig : -sig;
+                },
+                [&](int, int cnt) { return need_p ? cnt <= nu : cnt >= nu; }));
             const double a1 = lo + (hi - lo) * (double)nb / 65.0, b1 = lo + (hi - lo) * (double)(nb + 1) / 65.0;
             const double n_lo = nb > 0 ? a1 : lo, n_hi = nb < 64 ? b1 : hi;
             if (need_p) {
@@ -818,22 +959,27 @@ __device__ __forceinline__ void band_counts_min(const Shared<MM>& S, int lane, c
                                                 double& ln_, double& hn) {
     const int m = stencil_m<MM>(S);
     const double l0 = log(tau_b), l1 = log(tau_a);
-    double sig = 0.0;
-    if (lane == 0) sig = -tau_a;
-    if (lane == 1) sig = tau_a;
-    if (lane == 2) sig = -tau_b;
-    if (lane == 3) sig = tau_b;
-    const bool pos_lane = lane >= 8 && lane < 36, neg_lane = lane >= 36;
-    if (pos_lane) sig = exp(l0 + (l1 - l0) * (double)(lane - 8 + 1) / 29.0);
-    if (neg_lane) sig = -exp(l0 + (l1 - l0) * (double)(lane - 36 + 1) / 29.0);
-    const int c = (lane < 5 || lane >= 8) ? sturm<MM>(S, m, sig, sp.pivmin) : 0;
-    const int c0 = __shfl(c, 0, 64), c1 = __shfl(c, 1, 64), c2 = __shfl(c, 2, 64), c3 = __shfl(c, 3, 64);
+    auto shift = [&](int l) {
+        double sig = 0.0;
+        if (l == 0) sig = -tau_a;
+        if (l == 1) sig = tau_a;
+        if (l == 2) sig = -tau_b;
+        if (l == 3) sig = tau_b;
+        if (l >= 8 && l < 36) sig = exp(l0 + (l1 - l0) * (double)(l - 8 + 1) / 29.0);
+        if (l >= 36) sig = -exp(l0 + (l1 - l0) * (double)(l - 36 + 1) / 29.0);
+        return sig;
+    };
+    int c_lane = 0;  // the count of this lane's first shift
+    const uint64_t bal = sturm64<MM>(S, m, lane, sp.pivmin, shift, [&](int l, int cnt) {
+        if (l < 32) c_lane = cnt;
+        if (l < Lay<MM>::LW) nu = from_lane<MM>(cnt, 4);
+        // lambda_{nu+1} > sig (positive shifts), lambda_nu < sig (negative ones)
+        return l < 8 ? false : (l < 36 ? cnt <= nu : cnt >= nu);
+    });
+    const int c0 = from_lane<MM>(c_lane, 0), c1 = from_lane<MM>(c_lane, 1);
+    const int c2 = from_lane<MM>(c_lane, 2), c3 = from_lane<MM>(c_lane, 3);
     ca = c1 - c0;
     cb = c3 - c2;
-    nu = __shfl(c, 4, 64);
-    // lambda_{nu+1} > sig (positive lanes), lambda_nu < sig (negative lanes)
-    const bool above = pos_lane ? c <= nu : (neg_lane ? c >= nu : false);
-    const uint64_t bal = __ballot(above);
     const int nb1 = __popcll((bal >> 8) & 0xfffffffull);
     const int nb2 = __popcll(bal >> 36);
     lp = l0; hp = l1; ln_ = l0; hn = l1;
@@ -871,29 +1017,29 @@ __device__ __forceinline__ bool tri_factor(Shared<MM>& S) {
             if (dcur == 0.0) return false;
             const double rp = recip(dcur);
             const double f = sub * rp;
-            S.fd[i] = rp;                      // reciprocal of the pivot
-            S.fdu[i] = ucur;
-            S.fdl[i] = 0.0;
-            S.ffact[i] = f;
-            S.fswap[i] = 0;
+            S.g.fd[i] = rp;                      // reciprocal of the pivot
+            S.g.fdu[i] = ucur;
+            S.g.fdl[i] = 0.0;
+            S.g.ffact[i] = f;
+            S.g.fswap[i] = 0;
             dcur = dnext - f * ucur;
             ucur = unext;
         } else {                               // swap rows i and i + 1
             const double rp = recip(sub);
             const double f = dcur * rp;
-            S.fd[i] = rp;
-            S.fdu[i] = dnext;
-            S.fdl[i] = i < m - 2 ? unext : 0.0;  // second super-diagonal
-            S.ffact[i] = f;
-            S.fswap[i] = 1;
+            S.g.fd[i] = rp;
+            S.g.fdu[i] = dnext;
+            S.g.fdl[i] = i < m - 2 ? unext : 0.0;  // second super-diagonal
+            S.g.ffact[i] = f;
+            S.g.fswap[i] = 1;
             dcur = ucur - f * dnext;
             ucur = i < m - 2 ? -f * unext : unext;
         }
     }
     if (dcur == 0.0) return false;
-    S.fd[m - 1] = recip(dcur);
-    S.fdu[m - 1] = 0.0;
-    S.fdl[m - 1] = 0.0;
+    S.g.fd[m - 1] = recip(dcur);
+    S.g.fdu[m - 1] = 0.0;
+    S.g.fdl[m - 1] = 0.0;
     return true;
 }
 
@@ -904,9 +1050,9 @@ __device__ __forceinline__ void tri_solve(const Shared<MM>& S, double* b) {
     const int m = stencil_m<MM>(S);
     double bi = b[0];
     for (int i = 0; i < m - 1; ++i) {
-        const double f = S.ffact[i];
+        const double f = S.g.ffact[i];
         const double bn = b[i + 1];
-        if (!S.fswap[i]) {
+        if (!S.g.fswap[i]) {
             b[i] = bi;
             bi = bn - f * bi;
         } else {
@@ -914,14 +1060,14 @@ __device__ __forceinline__ void tri_solve(const Shared<MM>& S, double* b) {
             bi = bi - f * bn;
         }
     }
-    double x1 = bi * S.fd[m - 1];  // x_{i+1}
+    double x1 = bi * S.g.fd[m - 1];  // x_{i+1}
     b[m - 1] = x1;
     if (m < 2) return;
     double x2 = x1;                // x_{i+2}
-    x1 = (b[m - 2] - S.fdu[m - 2] * x2) * S.fd[m - 2];
+    x1 = (b[m - 2] - S.g.fdu[m - 2] * x2) * S.g.fd[m - 2];
     b[m - 2] = x1;
     for (int i = m - 3; i >= 0; --i) {
-        const double x = (b[i] - S.fdu[i] * x1 - S.fdl[i] * x2) * S.fd[i];
+        const double x = (b[i] - S.g.fdu[i] * x1 - S.g.fdl[i] * x2) * S.g.fd[i];
         b[i] = x;
         x2 = x1;
         x1 = x;
@@ -942,9 +1088,9 @@ __device__ __forceinline__ void apply_q(const double (&a)[Lay<MM>::R], Shared<MM
             if constexpr (MM <= 64) {
                 v = a[k];
             } else {
-                if (t.rb == k / 64) S.vb[t.c] = a[k % 64];
+                if (t.rb == k / 64) S.g.vb[t.c] = a[k % 64];
                 bsync<MM>();
-                v = S.vb[t.c];
+                v = S.g.vb[t.c];
             }
             if constexpr (NV == 3) {
                 double s0 = v * y[0], s1 = v * y[1], s2 = v * y[2];
@@ -973,8 +1119,8 @@ __device__ __forceinline__ void apply_q_blocked(const double (&a)[Lay<MM>::R], S
     static_assert(MM <= 64, "one-wave tiling only");
     const int p = stencil_m<MM>(S) - 2;
 #pragma unroll
-    for (int bb = 0; bb < 16; ++bb) {
-        const int b = FWD ? bb : 15 - bb;
+    for (int bb = 0; bb < Lay<MM>::R / 4; ++bb) {
+        const int b = FWD ? bb : Lay<MM>::R / 4 - 1 - bb;
         const int k0 = 4 * b;
         if (k0 < p) {
             const double v0 = a[k0], v1 = k0 + 1 < p ? a[k0 + 1] : 0.0;
@@ -990,8 +1136,8 @@ __device__ __forceinline__ void apply_q_blocked(const double (&a)[Lay<MM>::R], S
                 d[q][3] = v3 * y[q];
             }
 #pragma unroll
-            for (int q = 0; q < NV; ++q) wave_sum4(d[q][0], d[q][1], d[q][2], d[q][3]);
-            const double* G = S.G + 6 * b;  // G01 G02 G03 G12 G13 G23
+            for (int q = 0; q < NV; ++q) wave_sum4<MM>(d[q][0], d[q][1], d[q][2], d[q][3]);
+            const double* G = S.g.G + 6 * b;  // G01 G02 G03 G12 G13 G23
             const double g01 = G[0], g02 = G[1], g03 = G[2], g12 = G[3], g13 = G[4], g23 = G[5];
 #pragma unroll
             for (int q = 0; q < NV; ++q) {
@@ -1019,17 +1165,17 @@ __device__ __forceinline__ void reflector_gram(const double (&a)[Lay<MM>::R], Sh
     static_assert(MM <= 64, "one-wave tiling only");
     const int p = stencil_m<MM>(S) - 2;
 #pragma unroll
-    for (int b = 0; b < 16; ++b) {
+    for (int b = 0; b < Lay<MM>::R / 4; ++b) {
         const int k0 = 4 * b;
         if (k0 < p) {
             const double v0 = a[k0], v1 = k0 + 1 < p ? a[k0 + 1] : 0.0;
             const double v2 = k0 + 2 < p ? a[k0 + 2] : 0.0, v3 = k0 + 3 < p ? a[k0 + 3] : 0.0;
             double g01 = v0 * v1, g02 = v0 * v2, g03 = v0 * v3, g12 = v1 * v2;
             double g13 = v1 * v3, g23 = v2 * v3, z0 = 0.0, z1 = 0.0;
-            wave_sum4(g01, g02, g03, g12);
-            wave_sum4(g13, g23, z0, z1);
+            wave_sum4<MM>(g01, g02, g03, g12);
+            wave_sum4<MM>(g13, g23, z0, z1);
             if (t.tid == 0) {
-                double* G = S.G + 6 * b;
+                double* G = S.g.G + 6 * b;
                 G[0] = g01; G[1] = g02; G[2] = g03; G[3] = g12; G[4] = g13; G[5] = g23;
             }
         }
@@ -1045,13 +1191,13 @@ __device__ __forceinline__ void solve(const double (&a)[Lay<MM>::R], Shared<MM>&
     else apply_q<MM, NV, true>(a, S, t, y);
     if (t.rb == 0) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) S.rhs[v][t.c] = y[v];
+        for (int v = 0; v < NV; ++v) S.g.rhs[v][t.c] = y[v];
     }
     bsync<MM>();
-    if (t.tid < NV) tri_solve<MM>(S, S.rhs[t.tid]);
+    if (t.tid < NV) tri_solve<MM>(S, S.g.rhs[t.tid]);
     bsync<MM>();
 #pragma unroll
-    for (int v = 0; v < NV; ++v) y[v] = t.c < m ? S.rhs[v][t.c] : 0.0;
+    for (int v = 0; v < NV; ++v) y[v] = t.c < m ? S.g.rhs[v][t.c] : 0.0;
     bsync<MM>();
     if constexpr (MM <= 64) apply_q_blocked<MM, NV, false>(a, S, y);
     else apply_q<MM, NV, false>(a, S, t, y);
@@ -1059,7 +1205,7 @@ __device__ __forceinline__ void solve(const double (&a)[Lay<MM>::R], Shared<MM>&
 
 // (A~ z) row t.c for NV vectors read from S.zb; A~ re-evaluated from the nodes
 template <int K, int MM, int NV>
-__device__ __forceinline__ void matvec_lds(const Shared<MM>& S, const Tid& t, double e2, double (&out)[3]) {
+__device__ __forceinline__ void matvec_lds(const Shared<MM>& S, const Tid& t, double e2, int us, double (&out)[3]) {
     const int n = stencil_n<MM>(S), m = stencil_m<MM>(S), r = S.r, c = t.c;
     out[0] = out[1] = out[2] = 0.0;
     if (c < n) {
@@ -1068,19 +1214,19 @@ __device__ __forceinline__ void matvec_lds(const Shared<MM>& S, const Tid& t, do
             const double dx = xi - S.x[j], dy = yi - S.y[j], dz = zi - S.z[j];
             const double av = rbf_phi<K>(e2, (dx * dx + dy * dy) + dz * dz);
 #pragma unroll
-            for (int v = 0; v < NV; ++v) out[v] = fma(av, S.zb[j], out[v]);
+            for (int v = 0; v < NV; ++v) out[v] = fma(av, S.g.zb[j], out[v]);
         }
         for (int k = 0; k < r; ++k) {
-            const double u = S.U[c * RMAX + k];
+            const double u = S.U[c * us + k];
 #pragma unroll
-            for (int v = 0; v < NV; ++v) out[v] = fma(u, S.zb[n + k], out[v]);
+            for (int v = 0; v < NV; ++v) out[v] = fma(u, S.g.zb[n + k], out[v]);
         }
     } else if (c < m) {
         const int k = c - n;
         for (int j = 0; j < n; ++j) {
-            const double u = S.U[j * RMAX + k];
+            const double u = S.U[j * us + k];
 #pragma unroll
-            for (int v = 0; v < NV; ++v) out[v] = fma(u, S.zb[j], out[v]);
+            for (int v = 0; v < NV; ++v) out[v] = fma(u, S.g.zb[j], out[v]);
         }
     }
 }
@@ -1090,17 +1236,17 @@ __device__ __forceinline__ void matvec_lds(const Shared<MM>& S, const Tid& t, do
 // partial pivoting on these ill-conditioned saddle systems; one step brings it
 // to that level.
 template <int K, int MM, int NV>
-__device__ __forceinline__ void solve_refined(const double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t, double e2,
+__device__ __forceinline__ void solve_refined(const double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t, double e2, int us,
                                               double (&y)[3]) {
     const double b[3] = {y[0], y[1], y[2]};
     solve<MM, NV>(a, S, t, y);
     if (t.rb == 0) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) S.zb[t.c] = y[v];
+        for (int v = 0; v < NV; ++v) S.g.zb[t.c] = y[v];
     }
     bsync<MM>();
     double az[3];
-    matvec_lds<K, MM, NV>(S, t, e2, az);
+    matvec_lds<K, MM, NV>(S, t, e2, us, az);
     bsync<MM>();
     double r[3] = {0.0, 0.0, 0.0};
 #pragma unroll
@@ -1128,7 +1274,7 @@ __device__ __forceinline__ void build_border(Shared<MM>& S, const Tid& t, int de
     const int n = stencil_n<MM>(S);
     const int jr = 64 * t.rb + t.lane;
     if (degree == 0) {
-        if (t.cb == 0 && jr < n) S.U[jr * RMAX] = 1.0;
+        if (t.cb == 0 && jr < n) S.U[jr] = 1.0;
         if (t.tid < RMAX) S.T[t.tid * RMAX] = t.tid == 0 ? 1.0 : 0.0;
         if (t.tid == 0) S.r = 1;
         bsync<MM>();
@@ -1177,7 +1323,7 @@ __device__ __forceinline__ void build_border(Shared<MM>& S, const Tid& t, int de
                 u[l] *= inv;
                 tc[l] *= inv;
                 keep[l] = true;
-                if (act && t.cb == 0) S.U[jr * RMAX + r] = u[l];
+                if (act && t.cb == 0) S.U[jr * M + r] = u[l];
                 if (t.tid < RMAX) S.T[t.tid * RMAX + r] = tc[l];
                 ++r;
             }
@@ -1188,14 +1334,6 @@ __device__ __forceinline__ void build_border(Shared<MM>& S, const Tid& t, int de
 }
 
 // ------------------------------------------------------ kappa evaluations ----
-template <int K, int MM>
-__device__ __forceinline__ Spectrum eval_spectrum(double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t, double eps,
-                                                  int rounds, double rel = 0.0) {
-    build_matrix<K, MM>(a, S, t, eps * eps);
-    tridiagonalise<MM>(a, S, t, stencil_m<MM>(S));
-    return spectrum_max<MM>(S, t.lane, rounds, rel);
-}
-
 // kappa_2(T) > target ?  (non-finite counts as above, like an infinite kappa)
 // kappa > target exactly when some |lambda| < max|lambda| / target.  With
 // max |lambda| known to lie in [alo, ahi], an eigenvalue below alo / target
@@ -1222,6 +1360,249 @@ __device__ __forceinline__ bool kappa_above(const Shared<MM>& S, int lane, Spect
 }
 
 // --------------------------------------------------------------- stencil ----
+// What process_stencil found before the search: the thread's node, its unit
+// normal and scaled offset, the stencil radius, and whether nodes coincide.
+struct Gathered {
+    double px, py, pz, nx, ny, nz, xi, yi, zi, rho, irho, dupf;
+};
+
+// Shape parameter, kappa_2 and weights of stencil s (see process_stencil).
+template <int K, int MM>
+__device__ __forceinline__ void solve_stencil(const Job& J, int64_t s, Shared<MM>& S, const Tid& t,
+                                              const Gathered& G0) {
+    const WOpts& o = J.o;
+    const int n = o.n, c = t.c, us = border_cols(o.degree);
+    const double px = G0.px, py = G0.py, pz = G0.pz, nx = G0.nx, ny = G0.ny, nz = G0.nz;
+    const double xi = G0.xi, yi = G0.yi, zi = G0.zi, rho = G0.rho, irho = G0.irho, dupf = G0.dupf;
+    int status = RBFFD_ST_OK;
+    int evals = 0;
+    double a[Lay<MM>::R];
+    double eps;
+    if (dupf > 0.0) status = RBFFD_ST_DUPLICATE;
+
+    // ---- shape parameter: one evaluation (matrix, tridiagonal form, max |lambda|)
+    // per turn of the loop, so that its code is in the kernel once
+    enum Phase { LEARN, LOW, HIGH, MID, FINAL };
+    double amin_known = 0.0;  // min |lambda| if already found
+    double lo = 0.0, hi = 0.0;
+    int ph = FINAL, q = 0;
+    if (o.mode == RBFFD_EPS_FIXED) {
+        eps = o.eps_fixed;
+    } else if (o.mode == RBFFD_EPS_GIVEN) {
+        eps = J.eps_in[s];
+    } else {
+        lo = o.br_lo / rho;
+        hi = o.br_hi / rho;
+        eps = lo;
+        ph = LOW;
+        if (o.mode == RBFFD_EPS_LEARNED) {
+            const double e = J.eps_in[s];
+            if (isfinite(e) && e > 0.0) {
+                eps = e;
+                ph = LEARN;
+            } else if (status == RBFFD_ST_OK) {
+                status = RBFFD_ST_FALLBACK;
+            }
+        }
+    }
+    Spectrum sp{};
+    // What follows an evaluation: the next eps (false) or the end (true).
+    auto advance = [&]() __attribute__((always_inline)) {
+        // max |lambda| of a proposal to band_rel: also the reported kappa's if kept
+        sp = spectrum_max<MM>(S, t.lane, ph == FINAL || ph == LEARN ? 8 : 2, ph == LEARN ? o.band_rel : 0.0);
+        ++evals;
+        if (ph == FINAL) return true;
+        const bool good = sp.finite && sp.amax > 0.0;
+        if (ph == LEARN) {
+            if (good) {
+                int c_lo, c_hi, nu;  // |lambda| below amax/band_lo and below amax/band_hi
+                const double tau_lo = sp.amax / o.band_lo, tau_hi = sp.amax / o.band_hi;
+                double lp, hp, ln_, hn;
+                band_counts_min<MM>(S, t.lane, sp, tau_lo, tau_hi, c_lo, c_hi, nu, lp, hp, ln_, hn);
+                if (c_lo > 0 && c_hi == 0) {  // band_lo < kappa <= band_hi
+                    // min |lambda| lies in [tau_hi, tau_lo): its first round is done
+                    amin_known = min_abs_refine<MM>(S, t.lane, sp, nu, lp, hp, ln_, hn, 6, o.band_rel);
+                    return true;
+                }
+            }
+            if (status == RBFFD_ST_OK) status = RBFFD_ST_FALLBACK;
+            eps = lo;
+            ph = LOW;
+            return false;
+        }
+        if (ph == MID && o.band_stop && good) {
+            int c_lo, c_hi;
+            small_counts<MM>(S, t.lane, sp, sp.amax / o.band_lo, sp.amax / o.band_hi, c_lo, c_hi);
+            if (c_lo > 0 && c_hi == 0) {
+                // six more rounds: the same brackets as eight from the start,
+                // full precision for the reported kappa
+                spectrum_refine<MM>(S, t.lane, sp, 6);
+                return true;
+            }
+        }
+        const bool above = kappa_above<MM>(S, t.lane, sp, o.kappa_target);
+        if (ph == LOW) {
+            if (!above && q < o.max_expand) {
+                ++q;
+                lo *= 0.5;
+                eps = lo;
+                return false;
+            }
+            if (!above && status == RBFFD_ST_OK) status = RBFFD_ST_NO_BRACKET;
+            q = 0;
+            eps = hi;
+            ph = HIGH;
+            return false;
+        }
+        if (ph == HIGH) {
+            if (above && q < o.max_expand) {
+                ++q;
+                hi *= 2.0;
+                eps = hi;
+                return false;
+            }
+            if (above && status == RBFFD_ST_OK) status = RBFFD_ST_NO_BRACKET;
+        } else if (above) {
+            lo = eps;
+        } else {
+            hi = eps;
+        }
+        ph = hi - lo > o.eps_tol ? MID : FINAL;
+        eps = 0.5 * (lo + hi);
+        return false;
+    };
+    // With four waves the first one searches alone (the other three would
+    // only repeat it) and hands over eps.
+    const bool lead = MM <= 64 || t.rb + t.cb == 0;
+    for (;;) {
+        build_matrix<K, MM>(a, S, t, eps * eps, us);
+        tridiagonalise<MM>(a, S, t, stencil_m<MM>(S));
+        bool done = false;
+        if (lead) done = advance();
+        if constexpr (MM == 128) {
+            if (t.tid == 0) {
+                S.eps = eps;
+                S.done = done;
+            }
+            bsync<MM>();
+            eps = S.eps;
+            done = __builtin_amdgcn_readfirstlane(S.done);
+        }
+        if (done) break;
+    }
+    // ---- kappa_2 at the final eps
+    double kappa = NAN;
+    if (!lead) {
+        // outputs and the status are the first wave's
+    } else if (sp.finite && sp.amax > 0.0) {
+        const double amin = amin_known > 0.0 ? amin_known : spectrum_min_abs<MM>(S, t.lane, sp);
+        kappa = sp.amax / amin;
+    } else if (status == RBFFD_ST_OK) {
+        status = RBFFD_ST_NONFINITE;
+    }
+    if (lead && !sp.finite && status == RBFFD_ST_OK) status = RBFFD_ST_NONFINITE;
+    if (t.tid == 0) {
+        if (J.eps) J.eps[s] = eps;
+        if (J.kappa) J.kappa[s] = kappa;
+        if (J.nevals) J.nevals[s] = evals;
+    }
+    if (J.kappa_only) {
+        if (t.tid == 0 && J.status) J.status[s] = status;
+        bsync<MM>();
+        return;
+    }
+
+    // ---- weights: w = (A~^{-1} r)[:n], r = sum_d (B^d)^T g_d, g_d = (A~^{-1} b_d)[:n]
+    if (t.tid == 0) S.fact_ok = sp.finite ? (int)tri_factor<MM>(S) : 0;
+    bsync<MM>();
+    const int m = stencil_m<MM>(S);
+    if (!S.fact_ok) {
+        if (status == RBFFD_ST_OK) status = sp.finite ? RBFFD_ST_SINGULAR : RBFFD_ST_NONFINITE;
+        if (t.tid == 0 && J.status) J.status[s] = status;
+        if (c < n && t.rb == 0) J.w[s * n + c] = NAN;
+        bsync<MM>();
+        return;
+    }
+    const double e2 = eps * eps;
+    const double n0x = S.nrm0[0], n0y = S.nrm0[1], n0z = S.nrm0[2];
+    // b_d (row 1 of B^d) as an m-vector, component c
+    double b[3] = {0.0, 0.0, 0.0};
+    if (c < n) {
+        const double dx = S.x[0] - px, dy = S.y[0] - py, dz = S.z[0] - pz;  // x_1 - x_j
+        const double r2 = (dx * dx + dy * dy) + dz * dz;
+        const double ps = rbf_psi<K>(e2, r2);
+        const double dn = n0x * dx + n0y * dy + n0z * dz;
+        b[0] = ps * (dx - n0x * dn);
+        b[1] = ps * (dy - n0y * dn);
+        b[2] = ps * (dz - n0z * dn);
+    } else if (c < m && o.degree > 0) {
+        const int k = c - n;  // grad q_k at the centre (xi = 0): linear coefficients / rho
+        const double gx = S.T[1 * RMAX + k] * irho, gy = S.T[2 * RMAX + k] * irho, gz = S.T[3 * RMAX + k] * irho;
+        const double dn = n0x * gx + n0y * gy + n0z * gz;
+        b[0] = gx - n0x * dn;
+        b[1] = gy - n0y * dn;
+        b[2] = gz - n0z * dn;
+    }
+    if constexpr (MM <= 64) reflector_gram<MM>(a, S, t);
+    // g_d: plain solve.  Refining this solve as well as the final one does not
+    // lower the error of w (measured against 60-digit weights: both ways
+    // 0.02-0.07 kappa u at kappa_T = 1e10 and 1e12; without any refinement
+    // 0.1-0.28 kappa u), so only the final solve is refined.
+    solve<MM, 3>(a, S, t, b);
+    // h_i = Pi_i g_i
+    double hx = 0, hy = 0, hz = 0;
+    if (c < n) {
+        const double dn = nx * b[0] + ny * b[1] + nz * b[2];
+        hx = b[0] - nx * dn;
+        hy = b[1] - ny * dn;
+        hz = b[2] - nz * dn;
+    }
+    if (t.rb == 0) {
+        S.h(0)[c] = hx;
+        S.h(1)[c] = hy;
+        S.h(2)[c] = hz;
+    }
+    bsync<MM>();
+    // r_j = sum_i psi(r_ij) (x_i - x_j) . h_i   (j = c < n)
+    double rj = 0.0;
+    const double *hs0 = S.h(0), *hs1 = S.h(1), *hs2 = S.h(2);
+    if (c < n) {
+#pragma unroll 4
+        for (int i = 0; i < n; ++i) {
+            const double dx = S.x[i] - px, dy = S.y[i] - py, dz = S.z[i] - pz;
+            const double r2 = (dx * dx + dy * dy) + dz * dz;
+            const double ps = rbf_psi<K>(e2, r2);
+            rj = fma(ps, dx * hs0[i] + dy * hs1[i] + dz * hs2[i], rj);
+        }
+    }
+    // r_{n+k} = sum_i grad q_k(x_i) . h_i
+    if (o.degree > 0) {
+        const int r = S.r;
+        for (int k = 0; k < r; ++k) {
+            double cv = 0.0;
+            if (c < n) {
+                const double* T = S.T;
+                double gx = T[1 * RMAX + k], gy = T[2 * RMAX + k], gz = T[3 * RMAX + k];
+                if (o.degree == 2) {
+                    const double t4 = T[4 * RMAX + k], t5 = T[5 * RMAX + k], t6 = T[6 * RMAX + k];
+                    const double t7 = T[7 * RMAX + k], t8 = T[8 * RMAX + k], t9 = T[9 * RMAX + k];
+                    gx += 2.0 * t4 * xi + t7 * yi + t8 * zi;
+                    gy += 2.0 * t5 * yi + t7 * xi + t9 * zi;
+                    gz += 2.0 * t6 * zi + t8 * xi + t9 * yi;
+                }
+                cv = (gx * hx + gy * hy + gz * hz) * irho;
+            }
+            cv = sum_cols<MM>(cv, S, t);
+            if (c == n + k) rj = cv;
+        }
+    }
+    double wv[3] = {rj, 0.0, 0.0};
+    solve_refined<K, MM, 1>(a, S, t, e2, us, wv);
+    if (c < n && t.rb == 0) J.w[s * n + c] = wv[0];
+    if (t.tid == 0 && J.status) J.status[s] = status;
+    bsync<MM>();
+}
+
 // The whole computation for stencil s of job J by the waves of one stencil.
 template <int K, int MM>
 __device__ __forceinline__ void process_stencil(const Job& J, int64_t s, Shared<MM>& S, const Tid& t) {
@@ -1291,209 +1672,21 @@ __device__ __forceinline__ void process_stencil(const Job& J, int64_t s, Shared<
     build_border<MM>(S, t, o.degree, o.rank_tol, xr, yr, zr);
     if (t.tid == 0) S.m = n + S.r;
     bsync<MM>();
-    int status = RBFFD_ST_OK;
-    int evals = 0;
-    double a[Lay<MM>::R];
-    double eps;
-    if (dupf > 0.0) status = RBFFD_ST_DUPLICATE;
-
-    // ---- shape parameter: one evaluation (matrix, tridiagonal form, max |lambda|)
-    // per turn of the loop, so that its code is in the kernel once
-    enum Phase { LEARN, LOW, HIGH, MID, FINAL };
-    double amin_known = 0.0;  // min |lambda| if already found
-    double lo = 0.0, hi = 0.0;
-    int ph = FINAL, q = 0;
-    if (o.mode == RBFFD_EPS_FIXED) {
-        eps = o.eps_fixed;
-    } else if (o.mode == RBFFD_EPS_GIVEN) {
-        eps = J.eps_in[s];
+    const Gathered G{px, py, pz, nx, ny, nz, xi, yi, zi, rho, irho, dupf};
+    if constexpr (Lay<MM>::SPW == 1) {
+        solve_stencil<K, MM>(J, s, S, t, G);
     } else {
-        lo = o.br_lo / rho;
-        hi = o.br_hi / rho;
-        eps = lo;
-        ph = LOW;
-        if (o.mode == RBFFD_EPS_LEARNED) {
-            const double e = J.eps_in[s];
-            if (isfinite(e) && e > 0.0) {
-                eps = e;
-                ph = LEARN;
-            } else if (status == RBFFD_ST_OK) {
-                status = RBFFD_ST_FALLBACK;
-            }
+        // m differs between the halves only where one of them dropped a border
+        // column: then they run one after the other, so that m bounds the
+        // loops as a scalar.  The loop runs on the mask of the lanes left, a
+        // scalar: a loop on a lane's own flag gets merged into one pass.
+        const int m = S.m;
+        for (uint64_t left = __ballot(true); left;) {
+            const int mu = __builtin_amdgcn_readlane(m, __builtin_ctzll(left));
+            if (m == mu) solve_stencil<K, MM>(J, s, S, t, G);
+            left &= ~__ballot(m == mu);
         }
     }
-    Spectrum sp;
-    for (;;) {
-        // max |lambda| of a proposal to band_rel: also the reported kappa's if kept
-        sp = eval_spectrum<K, MM>(a, S, t, eps, ph == FINAL || ph == LEARN ? 8 : 2, ph == LEARN ? o.band_rel : 0.0);
-        ++evals;
-        if (ph == FINAL) break;
-        const bool good = sp.finite && sp.amax > 0.0;
-        if (ph == LEARN) {
-            if (good) {
-                int c_lo, c_hi, nu;  // |lambda| below amax/band_lo and below amax/band_hi
-                const double tau_lo = sp.amax / o.band_lo, tau_hi = sp.amax / o.band_hi;
-                double lp, hp, ln_, hn;
-                band_counts_min<MM>(S, t.lane, sp, tau_lo, tau_hi, c_lo, c_hi, nu, lp, hp, ln_, hn);
-                if (c_lo > 0 && c_hi == 0) {  // band_lo < kappa <= band_hi
-                    // min |lambda| lies in [tau_hi, tau_lo): its first round is done
-                    amin_known = min_abs_refine<MM>(S, t.lane, sp, nu, lp, hp, ln_, hn, 6, o.band_rel);
-                    break;
-                }
-            }
-            if (status == RBFFD_ST_OK) status = RBFFD_ST_FALLBACK;
-            eps = lo;
-            ph = LOW;
-            continue;
-        }
-        if (ph == MID && o.band_stop && good) {
-            int c_lo, c_hi;
-            small_counts<MM>(S, t.lane, sp, sp.amax / o.band_lo, sp.amax / o.band_hi, c_lo, c_hi);
-            if (c_lo > 0 && c_hi == 0) {
-                // six more rounds: the same brackets as eight from the start,
-                // full precision for the reported kappa
-                spectrum_refine<MM>(S, t.lane, sp, 6);
-                break;
-            }
-        }
-        const bool above = kappa_above<MM>(S, t.lane, sp, o.kappa_target);
-        if (ph == LOW) {
-            if (!above && q < o.max_expand) {
-                ++q;
-                lo *= 0.5;
-                eps = lo;
-                continue;
-            }
-            if (!above && status == RBFFD_ST_OK) status = RBFFD_ST_NO_BRACKET;
-            q = 0;
-            eps = hi;
-            ph = HIGH;
-            continue;
-        }
-        if (ph == HIGH) {
-            if (above && q < o.max_expand) {
-                ++q;
-                hi *= 2.0;
-                eps = hi;
-                continue;
-            }
-            if (above && status == RBFFD_ST_OK) status = RBFFD_ST_NO_BRACKET;
-        } else if (above) {
-            lo = eps;
-        } else {
-            hi = eps;
-        }
-        ph = hi - lo > o.eps_tol ? MID : FINAL;
-        eps = 0.5 * (lo + hi);
-    }
-    // ---- kappa_2 at the final eps
-    double kappa = NAN;
-    if (sp.finite && sp.amax > 0.0) {
-        const double amin = amin_known > 0.0 ? amin_known : spectrum_min_abs<MM>(S, t.lane, sp);
-        kappa = sp.amax / amin;
-    } else if (status == RBFFD_ST_OK) {
-        status = RBFFD_ST_NONFINITE;
-    }
-    if (!sp.finite && status == RBFFD_ST_OK) status = RBFFD_ST_NONFINITE;
-    if (t.tid == 0) {
-        if (J.eps) J.eps[s] = eps;
-        if (J.kappa) J.kappa[s] = kappa;
-        if (J.nevals) J.nevals[s] = evals;
-    }
-    if (J.kappa_only) {
-        if (t.tid == 0 && J.status) J.status[s] = status;
-        bsync<MM>();
-        return;
-    }
-
-    // ---- weights: w = (A~^{-1} r)[:n], r = sum_d (B^d)^T g_d, g_d = (A~^{-1} b_d)[:n]
-    if (t.tid == 0) S.fact_ok = sp.finite ? (int)tri_factor<MM>(S) : 0;
-    bsync<MM>();
-    const int m = stencil_m<MM>(S);
-    if (!S.fact_ok) {
-        if (status == RBFFD_ST_OK) status = sp.finite ? RBFFD_ST_SINGULAR : RBFFD_ST_NONFINITE;
-        if (t.tid == 0 && J.status) J.status[s] = status;
-        if (c < n && t.rb == 0) J.w[s * n + c] = NAN;
-        bsync<MM>();
-        return;
-    }
-    const double e2 = eps * eps;
-    const double n0x = S.nrm0[0], n0y = S.nrm0[1], n0z = S.nrm0[2];
-    // b_d (row 1 of B^d) as an m-vector, component c
-    double b[3] = {0.0, 0.0, 0.0};
-    if (c < n) {
-        const double dx = S.x[0] - px, dy = S.y[0] - py, dz = S.z[0] - pz;  // x_1 - x_j
-        const double r2 = (dx * dx + dy * dy) + dz * dz;
-        const double ps = rbf_psi<K>(e2, r2);
-        const double dn = n0x * dx + n0y * dy + n0z * dz;
-        b[0] = ps * (dx - n0x * dn);
-        b[1] = ps * (dy - n0y * dn);
-        b[2] = ps * (dz - n0z * dn);
-    } else if (c < m && o.degree > 0) {
-        const int k = c - n;  // grad q_k at the centre (xi = 0): linear coefficients / rho
-        const double gx = S.T[1 * RMAX + k] * irho, gy = S.T[2 * RMAX + k] * irho, gz = S.T[3 * RMAX + k] * irho;
-        const double dn = n0x * gx + n0y * gy + n0z * gz;
-        b[0] = gx - n0x * dn;
-        b[1] = gy - n0y * dn;
-        b[2] = gz - n0z * dn;
-    }
-    if constexpr (MM <= 64) reflector_gram<MM>(a, S, t);
-    // g_d: plain solve.  Refining this solve as well as the final one does not
-    // lower the error of w (measured against 60-digit weights: both ways
-    // 0.02-0.07 kappa u at kappa_T = 1e10 and 1e12; without any refinement
-    // 0.1-0.28 kappa u), so only the final solve is refined.
-    solve<MM, 3>(a, S, t, b);
-    // h_i = Pi_i g_i
-    double hx = 0, hy = 0, hz = 0;
-    if (c < n) {
-        const double dn = nx * b[0] + ny * b[1] + nz * b[2];
-        hx = b[0] - nx * dn;
-        hy = b[1] - ny * dn;
-        hz = b[2] - nz * dn;
-    }
-    if (t.rb == 0) {
-        S.hx[c] = hx;
-        S.hy[c] = hy;
-        S.hz[c] = hz;
-    }
-    bsync<MM>();
-    // r_j = sum_i psi(r_ij) (x_i - x_j) . h_i   (j = c < n)
-    double rj = 0.0;
-    if (c < n) {
-#pragma unroll 4
-        for (int i = 0; i < n; ++i) {
-            const double dx = S.x[i] - px, dy = S.y[i] - py, dz = S.z[i] - pz;
-            const double r2 = (dx * dx + dy * dy) + dz * dz;
-            const double ps = rbf_psi<K>(e2, r2);
-            rj = fma(ps, dx * S.hx[i] + dy * S.hy[i] + dz * S.hz[i], rj);
-        }
-    }
-    // r_{n+k} = sum_i grad q_k(x_i) . h_i
-    if (o.degree > 0) {
-        const int r = S.r;
-        for (int k = 0; k < r; ++k) {
-            double cv = 0.0;
-            if (c < n) {
-                const double* T = S.T;
-                double gx = T[1 * RMAX + k], gy = T[2 * RMAX + k], gz = T[3 * RMAX + k];
-                if (o.degree == 2) {
-                    const double t4 = T[4 * RMAX + k], t5 = T[5 * RMAX + k], t6 = T[6 * RMAX + k];
-                    const double t7 = T[7 * RMAX + k], t8 = T[8 * RMAX + k], t9 = T[9 * RMAX + k];
-                    gx += 2.0 * t4 * xi + t7 * yi + t8 * zi;
-                    gy += 2.0 * t5 * yi + t7 * xi + t9 * zi;
-                    gz += 2.0 * t6 * zi + t8 * xi + t9 * yi;
-                }
-                cv = (gx * hx + gy * hy + gz * hz) * irho;
-            }
-            cv = sum_cols<MM>(cv, S, t);
-            if (c == n + k) rj = cv;
-        }
-    }
-    double wv[3] = {rj, 0.0, 0.0};
-    solve_refined<K, MM, 1>(a, S, t, e2, wv);
-    if (c < n && t.rb == 0) J.w[s * n + c] = wv[0];
-    if (t.tid == 0 && J.status) J.status[s] = status;
-    bsync<MM>();
 }
 
 }  // namespace rbw

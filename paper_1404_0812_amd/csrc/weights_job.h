@@ -30,6 +30,18 @@ struct Job {
     int kappa_only;
 };
 
+#ifdef __HIPCC__
+__host__ __device__
+#endif
 inline int border_cols(int degree) { return degree == 0 ? 1 : (degree == 1 ? 4 : 10); }
+
+// Tiling of the weights kernels: the smallest that holds n + border rows.
+inline int tiling(const WOpts& o) {
+    const int m = o.n + border_cols(o.degree);
+    return m <= 32 ? 32 : (m <= 48 ? 48 : (m <= 64 ? 64 : 128));
+}
+// The persistent launches have no half-wavefront form (its first run ended
+// with a GPU fault whose cause was not found): m <= 32 runs there as m <= 48.
+inline int batch_tiling(const WOpts& o) { return tiling(o) < 48 ? 48 : tiling(o); }
 
 }  // namespace rbw

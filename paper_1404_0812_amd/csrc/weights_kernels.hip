@@ -14,7 +14,7 @@
 // against a kappa band.
 //
 // How, on gfx950: the m x m matrix lives in registers.  m <= 64: one
-// wavefront per stencil, lane i holding column i.  m <= 128: four
+// wavefront per stencil, lane i holding column i (m <= 32: half a wavefront).  m <= 128: four
 // wavefronts per stencil, wave (rb, cb) holding rows 64 rb .. 64 rb + 63 of
 // columns 64 cb + lane.  A~ is reduced to tridiagonal form T = Q^T A~ Q by
 // Householder reflections; the pivot column of each step is row k+1 after the
@@ -39,7 +39,7 @@
 #error "RBW_K (radial kernel) must be defined"
 #endif
 #ifndef RBW_MM
-#error "RBW_MM (64 or 128) must be defined"
+#error "RBW_MM (32, 48, 64 or 128) must be defined"
 #endif
 
 using namespace rbw;
@@ -51,8 +51,8 @@ __device__ __forceinline__ Tid make_tid(int threads_base) {
     Tid t;
     t.l15 = threadIdx.x & 15;
     if constexpr (MM <= 64) {
-        // one wavefront per stencil: block indices are compile-time zero
-        t.lane = threadIdx.x & 63;
+        // one wavefront (or half of one) per stencil: block indices are compile-time zero
+        t.lane = threadIdx.x & (Lay<MM>::LW - 1);
         t.tid = t.lane;
         t.rb = 0;
         t.cb = 0;
@@ -69,19 +69,21 @@ __device__ __forceinline__ Tid make_tid(int threads_base) {
     return t;
 }
 
-// One workgroup (one or four wavefronts) per stencil.
+// One workgroup (one or four wavefronts) per stencil, or per two stencils.
 template <int K, int MM>
-__global__ __launch_bounds__(64 * Lay<MM>::NB * Lay<MM>::NB, 2) void k_weights(Job J) {
-    __shared__ Shared<MM> S;
-    const int64_t s = blockIdx.x;
+__global__ __launch_bounds__(64 * Lay<MM>::WAVES, Lay<MM>::OCC) void k_weights(Job J) {
+    constexpr int SPW = Lay<MM>::SPW;
+    __shared__ Shared<MM> S[SPW];
+    const int h = SPW == 2 ? threadIdx.x >> 5 : 0;
+    const int64_t s = (int64_t)blockIdx.x * SPW + h;
     if (s >= J.N) return;
-    process_stencil<K, MM>(J, s, S, make_tid<MM>(0));
+    process_stencil<K, MM>(J, s, S[h], make_tid<MM>(0));
 }
 
 // Persistent launch over many stencil sets.  Each workgroup (four wavefronts)
 // takes work items from a global counter until none are left.  An item is a
-// run of `count` stencils of one set.  MM = 64 (m <= 64): the four waves take
-// every fourth stencil of the item, one wave per stencil.  MM = 128 (m <= 128):
+// run of `count` stencils of one set.  m <= 64: the four waves take
+// every fourth stencil of the item, one wave per stencil.  m <= 128:
 // the four waves do the item's stencils one after another, together.  One
 // kernel per tiling: the two register tilings in one kernel need more than 256
 // VGPRs and spill.
@@ -101,7 +103,8 @@ __global__ __launch_bounds__(256, 2) void k_weights_batched(const Job* __restric
         const WorkItem w = items[it];
         const Job& J = jobs[w.job];
         if constexpr (MM <= 64) {
-            for (int q = wave; q < w.count; q += 4) process_stencil<K, MM>(J, w.start + q, S[wave], make_tid<MM>(64 * wave));
+            for (int q = wave; q < w.count; q += 4)
+                process_stencil<K, MM>(J, w.start + q, S[wave], make_tid<MM>(64 * wave));
         } else {
             for (int q = 0; q < w.count; ++q) process_stencil<K, MM>(J, w.start + q, S[0], make_tid<MM>(0));
         }
@@ -115,18 +118,21 @@ namespace rbw {
 
 template <int K, int MM>
 void launch_weights(hipStream_t st, const Job& J) {
-    const dim3 g((unsigned)J.N), b(64 * Lay<MM>::NB * Lay<MM>::NB);
+    const dim3 g((unsigned)((J.N + Lay<MM>::SPW - 1) / Lay<MM>::SPW)), b(64 * Lay<MM>::WAVES);
     hipLaunchKernelGGL((k_weights<K, MM>), g, b, 0, st, J);
 }
 
 template <int K, int MM>
 void launch_weights_batched(hipStream_t st, const Job* jobs, const WorkItem* items, int nitems, int* cursor,
                             int grid) {
+    if (grid > nitems) grid = nitems;
     hipLaunchKernelGGL((k_weights_batched<K, MM>), dim3((unsigned)grid), dim3(256), 0, st, jobs, items, nitems,
                        cursor);
 }
 
 template void launch_weights<RBW_K, RBW_MM>(hipStream_t, const Job&);
+#if RBW_MM > 32
 template void launch_weights_batched<RBW_K, RBW_MM>(hipStream_t, const Job*, const WorkItem*, int, int*, int);
+#endif
 
 }  // namespace rbw
