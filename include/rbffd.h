@@ -267,6 +267,8 @@ typedef struct {
  * s * sum_N + (N_0 + ... + N_{t-1}) + i.  surf is a HOST array.
  * Errors: nsurf < 1 or any surface invalid as in rbffd_op_create. */
 int rbffd_op_create_batched(rbffd_ctx ctx, int32_t nsurf, const rbffd_op_surface* surf, rbffd_op* out);
+/* The context keeps the device memory of its last destroyed operator (up to
+ * 2 GiB) for the next one; rbffd_destroy frees it. */
 int rbffd_op_destroy(rbffd_op op);
 
 /* Layout statistics of an operator (HOST outputs, each nullable): slices of

@@ -6,6 +6,7 @@
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
+#include <mutex>
 #include <string>
 
 #include "rbffd.h"
@@ -17,6 +18,12 @@ struct rbffd_ctx_s {
     // growable scratch owned by the context
     void* scratch = nullptr;
     size_t scratch_bytes = 0;
+    // the last destroyed operator's device memory, for the next one (see
+    // slab_take in step.hip); the mutex is for operators destroyed by another
+    // thread than the context's
+    std::mutex spare_mu;
+    void* spare = nullptr;
+    size_t spare_bytes = 0;
     // work list of the batched weights launch (kept apart from scratch, which kNN uses)
     void* batch = nullptr;
     size_t batch_bytes = 0;
@@ -49,9 +56,11 @@ struct rbffd_op_s {
     uint16_t* lidx = nullptr;     // slot entries as positions in the slice's halo list
     int32_t* halo = nullptr;      // OP_HALO_MAX sorted distinct neighbour rows per slice
     int32_t* perm = nullptr;      // internal row -> caller row (-1 for padding), P entries
-    // state workspace (internal order), allocated on first step
-    void* work = nullptr;
-    size_t work_bytes = 0;
+    void* work = nullptr;         // state workspace (internal order)
+    void* slab = nullptr;         // the one device allocation that holds the arrays above and the counters
+    size_t slab_bytes = 0;
+    rbffd_ctx home = nullptr;     // the context that built it
+    bool roamed = false;          // used on another context's stream
     // vectors of the implicit (BDF) stepper, allocated on first use
     void* impl = nullptr;
     size_t impl_bytes = 0;

@@ -75,6 +75,10 @@ extern "C" int rbffd_destroy(rbffd_ctx ctx) {
         (void)hipStreamSynchronize(ctx->stream);
         (void)hipFree(ctx->scratch);
     }
+    if (ctx->spare) {
+        (void)hipStreamSynchronize(ctx->stream);
+        (void)hipFree(ctx->spare);
+    }
     if (ctx->batch) {
         (void)hipStreamSynchronize(ctx->stream);
         (void)hipFree(ctx->batch);

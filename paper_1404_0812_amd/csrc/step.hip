@@ -29,6 +29,7 @@
 #include <mutex>
 #include <cstring>
 #include <new>
+#include <utility>
 #include <vector>
 
 namespace {
@@ -55,125 +56,135 @@ __global__ void k_inverse_perm(int64_t N, const int32_t* __restrict__ perm, int3
     else *bad = 1;
 }
 
-// Rows of one surface into the slices.  row0: first internal row of the
-// surface, col0: its first caller row; gperm: internal row -> caller row.
-// A stencil entry outside [0, N), or a row that perm does not reach, sets
-// *bad; the slot then points at the row itself with weight 0 (the operator is
-// discarded by the caller, but nothing reads out of bounds meanwhile).
-__global__ void k_build_sell(int64_t N, int n, int64_t row0, int64_t col0, const int32_t* __restrict__ idx,
-                             const double* __restrict__ w, const int32_t* __restrict__ perm,
-                             const int32_t* __restrict__ iperm, const OpSlice* __restrict__ slices,
-                             double* __restrict__ wd64, double* __restrict__ w64, int32_t* __restrict__ idx32,
-                             float* __restrict__ w32, int32_t* __restrict__ gperm, int* __restrict__ bad) {
-    int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (p >= N) return;
-    int64_t i = perm ? perm[p] : p;
-    if (i < 0 || i >= N || iperm[p] < 0) {  // out of range, or perm misses caller row p
-        *bad = 1;
-        i = i < 0 || i >= N ? 0 : i;
+// One 256-thread block per slice of one surface: its slot entries (internal
+// row indices), weights in both precisions and halo, i.e. the sorted distinct
+// rows the slice's 64 rows read (off-diagonal slots) with every slot entry as
+// a position in that list.  Slices with more than OP_HALO_MAX distinct rows
+// keep halo = -1 and are read directly.
+//
+// Thread (r, q) takes slots q, q + 4, ... of row r: four lanes read 16 (index)
+// or 32 (weight) bytes of a row, and the block writes 256 consecutive
+// elements.  The distinct rows come from a hash table in LDS (at most
+// OP_HALO_MAX + 255 entries of HB_SLOTS), are sorted (bitonic, u <= 640), and
+// the table then answers where each entry sits.  At N = 2e5, n = 50 a thread
+// per row (reads 200 and 400 bytes apart) took 0.76 ms and a sort of all 3136
+// entries per slice 0.91 ms; this kernel takes 0.17 ms for both (waits on the
+// dependent loads perm -> idx -> iperm).
+//
+// slice0, off0: first slice of the surface and its slot offset; row0, col0:
+// its first internal and first caller row; gperm: internal row -> caller row
+// (-1 on padding rows).  A stencil entry outside [0, N), or a row that perm
+// does not reach, sets *bad; the slot then points at the row itself with
+// weight 0 (the operator is discarded by the caller, but nothing reads out of
+// bounds meanwhile).
+constexpr int HB_SLOTS = 2048;
+static_assert(OP_HALO_MAX + 256 < HB_SLOTS && OP_HALO_MAX <= 1024, "halo hash table");
+
+__device__ __forceinline__ int halo_slot(int32_t j) { return (int)(((uint32_t)j * 2654435761u) >> 21); }
+
+__global__ __launch_bounds__(256) void k_build_slices(int64_t N, int n, int64_t slice0, int64_t off0, int64_t row0,
+                                                      int64_t col0, const int32_t* __restrict__ idx,
+                                                      const double* __restrict__ w, const int32_t* __restrict__ perm,
+                                                      const int32_t* __restrict__ iperm, OpSlice* __restrict__ slices,
+                                                      double* __restrict__ wd64, double* __restrict__ w64,
+                                                      int32_t* __restrict__ idx32, float* __restrict__ w32,
+                                                      uint16_t* __restrict__ lidx, int32_t* __restrict__ halo,
+                                                      int32_t* __restrict__ gperm, int* __restrict__ bad) {
+    __shared__ int32_t key[HB_SLOTS];
+    __shared__ uint16_t pos[HB_SLOTS];
+    __shared__ int32_t uniq[1024];
+    __shared__ int cnt;
+    const int tid = threadIdx.x, r = tid >> 2, q = tid & 3;
+    const int64_t sl = blockIdx.x, p = sl * 64 + r;
+    const int ns = n - 1, rows = (int)(N - sl * 64 < 64 ? N - sl * 64 : 64);
+    const int64_t off = off0 + sl * 64 * ns;
+    for (int i = tid; i < HB_SLOTS; i += 256) key[i] = -1;
+    if (tid == 0) cnt = 0;
+    __syncthreads();
+    const bool live = r < rows;
+    int64_t i = 0;
+    if (live) {
+        i = perm ? perm[p] : p;
+        if (i < 0 || i >= N || iperm[p] < 0) {  // out of range, or perm misses caller row p
+            *bad = 1;
+            i = i < 0 || i >= N ? 0 : i;
+        }
+        if (q == 0) {
+            // slot 0 must be the row's own node: the FP32 difference form drops it
+            if (idx[i * n] != i) *bad = 1;
+            wd64[row0 + p] = w[i * n];
+        }
     }
-    const int64_t q = row0 + p;
-    const OpSlice sl = slices[q >> 6];
-    const int r = (int)(q & 63);
-    // slot 0 must be the row's own node: the FP32 difference form drops it
-    if (idx[i * n] != i) *bad = 1;
-    for (int k = 0; k < n; ++k) {
-        const int32_t c = idx[i * n + k];
+    if (q == 0) gperm[row0 + p] = live ? (int32_t)(col0 + i) : -1;
+    for (int k = q; live && k < ns; k += 4) {
+        const int32_t c = idx[i * n + 1 + k];
         const int32_t ip = (c >= 0 && c < N) ? iperm[c] : -1;
         const bool ok = ip >= 0;
         if (!ok) *bad = 1;
         const int32_t j = (int32_t)(row0 + (ok ? ip : p));
-        const double wk = ok ? w[i * n + k] : 0.0;
-        if (k == 0) {
-            wd64[q] = wk;
-        } else {
-            const int64_t q32 = sl.off32 + slot_pos(k - 1, n - 1, r);
-            idx32[q32] = j;
-            w32[q32] = (float)wk;
-            w64[q32] = wk;
+        const double wk = ok ? w[i * n + 1 + k] : 0.0;
+        const int64_t at = off + slot_pos(k, ns, r);
+        idx32[at] = j;
+        w32[at] = (float)wk;
+        w64[at] = wk;
+        for (int h = halo_slot(j);; h = (h + 1) & (HB_SLOTS - 1)) {
+            const int32_t old = key[h];
+            if (old == j) break;
+            if (old >= 0) continue;
+            // a full list stops the insertions: at most one more per thread gets past this test
+            if (*(volatile int*)&cnt > OP_HALO_MAX) break;
+            const int32_t was = atomicCAS(&key[h], -1, j);
+            if (was == j) break;
+            if (was < 0) {
+                const int u = atomicAdd(&cnt, 1);
+                if (u < 1024) uniq[u] = j;
+                break;
+            }
         }
     }
-    gperm[q] = (int32_t)(col0 + i);
-}
-
-// Halo of each slice for the FP32 path: the sorted distinct rows its 64 rows
-// read (off-diagonal slots), and every slot entry rewritten as a position in
-// that list.  One 256-thread block per slice: the <= 64 x 127 entries are
-// sorted in LDS (bitonic), de-duplicated with a block scan, and each entry is
-// located in the unique list by binary search.  Slices with more than
-// OP_HALO_MAX distinct rows keep halo = -1 and are read directly.
-constexpr int HB_CAP = 8192;  // >= 64 x 127 entries per slice
-
-__global__ __launch_bounds__(256) void k_build_halo(int64_t nslices, OpSlice* __restrict__ slices,
-                                                    const int32_t* __restrict__ idx32, uint16_t* __restrict__ lidx,
-                                                    int32_t* __restrict__ halo) {
-    __shared__ int32_t key[HB_CAP];
-    __shared__ int32_t cnt[256];
-    __shared__ int32_t uniq[OP_HALO_MAX];
-    const int64_t s = blockIdx.x;
-    if (s >= nslices) return;
-    const OpSlice sl = slices[s];
-    const int ns = sl.n - 1, rows = sl.rows, E = rows * ns, tid = threadIdx.x;
-    for (int i = tid; i < HB_CAP; i += 256)
-        key[i] = i < E ? idx32[sl.off32 + slot_pos(i % ns, ns, i / ns)] : 0x7fffffff;
     __syncthreads();
-    for (int size = 2; size <= HB_CAP; size <<= 1) {
+    const int u = cnt, H = u <= OP_HALO_MAX ? u : -1;
+    if (tid == 0) {
+        OpSlice o;
+        o.off32 = off;
+        o.n = n;
+        o.rows = rows;
+        o.halo = H;
+        o.pad = 0;
+        slices[slice0 + sl] = o;
+    }
+    if (H < 0) return;
+    int S = 64;
+    while (S < u) S <<= 1;
+    for (int t = u + tid; t < S; t += 256) uniq[t] = 0x7fffffff;
+    __syncthreads();
+    for (int size = 2; size <= S; size <<= 1) {
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = tid; i < HB_CAP / 2; i += 256) {
-                const int lo = 2 * i - (i & (stride - 1));  // first of the pair (stride apart)
-                const int hi = lo + stride;
-                const bool up = (lo & size) == 0;
-                const int a = key[lo], b = key[hi];
-                if ((a > b) == up) {
-                    key[lo] = b;
-                    key[hi] = a;
+            for (int t = tid; t < S / 2; t += 256) {
+                const int lo = 2 * t - (t & (stride - 1)), hi = lo + stride;  // the pair, stride apart
+                const int a = uniq[lo], b = uniq[hi];
+                if ((a > b) == ((lo & size) == 0)) {
+                    uniq[lo] = b;
+                    uniq[hi] = a;
                 }
             }
             __syncthreads();
         }
     }
-    // distinct keys among the E sorted entries: thread t counts its 32 consecutive ones
-    constexpr int PER = HB_CAP / 256;
-    int c = 0;
-    for (int q = 0; q < PER; ++q) {
-        const int i = tid * PER + q;
-        c += (i < E && (i == 0 || key[i] != key[i - 1])) ? 1 : 0;
-    }
-    cnt[tid] = c;
-    __syncthreads();
-    if (tid == 0) {
-        int run = 0;
-        for (int t = 0; t < 256; ++t) {
-            const int v = cnt[t];
-            cnt[t] = run;
-            run += v;
-        }
-        slices[s].halo = run <= OP_HALO_MAX ? run : -1;
-        key[HB_CAP - 1] = run <= OP_HALO_MAX ? run : -1;  // E < HB_CAP: the last slot is padding
+    for (int t = tid; t < u; t += 256) {
+        const int32_t j = uniq[t];
+        halo[(slice0 + sl) * OP_HALO_MAX + t] = j;
+        int h = halo_slot(j);
+        while (key[h] != j) h = (h + 1) & (HB_SLOTS - 1);
+        pos[h] = (uint16_t)t;
     }
     __syncthreads();
-    const int H = key[HB_CAP - 1];
-    if (H < 0) return;
-    int pos = cnt[tid];
-    for (int q = 0; q < PER; ++q) {
-        const int i = tid * PER + q;
-        if (i < E && (i == 0 || key[i] != key[i - 1])) {
-            uniq[pos] = key[i];
-            halo[s * OP_HALO_MAX + pos] = key[i];
-            ++pos;
-        }
-    }
-    __syncthreads();
-    for (int i = tid; i < E; i += 256) {
-        const int64_t at = sl.off32 + slot_pos(i % ns, ns, i / ns);
-        const int32_t j = idx32[at];
-        int lo = 0, hi = H - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (uniq[mid] < j) lo = mid + 1;
-            else hi = mid;
-        }
-        lidx[at] = (uint16_t)lo;
+    for (int k = q; live && k < ns; k += 4) {
+        const int64_t at = off + slot_pos(k, ns, r);
+        const int32_t j = idx32[at];  // written by this thread
+        int h = halo_slot(j);
+        while (key[h] != j) h = (h + 1) & (HB_SLOTS - 1);
+        lidx[at] = pos[h];
     }
 }
 
@@ -635,20 +646,13 @@ void enqueue_steps_t(hipStream_t st, int S, int R, const StageArgs& a, const int
     else enqueue_steps_f<T, false>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
 }
 
-int ensure_work(rbffd_op op) {
-    // 4 buffers (U, ACC, Y1, Y2) x 2 species x FP64, and the forcing (2 species)
-    size_t need = 5 * 2 * (size_t)op->P * sizeof(double);
-    if (op->work_bytes >= need) return RBFFD_OK;
-    if (op->work) {
-        (void)hipStreamSynchronize(op->ctx->stream);
-        (void)hipFree(op->work);
-        op->work = nullptr;
+// The flag of the stepper's last stage on the host side, allocated on first use.
+int ensure_flag(rbffd_op op) {
+    if (op->nonfinite_host) return RBFFD_OK;
+    if (hipHostMalloc(reinterpret_cast<void**>(&op->nonfinite_host), sizeof(int), hipHostMallocDefault) != hipSuccess) {
+        op->nonfinite_host = nullptr;
+        return set_error(op->ctx, RBFFD_E_NOMEM, "cannot allocate the host flag");
     }
-    if (hipMalloc(&op->work, need) != hipSuccess) {
-        op->work = nullptr;
-        return set_error(op->ctx, RBFFD_E_NOMEM, "cannot allocate %zu bytes of state", need);
-    }
-    op->work_bytes = need;
     return RBFFD_OK;
 }
 
@@ -668,88 +672,126 @@ void reset_kgraph(rbffd_op op) {
     op->kgraph_key = nullptr;
 }
 
-// Build the sliced operator of nsurf surfaces (validated by the callers).
+// Device memory of one operator.  A context keeps the last destroyed
+// operator's, up to SPARE_MAX bytes, for the next one of a similar size:
+// freeing and allocating 230 MB (2e5 rows, n = 50) took 5 ms, ten times the
+// build.  Given back when the context is destroyed or an allocation fails.
+constexpr size_t SPARE_MAX = (size_t)2 << 30;
+
+void* slab_take(rbffd_ctx ctx, size_t bytes, size_t& got) {
+    std::lock_guard<std::mutex> lock(ctx->spare_mu);
+    void* p = nullptr;
+    if (ctx->spare && ctx->spare_bytes >= bytes && ctx->spare_bytes / 4 <= bytes) {
+        p = ctx->spare;
+        got = ctx->spare_bytes;
+        ctx->spare = nullptr;
+        return p;
+    }
+    got = bytes;
+    if (hipMalloc(&p, bytes) == hipSuccess) return p;
+    if (!ctx->spare) return nullptr;
+    (void)hipGetLastError();
+    (void)hipFree(ctx->spare);
+    ctx->spare = nullptr;
+    return hipMalloc(&p, bytes) == hipSuccess ? p : nullptr;
+}
+// The caller has waited for the context's stream; hipFree itself waits for the
+// whole device, which an operator used on other streams needs.
+void slab_give(rbffd_ctx ctx, void* p, size_t bytes, bool keep) {
+    if (keep && bytes <= SPARE_MAX) {
+        std::lock_guard<std::mutex> lock(ctx->spare_mu);
+        std::swap(ctx->spare, p);
+        ctx->spare_bytes = bytes;
+    }
+    if (p) (void)hipFree(p);
+}
+
+// Every call on an operator names its context.
+void use_on(rbffd_op op, rbffd_ctx ctx) {
+    op->ctx = ctx;
+    if (ctx != op->home) op->roamed = true;
+}
+
+// Build the sliced operator of nsurf surfaces (validated by the callers).  All
+// device arrays of the operator, the state workspace included, are one
+// allocation; the inverse permutation is in the context's scratch.  Build,
+// two FP64 applications and release at N = 2e5, n = 50: 2.73 -> 0.39 ms, of
+// which 1.5 ms were the two kernels above and the rest 13 allocations.
 int create_op(rbffd_ctx ctx, int nsurf, const rbffd_op_surface* surf, rbffd_op* out) {
-    std::vector<OpSlice> sl;
-    std::vector<int64_t> row0(nsurf), col0(nsurf);
-    int64_t P = 0, N = 0, off32 = 0, maxN = 0;
+    int64_t P = 0, N = 0, slots = 0, maxN = 0, nslices = 0;
     int32_t nmax = 0;
     for (int s = 0; s < nsurf; ++s) {
-        row0[s] = P;
-        col0[s] = N;
-        const int64_t Ns = surf[s].N;
-        const int n = surf[s].n;
-        for (int64_t r = 0; r < Ns; r += 64) {
-            OpSlice o;
-            o.off32 = off32;
-            o.n = n;
-            o.rows = (int32_t)std::min<int64_t>(64, Ns - r);
-            o.halo = -1;
-            o.pad = 0;
-            sl.push_back(o);
-            off32 += 64 * (int64_t)(n - 1);
-        }
-        P += (Ns + 63) / 64 * 64;
-        N += Ns;
-        maxN = std::max(maxN, Ns);
-        nmax = std::max(nmax, n);
+        const int64_t sl = (surf[s].N + 63) / 64;
+        nslices += sl;
+        slots += 64 * sl * (surf[s].n - 1);
+        P += 64 * sl;
+        N += surf[s].N;
+        maxN = std::max(maxN, surf[s].N);
+        nmax = std::max(nmax, surf[s].n);
     }
     if (P > 0x7fffffffLL) return set_error(ctx, RBFFD_E_ARG, "operator too large: %lld rows", (long long)P);
+    int rc = ensure_scratch(ctx, (size_t)maxN * sizeof(int32_t) + 512);
+    if (rc) return rc;
+    int* bad = (int*)ctx->scratch;
+    int32_t* iperm = (int32_t*)((char*)ctx->scratch + 256);
     rbffd_op op = new (std::nothrow) rbffd_op_s();
     if (!op) return set_error(ctx, RBFFD_E_NOMEM, "host allocation failed");
-    op->ctx = ctx;
+    op->ctx = op->home = ctx;
     op->N = N;
     op->P = P;
     op->n = nmax;
     op->nsurf = nsurf;
-    op->nslices = (int64_t)sl.size();
-    bool ok = hipMalloc(&op->slices, std::max<size_t>(1, sl.size()) * sizeof(OpSlice)) == hipSuccess &&
-              hipMalloc(&op->wd64, std::max<int64_t>(1, P) * sizeof(double)) == hipSuccess &&
-              hipMalloc(&op->w64, std::max<int64_t>(1, off32) * sizeof(double)) == hipSuccess &&
-              hipMalloc(&op->idx32, std::max<int64_t>(1, off32) * sizeof(int32_t)) == hipSuccess &&
-              hipMalloc(&op->w32, std::max<int64_t>(1, off32) * sizeof(float)) == hipSuccess &&
-              hipMalloc(&op->lidx, std::max<int64_t>(1, off32) * sizeof(uint16_t)) == hipSuccess &&
-              hipMalloc(&op->halo, std::max<size_t>(1, sl.size()) * OP_HALO_MAX * sizeof(int32_t)) == hipSuccess &&
-              hipMalloc(&op->perm, std::max<int64_t>(1, P) * sizeof(int32_t)) == hipSuccess;
-    ok = ok && hipMalloc(&op->counters, sizeof(int64_t) + sizeof(int)) == hipSuccess &&
-         hipHostMalloc(reinterpret_cast<void**>(&op->nonfinite_host), sizeof(int), hipHostMallocDefault) == hipSuccess;
-    int32_t* iperm = nullptr;
-    int* bad = nullptr;
-    ok = ok && hipMalloc(&iperm, std::max<int64_t>(1, maxN) * sizeof(int32_t)) == hipSuccess;
-    ok = ok && hipMalloc(&bad, sizeof(int)) == hipSuccess;
-    if (!ok) {
+    op->nslices = nslices;
+    size_t bytes = 0;
+    auto take = [&](size_t b) {
+        const size_t o = bytes;
+        bytes += (b + 255) & ~(size_t)255;
+        return o;
+    };
+    const size_t o_sl = take(nslices * sizeof(OpSlice)), o_wd = take(P * sizeof(double));
+    const size_t o_w64 = take(slots * sizeof(double)), o_idx = take(slots * sizeof(int32_t));
+    const size_t o_w32 = take(slots * sizeof(float)), o_lidx = take(slots * sizeof(uint16_t));
+    const size_t o_halo = take(nslices * OP_HALO_MAX * sizeof(int32_t)), o_perm = take(P * sizeof(int32_t));
+    const size_t o_cnt = take(sizeof(int64_t) + sizeof(int));
+    // 4 state buffers (U, ACC, Y1, Y2) x 2 species x FP64, and the forcing (2 species)
+    const size_t o_work = take(5 * 2 * (size_t)P * sizeof(double));
+    op->slab = slab_take(ctx, bytes, op->slab_bytes);
+    if (!op->slab) {
         rbffd_op_destroy(op);
-        if (iperm) (void)hipFree(iperm);
-        if (bad) (void)hipFree(bad);
         return set_error(ctx, RBFFD_E_NOMEM, "operator allocation failed");
     }
+    char* base = (char*)op->slab;
+    op->slices = (OpSlice*)(base + o_sl);
+    op->wd64 = (double*)(base + o_wd);
+    op->w64 = (double*)(base + o_w64);
+    op->idx32 = (int32_t*)(base + o_idx);
+    op->w32 = (float*)(base + o_w32);
+    op->lidx = (uint16_t*)(base + o_lidx);
+    op->halo = (int32_t*)(base + o_halo);
+    op->perm = (int32_t*)(base + o_perm);
+    op->counters = base + o_cnt;
+    op->work = base + o_work;
     hipStream_t st = ctx->stream;
-    hipError_t e = hipMemcpyAsync(op->slices, sl.data(), sl.size() * sizeof(OpSlice), hipMemcpyHostToDevice, st);
-    // padding rows: perm -1; their slots are never read (rows >= OpSlice::rows are skipped)
-    if (e == hipSuccess) e = hipMemsetAsync(op->perm, 0xff, (size_t)P * sizeof(int32_t), st);
-    if (e == hipSuccess) e = hipMemsetAsync(bad, 0, sizeof(int), st);
+    hipError_t e = hipMemsetAsync(bad, 0, sizeof(int), st);
+    int64_t slice0 = 0, off0 = 0, col0 = 0;
     for (int s = 0; s < nsurf && e == hipSuccess; ++s) {
-        const int64_t Ns = surf[s].N;
+        const int64_t Ns = surf[s].N, sl = (Ns + 63) / 64;
         const dim3 g((unsigned)((Ns + BLK - 1) / BLK)), b(BLK);
         e = hipMemsetAsync(iperm, 0xff, (size_t)Ns * sizeof(int32_t), st);
         if (e != hipSuccess) break;
         hipLaunchKernelGGL(k_inverse_perm, g, b, 0, st, Ns, surf[s].perm, iperm, bad);
-        hipLaunchKernelGGL(k_build_sell, g, b, 0, st, Ns, surf[s].n, row0[s], col0[s], surf[s].idx, surf[s].w,
-                           surf[s].perm, iperm, op->slices, op->wd64, op->w64, op->idx32, op->w32, op->perm, bad);
+        hipLaunchKernelGGL(k_build_slices, dim3((unsigned)sl), dim3(256), 0, st, Ns, surf[s].n, slice0, off0,
+                           64 * slice0, col0, surf[s].idx, surf[s].w, surf[s].perm, iperm, op->slices, op->wd64, op->w64,
+                           op->idx32, op->w32, op->lidx, op->halo, op->perm, bad);
         e = hipGetLastError();
+        slice0 += sl;
+        off0 += 64 * sl * (surf[s].n - 1);
+        col0 += Ns;
     }
-    if (e == hipSuccess && !sl.empty()) {
-        hipLaunchKernelGGL(k_build_halo, dim3((unsigned)sl.size()), dim3(256), 0, st, (int64_t)sl.size(), op->slices,
-                           op->idx32, op->lidx, op->halo);
-        e = hipGetLastError();
-    }
-    // the slice table comes from pageable host memory and iperm is reused per surface: wait here
+    int bad_h = 0;
+    if (e == hipSuccess) e = hipMemcpyAsync(&bad_h, bad, sizeof(int), hipMemcpyDeviceToHost, st);
     const hipError_t e2 = hipStreamSynchronize(st);
     if (e == hipSuccess) e = e2;
-    int bad_h = 0;
-    if (e == hipSuccess) e = hipMemcpy(&bad_h, bad, sizeof(int), hipMemcpyDeviceToHost);
-    (void)hipFree(iperm);
-    (void)hipFree(bad);
     if (e != hipSuccess) {
         rbffd_op_destroy(op);
         return set_error(ctx, RBFFD_E_HIP, "operator build failed: %s", hipGetErrorString(e));
@@ -803,17 +845,8 @@ extern "C" int rbffd_op_destroy(rbffd_op op) {
     if (op->ctx) (void)hipStreamSynchronize(op->ctx->stream);
     reset_graph(op);
     reset_kgraph(op);
-    if (op->slices) (void)hipFree(op->slices);
-    if (op->wd64) (void)hipFree(op->wd64);
-    if (op->w64) (void)hipFree(op->w64);
-    if (op->idx32) (void)hipFree(op->idx32);
-    if (op->w32) (void)hipFree(op->w32);
-    if (op->lidx) (void)hipFree(op->lidx);
-    if (op->halo) (void)hipFree(op->halo);
-    if (op->perm) (void)hipFree(op->perm);
-    if (op->work) (void)hipFree(op->work);
+    if (op->slab) slab_give(op->ctx, op->slab, op->slab_bytes, !op->roamed);
     if (op->impl) (void)hipFree(op->impl);
-    if (op->counters) (void)hipFree(op->counters);
     if (op->nonfinite_host) (void)hipHostFree(op->nonfinite_host);
     delete op;
     return RBFFD_OK;
@@ -882,6 +915,7 @@ extern "C" int rbffd_apply_noalloc(rbffd_ctx ctx, rbffd_op op, int32_t prec, con
         if (ctx->device >= 0 && ctx->device < MAX_DEVICES) base = g_scratch_ptr[ctx->device];
     }
     if (!base) return set_error(ctx, RBFFD_E_HIP, "no scratch address for device %d", ctx->device);
+    if (ctx != op->home) op->roamed = true;
     hipStream_t st = ctx->stream;
     const dim3 g((unsigned)((P + BLK - 1) / BLK)), b(BLK);
     StageArgs a;
@@ -911,9 +945,7 @@ extern "C" int rbffd_apply_noalloc(rbffd_ctx ctx, rbffd_op op, int32_t prec, con
 extern "C" int rbffd_apply(rbffd_ctx ctx, rbffd_op op, int32_t prec, const double* u, double* Lu) {
     if (!ctx || !op || !u || !Lu) return set_error(ctx, RBFFD_E_ARG, "null argument");
     if (prec != RBFFD_F64 && prec != RBFFD_F32) return set_error(ctx, RBFFD_E_ARG, "prec must be F64 or F32");
-    op->ctx = ctx;
-    int rc = ensure_work(op);
-    if (rc) return rc;
+    use_on(op, ctx);
     hipStream_t st = ctx->stream;
     const int64_t N = op->N, P = op->P;
     const dim3 g((unsigned)((P + BLK - 1) / BLK)), b(BLK);
@@ -958,8 +990,8 @@ int step_impl(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, double* state, int32
     if (graph_steps < 0) return set_error(ctx, RBFFD_E_ARG, "graph_steps must be >= 0");
     if (forcing && !(std::isfinite(t0) && std::isfinite(lam)))
         return set_error(ctx, RBFFD_E_ARG, "t0 and lambda must be finite");
-    op->ctx = ctx;
-    int rc = ensure_work(op);
+    use_on(op, ctx);
+    int rc = ensure_flag(op);
     if (rc) return rc;
     hipStream_t st = ctx->stream;
     const int64_t N = op->N, P = op->P;
@@ -1399,7 +1431,7 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
     if (!(tol > 0.0) || maxit < 1) return set_error(ctx, RBFFD_E_ARG, "tol must be > 0 and maxit >= 1");
     if (forcing && !(std::isfinite(t0) && std::isfinite(lambda)))
         return set_error(ctx, RBFFD_E_ARG, "t0 and lambda must be finite");
-    op->ctx = ctx;
+    use_on(op, ctx);
     const int64_t N = op->N, P = op->P;
     const int S = nspecies;
     const bool react = reaction != RBFFD_REACT_NONE;
