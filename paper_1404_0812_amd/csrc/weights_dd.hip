@@ -14,21 +14,38 @@
 // kappa_2, and a pivoted LU factorisation for the solves.  Only the final
 // weights, eps and kappa_2 are rounded to FP64.
 //
-// One wavefront per stencil; the local matrix (m = n + 1 <= 48) lives in LDS,
-// lane j owning column j.  This path trades speed for precision: it exists
-// for the high targets of the convergence studies, not for the point-cloud
-// workloads.
+// One wavefront per stencil.  While eps is searched the local matrix lives in
+// registers, 32 FP64 words per lane for m = n + 1 <= 32: lane (c, h) holds the
+// rows of parity h of column c, so that both halves of the wavefront work on
+// every Householder step (m <= 48: lane c holds all of column c).  v and w of
+// a step reach the rows through DPP row broadcasts.  The final LU works in
+// LDS, in the space of the search's vectors.
+//
+// What bounds it: FP64 issue (a double-double multiply-add is 12 operations
+// where the sums carry their low words, 18 in an update).  Sums and updates
+// with full renormalisation after every operation, the matrix in 38 KB of
+// LDS, three divisions per quotient and 13 eigenvalue passes per decision
+// took 38.3 ms for 2562 stencils of 31 nodes to kappa_T = 1e18; now 5.2 ms
+// (40962 stencils: 551 -> 66 ms; 1200 of 47 nodes: 33 -> 15 ms).
 #include "common.h"
 #include "weights_job.h"
 
 #include <cmath>
+#include <type_traits>
 
 #pragma clang fp contract(off)
 
 namespace {
 
 constexpr int DD_MAX = 48;
-constexpr int LDA = DD_MAX + 1;
+
+template <int MM>
+struct DDL {
+    static constexpr int H = MM == 32 ? 2 : 1;    // lanes per column
+    static constexpr int R = MM / H;              // rows per lane: H i + h, i = 0 .. R - 1
+    static constexpr int BR = MM == 32 ? 4 : 16;  // rows per block of the reduction's code
+    static constexpr int LDA = MM + 1;
+};
 
 // ------------------------------------------------------ double-double ----
 // Unevaluated sums hi + lo with |lo| <= ulp(hi) / 2: the error-free sum of
@@ -74,13 +91,24 @@ __device__ __forceinline__ dd mul_d(dd a, double b) {
     p.lo += a.lo * b;
     return quick_two_sum(p.hi, p.lo);
 }
+// 1 / q to the last place or so: hardware reciprocal, two Newton steps
+__device__ __forceinline__ double recip1(double q) {
+    double r = __builtin_amdgcn_rcp(q);
+    r = __builtin_fma(r, __builtin_fma(-q, r, 1.0), r);
+    return __builtin_fma(r, __builtin_fma(-q, r, 1.0), r);
+}
+// a / b: the first quotient's remainder is exact in one FMA plus the low
+// words, and a second quotient of it leaves 2^-104 or so
 __device__ __forceinline__ dd dvd(dd a, dd b) {
-    const double q1 = a.hi / b.hi;
-    dd r = sub(a, mul_d(b, q1));
-    const double q2 = r.hi / b.hi;
-    r = sub(r, mul_d(b, q2));
-    const double q3 = r.hi / b.hi;
-    return add(quick_two_sum(q1, q2), mk(q3));
+    const double r = recip1(b.hi);
+    const double q1 = a.hi * r;
+    const double t = __builtin_fma(-q1, b.hi, a.hi);
+    const double rem = t + __builtin_fma(-q1, b.lo, a.lo);
+    const double q2 = rem * r;
+    const dd q = quick_two_sum(q1, q2);
+    // the second remainder's high part, for the bits the reciprocal lacks
+    const double t2 = __builtin_fma(-q2, b.hi, rem);
+    return quick_two_sum(q.hi, __builtin_fma(t2, r, q.lo));
 }
 __device__ __forceinline__ dd dsqrt(dd a) {
     if (!(a.hi > 0.0)) return mk(a.hi == 0.0 ? 0.0 : NAN);
@@ -89,18 +117,88 @@ __device__ __forceinline__ dd dsqrt(dd a) {
     const dd e = sub(a, two_prod(ax, ax));
     return two_sum(ax, e.hi * (x * 0.5));
 }
+// s += a b and s += t with the low word left unnormalised (normalise with
+// norm() before use elsewhere): the high words' sum is error-free, so a sum of
+// n terms is off by about n 2^-106 times the sum of their magnitudes, as it is
+// with a normalisation after every term.
+__device__ __forceinline__ void mac(dd& s, dd a, dd b) {
+    const double ph = a.hi * b.hi;
+    double pl = __builtin_fma(a.hi, b.hi, -ph);
+    pl = __builtin_fma(a.hi, b.lo, pl);
+    pl = __builtin_fma(a.lo, b.hi, pl);
+    const dd t = two_sum(s.hi, ph);
+    s.hi = t.hi;
+    s.lo += t.lo + pl;
+}
+__device__ __forceinline__ void acc(dd& s, dd t) {
+    const dd u = two_sum(s.hi, t.hi);
+    s.hi = u.hi;
+    s.lo += u.lo + t.lo;
+}
+__device__ __forceinline__ dd norm(dd s) { return quick_two_sum(s.hi, s.lo); }
 __device__ __forceinline__ double to_d(dd a) { return a.hi + a.lo; }
 __device__ __forceinline__ bool is_fin(dd a) { return isfinite(a.hi) && isfinite(a.lo); }
 
-__device__ __forceinline__ dd shfl_xor(dd v, int o) { return {__shfl_xor(v.hi, o, 64), __shfl_xor(v.lo, o, 64)}; }
-// Sum over the wavefront, the same value in every lane (same association everywhere).
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, false),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, false));
+}
+template <int CTRL>
+__device__ __forceinline__ dd dpp(dd v) {
+    return {dpp<CTRL>(v.hi), dpp<CTRL>(v.lo)};
+}
+// v of lane I of the caller's row of 16 lanes
+template <int I>
+__device__ __forceinline__ double row_lane(double v) {
+    double r = v;  // the builtin's type follows its operands
+    r = __builtin_amdgcn_update_dpp(r, v, 0x150 + I, 0xf, 0xf, true);
+    return r;
+}
+template <int I>
+__device__ __forceinline__ dd row_lane(dd v) {
+    return {row_lane<I>(v.hi), row_lane<I>(v.lo)};
+}
+__device__ __forceinline__ void swap16(double v, double& a, double& b) {
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    a = __hiloint2double((int)h[0], (int)l[0]);
+    b = __hiloint2double((int)h[1], (int)l[1]);
+}
+// a: the lower 32 lanes' value of v, b: the upper 32 lanes', in both halves
+__device__ __forceinline__ void swap32(double v, double& a, double& b) {
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    a = __hiloint2double((int)h[0], (int)l[0]);
+    b = __hiloint2double((int)h[1], (int)l[1]);
+}
+__device__ __forceinline__ void swap32(dd v, dd& a, dd& b) {
+    swap32(v.hi, a.hi, b.hi);
+    swap32(v.lo, a.lo, b.lo);
+}
+__device__ __forceinline__ dd halves_sum(dd v) {
+    dd a, b;
+    swap32(v, a, b);
+    acc(a, b);
+    return norm(a);
+}
+// Sum over the columns (each half of the wavefront holds all of them where
+// H = 2), the same value in every lane: the error-free sums of the high words
+// do not depend on the order of two operands.
+template <int MM>
 __device__ __forceinline__ dd wsum(dd v) {
-    for (int o = 1; o < 64; o <<= 1) {
-        const dd u = shfl_xor(v, o);
-        // order the operands by lane so that both partners add alike
-        v = (threadIdx.x & o) ? add(u, v) : add(v, u);
-    }
-    return v;
+    acc(v, dpp<0xB1>(v));   // quad_perm [1,0,3,2]
+    acc(v, dpp<0x4E>(v));   // quad_perm [2,3,0,1]
+    acc(v, dpp<0x141>(v));  // row_half_mirror
+    acc(v, dpp<0x140>(v));  // row_mirror
+    dd a, b;
+    swap16(v.hi, a.hi, b.hi);
+    swap16(v.lo, a.lo, b.lo);
+    acc(a, b);
+    if constexpr (DDL<MM>::H == 2) return norm(a);
+    else return halves_sum(a);
 }
 
 __device__ __forceinline__ void fence() {
@@ -109,14 +207,24 @@ __device__ __forceinline__ void fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+template <int MM>
 struct DDShared {
-    double x[DD_MAX], y[DD_MAX], z[DD_MAX];
-    double nh[3][DD_MAX], nl[3][DD_MAX];  // unit normals
-    double ah[DD_MAX * LDA], al[DD_MAX * LDA];
-    double dh[DD_MAX], dl[DD_MAX], eh[DD_MAX], el[DD_MAX], e2h[DD_MAX], e2l[DD_MAX];
-    double vh[DD_MAX], vl[DD_MAX], wh[DD_MAX], wl[DD_MAX];
-    double bh[4][DD_MAX], bl[4][DD_MAX];
-    int piv[DD_MAX];
+    struct Search {
+        double4 de[MM];  // d_i and e_{i-1}^2, high and low words
+        double eh[MM];
+        double ch[64], cl[64], vh[64], vl[64], wh[64], wl[64];  // pivot column, v, w
+    };
+    struct Factor {
+        double ah[MM * DDL<MM>::LDA], al[MM * DDL<MM>::LDA];
+    };
+    union {
+        Search f;
+        Factor g;
+    };
+    double x[MM], y[MM], z[MM];
+    double bh[4][MM], bl[4][MM];
+    double n0h[3], n0l[3];  // the centre's unit normal
+    int piv[MM];
 };
 
 __device__ __forceinline__ dd ld(const double* h, const double* l, int i) { return {h[i], l[i]}; }
@@ -124,14 +232,19 @@ __device__ __forceinline__ void st(double* h, double* l, int i, dd v) {
     h[i] = v.hi;
     l[i] = v.lo;
 }
-__device__ __forceinline__ dd A(const DDShared& S, int r, int c) { return {S.ah[r * LDA + c], S.al[r * LDA + c]}; }
-__device__ __forceinline__ void setA(DDShared& S, int r, int c, dd v) {
-    S.ah[r * LDA + c] = v.hi;
-    S.al[r * LDA + c] = v.lo;
+template <int MM>
+__device__ __forceinline__ dd A(const DDShared<MM>& S, int r, int c) {
+    return {S.g.ah[r * DDL<MM>::LDA + c], S.g.al[r * DDL<MM>::LDA + c]};
+}
+template <int MM>
+__device__ __forceinline__ void setA(DDShared<MM>& S, int r, int c, dd v) {
+    S.g.ah[r * DDL<MM>::LDA + c] = v.hi;
+    S.g.al[r * DDL<MM>::LDA + c] = v.lo;
 }
 
 // x_i - x_j as an exact double-double, squared distance
-__device__ __forceinline__ void diff3(const DDShared& S, int i, int j, dd (&d)[3]) {
+template <int MM>
+__device__ __forceinline__ void diff3(const DDShared<MM>& S, int i, int j, dd (&d)[3]) {
     d[0] = two_sum(S.x[i], -S.x[j]);
     d[1] = two_sum(S.y[i], -S.y[j]);
     d[2] = two_sum(S.z[i], -S.z[j]);
@@ -152,33 +265,67 @@ __device__ __forceinline__ dd psi(dd e2, dd r2) {
     return K == RBFFD_KERNEL_MQ ? dvd(e2, s) : neg(dvd(e2, mul(s, t)));
 }
 
-// A~ = [[A, 1], [1^T, 0]] at eps (lane j fills column j)
-template <int K>
-__device__ void build_dd(DDShared& S, int n, int m, double eps, int j) {
-    const dd e2 = two_prod(eps, eps);
-    if (j < m) {
-        for (int r = 0; r < m; ++r) {
-            dd v = mk(0.0);
-            if (r < n && j < n) {
-                dd d[3];
-                diff3(S, r, j, d);
-                v = phi<K>(e2, norm2(d));
-            } else if (r < n || j < n) {
-                v = mk(1.0);
-            }
-            setA(S, r, j, v);
-        }
+// Entry (r, c) of A~ = [[A, 1], [1^T, 0]] at eps^2 = e2
+template <int K, int MM>
+__device__ __forceinline__ dd entry(const DDShared<MM>& S, int n, int m, dd e2, int r, int c) {
+    if (r < n && c < n) {
+        dd d[3];
+        diff3(S, r, c, d);
+        return phi<K>(e2, norm2(d));
     }
-    fence();
+    return mk(r < m && c < m && (r < n || c < n) ? 1.0 : 0.0);
 }
 
-// Householder tridiagonalisation of A~ (symmetric, full storage in LDS):
-// S.d, S.e (and e^2) hold T.
-__device__ void tridiag_dd(DDShared& S, int m, int j) {
-    for (int k = 0; k < m - 2; ++k) {
-        const dd xr = (j > k + 1 && j < m) ? A(S, j, k) : mk(0.0);
-        const dd alpha = A(S, k + 1, k);
-        const dd xn2 = wsum(mul(xr, xr));
+// f(i) for the one constant i in [LO, HI) that equals the wave-uniform k
+template <int LO, int HI, typename F>
+__device__ __forceinline__ void at_row(int k, F&& f) {
+    if constexpr (HI - LO == 1) {
+        f(std::integral_constant<int, LO>{});
+        // keeps the branches apart: merged, they would index the array dynamically
+        asm volatile("; row %0" ::"n"(LO));
+    } else {
+        constexpr int MID = (LO + HI) / 2;
+        if (k < MID) at_row<LO, MID>(k, f);
+        else at_row<MID, HI>(k, f);
+    }
+}
+// f(i) for i = LO .. HI - 1 as constants
+template <int LO, int HI, typename F>
+__device__ __forceinline__ void each(F&& f) {
+    if constexpr (LO < HI) {
+        f(std::integral_constant<int, LO>{});
+        each<LO + 1, HI>(f);
+    }
+}
+
+// Row r of the register matrix at the lane's column, in every lane that has
+// the column.
+template <int MM>
+__device__ __forceinline__ dd row_at(const dd (&a)[DDL<MM>::R], int r) {
+    constexpr int H = DDL<MM>::H;
+    dd v = mk(0.0);
+    at_row<0, DDL<MM>::R>(r / H, [&](auto q) __attribute__((always_inline)) { v = a[decltype(q)::value]; });
+    if constexpr (H == 2) {
+        dd lo, hi;
+        swap32(v, lo, hi);
+        v = r & 1 ? hi : lo;
+    }
+    return v;
+}
+
+// Householder steps whose row k + 1 lies in block B of the lane's rows; the
+// code holds only the rows from that block on.
+template <int MM, int B>
+__device__ __forceinline__ void tridiag_block(dd (&a)[DDL<MM>::R], DDShared<MM>& S, int m, int c, int h, int l15, dd& x) {
+    constexpr int H = DDL<MM>::H, R = DDL<MM>::R, BR = DDL<MM>::BR;
+    const int k0 = B == 0 ? 0 : H * BR * B - 1, kend = m - 2 < H * BR * (B + 1) - 1 ? m - 2 : H * BR * (B + 1) - 1;
+#pragma unroll 1
+    for (int k = k0; k < kend; ++k) {
+        const dd alpha = ld(S.f.ch, S.f.cl, k + 1);
+        const bool tail = c > k + 1 && c < m;
+        dd t = mk(0.0);
+        if (tail) mac(t, x, x);
+        const dd xn2 = wsum<MM>(t);
         dd beta = alpha, tau = mk(0.0), scal = mk(0.0);
         if (xn2.hi > 0.0) {
             const dd nrm = dsqrt(add(mul(alpha, alpha), xn2));
@@ -186,126 +333,212 @@ __device__ void tridiag_dd(DDShared& S, int m, int j) {
             tau = dvd(sub(beta, alpha), beta);
             scal = dvd(mk(1.0), sub(alpha, beta));
         }
-        const dd vj = (j == k + 1) ? mk(1.0) : ((j > k + 1 && j < m) ? mul(xr, scal) : mk(0.0));
-        if (j == 0) {
-            st(S.dh, S.dl, k, A(S, k, k));
-            st(S.eh, S.el, k, beta);
+        const dd vj = (c == k + 1) ? mk(1.0) : (tail ? mul(x, scal) : mk(0.0));
+        if (c == k && h == 0) {
+            const dd e2 = mul(beta, beta);
+            S.f.de[k].x = x.hi;
+            S.f.de[k].y = x.lo;
+            S.f.eh[k] = beta.hi;
+            S.f.de[k + 1].z = e2.hi;
+            S.f.de[k + 1].w = e2.lo;
         }
-        if (j < DD_MAX) st(S.vh, S.vl, j, vj);
+        st(S.f.vh, S.f.vl, c, vj);
         fence();
-        // w = tau A v - (tau^2 / 2) (v^T A v) v over the trailing block
+        // w = tau A v - (tau^2 / 2) (v^T A v) v over the rows from k + 1 on
+        dd v[R / 16], w[R / 16];
+#pragma unroll
+        for (int g = 0; g < R / 16; ++g) v[g] = ld(S.f.vh, S.f.vl, H * (16 * g + l15) + h);
         dd p = mk(0.0);
-        if (j > k && j < m)
-            for (int r = k + 1; r < m; ++r) p = add(p, mul(A(S, r, j), ld(S.vh, S.vl, r)));
-        dd wj = (j > k && j < m) ? mul(tau, p) : mk(0.0);
-        const dd s = wsum(mul(wj, vj));
+        each<BR * B, R>([&](auto q) __attribute__((always_inline)) {
+            constexpr int i = decltype(q)::value;
+            mac(p, a[i], row_lane<i % 16>(v[i / 16]));
+        });
+        if constexpr (H == 2) p = halves_sum(p);
+        else p = norm(p);
+        dd wj = (c > k && c < m) ? mul(tau, p) : mk(0.0);
+        const dd s = wsum<MM>(mul(wj, vj));
         wj = sub(wj, mul(mul_d(mul(tau, s), 0.5), vj));
-        if (j < DD_MAX) st(S.wh, S.wl, j, wj);
+        st(S.f.wh, S.f.wl, c, wj);
         fence();
-        if (j > k && j < m)
-            for (int r = k + 1; r < m; ++r) {
-                const dd vr = ld(S.vh, S.vl, r), wr = ld(S.wh, S.wl, r);
-                setA(S, r, j, sub(sub(A(S, r, j), mul(vr, wj)), mul(wr, vj)));
-            }
+#pragma unroll
+        for (int g = 0; g < R / 16; ++g) w[g] = ld(S.f.wh, S.f.wl, H * (16 * g + l15) + h);
+        const dd nv = neg(vj), nw = neg(wj);
+        each<BR * B, R>([&](auto q) __attribute__((always_inline)) {
+            constexpr int i = decltype(q)::value;
+            mac(a[i], row_lane<i % 16>(v[i / 16]), nw);
+            mac(a[i], row_lane<i % 16>(w[i / 16]), nv);
+            a[i] = norm(a[i]);
+        });
+        x = row_at<MM>(a, k + 1);
+        st(S.f.ch, S.f.cl, c, x);
         fence();
     }
-    if (j == 0) {
-        if (m >= 2) {
-            st(S.dh, S.dl, m - 2, A(S, m - 2, m - 2));
-            st(S.eh, S.el, m - 2, A(S, m - 1, m - 2));
-        }
-        st(S.dh, S.dl, m - 1, A(S, m - 1, m - 1));
-    }
+    if constexpr (BR * (B + 1) < R) tridiag_block<MM, B + 1>(a, S, m, c, h, l15, x);
+}
+
+// S.f.de and S.f.eh: the tridiagonal form of A~(eps).
+template <int K, int MM>
+__device__ __forceinline__ void tridiag_dd(DDShared<MM>& S, int n, int m, double eps, int c, int h, int l15) {
+    constexpr int H = DDL<MM>::H, R = DDL<MM>::R;
+    const dd e2 = two_prod(eps, eps);
+    dd a[R];
+    each<0, R>([&](auto q) __attribute__((always_inline)) {
+        constexpr int i = decltype(q)::value;
+        a[i] = entry<K, MM>(S, n, m, e2, H * i + h, c);
+    });
+    dd x = row_at<MM>(a, 0);
     fence();
-    if (j < m - 1) {
-        const dd e = ld(S.eh, S.el, j);
-        st(S.e2h, S.e2l, j, mul(e, e));
+    st(S.f.ch, S.f.cl, c, x);
+    fence();
+    tridiag_block<MM, 0>(a, S, m, c, h, l15, x);
+    // trailing 2 x 2 block: x is row m - 2
+    const dd y = row_at<MM>(a, m - 1);
+    if (h == 0) {
+        if (c == m - 2) {
+            S.f.de[m - 2].x = x.hi;
+            S.f.de[m - 2].y = x.lo;
+        }
+        if (c == m - 1) {
+            const dd q = mul(x, x);
+            S.f.eh[m - 2] = x.hi;
+            S.f.de[m - 1].z = q.hi;
+            S.f.de[m - 1].w = q.lo;
+            S.f.de[m - 1].x = y.hi;
+            S.f.de[m - 1].y = y.lo;
+        }
     }
     fence();
 }
 
 // #eigenvalues of T below sigma (double-double recurrence, FP64 shift)
-__device__ int sturm_dd(const DDShared& S, int m, double sigma, double pivmin) {
-    dd q = sub(ld(S.dh, S.dl, 0), mk(sigma));
-    if (fabs(q.hi) < pivmin) q = mk(-pivmin);
-    int c = q.hi < 0.0 ? 1 : 0;
-    for (int i = 1; i < m; ++i) {
-        q = sub(sub(ld(S.dh, S.dl, i), mk(sigma)), dvd(ld(S.e2h, S.e2l, i - 1), q));
+template <int MM>
+__device__ __forceinline__ int sturm_dd(const DDShared<MM>& S, int m, double sigma, double pivmin) {
+    int cnt = 0;
+    dd q = mk(1.0);
+#pragma unroll 2
+    for (int i = 0; i < m; ++i) {
+        const double4 de = S.f.de[i];
+        // e^2 / q to about 2^-104
+        const double r = recip1(q.hi);
+        const double q1 = i ? de.z * r : 0.0;
+        const double t = __builtin_fma(-q1, q.hi, de.z);
+        const double q2 = i ? (t + __builtin_fma(-q1, q.lo, de.w)) * r : 0.0;
+        const dd d = two_sum(de.x, -sigma);
+        const dd u = two_sum(d.hi, -q1);
+        q = quick_two_sum(u.hi, u.lo + ((d.lo + de.y) - q2));
         if (fabs(q.hi) < pivmin) q = mk(-pivmin);
-        c += q.hi < 0.0 ? 1 : 0;
+        cnt += q.hi < 0.0 ? 1 : 0;
     }
-    return c;
+    return cnt;
 }
 
+// Brackets of lambda_1 and lambda_m; max |lambda| = max(-lambda_1, lambda_m).
 struct SpecDD {
-    double lo1, hi1, lo2, hi2, amax, pivmin;
+    double lo1, hi1, lo2, hi2, pivmin;
     bool finite;
+    __device__ double alo() const { return fmax(-hi1, lo2); }
+    __device__ double ahi() const { return fmax(-lo1, hi2); }
+    __device__ double amax() const { return 0.5 * (alo() + ahi()); }
 };
 
-// brackets of lambda_1 (lanes 0..31) and lambda_m (lanes 32..63), 33-way
-// multisection until they are a few ulps wide
-__device__ SpecDD spectrum_dd(const DDShared& S, int m, int lane) {
-    SpecDD sp;
-    double gl = INFINITY, gu = -INFINITY, emax2 = 0.0;
+// Multisection rounds on max |lambda| until its bracket is a few ulps wide, at
+// most `rounds`: while both ends can be the larger, half the lanes split each
+// bracket 33 ways; then all split one 65 ways.
+template <int MM>
+__device__ __forceinline__ void refine_dd(const DDShared<MM>& S, int m, int lane, SpecDD& sp, int rounds) {
+    for (int rd = 0; rd < rounds && sp.ahi() - sp.alo() > 4e-16 * sp.ahi(); ++rd) {
+        const bool need1 = !(sp.lo2 > -sp.lo1), need2 = !(-sp.hi1 > sp.hi2), both = need1 && need2;
+        const int parts = both ? 32 : 64, tt = lane & (parts - 1);
+        const bool top = both ? lane >= 32 : need2;  // lambda_m's bracket
+        const double lo = top ? sp.lo2 : sp.lo1, hi = top ? sp.hi2 : sp.hi1;
+        const double sig = lo + (hi - lo) * (double)(tt + 1) / (double)(parts + 1);
+        const uint64_t bal = __ballot(sturm_dd(S, m, sig, sp.pivmin) < (top ? m : 1));
+        auto cut = [&](double& l, double& u, int nb) {
+            const double w = (u - l) / (double)(parts + 1), l0 = l;
+            if (nb < parts) u = l0 + w * (double)(nb + 1);
+            if (nb > 0) l = l0 + w * (double)nb;
+        };
+        if (both) {
+            cut(sp.lo1, sp.hi1, __popcll(bal & 0xffffffffull));
+            cut(sp.lo2, sp.hi2, __popcll(bal >> 32));
+        } else if (need2) {
+            cut(sp.lo2, sp.hi2, __popcll(bal));
+        } else {
+            cut(sp.lo1, sp.hi1, __popcll(bal));
+        }
+    }
+}
+
+// Gershgorin interval (and the extreme diagonal entries, Rayleigh quotients:
+// lambda_1 <= min d, lambda_m >= max d), then `rounds` rounds.
+template <int MM>
+__device__ __forceinline__ SpecDD spectrum_dd(const DDShared<MM>& S, int m, int lane, int rounds) {
+    double ngl = -INFINITY, gu = -INFINITY, emax2 = 0.0, dmx = -INFINITY, ndm = -INFINITY;
     bool fin = true;
-    for (int i = 0; i < m; ++i) {
-        const double off = (i > 0 ? fabs(S.eh[i - 1]) : 0.0) + (i < m - 1 ? fabs(S.eh[i]) : 0.0);
-        gl = fmin(gl, S.dh[i] - off);
-        gu = fmax(gu, S.dh[i] + off);
-        if (i < m - 1) emax2 = fmax(emax2, S.e2h[i]);
-        fin = fin && isfinite(S.dh[i]) && (i == m - 1 || isfinite(S.eh[i]));
+    if (lane < m) {
+        const double d = S.f.de[lane].x, e = lane < m - 1 ? S.f.eh[lane] : 0.0;
+        const double off = (lane > 0 ? fabs(S.f.eh[lane - 1]) : 0.0) + fabs(e);
+        ngl = off - d;
+        gu = off + d;
+        dmx = d;
+        ndm = -d;
+        emax2 = lane < m - 1 ? S.f.de[lane + 1].z : 0.0;
+        fin = isfinite(d) && isfinite(e);
     }
-    sp.finite = fin;
+    for (int o = 1; o < 64; o <<= 1) {
+        ngl = fmax(ngl, __shfl_xor(ngl, o, 64));
+        gu = fmax(gu, __shfl_xor(gu, o, 64));
+        dmx = fmax(dmx, __shfl_xor(dmx, o, 64));
+        ndm = fmax(ndm, __shfl_xor(ndm, o, 64));
+        emax2 = fmax(emax2, __shfl_xor(emax2, o, 64));
+    }
+    SpecDD sp;
+    sp.finite = __ballot(!fin) == 0;
     sp.pivmin = 1e-290 * fmax(1.0, emax2);
-    const double w = gu - gl;
-    gl -= 4.0 * w * 2.3e-16 + 2.0 * sp.pivmin;
-    gu += 4.0 * w * 2.3e-16 + 2.0 * sp.pivmin;
-    double lo1 = gl, hi1 = gu, lo2 = gl, hi2 = gu;
-    const int g = lane >> 5, tt = lane & 31;
-    for (int rd = 0; fin && rd < 14; ++rd) {
-        if (hi1 - lo1 <= 4e-16 * fmax(fabs(lo1), fabs(hi1)) && hi2 - lo2 <= 4e-16 * fmax(fabs(lo2), fabs(hi2))) break;
-        const double lo = g ? lo2 : lo1, hi = g ? hi2 : hi1;
-        const double sig = lo + (hi - lo) * (double)(tt + 1) / 33.0;
-        const bool below = sturm_dd(S, m, sig, sp.pivmin) < (g ? m : 1);
-        const uint64_t bal = __ballot(below);
-        const int nb1 = __popcll(bal & 0xffffffffull), nb2 = __popcll(bal >> 32);
-        const double a1 = nb1 > 0 ? lo1 + (hi1 - lo1) * (double)nb1 / 33.0 : lo1;
-        const double b1 = nb1 < 32 ? lo1 + (hi1 - lo1) * (double)(nb1 + 1) / 33.0 : hi1;
-        const double a2 = nb2 > 0 ? lo2 + (hi2 - lo2) * (double)nb2 / 33.0 : lo2;
-        const double b2 = nb2 < 32 ? lo2 + (hi2 - lo2) * (double)(nb2 + 1) / 33.0 : hi2;
-        lo1 = a1; hi1 = b1; lo2 = a2; hi2 = b2;
-    }
-    sp.lo1 = lo1; sp.hi1 = hi1; sp.lo2 = lo2; sp.hi2 = hi2;
-    sp.amax = fmax(fabs(0.5 * (lo1 + hi1)), fabs(0.5 * (lo2 + hi2)));
+    const double pad = 4.0 * (gu + ngl) * 2.3e-16 + 2.0 * sp.pivmin;
+    sp.lo1 = -ngl - pad;
+    sp.hi2 = gu + pad;
+    sp.hi1 = fmin(sp.hi2, -ndm + pad);
+    sp.lo2 = fmax(sp.lo1, dmx - pad);
+    if (sp.finite) refine_dd(S, m, lane, sp, rounds);
     return sp;
 }
 
-// #|lambda| < tau (lanes 0..1)
-__device__ int count_small(const DDShared& S, int m, const SpecDD& sp, double tau, int lane) {
-    const int c = lane < 2 ? sturm_dd(S, m, lane == 0 ? -tau : tau, sp.pivmin) : 0;
-    return __shfl(c, 1, 64) - __shfl(c, 0, 64);
-}
-
-// kappa_2 > target, decided from the Sturm counts at max|lambda| / target
-__device__ bool above_dd(const DDShared& S, int m, const SpecDD& sp, double target, int lane) {
-    if (!sp.finite || !(sp.amax > 0.0)) return true;
-    const double alo = fmax(-sp.hi1, sp.lo2), ahi = fmax(-sp.lo1, sp.hi2);
-    if (count_small(S, m, sp, alo / target, lane) > 0) return true;
-    if (count_small(S, m, sp, ahi / target, lane) == 0) return false;
-    return count_small(S, m, sp, sp.amax / target, lane) > 0;
+// kappa_2 > target: some |lambda| < max |lambda| / target.  The counts at both
+// ends of max |lambda|'s bracket decide, and only where they differ the
+// bracket is refined.
+template <int MM>
+__device__ __forceinline__ bool above_dd(const DDShared<MM>& S, int m, SpecDD& sp, double target, int lane) {
+    if (!sp.finite || !(sp.amax() > 0.0)) return true;
+    for (int it = 0;; ++it) {
+        const double mid = sp.amax() / target;
+        double sig = 0.0;
+        if (lane == 0) sig = -sp.alo() / target;
+        if (lane == 1) sig = sp.alo() / target;
+        if (lane == 2) sig = -sp.ahi() / target;
+        if (lane == 3) sig = sp.ahi() / target;
+        if (lane == 4) sig = -mid;
+        if (lane == 5) sig = mid;
+        const int c = lane < 6 ? sturm_dd(S, m, sig, sp.pivmin) : 0;
+        if (__shfl(c, 1, 64) > __shfl(c, 0, 64)) return true;
+        if (__shfl(c, 3, 64) == __shfl(c, 2, 64)) return false;
+        if (it == 8 || sp.ahi() - sp.alo() <= 4e-16 * sp.ahi()) return __shfl(c, 5, 64) > __shfl(c, 4, 64);
+        refine_dd(S, m, lane, sp, 2);
+    }
 }
 
 // smallest |lambda| by geometric multisection on both sides of zero
-__device__ double min_abs_dd(const DDShared& S, int m, const SpecDD& sp, int lane) {
+template <int MM>
+__device__ __forceinline__ double min_abs_dd(const DDShared<MM>& S, int m, const SpecDD& sp, int lane) {
     const int nu = sturm_dd(S, m, 0.0, sp.pivmin);
-    const double L = sp.amax * 1e-40 + sp.pivmin, H = sp.amax * (1.0 + 1e-14);
-    double lp = log(L), hp = log(H), ln_ = log(L), hn = log(H);
+    const double L = sp.amax() * 1e-40 + sp.pivmin, Hh = sp.amax() * (1.0 + 1e-14);
+    double lp = log(L), hp = log(Hh), ln_ = log(L), hn = log(Hh);
     const int g = lane >> 5, tt = lane & 31;
     for (int rd = 0; rd < 16 && fmax(hp - lp, hn - ln_) > 1e-14; ++rd) {
         const double lo = g ? ln_ : lp, hi = g ? hn : hp;
         const double sig = exp(lo + (hi - lo) * (double)(tt + 1) / 33.0);
-        const bool above = g == 0 ? sturm_dd(S, m, sig, sp.pivmin) <= nu : sturm_dd(S, m, -sig, sp.pivmin) >= nu;
-        const uint64_t bal = __ballot(above);
+        const int cnt = sturm_dd(S, m, g ? -sig : sig, sp.pivmin);
+        const uint64_t bal = __ballot(g ? cnt >= nu : cnt <= nu);
         const int nb1 = __popcll(bal & 0xffffffffull), nb2 = __popcll(bal >> 32);
         const double a1 = lp + (hp - lp) * (double)nb1 / 33.0, b1 = lp + (hp - lp) * (double)(nb1 + 1) / 33.0;
         const double a2 = ln_ + (hn - ln_) * (double)nb2 / 33.0, b2 = ln_ + (hn - ln_) * (double)(nb2 + 1) / 33.0;
@@ -319,17 +552,20 @@ __device__ double min_abs_dd(const DDShared& S, int m, const SpecDD& sp, int lan
     return fmin(pos, ng);
 }
 
-template <int K>
-__device__ SpecDD eval_dd(DDShared& S, int n, int m, double eps, int lane) {
-    build_dd<K>(S, n, m, eps, lane);
-    tridiag_dd(S, m, lane);
-    return spectrum_dd(S, m, lane);
+// a - b c
+__device__ __forceinline__ dd nmac(dd a, dd b, dd c) {
+    mac(a, neg(b), c);
+    return norm(a);
 }
 
-// LU with partial pivoting of A~ in place; false on a zero pivot
-__device__ bool lu_dd(DDShared& S, int m, int lane) {
+// LU with partial pivoting of A~ in place (lane (c, h): column c, rows of
+// parity h); false on a zero pivot
+template <int MM>
+__device__ bool lu_dd(DDShared<MM>& S, int m, int c, int h) {
+    constexpr int H = DDL<MM>::H, LDA = DDL<MM>::LDA;
+    const int lane = threadIdx.x;
     for (int k = 0; k < m; ++k) {
-        const double v = (lane >= k && lane < m) ? fabs(S.ah[lane * LDA + k]) : -1.0;
+        const double v = (lane >= k && lane < m) ? fabs(S.g.ah[lane * LDA + k]) : -1.0;
         double mx = v;
         for (int o = 1; o < 64; o <<= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
         const uint64_t hit = __ballot(v == mx && v >= 0.0);
@@ -345,9 +581,9 @@ __device__ bool lu_dd(DDShared& S, int m, int lane) {
         const dd piv = A(S, k, k);
         if (lane > k && lane < m) setA(S, lane, k, dvd(A(S, lane, k), piv));
         fence();
-        if (lane > k && lane < m) {
-            const dd ukj = A(S, k, lane);
-            for (int r = k + 1; r < m; ++r) setA(S, r, lane, sub(A(S, r, lane), mul(A(S, r, k), ukj)));
+        if (c > k && c < m) {
+            const dd ukj = A(S, k, c);
+            for (int r = k + 1 + ((k + 1 + h) & (H - 1)); r < m; r += H) setA(S, r, c, nmac(A(S, r, c), A(S, r, k), ukj));
         }
         fence();
     }
@@ -355,7 +591,8 @@ __device__ bool lu_dd(DDShared& S, int m, int lane) {
 }
 
 // b_v <- A~^{-1} b_v for the first nb right-hand sides in S.bh/bl
-__device__ void lu_solve_dd(DDShared& S, int m, int nb, int lane) {
+template <int MM>
+__device__ void lu_solve_dd(DDShared<MM>& S, int m, int nb, int lane) {
     if (lane < nb)
         for (int k = 0; k < m; ++k) {
             const int p = S.piv[k];
@@ -367,31 +604,37 @@ __device__ void lu_solve_dd(DDShared& S, int m, int nb, int lane) {
         }
     fence();
     for (int k = 0; k < m; ++k) {  // L (unit diagonal)
-        if (lane > k && lane < m)
+        if (lane > k && lane < m) {
+            const dd l = A(S, lane, k);
             for (int v = 0; v < nb; ++v)
-                st(S.bh[v], S.bl[v], lane, sub(ld(S.bh[v], S.bl[v], lane), mul(A(S, lane, k), ld(S.bh[v], S.bl[v], k))));
+                st(S.bh[v], S.bl[v], lane, nmac(ld(S.bh[v], S.bl[v], lane), l, ld(S.bh[v], S.bl[v], k)));
+        }
         fence();
     }
     for (int k = m - 1; k >= 0; --k) {  // U
-        if (lane == k)
-            for (int v = 0; v < nb; ++v) st(S.bh[v], S.bl[v], k, dvd(ld(S.bh[v], S.bl[v], k), A(S, k, k)));
+        if (lane < nb) st(S.bh[lane], S.bl[lane], k, dvd(ld(S.bh[lane], S.bl[lane], k), A(S, k, k)));
         fence();
-        if (lane < k)
+        if (lane < k) {
+            const dd u = A(S, lane, k);
             for (int v = 0; v < nb; ++v)
-                st(S.bh[v], S.bl[v], lane, sub(ld(S.bh[v], S.bl[v], lane), mul(A(S, lane, k), ld(S.bh[v], S.bl[v], k))));
+                st(S.bh[v], S.bl[v], lane, nmac(ld(S.bh[v], S.bl[v], lane), u, ld(S.bh[v], S.bl[v], k)));
+        }
         fence();
     }
 }
 
-template <int K>
-__global__ __launch_bounds__(64) void k_weights_dd(rbw::Job J) {
-    __shared__ DDShared S;
+template <int K, int MM>
+__global__ __launch_bounds__(64, 2) void k_weights_dd(rbw::Job J) {
+    constexpr int H = DDL<MM>::H, R = DDL<MM>::R;
+    __shared__ DDShared<MM> S;
     const int64_t s = blockIdx.x;
     if (s >= J.N) return;
     const rbw::WOpts& o = J.o;
     const int n = o.n, m = n + 1, lane = threadIdx.x;
-    // gather: coordinates, unit normals in double-double
+    const int c = H == 2 ? lane & 31 : lane, h = H == 2 ? lane >> 5 : 0, l15 = lane & 15;
+    // gather: coordinates; unit normals in double-double (lanes of the first half)
     bool bad = false, badn = false;
+    dd nu[3] = {mk(0.0), mk(0.0), mk(0.0)};
     if (lane < n) {
         int64_t node = J.idx[s * n + lane];
         bad = node < 0 || node >= J.N;
@@ -403,9 +646,11 @@ __global__ __launch_bounds__(64) void k_weights_dd(rbw::Job J) {
         const dd nn = dsqrt(add(add(mul(nx, nx), mul(ny, ny)), mul(nz, nz)));
         badn = !(nn.hi > 0.0 && isfinite(nn.hi));
         const dd inv = badn ? mk(0.0) : dvd(mk(1.0), nn);
-        st(S.nh[0], S.nl[0], lane, mul(nx, inv));
-        st(S.nh[1], S.nl[1], lane, mul(ny, inv));
-        st(S.nh[2], S.nl[2], lane, mul(nz, inv));
+        nu[0] = mul(nx, inv);
+        nu[1] = mul(ny, inv);
+        nu[2] = mul(nz, inv);
+        if (lane == 0)
+            for (int q = 0; q < 3; ++q) st(S.n0h, S.n0l, q, nu[q]);
     }
     fence();
     bool dup = false;
@@ -418,11 +663,12 @@ __global__ __launch_bounds__(64) void k_weights_dd(rbw::Job J) {
         dup = lane > 0 && r2.hi == 0.0;
     }
     if (__ballot(bad) || __ballot(badn)) {
+        const bool any_bad = __ballot(bad) != 0;
         if (lane == 0) {
             if (J.eps) J.eps[s] = NAN;
             if (J.kappa) J.kappa[s] = NAN;
             if (J.nevals) J.nevals[s] = 0;
-            if (J.status) J.status[s] = __ballot(bad) ? RBFFD_ST_BAD_INDEX : RBFFD_ST_BAD_NORMAL;
+            if (J.status) J.status[s] = any_bad ? RBFFD_ST_BAD_INDEX : RBFFD_ST_BAD_NORMAL;
         }
         if (lane < n) J.w[s * n + lane] = NAN;
         return;
@@ -431,49 +677,58 @@ __global__ __launch_bounds__(64) void k_weights_dd(rbw::Job J) {
     double rmax = r20;
     for (int o2 = 1; o2 < 64; o2 <<= 1) rmax = fmax(rmax, __shfl_xor(rmax, o2, 64));
     const double rho = sqrt(rmax);
-    int evals = 0;
-    double eps;
-    SpecDD sp;
+    // shape parameter: one evaluation per turn, so that its code is there once
+    enum Phase { LOW, HIGH, MID, FINAL };
+    int evals = 0, ph = FINAL, q = 0;
+    double eps, lo = 0.0, hi = 0.0;
     if (o.mode == RBFFD_EPS_FIXED) {
         eps = o.eps_fixed;
     } else if (o.mode == RBFFD_EPS_GIVEN) {
         eps = J.eps_in[s];
     } else {
-        double lo = o.br_lo / rho, hi = o.br_hi / rho;
-        sp = eval_dd<K>(S, n, m, lo, lane);
+        lo = o.br_lo / rho;
+        hi = o.br_hi / rho;
+        eps = lo;
+        ph = LOW;
+    }
+    SpecDD sp;
+    for (;;) {
+        tridiag_dd<K, MM>(S, n, m, eps, c, h, l15);
+        sp = spectrum_dd(S, m, lane, ph == FINAL ? 24 : 2);
         ++evals;
-        bool ab = above_dd(S, m, sp, o.kappa_target, lane);
-        for (int q = 0; !ab && q < o.max_expand; ++q) {
-            lo *= 0.5;
-            sp = eval_dd<K>(S, n, m, lo, lane);
-            ++evals;
-            ab = above_dd(S, m, sp, o.kappa_target, lane);
+        if (ph == FINAL) break;
+        const bool above = above_dd(S, m, sp, o.kappa_target, lane);
+        if (ph == LOW) {
+            if (!above && q < o.max_expand) {
+                ++q;
+                lo *= 0.5;
+                eps = lo;
+                continue;
+            }
+            if (!above && status == RBFFD_ST_OK) status = RBFFD_ST_NO_BRACKET;
+            q = 0;
+            eps = hi;
+            ph = HIGH;
+            continue;
         }
-        bool ok = ab;
-        sp = eval_dd<K>(S, n, m, hi, lane);
-        ++evals;
-        ab = above_dd(S, m, sp, o.kappa_target, lane);
-        for (int q = 0; ab && q < o.max_expand; ++q) {
-            hi *= 2.0;
-            sp = eval_dd<K>(S, n, m, hi, lane);
-            ++evals;
-            ab = above_dd(S, m, sp, o.kappa_target, lane);
+        if (ph == HIGH) {
+            if (above && q < o.max_expand) {
+                ++q;
+                hi *= 2.0;
+                eps = hi;
+                continue;
+            }
+            if (above && status == RBFFD_ST_OK) status = RBFFD_ST_NO_BRACKET;
+        } else if (above) {
+            lo = eps;
+        } else {
+            hi = eps;
         }
-        ok = ok && !ab;
-        if (!ok && status == RBFFD_ST_OK) status = RBFFD_ST_NO_BRACKET;
-        while (hi - lo > o.eps_tol) {
-            const double mid = 0.5 * (lo + hi);
-            sp = eval_dd<K>(S, n, m, mid, lane);
-            ++evals;
-            if (above_dd(S, m, sp, o.kappa_target, lane)) lo = mid;
-            else hi = mid;
-        }
+        ph = hi - lo > o.eps_tol ? MID : FINAL;
         eps = 0.5 * (lo + hi);
     }
-    sp = eval_dd<K>(S, n, m, eps, lane);
-    ++evals;
     double kappa = NAN;
-    if (sp.finite && sp.amax > 0.0) kappa = sp.amax / min_abs_dd(S, m, sp, lane);
+    if (sp.finite && sp.amax() > 0.0) kappa = sp.amax() / min_abs_dd(S, m, sp, lane);
     else if (status == RBFFD_ST_OK) status = RBFFD_ST_NONFINITE;
     if (lane == 0) {
         if (J.eps) J.eps[s] = eps;
@@ -481,59 +736,63 @@ __global__ __launch_bounds__(64) void k_weights_dd(rbw::Job J) {
         if (J.nevals) J.nevals[s] = evals;
     }
     // weights: LU of A~(eps), g_d = (A~^{-1} b_d)[:n], r = sum_d (B^d)^T g_d, w = (A~^{-1} r)[:n]
-    build_dd<K>(S, n, m, eps, lane);
     const dd e2 = two_prod(eps, eps);
-    const dd n0[3] = {ld(S.nh[0], S.nl[0], 0), ld(S.nh[1], S.nl[1], 0), ld(S.nh[2], S.nl[2], 0)};
+    fence();
+    if (c < m)
+        for (int r = h; r < m; r += H) setA(S, r, c, entry<K, MM>(S, n, m, e2, r, c));
     if (lane < m) {
         dd b[3] = {mk(0.0), mk(0.0), mk(0.0)};
         if (lane < n) {  // row 1 of B^d: psi(r_1j) [Pi_1 (x_1 - x_j)]_d; the ones border has zero gradient
             dd d[3];
             diff3(S, 0, lane, d);
             const dd ps = psi<K>(e2, norm2(d));
+            const dd n0[3] = {ld(S.n0h, S.n0l, 0), ld(S.n0h, S.n0l, 1), ld(S.n0h, S.n0l, 2)};
             const dd dn = add(add(mul(n0[0], d[0]), mul(n0[1], d[1])), mul(n0[2], d[2]));
-            for (int c = 0; c < 3; ++c) b[c] = mul(ps, sub(d[c], mul(n0[c], dn)));
+            for (int t = 0; t < 3; ++t) b[t] = mul(ps, sub(d[t], mul(n0[t], dn)));
         }
-        for (int c = 0; c < 3; ++c) st(S.bh[c], S.bl[c], lane, b[c]);
+        for (int t = 0; t < 3; ++t) st(S.bh[t], S.bl[t], lane, b[t]);
     }
     fence();
-    if (!lu_dd(S, m, lane)) {
+    if (!lu_dd(S, m, c, h)) {
         if (status == RBFFD_ST_OK) status = RBFFD_ST_SINGULAR;
         if (lane == 0 && J.status) J.status[s] = status;
         if (lane < n) J.w[s * n + lane] = NAN;
         return;
     }
     lu_solve_dd(S, m, 3, lane);
-    // h_i = Pi_i g_i, kept in S.v/S.w/S.d (free now) as three vectors
+    // h_i = Pi_i g_i, in place
     if (lane < n) {
-        dd g[3] = {ld(S.bh[0], S.bl[0], lane), ld(S.bh[1], S.bl[1], lane), ld(S.bh[2], S.bl[2], lane)};
-        const dd nu[3] = {ld(S.nh[0], S.nl[0], lane), ld(S.nh[1], S.nl[1], lane), ld(S.nh[2], S.nl[2], lane)};
+        dd g[3];
+        for (int t = 0; t < 3; ++t) g[t] = ld(S.bh[t], S.bl[t], lane);
         const dd dn = add(add(mul(nu[0], g[0]), mul(nu[1], g[1])), mul(nu[2], g[2]));
-        st(S.vh, S.vl, lane, sub(g[0], mul(nu[0], dn)));
-        st(S.wh, S.wl, lane, sub(g[1], mul(nu[1], dn)));
-        st(S.dh, S.dl, lane, sub(g[2], mul(nu[2], dn)));
+        for (int t = 0; t < 3; ++t) st(S.bh[t], S.bl[t], lane, sub(g[t], mul(nu[t], dn)));
     }
     fence();
     // r_j = sum_i psi(r_ij) (x_i - x_j) . h_i, r_n = 0
-    if (lane < m) {
-        dd rj = mk(0.0);
-        if (lane < n)
-            for (int i = 0; i < n; ++i) {
-                dd d[3];
-                diff3(S, i, lane, d);
-                const dd ps = psi<K>(e2, norm2(d));
-                const dd dot = add(add(mul(d[0], ld(S.vh, S.vl, i)), mul(d[1], ld(S.wh, S.wl, i))),
-                                   mul(d[2], ld(S.dh, S.dl, i)));
-                rj = add(rj, mul(ps, dot));
-            }
-        st(S.bh[3], S.bl[3], lane, rj);
-    }
+    dd rj = mk(0.0);
+    if (c < n)
+        for (int i = h; i < n; i += H) {
+            dd d[3];
+            diff3(S, i, c, d);
+            const dd ps = psi<K>(e2, norm2(d));
+            dd dot = mk(0.0);
+            for (int t = 0; t < 3; ++t) mac(dot, d[t], ld(S.bh[t], S.bl[t], i));
+            mac(rj, ps, norm(dot));
+        }
+    rj = H == 2 ? halves_sum(rj) : norm(rj);
     fence();
-    // the solve for w reads slot 3 only: move it to slot 0
-    if (lane < m) st(S.bh[0], S.bl[0], lane, ld(S.bh[3], S.bl[3], lane));
+    if (lane < m) st(S.bh[0], S.bl[0], lane, rj);
     fence();
     lu_solve_dd(S, m, 1, lane);
     if (lane < n) J.w[s * n + lane] = to_d(ld(S.bh[0], S.bl[0], lane));
     if (lane == 0 && J.status) J.status[s] = status;
+}
+
+template <int MM>
+void launch_dd(hipStream_t st, const rbw::Job& J) {
+    const dim3 g((unsigned)J.N), b(64);
+    if (J.o.kernel == RBFFD_KERNEL_MQ) hipLaunchKernelGGL((k_weights_dd<RBFFD_KERNEL_MQ, MM>), g, b, 0, st, J);
+    else hipLaunchKernelGGL((k_weights_dd<RBFFD_KERNEL_IMQ, MM>), g, b, 0, st, J);
 }
 
 }  // namespace
@@ -580,9 +839,9 @@ extern "C" int rbffd_build_weights_dd(rbffd_ctx ctx, int64_t N, const double* xy
     J.status = status;
     J.nevals = nevals;
     J.kappa_only = 0;
-    const dim3 g((unsigned)N), b(64);
-    if (J.o.kernel == RBFFD_KERNEL_MQ) hipLaunchKernelGGL(k_weights_dd<RBFFD_KERNEL_MQ>, g, b, 0, ctx->stream, J);
-    else hipLaunchKernelGGL(k_weights_dd<RBFFD_KERNEL_IMQ>, g, b, 0, ctx->stream, J);
+    // two lanes per column as long as they fit; past that one lane holds a column
+    if (J.o.n + 1 <= 32) launch_dd<32>(ctx->stream, J);
+    else launch_dd<DD_MAX>(ctx->stream, J);
     HIP_TRY(ctx, hipGetLastError());
     return RBFFD_OK;
 }

@@ -65,3 +65,27 @@ def test_two_stencils_per_wave_match_single_rows(lib):
     for f in ("w", "eps", "kappa", "status", "nevals"):
         assert torch.equal(getattr(a, f)[p], getattr(b, f)), f
     assert (a.status == 0).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kernel", ["mq", "imq"])
+@pytest.mark.parametrize("n", [2, 3, 9, 16, 17, 30, 31, 32, 33, 46, 47])
+def test_double_double_tiling_edges(lib, n, kernel):
+    """m = n + 1 around the rows of a lane (multiples of 4 and 16) and at both
+    sides of 32; well conditioned, so the FP64 oracle holds to its own error."""
+    import torch
+
+    X, nrm = jittered_torus(9, 27)
+    idx = oracle_knn(X, n)
+    eps = 6.0
+    r = lib.build_weights_dd(torch.as_tensor(X).cuda(), torch.as_tensor(nrm).cuda(), n, kernel=kernel, degree=0,
+                             eps_mode="fixed", eps=eps)
+    assert (r.status.cpu().numpy() == 0).all()
+    rows = [0, 121, 242]
+    wo = oracle_weights(X, nrm, idx, np.full(len(X), eps), rows=rows, kernel=kernel, degree=0)
+    w, kap = r.w.cpu().numpy(), r.kappa.cpu().numpy()
+    for t, i in enumerate(rows):
+        k = stencil_kappa(X[idx[i]], eps, kernel=kernel, degree=0)
+        assert abs(kap[i] - k) <= max(1e-12, 20 * k * U) * k, (i, kap[i], k)
+        err = np.linalg.norm(w[i] - wo[t]) / np.linalg.norm(wo[t])
+        assert err <= max(1e-12, 0.5 * k * U), (i, err, k)
