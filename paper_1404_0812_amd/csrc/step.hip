@@ -1139,10 +1139,9 @@ extern "C" int rbffd_step_forced(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, d
 // (its eigenvalues have real part >= 1 whenever L's are in the left half
 // plane, the stability property of Sec. 5).  Vectors are FP64 in internal
 // order, one array per species; every scalar of the iteration stays on the
-// device, the host reads the residual norm once per iteration to stop.
+// device; the host reads the residual norm every few iterations to stop.
 namespace {
 
-constexpr int RED_BLOCKS = 512;
 
 struct BdfCoef {
     double a[5], b[4];
@@ -1181,33 +1180,19 @@ struct KrylovScalars {
     int pad;
 };
 
-// Iterations launched between two reads of the scalars by the host; the
-// kernels of iterations after convergence (or a breakdown) return at once.
+// Iterations of one graph; the host reads the scalars after as many graphs as
+// the species' last solve took, and the kernels of iterations after
+// convergence (or a breakdown) return at once.
 constexpr int KRYLOV_BATCH = 8;
+// Block partials that a kernel sums by itself, two loads per thread; more are
+// first summed by a kernel of one block, whose launch (2 us) then costs less
+// than all of them read by every block of the next kernel.
+constexpr int PART_DIRECT = 512;
 
 struct HistPtrs {
     const double* u[4];   // u^n, u^{n-1}, ... (one species)
     const double* r[4];   // R_s at those states (nullable entries when no reaction)
 };
-
-// b = (-sum_{j>=1} a_j u^{n+1-j} + dt sum_j b_j R^{n+1-j} + dt ef F) / a_0
-// (0 on padding rows, whose reaction values are not zero in general)
-__global__ void k_bdf_rhs(int64_t P, int k, BdfCoef c, HistPtrs h, const double* __restrict__ F, double ef,
-                          double dt, const int32_t* __restrict__ perm, double* __restrict__ out) {
-    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (p >= P) return;
-    if (perm[p] < 0) {
-        out[p] = 0.0;
-        return;
-    }
-    double v = 0.0;
-    for (int j = 1; j <= k; ++j) {
-        v = fma(-c.a[j], h.u[j - 1][p], v);
-        if (h.r[j - 1]) v = fma(dt * c.b[j - 1], h.r[j - 1][p], v);
-    }
-    if (F) v = fma(dt * ef, F[p], v);
-    out[p] = v / c.a[0];
-}
 
 // R(u) for both species of one state (rows in internal order, per-species arrays).
 template <int R>
@@ -1221,173 +1206,279 @@ __global__ void k_reaction2(int64_t P, const double* __restrict__ u, const doubl
     rv[p] = r[1];
 }
 
-// out = x - gamma L x (live rows; padding rows keep their zero).  With ks
-// (inside the iteration, also inside its graph) gamma comes from ks and the
-// kernel is a no-op once the solve is done.
-__global__ __launch_bounds__(BLK) void k_amul(StageArgs a, const int32_t* __restrict__ idx,
-                                              const double* __restrict__ w, const double* __restrict__ X,
-                                              double gamma, double* __restrict__ out,
-                                              const KrylovScalars* __restrict__ ks) {
-    if (ks) {
-        if (ks->done) return;
-        gamma = ks->gamma;
+// L y at row rp.p, the neighbour values given by val(j) (FP64, one species; the
+// slot order and the form of apply_row_halo).  Every lane of the wavefront
+// takes part.
+template <typename V>
+__device__ __forceinline__ double laplacian_of(const StageArgs& a, const RowPos& rp, const int32_t* __restrict__ idx,
+                                               const double* __restrict__ w, double yi, V&& val) {
+    __shared__ double ylds[BLK / 64][OP_HALO_MAX];
+    double* yl = ylds[threadIdx.x >> 6];
+    const bool staged = rp.halo >= 0;
+    if (staged) {
+        const int32_t* h = a.halo + rp.slice * OP_HALO_MAX;
+        for (int t = rp.lane; t < rp.halo; t += 64) yl[t] = val(h[t]);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    const RowPos rp = row_pos<double>(a);
-    if (rp.slice < 0) return;
-    double yi[2] = {0.0, 0.0};
-    if (rp.live) yi[0] = X[rp.p];
+    if (!rp.live) return 0.0;
+    const double wd = __builtin_nontemporal_load(a.wd64 + rp.p);
+    const double y2[2] = {yi, 0.0};
     double lap[2];
-    laplacian_row<double, 1>(a, rp, idx, w, X, yi, lap);
-    if (rp.live) out[rp.p] = fma(-gamma, lap[0], yi[0]);
+    if (staged) {
+        apply_row_halo<double, 1>(rp, a.lidx, w, yl, y2, wd, lap);
+        return lap[0];
+    }
+    double acc = wd * yi;
+#pragma unroll 8
+    for (int k = 0; k < rp.ns; ++k) {
+        const int64_t at = rp.base + slot_pos(k, rp.ns, rp.lane);
+        acc = fma(w[at], val(idx[at]), acc);
+    }
+    return acc;
 }
 
 __device__ __forceinline__ double wave_sum_block(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
-
-// Block sums of up to two dot products over P rows; partials[blk * 2 + q].
-__device__ __forceinline__ double block_sum(double v, double* sh) {
-    v = wave_sum_block(v);
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    if (l == 0) sh[w] = v;
+// Sums of two values over a block of 256, the same bits in every thread
+// (sh: 8 words; a barrier on entry, so that sh may be used again).
+__device__ __forceinline__ void block_sum2(double& v0, double& v1, double* sh) {
+    v0 = wave_sum_block(v0);
+    v1 = wave_sum_block(v1);
     __syncthreads();
-    double t = 0.0;
-    if (threadIdx.x == 0)
-        for (int i = 0; i < (int)(blockDim.x >> 6); ++i) t += sh[i];
+    if ((threadIdx.x & 63) == 0) {
+        sh[2 * (threadIdx.x >> 6)] = v0;
+        sh[2 * (threadIdx.x >> 6) + 1] = v1;
+    }
     __syncthreads();
-    return t;
+    v0 = (sh[0] + sh[2]) + (sh[4] + sh[6]);
+    v1 = (sh[1] + sh[3]) + (sh[5] + sh[7]);
+}
+// Block partials (pairs) summed in a fixed order: deterministic, and the same
+// in every block that does it.
+__device__ __forceinline__ void sum_partials(const double2* __restrict__ part, int np, double& d0, double& d1,
+                                             double* sh) {
+    d0 = d1 = 0.0;
+    for (int i = threadIdx.x; i < np; i += 256) {
+        const double2 v = part[i];
+        d0 += v.x;
+        d1 += v.y;
+    }
+    block_sum2(d0, d1, sh);
+}
+__global__ __launch_bounds__(256) void k_sum_partials(const double2* __restrict__ part, int np, double2* out) {
+    __shared__ double sh[8];
+    double d0, d1;
+    sum_partials(part, np, d0, d1, sh);
+    if (threadIdx.x == 0) *out = make_double2(d0, d1);
 }
 
-template <int NQ>
-__global__ __launch_bounds__(256) void k_dots(int64_t P, const double* __restrict__ a0, const double* __restrict__ b0,
-                                              const double* __restrict__ a1, const double* __restrict__ b1,
-                                              double* __restrict__ partials, const KrylovScalars* __restrict__ ks) {
-    if (ks && ks->done) return;
-    __shared__ double sh[4];
-    double s0 = 0.0, s1 = 0.0;
-    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < P; p += (int64_t)gridDim.x * blockDim.x) {
-        s0 = fma(a0[p], b0[p], s0);
-        if (NQ == 2) s1 = fma(a1[p], b1[p], s1);
-    }
-    const double t0 = block_sum(s0, sh);
-    double t1 = 0.0;
-    if (NQ == 2) t1 = block_sum(s1, sh);
-    if (threadIdx.x == 0) {
-        partials[2 * blockIdx.x] = t0;
-        partials[2 * blockIdx.x + 1] = t1;
-    }
-}
-
-// Sum the block partials in a fixed order (one wave): deterministic.
-__device__ __forceinline__ void sum_partials(const double* __restrict__ partials, double& d0, double& d1) {
-    double s0 = 0.0, s1 = 0.0;
-    for (int i = threadIdx.x; i < RED_BLOCKS; i += 64) {
-        s0 += partials[2 * i];
-        s1 += partials[2 * i + 1];
-    }
-    d0 = wave_sum_block(s0);
-    d1 = wave_sum_block(s1);
-}
-
-// Scalar steps of the iteration (one wave each); every mode but 0 is a no-op
-// once the solve is done.
-// MODE 0 (start; d0 = b.b, d1 = r.r, rhat = r): bb, rr = rr0 = rho = d1,
-//         alpha = omega = 1, tol and gamma stored; iters = 0 on the first
-//         start of a solve; done at once if r already meets tol
-// MODE 2: alpha = rho / d0 (d0 = rhat.v)
-// MODE 3: omega = d0 / d1 (t.s / t.t)
-// MODE 4 (end of an iteration; d0 = r.r, d1 = rhat.r): rr = d0; converged,
-//         non-finite, or else rho' = d1 and beta = (rho' / rho) (alpha / omega)
-//         for the next iteration, unless |rho'| <= 1e-14 ||rhat|| ||r|| or
-//         omega = 0 (breakdown: the host restarts from the true residual)
-__device__ __forceinline__ int residual_state(const KrylovScalars* ks, double rr) {
+__device__ __forceinline__ int residual_state(const KrylovScalars& k, double rr) {
     if (!(rr <= 1.79e308)) return 3;
-    const double lim = ks->bb > 0.0 ? ks->tol2 * ks->bb : ks->tol2;
+    const double lim = k.bb > 0.0 ? k.tol2 * k.bb : k.tol2;
     return rr <= lim ? 1 : 0;
 }
-
-template <int MODE>
-__global__ void k_krylov_scalar(const double* __restrict__ partials, KrylovScalars* __restrict__ ks, double tol,
-                                int first, double gamma) {
-    if (MODE != 0 && ks->done) return;
-    double d0, d1;
-    sum_partials(partials, d0, d1);
-    if (threadIdx.x != 0) return;
-    if (MODE == 0) {
-        ks->bb = d0;
-        ks->rr = ks->rr0 = ks->rho = d1;
-        ks->alpha = ks->omega = 1.0;
-        ks->beta = 0.0;
-        ks->tol2 = tol * tol;
-        ks->gamma = gamma;
-        ks->breakdown = 0;
-        if (first) ks->iters = 0;
-        ks->done = residual_state(ks, d1);
-    } else if (MODE == 2) {
-        if (d0 == 0.0) ks->breakdown = 1;
-        ks->alpha = ks->breakdown ? 0.0 : ks->rho / d0;
-    } else if (MODE == 3) {
-        ks->omega = d1 > 0.0 ? d0 / d1 : 0.0;
-    } else {
-        ks->iters += 1;
-        ks->rr = d0;
-        const int st = residual_state(ks, d0);
-        if (st) {
-            ks->done = st;
-            return;
-        }
-        const double rho = d1;
-        if (ks->breakdown || !(std::fabs(rho) > 1e-14 * std::sqrt(ks->rr0 * d0)) || ks->omega == 0.0) {
-            ks->breakdown = 1;
-            ks->done = 2;
-            return;
-        }
-        ks->beta = (rho / ks->rho) * (ks->alpha / ks->omega);
-        ks->rho = rho;
+// End of an iteration (rr = r.r, rho = rhat.r): converged, non-finite, or else
+// beta = (rho' / rho) (alpha / omega) for the next one, unless |rho'| <= 1e-14
+// ||rhat|| ||r|| or omega = 0 (breakdown: the host restarts from the true
+// residual).
+__device__ __forceinline__ void end_iteration(KrylovScalars& k, double rr, double rho) {
+    k.iters += 1;
+    k.rr = rr;
+    k.done = residual_state(k, rr);
+    if (k.done) return;
+    if (k.breakdown || !(std::fabs(rho) > 1e-14 * std::sqrt(k.rr0 * rr)) || k.omega == 0.0) {
+        k.breakdown = 1;
+        k.done = 2;
+        return;
     }
+    k.beta = (rho / k.rho) * (k.alpha / k.omega);
+    k.rho = rho;
 }
 
-// r = b - Ax; rhat = r; p = v = 0
-__global__ void k_kry_init(int64_t P, const double* __restrict__ b, const double* __restrict__ ax,
-                           double* __restrict__ r, double* __restrict__ rh, double* __restrict__ pv,
-                           double* __restrict__ v) {
-    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (p >= P) return;
-    const double rv = b[p] - ax[p];
-    r[p] = rv;
-    rh[p] = rv;
-    pv[p] = 0.0;
-    v[p] = 0.0;
+// Start (FIRST: of a step's solve; else after a breakdown): r = rhat = b - (x -
+// gamma L x), p = v = 0, partials of b.b and r.r.  FIRST also forms the right
+// hand side b = (-sum_{j>=1} a_j u^{n+1-j} + dt sum_j b_j R^{n+1-j} + dt ef F)
+// / a_0 and x = u^n.  Padding rows are written as
+// zero in every vector, here and below.
+template <bool FIRST>
+__global__ __launch_bounds__(BLK) void k_kry_start(StageArgs a, const int32_t* __restrict__ idx,
+                                                   const double* __restrict__ w, int nk, BdfCoef c, HistPtrs hp,
+                                                   const double* __restrict__ F, double ef, double dt, double gamma,
+                                                   double* __restrict__ b, double* __restrict__ x,
+                                                   double* __restrict__ r, double* __restrict__ rh,
+                                                   double* __restrict__ pv, double* __restrict__ v,
+                                                   double2* __restrict__ part) {
+    __shared__ double sh[8];
+    const RowPos rp = row_pos<double>(a);
+    const int64_t p = rp.p;
+    const double* __restrict__ x0 = FIRST ? hp.u[0] : x;
+    const double yi = rp.live ? x0[p] : 0.0;
+    const double lap = laplacian_of(a, rp, idx, w, yi, [&](int64_t j) { return x0[j]; });
+    double bb = 0.0, rr = 0.0;
+    if (rp.slice >= 0) {
+        double bv = 0.0;
+        if constexpr (FIRST) {
+            for (int j = 1; j <= nk && rp.live; ++j) {
+                bv = fma(-c.a[j], hp.u[j - 1][p], bv);
+                if (hp.r[j - 1]) bv = fma(dt * c.b[j - 1], hp.r[j - 1][p], bv);
+            }
+            if (F && rp.live) bv = fma(dt * ef, F[p], bv);
+            bv /= c.a[0];
+            b[p] = bv;
+            x[p] = yi;
+        } else {
+            bv = b[p];
+        }
+        const double rv = bv - fma(-gamma, lap, yi);
+        r[p] = rv;
+        rh[p] = rv;
+        pv[p] = 0.0;
+        v[p] = 0.0;
+        bb = bv * bv;
+        rr = rv * rv;
+    }
+    block_sum2(bb, rr, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = make_double2(bb, rr);
+}
+// bb, rr = rr0 = rho = r.r; alpha = omega = 1, tol and gamma stored; iters = 0
+// on the first start of a solve; done at once if r already meets tol
+__global__ __launch_bounds__(256) void k_kry_begin(const double2* __restrict__ part, int np, KrylovScalars* ks,
+                                                   double tol, int first, double gamma) {
+    __shared__ double sh[8];
+    double d0, d1;
+    sum_partials(part, np, d0, d1, sh);
+    if (threadIdx.x != 0) return;
+    ks->bb = d0;
+    ks->rr = ks->rr0 = ks->rho = d1;
+    ks->alpha = ks->omega = 1.0;
+    ks->beta = 0.0;
+    ks->tol2 = tol * tol;
+    ks->gamma = gamma;
+    ks->breakdown = 0;
+    if (first) ks->iters = 0;
+    ks->done = residual_state(*ks, d1);
 }
 
-// p = r + beta (p - omega v)
-__global__ void k_kry_p(int64_t P, const KrylovScalars* __restrict__ ks, const double* __restrict__ r,
-                        double* __restrict__ pv, const double* __restrict__ v) {
-    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (p >= P || ks->done) return;
-    const double beta = ks->beta, omega = ks->omega;
-    pv[p] = fma(beta, fma(-omega, v[p], pv[p]), r[p]);
+// One iteration is three kernels.  What neighbours need of p and s is formed
+// from the vectors of the kernel before while it is gathered, so neither is a
+// pass of its own; scalars are formed from the block partials by every block
+// alike and stored by block 0, in the other of two copies where other blocks
+// still read the old one.  What bounds it is the latency of a launch
+// and of its dependent loads (7.6, 7.0 and 3.7 us at N = 10242, n = 31), and
+// above N = 1e5 the operator's bytes, read twice.  Against eleven kernels an
+// iteration: ten steps at N = 10242 26.1 -> 13.4 ms, five at N = 2500 9.1 ->
+// 4.5 ms, five at N = 1e5, n = 50 21.8 -> 14.7 ms, three at N = 6e5 37.0 ->
+// 35.7 ms.
+//
+// k_kry_pv: the last iteration's end unless FIRST of a launch sequence (then ks_in is
+// final); p' = r + beta (p - omega v), v' = p' - gamma L p', partials rhat.v'
+template <bool FIRST>
+__global__ __launch_bounds__(BLK) void k_kry_pv(StageArgs a, const int32_t* __restrict__ idx,
+                                                const double* __restrict__ w, const double2* __restrict__ part_in,
+                                                int np, const KrylovScalars* ks_in, KrylovScalars* ks_out,
+                                                const double* __restrict__ r, const double* __restrict__ rh,
+                                                const double* __restrict__ pv, const double* __restrict__ v,
+                                                double* __restrict__ p_out, double* __restrict__ v_out,
+                                                double2* __restrict__ part) {
+    __shared__ double sh[8];
+    const bool writer = blockIdx.x == 0 && threadIdx.x == 0;
+    KrylovScalars k = *ks_in;
+    if constexpr (!FIRST) {
+        if (!k.done) {
+            double d0, d1;
+            sum_partials(part_in, np, d0, d1, sh);
+            end_iteration(k, d0, d1);
+        }
+        if (writer) *ks_out = k;
+    }
+    if (k.done) return;
+    const RowPos rp = row_pos<double>(a);
+    auto val = [&](int64_t j) { return fma(k.beta, fma(-k.omega, v[j], pv[j]), r[j]); };
+    const double yi = rp.live ? val(rp.p) : 0.0;
+    const double lap = laplacian_of(a, rp, idx, w, yi, val);
+    double d = 0.0, z = 0.0;
+    if (rp.slice >= 0) {
+        const double o = fma(-k.gamma, lap, yi);
+        p_out[rp.p] = yi;
+        v_out[rp.p] = o;
+        d = rh[rp.p] * o;
+    }
+    block_sum2(d, z, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = make_double2(d, 0.0);
 }
-
-// s = r - alpha v
-__global__ void k_kry_s(int64_t P, const KrylovScalars* __restrict__ ks, const double* __restrict__ r,
-                        const double* __restrict__ v, double* __restrict__ s) {
-    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (p >= P || ks->done) return;
-    s[p] = fma(-ks->alpha, v[p], r[p]);
+// alpha = rho / rhat.v; s = r - alpha v, t = s - gamma L s, partials t.s and t.t
+__global__ __launch_bounds__(BLK) void k_kry_st(StageArgs a, const int32_t* __restrict__ idx,
+                                                const double* __restrict__ w, const double2* __restrict__ part_in,
+                                                int np, KrylovScalars* ks, const double* __restrict__ r,
+                                                const double* __restrict__ v, double* __restrict__ sv,
+                                                double* __restrict__ tv, double2* __restrict__ part) {
+    __shared__ double sh[8];
+    if (ks->done) return;
+    const double gamma = ks->gamma;
+    double d0, d1;
+    sum_partials(part_in, np, d0, d1, sh);
+    const bool broken = d0 == 0.0;
+    const double alpha = broken ? 0.0 : ks->rho / d0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {  // no block reads these two here
+        ks->alpha = alpha;
+        if (broken) ks->breakdown = 1;
+    }
+    const RowPos rp = row_pos<double>(a);
+    auto val = [&](int64_t j) { return fma(-alpha, v[j], r[j]); };
+    const double yi = rp.live ? val(rp.p) : 0.0;
+    const double lap = laplacian_of(a, rp, idx, w, yi, val);
+    double ts = 0.0, tt = 0.0;
+    if (rp.slice >= 0) {
+        const double o = fma(-gamma, lap, yi);
+        sv[rp.p] = yi;
+        tv[rp.p] = o;
+        ts = o * yi;
+        tt = o * o;
+    }
+    block_sum2(ts, tt, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = make_double2(ts, tt);
 }
-
-// x += alpha p + omega s; r = s - omega t
-__global__ void k_kry_xr(int64_t P, const KrylovScalars* __restrict__ ks, const double* __restrict__ pv,
-                         const double* __restrict__ s, const double* __restrict__ t, double* __restrict__ x,
-                         double* __restrict__ r) {
-    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (p >= P || ks->done) return;
-    const double alpha = ks->alpha, omega = ks->omega;
-    const double sv = s[p];
-    x[p] = fma(omega, sv, fma(alpha, pv[p], x[p]));
-    r[p] = fma(-omega, t[p], sv);
+// omega = t.s / t.t; x += alpha p + omega s, r = s - omega t, partials r.r and rhat.r
+__global__ __launch_bounds__(256) void k_kry_xr(int64_t P, const double2* __restrict__ part_in, int np,
+                                                KrylovScalars* ks, const double* __restrict__ pv,
+                                                const double* __restrict__ sv, const double* __restrict__ tv,
+                                                const double* __restrict__ rh, double* __restrict__ x,
+                                                double* __restrict__ r, double2* __restrict__ part) {
+    __shared__ double sh[8];
+    if (ks->done) return;
+    double d0, d1;
+    sum_partials(part_in, np, d0, d1, sh);
+    const double omega = d1 > 0.0 ? d0 / d1 : 0.0, alpha = ks->alpha;
+    if (blockIdx.x == 0 && threadIdx.x == 0) ks->omega = omega;  // no block reads it here
+    const int64_t p = blockIdx.x * (int64_t)256 + threadIdx.x;
+    double rr = 0.0, hr = 0.0;
+    if (p < P) {
+        const double s = sv[p];
+        x[p] = fma(omega, s, fma(alpha, pv[p], x[p]));
+        const double q = fma(-omega, tv[p], s);
+        r[p] = q;
+        rr = q * q;
+        hr = rh[p] * q;
+    }
+    block_sum2(rr, hr, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = make_double2(rr, hr);
+}
+// End of the last iteration of a launch sequence; the scalars move to *ks_out.
+__global__ __launch_bounds__(256) void k_kry_end(const double2* __restrict__ part, int np, const KrylovScalars* ks_in,
+                                                 KrylovScalars* ks_out) {
+    __shared__ double sh[8];
+    KrylovScalars k = *ks_in;
+    if (!k.done) {
+        double d0, d1;
+        sum_partials(part, np, d0, d1, sh);
+        end_iteration(k, d0, d1);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) *ks_out = k;
 }
 
 __global__ void k_copy(int64_t P, const double* __restrict__ src, double* __restrict__ dst) {
@@ -1435,14 +1526,21 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
     const int64_t N = op->N, P = op->P;
     const int S = nspecies;
     const bool react = reaction != RBFFD_REACT_NONE;
-    // layout: U[s][order], R[s][order] (reaction), F[s], b, x, r, rh, p, v, s, t; partials; scalars
-    const int nvec = S * order * (react ? 2 : 1) + S + 8;
+    // layout: scalars (two copies), summed partials, three sets of block partials;
+    // U[s][order], R[s][order] (reaction), F[s], b, x, r, rh, p and v (two each), s, t
+    const int nvec = S * order * (react ? 2 : 1) + S + 10;
+    const int nblk = (int)stage_grid(op->nslices).x;
+    const size_t head = (1024 + 3 * (size_t)nblk * sizeof(double2) + 255) & ~(size_t)255;
     const size_t vbytes = (size_t)P * sizeof(double);
-    const size_t bytes = nvec * vbytes + 2 * RED_BLOCKS * sizeof(double) + 256;
-    int rc = ensure_impl(op, bytes);
+    int rc = ensure_impl(op, head + nvec * vbytes);
     if (rc) return rc;
     hipStream_t st = ctx->stream;
-    double* base = (double*)op->impl;
+    static_assert(2 * sizeof(KrylovScalars) <= 512, "scalars");
+    KrylovScalars* ks = (KrylovScalars*)op->impl;
+    double2* psum = (double2*)((char*)op->impl + 512);
+    double2* part[3];
+    for (int q = 0; q < 3; ++q) part[q] = (double2*)((char*)op->impl + 1024) + (size_t)q * nblk;
+    double* base = (double*)((char*)op->impl + head);
     auto vec = [&](int i) { return base + (size_t)i * P; };
     int vi = 0;
     double* U[2][4] = {};
@@ -1458,12 +1556,10 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
     double* x = vec(vi++);
     double* r = vec(vi++);
     double* rh = vec(vi++);
-    double* pv = vec(vi++);
-    double* v = vec(vi++);
-    double* sv = vec(vi++);
-    double* tv = vec(vi++);
-    double* partials = vec(vi);
-    KrylovScalars* ks = reinterpret_cast<KrylovScalars*>(partials + 2 * RED_BLOCKS);
+    double* pv[2] = {vec(vi), vec(vi + 1)};
+    double* v[2] = {vec(vi + 2), vec(vi + 3)};
+    double* sv = vec(vi + 4);
+    double* tv = vec(vi + 5);
     const dim3 g((unsigned)((P + BLK - 1) / BLK)), b(BLK);
     StageArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -1502,7 +1598,15 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
     int64_t iters = 0;
     double worst = 0.0;
     int result = RBFFD_OK;
-    const unsigned rg = RED_BLOCKS;
+    int expect[2] = {1, 1};  // graphs of the species' last solve
+    const dim3 sg = stage_grid(a.nslices);
+    // what the next kernel sums: the block partials of set q, or their sum
+    const int npart = nblk <= PART_DIRECT ? nblk : 1;
+    auto summed = [&](int q) -> const double2* {
+        if (npart == nblk) return part[q];
+        hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, st, part[q], nblk, psum + q);
+        return psum + q;
+    };
     for (int64_t n = 0; n < nsteps && result == RBFFD_OK; ++n) {
         const int k = std::min(order, have);
         const BdfCoef c = bdf_coef(k);
@@ -1517,41 +1621,53 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
                 h.r[j] = react ? Rh[s][slot[j]] : nullptr;
             }
             const double ef = forcing ? std::exp(lambda * t1) : 0.0;
-            hipLaunchKernelGGL(k_bdf_rhs, g, b, 0, st, P, k, c, h, forcing ? (const double*)Fi[s] : nullptr, ef, dt,
-                               op->perm, bvec);
             const double gamma = dt * D[s] / c.a[0];
             // (re)start from the true residual of x
             auto krylov_start = [&](int first) {
-                hipLaunchKernelGGL(k_amul, stage_grid(a.nslices), b, 0, st, a, op->idx32, op->w64, x, gamma, tv,
-                                   (const KrylovScalars*)nullptr);
-                hipLaunchKernelGGL(k_kry_init, g, b, 0, st, P, bvec, tv, r, rh, pv, v);
-                hipLaunchKernelGGL(k_dots<2>, dim3(rg), dim3(256), 0, st, P, bvec, bvec, r, r, partials,
-                                   (const KrylovScalars*)nullptr);
-                hipLaunchKernelGGL(k_krylov_scalar<0>, dim3(1), dim3(64), 0, st, partials, ks, tol, first, gamma);
+                if (first)
+                    hipLaunchKernelGGL(k_kry_start<true>, sg, b, 0, st, a, op->idx32, op->w64, k, c, h,
+                                       forcing ? (const double*)Fi[s] : nullptr, ef, dt, gamma, bvec, x, r, rh, pv[0],
+                                       v[0], part[0]);
+                else
+                    hipLaunchKernelGGL(k_kry_start<false>, sg, b, 0, st, a, op->idx32, op->w64, k, c, h, nullptr, ef, dt,
+                                       gamma, bvec, x, r, rh, pv[0], v[0], part[0]);
+                const double2* ps = summed(0);
+                hipLaunchKernelGGL(k_kry_begin, dim3(1), dim3(256), 0, st, ps, npart, ks, tol, first, gamma);
             };
-            // one iteration; every kernel takes its scalars (gamma too) from ks,
-            // so the same launches serve every species, step and tolerance
-            auto iteration = [&]() {
-                hipLaunchKernelGGL(k_kry_p, g, b, 0, st, P, ks, r, pv, v);
-                hipLaunchKernelGGL(k_amul, stage_grid(a.nslices), b, 0, st, a, op->idx32, op->w64, pv, 0.0, v, ks);
-                hipLaunchKernelGGL(k_dots<1>, dim3(rg), dim3(256), 0, st, P, rh, v, nullptr, nullptr, partials, ks);
-                hipLaunchKernelGGL(k_krylov_scalar<2>, dim3(1), dim3(64), 0, st, partials, ks, 0.0, 0, 0.0);
-                hipLaunchKernelGGL(k_kry_s, g, b, 0, st, P, ks, r, v, sv);
-                hipLaunchKernelGGL(k_amul, stage_grid(a.nslices), b, 0, st, a, op->idx32, op->w64, sv, 0.0, tv, ks);
-                hipLaunchKernelGGL(k_dots<2>, dim3(rg), dim3(256), 0, st, P, tv, sv, tv, tv, partials, ks);
-                hipLaunchKernelGGL(k_krylov_scalar<3>, dim3(1), dim3(64), 0, st, partials, ks, 0.0, 0, 0.0);
-                hipLaunchKernelGGL(k_kry_xr, g, b, 0, st, P, ks, pv, sv, tv, x, r);
-                hipLaunchKernelGGL(k_dots<2>, dim3(rg), dim3(256), 0, st, P, r, r, rh, r, partials, ks);
-                hipLaunchKernelGGL(k_krylov_scalar<4>, dim3(1), dim3(64), 0, st, partials, ks, 0.0, 0, 0.0);
+            // `count` iterations; every kernel takes its scalars (gamma too) from
+            // ks, so the same launches serve every species, step and tolerance.
+            // ks[0] holds them before and after.
+            auto iterations = [&](int count) {
+                int cur = 0;
+                const double2* ps = nullptr;
+                for (int q = 0; q < count; ++q) {
+                    const int from = q & 1, to = 1 - from;
+                    if (q == 0) {
+                        hipLaunchKernelGGL(k_kry_pv<true>, sg, b, 0, st, a, op->idx32, op->w64, nullptr, 0, ks, ks, r,
+                                           rh, pv[from], v[from], pv[to], v[to], part[0]);
+                    } else {
+                        hipLaunchKernelGGL(k_kry_pv<false>, sg, b, 0, st, a, op->idx32, op->w64, ps, npart, ks + cur,
+                                           ks + 1 - cur, r, rh, pv[from], v[from], pv[to], v[to], part[0]);
+                        cur = 1 - cur;
+                    }
+                    ps = summed(0);
+                    hipLaunchKernelGGL(k_kry_st, sg, b, 0, st, a, op->idx32, op->w64, ps, npart, ks + cur, r, v[to], sv, tv,
+                                       part[1]);
+                    ps = summed(1);
+                    hipLaunchKernelGGL(k_kry_xr, sg, b, 0, st, P, ps, npart, ks + cur, pv[to], sv, tv, rh, x, r,
+                                       part[2]);
+                    ps = summed(2);
+                }
+                hipLaunchKernelGGL(k_kry_end, dim3(1), dim3(256), 0, st, ps, npart, ks + cur, ks);
             };
-            // KRYLOV_BATCH iterations from one HIP graph (88 launches), captured
-            // once per operator and vector layout
+            // KRYLOV_BATCH iterations (an even number: p and v end where they began)
+            // from one HIP graph, captured once per operator and vector layout
             auto batch_graph = [&]() -> int {
                 if (!op->kgraph || op->kgraph_key != (const void*)x) {
                     reset_kgraph(op);
                     hipGraph_t graph;
                     HIP_TRY(ctx, hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-                    for (int q = 0; q < KRYLOV_BATCH; ++q) iteration();
+                    iterations(KRYLOV_BATCH);
                     hipError_t ce = hipStreamEndCapture(st, &graph);
                     if (ce != hipSuccess)
                         return set_error(ctx, RBFFD_E_HIP, "graph capture failed: %s", hipGetErrorString(ce));
@@ -1567,13 +1683,24 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
                 return RBFFD_OK;
             };
             // initial guess: the current state
-            hipLaunchKernelGGL(k_copy, g, b, 0, st, P, U[s][slot[0]], x);
             krylov_start(1);
             HIP_TRY(ctx, hipGetLastError());
             bool conv = false;
             double relres = 0.0;
-            int restarts = 0;
+            int restarts = 0, graphs = 0;
             for (;;) {
+                // a solve takes about as many graphs as the species' last one
+                // did: launch all but one of them (at most seven) unread
+                for (bool first = graphs == 0; first && graphs + 1 < expect[s] && graphs < 7 &&
+                                               maxit >= (graphs + 1) * KRYLOV_BATCH;
+                     ++graphs) {
+                    const int rc = batch_graph();
+                    if (rc) {
+                        result = rc;
+                        break;
+                    }
+                }
+                if (result != RBFFD_OK) break;
                 KrylovScalars hs;
                 HIP_TRY(ctx, hipMemcpyAsync(&hs, ks, sizeof(hs), hipMemcpyDeviceToHost, st));
                 HIP_TRY(ctx, hipStreamSynchronize(st));
@@ -1602,12 +1729,14 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
                         result = rc;
                         break;
                     }
+                    ++graphs;
                 } else {
-                    for (int q = 0; q < maxit - used; ++q) iteration();
+                    iterations(maxit - used);
                 }
                 HIP_TRY(ctx, hipGetLastError());
             }
             if (result != RBFFD_OK) break;
+            expect[s] = graphs;
             worst = std::max(worst, relres);
             hipLaunchKernelGGL(k_copy, g, b, 0, st, P, x, U[s][newslot]);
             if (!conv) {
