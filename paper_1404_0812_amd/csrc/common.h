@@ -48,6 +48,7 @@ struct rbffd_op_s {
     int32_t n = 0;        // largest stencil size
     int32_t nsurf = 0;
     int64_t nslices = 0;
+    int64_t slots = 0;    // off-diagonal slots of all slices
     OpSlice* slices = nullptr;    // device, nslices
     double* wd64 = nullptr;       // FP64 diagonal weight of every internal row (P)
     int32_t* idx32 = nullptr;     // off-diagonal slots 1..n-1 of row (slice, r) at off32 + slot_pos(k-1, n-1, r)

@@ -248,6 +248,7 @@ struct StageArgs {
     const void* F;
     double lam, t0, toff;   // toff = (step_in_launch + c_stage), set per launch
     const int64_t* steps_done;
+    bool keep;              // host: the KEEP kernels (keep_slots)
 };
 
 // Blocks are dispatched round-robin over the 8 XCDs; remap them so that each
@@ -329,17 +330,29 @@ typedef int i4v __attribute__((ext_vector_type(4)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef double d2v __attribute__((ext_vector_type(2)));
 
-// four consecutive slots of one lane (streamed once: non-temporal)
+// The operator's slots are read once per stage.  KEEP: ordinary loads, which
+// leave them in the caches (256 MB behind the L2s) for the next stage; else
+// non-temporal ones, so that an operator which cannot stay there at least does
+// not drive out the state.
+template <bool KEEP, typename V>
+__device__ __forceinline__ V ld(const V* p) {
+    if constexpr (KEEP) return *p;
+    else return __builtin_nontemporal_load(p);
+}
+
+// four consecutive slots of one lane
+template <bool KEEP>
 __device__ __forceinline__ void load4(const int32_t* ix, const float* wx, int (&j)[4], float (&w)[4]) {
-    const i4v jv = __builtin_nontemporal_load(reinterpret_cast<const i4v*>(ix));
-    const f4v wv = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(wx));
+    const i4v jv = ld<KEEP>(reinterpret_cast<const i4v*>(ix));
+    const f4v wv = ld<KEEP>(reinterpret_cast<const f4v*>(wx));
     j[0] = jv.x; j[1] = jv.y; j[2] = jv.z; j[3] = jv.w;
     w[0] = wv.x; w[1] = wv.y; w[2] = wv.z; w[3] = wv.w;
 }
+template <bool KEEP>
 __device__ __forceinline__ void load4(const int32_t* ix, const double* wx, int (&j)[4], double (&w)[4]) {
-    const i4v jv = __builtin_nontemporal_load(reinterpret_cast<const i4v*>(ix));
-    const d2v w0 = __builtin_nontemporal_load(reinterpret_cast<const d2v*>(wx));
-    const d2v w1 = __builtin_nontemporal_load(reinterpret_cast<const d2v*>(wx) + 1);
+    const i4v jv = ld<KEEP>(reinterpret_cast<const i4v*>(ix));
+    const d2v w0 = ld<KEEP>(reinterpret_cast<const d2v*>(wx));
+    const d2v w1 = ld<KEEP>(reinterpret_cast<const d2v*>(wx) + 1);
     j[0] = jv.x; j[1] = jv.y; j[2] = jv.z; j[3] = jv.w;
     w[0] = w0.x; w[1] = w0.y; w[2] = w1.x; w[3] = w1.y;
 }
@@ -361,7 +374,7 @@ __device__ __forceinline__ void accumulate(const T* __restrict__ Y, int j, T wk,
 // L applied to the stage input of row rp.p by direct gathers, in slot order.
 // FP32: difference form over the n-1 off-diagonal slots; FP64: the diagonal
 // term wd u_i, then the off-diagonal slots (plain form).
-template <typename T, int S>
+template <typename T, int S, bool KEEP>
 __device__ __forceinline__ void apply_row(const RowPos& rp, const int32_t* __restrict__ idx,
                                           const T* __restrict__ w, const T* __restrict__ Y, const T (&yi)[2],
                                           T wd, T (&acc)[2]) {
@@ -374,8 +387,8 @@ __device__ __forceinline__ void apply_row(const RowPos& rp, const int32_t* __res
     for (; g + 2 <= G; g += 2) {  // eight slots in flight
         int j[8];
         T wk[8];
-        load4(ix + 256 * g, wx + 256 * g, *reinterpret_cast<int(*)[4]>(j), *reinterpret_cast<T(*)[4]>(wk));
-        load4(ix + 256 * (g + 1), wx + 256 * (g + 1), *reinterpret_cast<int(*)[4]>(j + 4),
+        load4<KEEP>(ix + 256 * g, wx + 256 * g, *reinterpret_cast<int(*)[4]>(j), *reinterpret_cast<T(*)[4]>(wk));
+        load4<KEEP>(ix + 256 * (g + 1), wx + 256 * (g + 1), *reinterpret_cast<int(*)[4]>(j + 4),
               *reinterpret_cast<T(*)[4]>(wk + 4));
 #pragma unroll
         for (int t = 0; t < 8; ++t) accumulate<T, S>(Y, j[t], wk[t], yi, s0, s1);
@@ -383,31 +396,20 @@ __device__ __forceinline__ void apply_row(const RowPos& rp, const int32_t* __res
     if (g < G) {
         int j[4];
         T wk[4];
-        load4(ix + 256 * g, wx + 256 * g, j, wk);
+        load4<KEEP>(ix + 256 * g, wx + 256 * g, j, wk);
 #pragma unroll
         for (int t = 0; t < 4; ++t) accumulate<T, S>(Y, j[t], wk[t], yi, s0, s1);
     }
     const int32_t* ir = idx + rp.base + 256 * G + rp.lane;
     const T* wr = w + rp.base + 256 * G + rp.lane;
     for (int t = 0; t < ns - 4 * G; ++t)
-        accumulate<T, S>(Y, __builtin_nontemporal_load(ir + 64 * t), __builtin_nontemporal_load(wr + 64 * t), yi,
+        accumulate<T, S>(Y, ld<KEEP>(ir + 64 * t), ld<KEEP>(wr + 64 * t), yi,
                          s0, s1);
     acc[0] = s0;
     acc[1] = s1;
 }
 
 typedef unsigned short u4v __attribute__((ext_vector_type(4)));
-
-// Stage the slice's halo values (all 64 lanes of the wavefront take part).
-template <typename T, int S>
-__device__ __forceinline__ void load_halo(const RowPos& rp, const int32_t* __restrict__ halo,
-                                          const T* __restrict__ Y, typename Vec<T, S>::type* ylds) {
-    const int32_t* h = halo + rp.slice * OP_HALO_MAX;
-    for (int t = rp.lane; t < rp.halo; t += 64) ylds[t] = reinterpret_cast<const typename Vec<T, S>::type*>(Y)[h[t]];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 template <typename T, int S>
 __device__ __forceinline__ void halo_value(const typename Vec<T, S>::type* ylds, int l, T (&y)[2]) {
@@ -422,108 +424,192 @@ __device__ __forceinline__ void halo_value(const typename Vec<T, S>::type* ylds,
 }
 
 // four consecutive weights of one lane
+template <bool KEEP>
 __device__ __forceinline__ void loadw4(const float* wx, float (&w)[4]) {
-    const f4v wv = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(wx));
+    const f4v wv = ld<KEEP>(reinterpret_cast<const f4v*>(wx));
     w[0] = wv.x; w[1] = wv.y; w[2] = wv.z; w[3] = wv.w;
 }
+template <bool KEEP>
 __device__ __forceinline__ void loadw4(const double* wx, double (&w)[4]) {
-    const d2v w0 = __builtin_nontemporal_load(reinterpret_cast<const d2v*>(wx));
-    const d2v w1 = __builtin_nontemporal_load(reinterpret_cast<const d2v*>(wx) + 1);
+    const d2v w0 = ld<KEEP>(reinterpret_cast<const d2v*>(wx));
+    const d2v w1 = ld<KEEP>(reinterpret_cast<const d2v*>(wx) + 1);
     w[0] = w0.x; w[1] = w0.y; w[2] = w1.x; w[3] = w1.y;
 }
 
-// The n-1 off-diagonal slots with neighbour values from the staged halo (same
-// slot order as apply_row): FP32 difference form, FP64 plain form after the
-// diagonal term.
-template <typename T, int S>
-__device__ __forceinline__ void apply_row_halo(const RowPos& rp, const uint16_t* __restrict__ lidx,
-                                               const T* __restrict__ w, const typename Vec<T, S>::type* ylds,
-                                               const T (&yi)[2], T wd, T (&acc)[2]) {
-    constexpr bool diff = sizeof(T) == 4;
-    const int ns = rp.ns;
-    const int G = ns >> 2;
-    const uint16_t* lx = lidx + rp.base + 4 * rp.lane;
-    const T* wx = w + rp.base + 4 * rp.lane;
-    T s0 = wd * yi[0], s1 = wd * yi[1];
-    auto acc1 = [&](int l, T wk) {
-        T y[2];
-        halo_value<T, S>(ylds, l, y);
-        if (diff) {
-            s0 = fma(wk, y[0] - yi[0], s0);
-            if (S == 2) s1 = fma(wk, y[1] - yi[1], s1);
-        } else {
-            s0 = fma(wk, y[0], s0);
-            if (S == 2) s1 = fma(wk, y[1], s1);
-        }
-    };
-    int g = 0;
-    for (; g + 4 <= G; g += 4) {  // sixteen slots in flight
-        u4v lv[4];
-        T wv[4][4];
+// The n-1 off-diagonal slots with neighbour values from the staged halo, in
+// slot order as apply_row.  Up to some 1e5 rows a stage is bound by its chain of
+// dependent loads (slice -> halo list -> neighbour values, 0.5-0.8 us each).  So
+// the first 256 entries of the halo list are read without waiting for the
+// slice; neighbour values, the first sixteen slots and the tail are all in
+// flight before the first of them is used; and sixteen slots are read ahead of
+// those being summed.  Against reading the halo first and then sixteen slots at
+// a time, 1000 FP64 steps at N = 2500, n = 31 took 20.4 -> 15.1 ms.
+constexpr int HALO_AHEAD = 4;  // halo entries per lane
+static_assert(64 * HALO_AHEAD <= OP_HALO_MAX, "halo lists are OP_HALO_MAX long");
+template <typename T>
+struct Slots {
+    u4v l[4];
+    T w[4][4];
+};
+// Groups past the last are read as the last: a load under a condition would
+// make the compiler wait for every load after it as well.
+template <typename T, bool KEEP>
+__device__ __forceinline__ void load_slots(const uint16_t* lx, const T* wx, int g, int G, Slots<T>& b) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            lv[q] = __builtin_nontemporal_load(reinterpret_cast<const u4v*>(lx + 256 * (g + q)));
-            loadw4(wx + 256 * (g + q), wv[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            acc1(lv[q].x, wv[q][0]);
-            acc1(lv[q].y, wv[q][1]);
-            acc1(lv[q].z, wv[q][2]);
-            acc1(lv[q].w, wv[q][3]);
-        }
+    for (int q = 0; q < 4; ++q) {
+        const int at = 256 * (g + q < G ? g + q : G - 1);
+        b.l[q] = ld<KEEP>(reinterpret_cast<const u4v*>(lx + at));
+        loadw4<KEEP>(wx + at, b.w[q]);
     }
-    for (; g < G; ++g) {
-        const u4v lv = __builtin_nontemporal_load(reinterpret_cast<const u4v*>(lx + 256 * g));
-        T wv[4];
-        loadw4(wx + 256 * g, wv);
-        acc1(lv.x, wv[0]);
-        acc1(lv.y, wv[1]);
-        acc1(lv.z, wv[2]);
-        acc1(lv.w, wv[3]);
-    }
-    const uint16_t* lr = lidx + rp.base + 256 * G + rp.lane;
-    const T* wr = w + rp.base + 256 * G + rp.lane;
-    for (int t = 0; t < ns - 4 * G; ++t) acc1(__builtin_nontemporal_load(lr + 64 * t), __builtin_nontemporal_load(wr + 64 * t));
-    acc[0] = s0;
-    acc[1] = s1;
 }
+
+// Y: NV state vectors; conv() makes a neighbour's value of their entries.
+template <typename T, int S, int NV, bool KEEP>
+struct RowAhead {
+    using V = typename Vec<T, S>::type;
+    V y[NV][HALO_AHEAD];
+    Slots<T> a;
+    uint16_t lt[3];
+    T wt[3];
+
+    __device__ __forceinline__ void load(const StageArgs& arg, const RowPos& rp, const T* __restrict__ w,
+                                         const T* const (&Y)[NV]) {
+        if (rp.slice < 0) return;
+        const int32_t* h = arg.halo + rp.slice * OP_HALO_MAX + rp.lane;
+        int j[HALO_AHEAD];
+#pragma unroll
+        for (int q = 0; q < HALO_AHEAD; ++q) j[q] = h[64 * q];
+        if (rp.halo < 0 || rp.ns == 0) return;
+        const int G = rp.ns >> 2, tail = rp.ns & 3;
+        const int64_t at = rp.base + (tail ? 256 * G : 0) + rp.lane;
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const int64_t k = at + 64 * (t < tail ? t : 0);
+            lt[t] = ld<KEEP>(arg.lidx + k);
+            wt[t] = ld<KEEP>(w + k);
+        }
+        if (G) load_slots<T, KEEP>(arg.lidx + rp.base + 4 * rp.lane, w + rp.base + 4 * rp.lane, 0, G, a);
+#pragma unroll
+        for (int q = 0; q < HALO_AHEAD; ++q) {
+            const int64_t k = rp.lane + 64 * q < rp.halo ? j[q] : rp.p;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) y[v][q] = reinterpret_cast<const V*>(Y[v])[k];
+        }
+    }
+    // every lane of the wavefront; rp.halo >= 0
+    template <typename C>
+    __device__ __forceinline__ void finish(const StageArgs& arg, const RowPos& rp, const T* __restrict__ w,
+                                           const T* const (&Y)[NV], C&& conv, V* yl, const T (&yi)[2], T wd,
+                                           T (&acc)[2]) {
+#pragma unroll
+        for (int q = 0; q < HALO_AHEAD; ++q) {
+            if (rp.lane + 64 * q < rp.halo) {
+                V e[NV];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) e[v] = y[v][q];
+                yl[rp.lane + 64 * q] = conv(e);
+            }
+        }
+        for (int t = rp.lane + 64 * HALO_AHEAD; t < rp.halo; t += 64) {
+            const int64_t j = arg.halo[rp.slice * OP_HALO_MAX + t];
+            V e[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) e[v] = reinterpret_cast<const V*>(Y[v])[j];
+            yl[t] = conv(e);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (!rp.live) return;
+        constexpr bool diff = sizeof(T) == 4;
+        T s0 = wd * yi[0], s1 = wd * yi[1];
+        auto acc1 = [&](int l, T wk) {
+            T n[2];
+            halo_value<T, S>(yl, l, n);
+            s0 = fma(wk, diff ? n[0] - yi[0] : n[0], s0);
+            if (S == 2) s1 = fma(wk, diff ? n[1] - yi[1] : n[1], s1);
+        };
+        const int G = rp.ns >> 2, tail = rp.ns & 3;
+        auto sum = [&](const Slots<T>& b, int groups) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (q < groups) {
+                    acc1(b.l[q].x, b.w[q][0]);
+                    acc1(b.l[q].y, b.w[q][1]);
+                    acc1(b.l[q].z, b.w[q][2]);
+                    acc1(b.l[q].w, b.w[q][3]);
+                }
+            }
+        };
+        const uint16_t* lx = arg.lidx + rp.base + 4 * rp.lane;
+        const T* wx = w + rp.base + 4 * rp.lane;
+        Slots<T> b;
+        int g = 0;
+        while (g + 8 < G) {
+            load_slots<T, KEEP>(lx, wx, g + 4, G, b);
+            sum(a, 4);
+            load_slots<T, KEEP>(lx, wx, g + 8, G, a);
+            sum(b, 4);
+            g += 8;
+        }
+        if (g + 4 < G) {
+            load_slots<T, KEEP>(lx, wx, g + 4, G, b);
+            sum(a, 4);
+            sum(b, G - g - 4);
+        } else {
+            sum(a, G - g);
+        }
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+            if (t < tail) acc1(lt[t], wt[t]);
+        acc[0] = s0;
+        acc[1] = s1;
+    }
+};
 
 // L applied to the stage input of row rp.p: through the staged halo when the
 // slice has one, otherwise by direct gathers.  Every lane of the wavefront
 // must call this (the halo is loaded cooperatively).
-template <typename T, int S>
+template <typename T, int S, bool KEEP>
 __device__ __forceinline__ void laplacian_row(const StageArgs& a, const RowPos& rp, const int32_t* __restrict__ idx,
                                               const T* __restrict__ w, const T* __restrict__ Y, const T (&yi)[2],
                                               T (&lap)[2]) {
-    __shared__ typename Vec<T, S>::type ylds[BLK / 64][OP_HALO_MAX];
+    using V = typename Vec<T, S>::type;
+    __shared__ V ylds[BLK / 64][OP_HALO_MAX];
+    const T* const ys[1] = {Y};
+    RowAhead<T, S, 1, KEEP> ahead;
+    ahead.load(a, rp, w, ys);
     T wd = (T)0;
     if constexpr (sizeof(T) == 8) {
-        if (rp.live) wd = __builtin_nontemporal_load(a.wd64 + rp.p);
+        if (rp.live) wd = ld<KEEP>(a.wd64 + rp.p);
     }
     if (rp.halo >= 0) {
-        auto* yl = ylds[threadIdx.x >> 6];
-        load_halo<T, S>(rp, a.halo, Y, yl);
-        if (rp.live) apply_row_halo<T, S>(rp, a.lidx, w, yl, yi, wd, lap);
+        ahead.finish(a, rp, w, ys, [](const V (&e)[1]) { return e[0]; }, ylds[threadIdx.x >> 6], yi, wd, lap);
         return;
     }
-    if (rp.live) apply_row<T, S>(rp, idx, w, Y, yi, wd, lap);
+    if (rp.live) apply_row<T, S, KEEP>(rp, idx, w, Y, yi, wd, lap);
 }
 
 // RK4 stage `ST` (0..3).  Y: stage input; U: state at the start of the step;
 // ACC: accumulator; YN: next stage input (stages 0-2) -- stage 3 updates U
 // (FP32: YN is then the compensation term of the update).
-template <typename T, int S, int R, int ST, bool FORCED>
+template <typename T, int S, int R, int ST, bool FORCED, bool KEEP>
 __global__ __launch_bounds__(BLK) void k_rk4_stage(StageArgs a, const int32_t* __restrict__ idx,
                                                    const T* __restrict__ w, const T* __restrict__ Y,
                                                    T* __restrict__ U, T* __restrict__ ACC, T* __restrict__ YN) {
     const RowPos rp = row_pos<T>(a);
     if (rp.slice < 0) return;  // the whole wavefront
     const int64_t p = rp.p;
-    T yi[2] = {0, 0};
-    if (rp.live) vload<T, S>(Y, p, yi);
+    T yi[2] = {0, 0}, u[2], c[2], e[2], f[2], o[2];
+    if (rp.live) {  // all that the row needs, before its neighbours are waited for
+        vload<T, S>(Y, p, yi);
+        vload<T, S>(U, p, u);
+        if constexpr (ST > 0) vload<T, S>(ACC, p, c);
+        if constexpr (ST == 3 && sizeof(T) == 4) vload<T, S>(YN, p, e);
+        if constexpr (FORCED) vload<T, S>(reinterpret_cast<const T*>(a.F), p, f);
+    }
     T lap[2];
-    laplacian_row<T, S>(a, rp, idx, w, Y, yi, lap);
+    laplacian_row<T, S, KEEP>(a, rp, idx, w, Y, yi, lap);
     if (!rp.live) return;
     T r[2];
     reaction<T, R>(yi, r, a.rp);
@@ -533,22 +619,16 @@ __global__ __launch_bounds__(BLK) void k_rk4_stage(StageArgs a, const int32_t* _
     if constexpr (FORCED) {
         const double t = a.t0 + ((double)*a.steps_done + a.toff) * a.dt;  // uniform
         const T ef = (T)exp(a.lam * t);
-        T f[2];
-        vload<T, S>(reinterpret_cast<const T*>(a.F), p, f);
         k[0] = fma(ef, f[0], k[0]);
         k[1] = fma(ef, f[1], k[1]);
     }
     const T dt = (T)a.dt;
-    T u[2], c[2], o[2];
     if (ST == 0) {
-        vload<T, S>(U, p, u);
         o[0] = u[0] + (T)0.5 * dt * k[0];
         o[1] = u[1] + (T)0.5 * dt * k[1];
         vstore<T, S>(ACC, p, k);
         vstore<T, S>(YN, p, o);
     } else if (ST == 1 || ST == 2) {
-        vload<T, S>(U, p, u);
-        vload<T, S>(ACC, p, c);
         const T h = ST == 1 ? (T)0.5 * dt : dt;
         o[0] = u[0] + h * k[0];
         o[1] = u[1] + h * k[1];
@@ -557,14 +637,10 @@ __global__ __launch_bounds__(BLK) void k_rk4_stage(StageArgs a, const int32_t* _
         vstore<T, S>(ACC, p, c);
         vstore<T, S>(YN, p, o);
     } else {
-        vload<T, S>(U, p, u);
-        vload<T, S>(ACC, p, c);
         if constexpr (sizeof(T) == 4) {
             // FP32 state: compensated (Kahan) update, the running rounding error
             // kept in YN; over 1e4 steps of increments ~1e-4 of the state the
             // plain update drifts by several 1e-5 against FP64
-            T e[2];
-            vload<T, S>(YN, p, e);
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const T d = dt / (T)6 * (c[q] + k[q]) - e[q];
@@ -591,7 +667,7 @@ __global__ void k_set_steps(int64_t* steps_done, int* nonfinite) {
 }
 
 // one operator application (stage-free): out = L y (reaction-free, D = 1)
-template <typename T>
+template <typename T, bool KEEP>
 __global__ __launch_bounds__(BLK) void k_apply(StageArgs a, const int32_t* __restrict__ idx, const T* __restrict__ w,
                                                const T* __restrict__ Y, T* __restrict__ out) {
     const RowPos rp = row_pos<T>(a);
@@ -599,40 +675,63 @@ __global__ __launch_bounds__(BLK) void k_apply(StageArgs a, const int32_t* __res
     T yi[2] = {0, 0};
     if (rp.live) vload<T, 1>(Y, rp.p, yi);
     T lap[2];
-    laplacian_row<T, 1>(a, rp, idx, w, Y, yi, lap);
+    laplacian_row<T, 1, KEEP>(a, rp, idx, w, Y, yi, lap);
     if (rp.live) out[rp.p] = lap[0];
 }
 
-// blocks of one stage launch: four slices each
+// KEEP up to about what the 256 MB cache holds: (slot + index) bytes against
+// non-temporal loads, 40 steps each.  FP32: 118 MB 2.38 -> 2.22 ms, 176 MB
+// 6.21 -> 5.17, 235 MB 8.06 -> 6.91, 265 MB 9.11 -> 8.59, but 294 MB 9.87 ->
+// 10.64, 588 MB 17.6 -> 19.8.  FP64 moves more besides the slots and loses
+// later: 98 MB 2.73 -> 2.18 ms, 217 MB 8.32 -> 5.99, 294 MB 11.8 -> 10.8, 490 MB
+// 18.5 -> 18.2, 600 MB 24.2 -> 24.5.
+template <typename T>
+bool keep_slots(int64_t slots) {
+    return slots * (int64_t)(sizeof(T) + sizeof(uint16_t)) <= (int64_t)(sizeof(T) == 4 ? 256 : 512) << 20;
+}
+
+StageArgs stage_args(rbffd_op op, bool f64) {
+    StageArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.nslices = op->nslices;
+    a.slices = op->slices;
+    a.lidx = op->lidx;
+    a.halo = op->halo;
+    a.wd64 = op->wd64;
+    a.keep = f64 ? keep_slots<double>(op->slots) : keep_slots<float>(op->slots);
+    return a;
+}
+
+// Blocks of a stage launch: four slices each.
 inline dim3 stage_grid(int64_t nslices) { return dim3((unsigned)((nslices + BLK / 64 - 1) / (BLK / 64))); }
 
 // One RK4 step, the i-th of its launch sequence; stage times t_n + c dt with
 // c = 0, 1/2, 1/2, 1.
-template <typename T, int S, int R, bool FORCED>
+template <typename T, int S, int R, bool FORCED, bool KEEP>
 void enqueue_step(hipStream_t st, StageArgs a, int64_t i, const int32_t* idx, const T* w, T* U, T* ACC, T* Y1,
                   T* Y2, T* COMP) {
     const dim3 g = stage_grid(a.nslices), b(BLK);
     a.toff = (double)i;
-    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 0, FORCED>), g, b, 0, st, a, idx, w, U, U, ACC, Y1);
+    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 0, FORCED, KEEP>), g, b, 0, st, a, idx, w, U, U, ACC, Y1);
     a.toff = (double)i + 0.5;
-    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 1, FORCED>), g, b, 0, st, a, idx, w, Y1, U, ACC, Y2);
-    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 2, FORCED>), g, b, 0, st, a, idx, w, Y2, U, ACC, Y1);
+    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 1, FORCED, KEEP>), g, b, 0, st, a, idx, w, Y1, U, ACC, Y2);
+    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 2, FORCED, KEEP>), g, b, 0, st, a, idx, w, Y2, U, ACC, Y1);
     a.toff = (double)i + 1.0;
-    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 3, FORCED>), g, b, 0, st, a, idx, w, Y1, U, ACC, COMP);
+    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 3, FORCED, KEEP>), g, b, 0, st, a, idx, w, Y1, U, ACC, COMP);
 }
 
-template <typename T, bool FORCED>
+template <typename T, bool FORCED, bool KEEP>
 void enqueue_steps_f(hipStream_t st, int S, int R, const StageArgs& a, const int32_t* idx, const T* w, T* U, T* ACC,
                      T* COMP, T* Y1, T* Y2, int64_t steps) {
     for (int64_t i = 0; i < steps; ++i) {
         if (S == 1) {
-            enqueue_step<T, 1, RBFFD_REACT_NONE, FORCED>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
+            enqueue_step<T, 1, RBFFD_REACT_NONE, FORCED, KEEP>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
         } else if (R == RBFFD_REACT_SCHNAKENBERG) {
-            enqueue_step<T, 2, RBFFD_REACT_SCHNAKENBERG, FORCED>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
+            enqueue_step<T, 2, RBFFD_REACT_SCHNAKENBERG, FORCED, KEEP>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
         } else if (R == RBFFD_REACT_TURING) {
-            enqueue_step<T, 2, RBFFD_REACT_TURING, FORCED>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
+            enqueue_step<T, 2, RBFFD_REACT_TURING, FORCED, KEEP>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
         } else {
-            enqueue_step<T, 2, RBFFD_REACT_NONE, FORCED>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
+            enqueue_step<T, 2, RBFFD_REACT_NONE, FORCED, KEEP>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
         }
     }
     // forced stages read the step counter: advance it past this sequence
@@ -642,8 +741,17 @@ void enqueue_steps_f(hipStream_t st, int S, int R, const StageArgs& a, const int
 template <typename T>
 void enqueue_steps_t(hipStream_t st, int S, int R, const StageArgs& a, const int32_t* idx, const T* w, T* U, T* ACC,
                      T* COMP, T* Y1, T* Y2, int64_t steps) {
-    if (a.F) enqueue_steps_f<T, true>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
-    else enqueue_steps_f<T, false>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
+    if (a.F && a.keep) enqueue_steps_f<T, true, true>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
+    else if (a.F) enqueue_steps_f<T, true, false>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
+    else if (a.keep) enqueue_steps_f<T, false, true>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
+    else enqueue_steps_f<T, false, false>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
+}
+
+template <typename T>
+void enqueue_apply(hipStream_t st, const StageArgs& a, const int32_t* idx, const T* w, const T* Y, T* out) {
+    const dim3 g = stage_grid(a.nslices), b(BLK);
+    if (a.keep) hipLaunchKernelGGL((k_apply<T, true>), g, b, 0, st, a, idx, w, Y, out);
+    else hipLaunchKernelGGL((k_apply<T, false>), g, b, 0, st, a, idx, w, Y, out);
 }
 
 // The flag of the stepper's last stage on the host side, allocated on first use.
@@ -742,6 +850,7 @@ int create_op(rbffd_ctx ctx, int nsurf, const rbffd_op_surface* surf, rbffd_op* 
     op->n = nmax;
     op->nsurf = nsurf;
     op->nslices = nslices;
+    op->slots = slots;
     size_t bytes = 0;
     auto take = [&](size_t b) {
         const size_t o = bytes;
@@ -918,24 +1027,18 @@ extern "C" int rbffd_apply_noalloc(rbffd_ctx ctx, rbffd_op op, int32_t prec, con
     if (ctx != op->home) op->roamed = true;
     hipStream_t st = ctx->stream;
     const dim3 g((unsigned)((P + BLK - 1) / BLK)), b(BLK);
-    StageArgs a;
-    std::memset(&a, 0, sizeof(a));
-    a.nslices = op->nslices;
-    a.slices = op->slices;
-    a.lidx = op->lidx;
-    a.halo = op->halo;
-    a.wd64 = op->wd64;
+    StageArgs a = stage_args(op, prec == RBFFD_F64);
     if (prec == RBFFD_F64) {
         double* Y = (double*)base;
         double* out = Y + P;
         hipLaunchKernelGGL(k_load_state<double>, g, b, 0, st, P, N, 1, u, op->perm, Y);
-        hipLaunchKernelGGL(k_apply<double>, stage_grid(a.nslices), b, 0, st, a, op->idx32, op->w64, Y, out);
+        enqueue_apply<double>(st, a, op->idx32, op->w64, Y, out);
         hipLaunchKernelGGL(k_store_state<double>, g, b, 0, st, P, N, 1, out, op->perm, Lu);
     } else {
         float* Y = (float*)base;
         float* out = Y + P;
         hipLaunchKernelGGL(k_load_state<float>, g, b, 0, st, P, N, 1, u, op->perm, Y);
-        hipLaunchKernelGGL(k_apply<float>, stage_grid(a.nslices), b, 0, st, a, op->idx32, op->w32, Y, out);
+        enqueue_apply<float>(st, a, op->idx32, op->w32, Y, out);
         hipLaunchKernelGGL(k_store_state<float>, g, b, 0, st, P, N, 1, out, op->perm, Lu);
     }
     HIP_TRY(ctx, hipGetLastError());
@@ -949,24 +1052,18 @@ extern "C" int rbffd_apply(rbffd_ctx ctx, rbffd_op op, int32_t prec, const doubl
     hipStream_t st = ctx->stream;
     const int64_t N = op->N, P = op->P;
     const dim3 g((unsigned)((P + BLK - 1) / BLK)), b(BLK);
-    StageArgs a;
-    std::memset(&a, 0, sizeof(a));
-    a.nslices = op->nslices;
-    a.slices = op->slices;
-    a.lidx = op->lidx;
-    a.halo = op->halo;
-    a.wd64 = op->wd64;
+    StageArgs a = stage_args(op, prec == RBFFD_F64);
     if (prec == RBFFD_F64) {
         double* Y = (double*)op->work;
         double* out = Y + P;
         hipLaunchKernelGGL(k_load_state<double>, g, b, 0, st, P, N, 1, u, op->perm, Y);
-        hipLaunchKernelGGL(k_apply<double>, stage_grid(a.nslices), b, 0, st, a, op->idx32, op->w64, Y, out);
+        enqueue_apply<double>(st, a, op->idx32, op->w64, Y, out);
         hipLaunchKernelGGL(k_store_state<double>, g, b, 0, st, P, N, 1, out, op->perm, Lu);
     } else {
         float* Y = (float*)op->work;
         float* out = Y + P;
         hipLaunchKernelGGL(k_load_state<float>, g, b, 0, st, P, N, 1, u, op->perm, Y);
-        hipLaunchKernelGGL(k_apply<float>, stage_grid(a.nslices), b, 0, st, a, op->idx32, op->w32, Y, out);
+        enqueue_apply<float>(st, a, op->idx32, op->w32, Y, out);
         hipLaunchKernelGGL(k_store_state<float>, g, b, 0, st, P, N, 1, out, op->perm, Lu);
     }
     HIP_TRY(ctx, hipGetLastError());
@@ -996,13 +1093,7 @@ int step_impl(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, double* state, int32
     hipStream_t st = ctx->stream;
     const int64_t N = op->N, P = op->P;
     const dim3 g((unsigned)((P + BLK - 1) / BLK)), b(BLK);
-    StageArgs a;
-    std::memset(&a, 0, sizeof(a));
-    a.nslices = op->nslices;
-    a.slices = op->slices;
-    a.lidx = op->lidx;
-    a.halo = op->halo;
-    a.wd64 = op->wd64;
+    StageArgs a = stage_args(op, prec == RBFFD_F64);
     a.D[0] = D[0];
     a.D[1] = nspecies == 2 ? D[1] : 0.0;
     a.dt = dt;
@@ -1206,38 +1297,49 @@ __global__ void k_reaction2(int64_t P, const double* __restrict__ u, const doubl
     rv[p] = r[1];
 }
 
-// L y at row rp.p, the neighbour values given by val(j) (FP64, one species; the
-// slot order and the form of apply_row_halo).  Every lane of the wavefront
-// takes part.
-template <typename V>
-__device__ __forceinline__ double laplacian_of(const StageArgs& a, const RowPos& rp, const int32_t* __restrict__ idx,
-                                               const double* __restrict__ w, double yi, V&& val) {
-    __shared__ double ylds[BLK / 64][OP_HALO_MAX];
-    double* yl = ylds[threadIdx.x >> 6];
-    const bool staged = rp.halo >= 0;
-    if (staged) {
-        const int32_t* h = a.halo + rp.slice * OP_HALO_MAX;
-        for (int t = rp.lane; t < rp.halo; t += 64) yl[t] = val(h[t]);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// L y at row rp.p, neighbour values made by conv() from entries of NV vectors
+// (FP64, one species; in slot order).
+// load() first, then sum(); every lane of the wavefront takes part in both.
+template <int NV, bool KEEP>
+struct LaplacianOf {
+    RowAhead<double, 1, NV, KEEP> ahead;
+    double own[NV];
+    double wd;
+
+    __device__ __forceinline__ void load(const StageArgs& a, const RowPos& rp, const double* __restrict__ w,
+                                         const double* const (&Y)[NV]) {
+        if (rp.live) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) own[v] = Y[v][rp.p];
+            wd = ld<KEEP>(a.wd64 + rp.p);
+        }
+        ahead.load(a, rp, w, Y);
     }
-    if (!rp.live) return 0.0;
-    const double wd = __builtin_nontemporal_load(a.wd64 + rp.p);
-    const double y2[2] = {yi, 0.0};
-    double lap[2];
-    if (staged) {
-        apply_row_halo<double, 1>(rp, a.lidx, w, yl, y2, wd, lap);
-        return lap[0];
-    }
-    double acc = wd * yi;
+    template <typename C>
+    __device__ __forceinline__ double sum(const StageArgs& a, const RowPos& rp, const int32_t* __restrict__ idx,
+                                          const double* __restrict__ w, const double* const (&Y)[NV], double yi,
+                                          C&& conv) {
+        __shared__ double ylds[BLK / 64][OP_HALO_MAX];
+        const double y2[2] = {yi, 0.0};
+        double lap[2] = {0.0, 0.0};
+        if (rp.halo >= 0) {
+            ahead.finish(a, rp, w, Y, conv, ylds[threadIdx.x >> 6], y2, wd, lap);
+            return lap[0];
+        }
+        if (!rp.live) return 0.0;
+        double acc = wd * yi;
 #pragma unroll 8
-    for (int k = 0; k < rp.ns; ++k) {
-        const int64_t at = rp.base + slot_pos(k, rp.ns, rp.lane);
-        acc = fma(w[at], val(idx[at]), acc);
+        for (int k = 0; k < rp.ns; ++k) {
+            const int64_t at = rp.base + slot_pos(k, rp.ns, rp.lane);
+            const int64_t j = idx[at];
+            double e[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) e[v] = Y[v][j];
+            acc = fma(w[at], conv(e), acc);
+        }
+        return acc;
     }
-    return acc;
-}
+};
 
 __device__ __forceinline__ double wave_sum_block(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -1259,21 +1361,37 @@ __device__ __forceinline__ void block_sum2(double& v0, double& v1, double* sh) {
 }
 // Block partials (pairs) summed in a fixed order: deterministic, and the same
 // in every block that does it.
-__device__ __forceinline__ void sum_partials(const double2* __restrict__ part, int np, double& d0, double& d1,
-                                             double* sh) {
-    d0 = d1 = 0.0;
-    for (int i = threadIdx.x; i < np; i += 256) {
-        const double2 v = part[i];
-        d0 += v.x;
-        d1 += v.y;
+struct Partials {
+    double d0, d1;
+    // the loads; few of them in every kernel but k_sum_partials
+    __device__ __forceinline__ Partials(const double2* __restrict__ part, int np) : d0(0.0), d1(0.0) {
+        for (int i = threadIdx.x; i < np; i += 256) {
+            const double2 v = part[i];
+            d0 += v.x;
+            d1 += v.y;
+        }
     }
-    block_sum2(d0, d1, sh);
-}
+    __device__ __forceinline__ void sum(double* sh) { block_sum2(d0, d1, sh); }
+};
+// At most PART_DIRECT of them, both loads of a thread in flight at once.
+struct FewPartials {
+    double2 a, b;
+    __device__ __forceinline__ FewPartials(const double2* __restrict__ part, int np)
+        : a(make_double2(0.0, 0.0)), b(make_double2(0.0, 0.0)) {
+        if ((int)threadIdx.x < np) a = part[threadIdx.x];
+        if ((int)threadIdx.x + 256 < np) b = part[threadIdx.x + 256];
+    }
+    __device__ __forceinline__ void sum(double& d0, double& d1, double* sh) const {
+        d0 = a.x + b.x;
+        d1 = a.y + b.y;
+        block_sum2(d0, d1, sh);
+    }
+};
 __global__ __launch_bounds__(256) void k_sum_partials(const double2* __restrict__ part, int np, double2* out) {
     __shared__ double sh[8];
-    double d0, d1;
-    sum_partials(part, np, d0, d1, sh);
-    if (threadIdx.x == 0) *out = make_double2(d0, d1);
+    Partials d(part, np);
+    d.sum(sh);
+    if (threadIdx.x == 0) *out = make_double2(d.d0, d.d1);
 }
 
 __device__ __forceinline__ int residual_state(const KrylovScalars& k, double rr) {
@@ -1304,7 +1422,7 @@ __device__ __forceinline__ void end_iteration(KrylovScalars& k, double rr, doubl
 // hand side b = (-sum_{j>=1} a_j u^{n+1-j} + dt sum_j b_j R^{n+1-j} + dt ef F)
 // / a_0 and x = u^n.  Padding rows are written as
 // zero in every vector, here and below.
-template <bool FIRST>
+template <bool FIRST, bool KEEP>
 __global__ __launch_bounds__(BLK) void k_kry_start(StageArgs a, const int32_t* __restrict__ idx,
                                                    const double* __restrict__ w, int nk, BdfCoef c, HistPtrs hp,
                                                    const double* __restrict__ F, double ef, double dt, double gamma,
@@ -1316,8 +1434,11 @@ __global__ __launch_bounds__(BLK) void k_kry_start(StageArgs a, const int32_t* _
     const RowPos rp = row_pos<double>(a);
     const int64_t p = rp.p;
     const double* __restrict__ x0 = FIRST ? hp.u[0] : x;
-    const double yi = rp.live ? x0[p] : 0.0;
-    const double lap = laplacian_of(a, rp, idx, w, yi, [&](int64_t j) { return x0[j]; });
+    const double* const ys[1] = {x0};
+    LaplacianOf<1, KEEP> L;
+    L.load(a, rp, w, ys);
+    const double yi = rp.live ? L.own[0] : 0.0;
+    const double lap = L.sum(a, rp, idx, w, ys, yi, [](const double (&e)[1]) { return e[0]; });
     double bb = 0.0, rr = 0.0;
     if (rp.slice >= 0) {
         double bv = 0.0;
@@ -1350,7 +1471,7 @@ __global__ __launch_bounds__(256) void k_kry_begin(const double2* __restrict__ p
                                                    double tol, int first, double gamma) {
     __shared__ double sh[8];
     double d0, d1;
-    sum_partials(part, np, d0, d1, sh);
+    FewPartials(part, np).sum(d0, d1, sh);
     if (threadIdx.x != 0) return;
     ks->bb = d0;
     ks->rr = ks->rr0 = ks->rho = d1;
@@ -1376,7 +1497,7 @@ __global__ __launch_bounds__(256) void k_kry_begin(const double2* __restrict__ p
 //
 // k_kry_pv: the last iteration's end unless FIRST of a launch sequence (then ks_in is
 // final); p' = r + beta (p - omega v), v' = p' - gamma L p', partials rhat.v'
-template <bool FIRST>
+template <bool FIRST, bool KEEP>
 __global__ __launch_bounds__(BLK) void k_kry_pv(StageArgs a, const int32_t* __restrict__ idx,
                                                 const double* __restrict__ w, const double2* __restrict__ part_in,
                                                 int np, const KrylovScalars* ks_in, KrylovScalars* ks_out,
@@ -1387,19 +1508,23 @@ __global__ __launch_bounds__(BLK) void k_kry_pv(StageArgs a, const int32_t* __re
     __shared__ double sh[8];
     const bool writer = blockIdx.x == 0 && threadIdx.x == 0;
     KrylovScalars k = *ks_in;
+    const FewPartials sums(part_in, FIRST ? 0 : np);
+    const RowPos rp = row_pos<double>(a);
+    const double* const ys[3] = {r, pv, v};
+    LaplacianOf<3, KEEP> L;
+    L.load(a, rp, w, ys);
     if constexpr (!FIRST) {
         if (!k.done) {
             double d0, d1;
-            sum_partials(part_in, np, d0, d1, sh);
+            sums.sum(d0, d1, sh);
             end_iteration(k, d0, d1);
         }
         if (writer) *ks_out = k;
     }
     if (k.done) return;
-    const RowPos rp = row_pos<double>(a);
-    auto val = [&](int64_t j) { return fma(k.beta, fma(-k.omega, v[j], pv[j]), r[j]); };
-    const double yi = rp.live ? val(rp.p) : 0.0;
-    const double lap = laplacian_of(a, rp, idx, w, yi, val);
+    auto val = [&](const double (&e)[3]) { return fma(k.beta, fma(-k.omega, e[2], e[1]), e[0]); };
+    const double yi = rp.live ? val(L.own) : 0.0;
+    const double lap = L.sum(a, rp, idx, w, ys, yi, val);
     double d = 0.0, z = 0.0;
     if (rp.slice >= 0) {
         const double o = fma(-k.gamma, lap, yi);
@@ -1411,26 +1536,32 @@ __global__ __launch_bounds__(BLK) void k_kry_pv(StageArgs a, const int32_t* __re
     if (threadIdx.x == 0) part[blockIdx.x] = make_double2(d, 0.0);
 }
 // alpha = rho / rhat.v; s = r - alpha v, t = s - gamma L s, partials t.s and t.t
+template <bool KEEP>
 __global__ __launch_bounds__(BLK) void k_kry_st(StageArgs a, const int32_t* __restrict__ idx,
                                                 const double* __restrict__ w, const double2* __restrict__ part_in,
                                                 int np, KrylovScalars* ks, const double* __restrict__ r,
                                                 const double* __restrict__ v, double* __restrict__ sv,
                                                 double* __restrict__ tv, double2* __restrict__ part) {
     __shared__ double sh[8];
-    if (ks->done) return;
-    const double gamma = ks->gamma;
+    const int done = ks->done;
+    const double gamma = ks->gamma, rho = ks->rho;
+    const FewPartials sums(part_in, np);
+    const RowPos rp = row_pos<double>(a);
+    const double* const ys[2] = {r, v};
+    LaplacianOf<2, KEEP> L;
+    L.load(a, rp, w, ys);
+    if (done) return;
     double d0, d1;
-    sum_partials(part_in, np, d0, d1, sh);
+    sums.sum(d0, d1, sh);
     const bool broken = d0 == 0.0;
-    const double alpha = broken ? 0.0 : ks->rho / d0;
+    const double alpha = broken ? 0.0 : rho / d0;
     if (blockIdx.x == 0 && threadIdx.x == 0) {  // no block reads these two here
         ks->alpha = alpha;
         if (broken) ks->breakdown = 1;
     }
-    const RowPos rp = row_pos<double>(a);
-    auto val = [&](int64_t j) { return fma(-alpha, v[j], r[j]); };
-    const double yi = rp.live ? val(rp.p) : 0.0;
-    const double lap = laplacian_of(a, rp, idx, w, yi, val);
+    auto val = [&](const double (&e)[2]) { return fma(-alpha, e[1], e[0]); };
+    const double yi = rp.live ? val(L.own) : 0.0;
+    const double lap = L.sum(a, rp, idx, w, ys, yi, val);
     double ts = 0.0, tt = 0.0;
     if (rp.slice >= 0) {
         const double o = fma(-gamma, lap, yi);
@@ -1449,20 +1580,30 @@ __global__ __launch_bounds__(256) void k_kry_xr(int64_t P, const double2* __rest
                                                 const double* __restrict__ rh, double* __restrict__ x,
                                                 double* __restrict__ r, double2* __restrict__ part) {
     __shared__ double sh[8];
-    if (ks->done) return;
-    double d0, d1;
-    sum_partials(part_in, np, d0, d1, sh);
-    const double omega = d1 > 0.0 ? d0 / d1 : 0.0, alpha = ks->alpha;
-    if (blockIdx.x == 0 && threadIdx.x == 0) ks->omega = omega;  // no block reads it here
+    const int done = ks->done;
+    const double alpha = ks->alpha;
+    const FewPartials sums(part_in, np);
     const int64_t p = blockIdx.x * (int64_t)256 + threadIdx.x;
+    double s = 0.0, t = 0.0, pi = 0.0, xi = 0.0, h = 0.0;
+    if (p < P) {
+        s = sv[p];
+        t = tv[p];
+        pi = pv[p];
+        xi = x[p];
+        h = rh[p];
+    }
+    if (done) return;
+    double d0, d1;
+    sums.sum(d0, d1, sh);
+    const double omega = d1 > 0.0 ? d0 / d1 : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) ks->omega = omega;  // no block reads it here
     double rr = 0.0, hr = 0.0;
     if (p < P) {
-        const double s = sv[p];
-        x[p] = fma(omega, s, fma(alpha, pv[p], x[p]));
-        const double q = fma(-omega, tv[p], s);
+        x[p] = fma(omega, s, fma(alpha, pi, xi));
+        const double q = fma(-omega, t, s);
         r[p] = q;
         rr = q * q;
-        hr = rh[p] * q;
+        hr = h * q;
     }
     block_sum2(rr, hr, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = make_double2(rr, hr);
@@ -1472,9 +1613,10 @@ __global__ __launch_bounds__(256) void k_kry_end(const double2* __restrict__ par
                                                  KrylovScalars* ks_out) {
     __shared__ double sh[8];
     KrylovScalars k = *ks_in;
+    const FewPartials sums(part, np);
     if (!k.done) {
         double d0, d1;
-        sum_partials(part, np, d0, d1, sh);
+        sums.sum(d0, d1, sh);
         end_iteration(k, d0, d1);
     }
     __syncthreads();
@@ -1561,13 +1703,7 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
     double* sv = vec(vi + 4);
     double* tv = vec(vi + 5);
     const dim3 g((unsigned)((P + BLK - 1) / BLK)), b(BLK);
-    StageArgs a;
-    std::memset(&a, 0, sizeof(a));
-    a.nslices = op->nslices;
-    a.slices = op->slices;
-    a.lidx = op->lidx;
-    a.halo = op->halo;
-    a.wd64 = op->wd64;
+    StageArgs a = stage_args(op, true);
     ReactParams rp;
     std::memset(&rp, 0, sizeof(rp));
     const int np = reaction == RBFFD_REACT_SCHNAKENBERG ? 3 : (reaction == RBFFD_REACT_TURING ? 5 : 0);
@@ -1625,11 +1761,11 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
             // (re)start from the true residual of x
             auto krylov_start = [&](int first) {
                 if (first)
-                    hipLaunchKernelGGL(k_kry_start<true>, sg, b, 0, st, a, op->idx32, op->w64, k, c, h,
+                    hipLaunchKernelGGL((a.keep ? k_kry_start<true, true> : k_kry_start<true, false>), sg, b, 0, st, a, op->idx32, op->w64, k, c, h,
                                        forcing ? (const double*)Fi[s] : nullptr, ef, dt, gamma, bvec, x, r, rh, pv[0],
                                        v[0], part[0]);
                 else
-                    hipLaunchKernelGGL(k_kry_start<false>, sg, b, 0, st, a, op->idx32, op->w64, k, c, h, nullptr, ef, dt,
+                    hipLaunchKernelGGL((a.keep ? k_kry_start<false, true> : k_kry_start<false, false>), sg, b, 0, st, a, op->idx32, op->w64, k, c, h, nullptr, ef, dt,
                                        gamma, bvec, x, r, rh, pv[0], v[0], part[0]);
                 const double2* ps = summed(0);
                 hipLaunchKernelGGL(k_kry_begin, dim3(1), dim3(256), 0, st, ps, npart, ks, tol, first, gamma);
@@ -1643,15 +1779,15 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
                 for (int q = 0; q < count; ++q) {
                     const int from = q & 1, to = 1 - from;
                     if (q == 0) {
-                        hipLaunchKernelGGL(k_kry_pv<true>, sg, b, 0, st, a, op->idx32, op->w64, nullptr, 0, ks, ks, r,
+                        hipLaunchKernelGGL((a.keep ? k_kry_pv<true, true> : k_kry_pv<true, false>), sg, b, 0, st, a, op->idx32, op->w64, nullptr, 0, ks, ks, r,
                                            rh, pv[from], v[from], pv[to], v[to], part[0]);
                     } else {
-                        hipLaunchKernelGGL(k_kry_pv<false>, sg, b, 0, st, a, op->idx32, op->w64, ps, npart, ks + cur,
+                        hipLaunchKernelGGL((a.keep ? k_kry_pv<false, true> : k_kry_pv<false, false>), sg, b, 0, st, a, op->idx32, op->w64, ps, npart, ks + cur,
                                            ks + 1 - cur, r, rh, pv[from], v[from], pv[to], v[to], part[0]);
                         cur = 1 - cur;
                     }
                     ps = summed(0);
-                    hipLaunchKernelGGL(k_kry_st, sg, b, 0, st, a, op->idx32, op->w64, ps, npart, ks + cur, r, v[to], sv, tv,
+                    hipLaunchKernelGGL((a.keep ? k_kry_st<true> : k_kry_st<false>), sg, b, 0, st, a, op->idx32, op->w64, ps, npart, ks + cur, r, v[to], sv, tv,
                                        part[1]);
                     ps = summed(1);
                     hipLaunchKernelGGL(k_kry_xr, sg, b, 0, st, P, ps, npart, ks + cur, pv[to], sv, tv, rh, x, r,
