@@ -294,7 +294,7 @@ __device__ __forceinline__ void vstore(T* __restrict__ Y, int64_t j, const T (&v
     }
 }
 
-// Row of the calling thread: slice and lane.  Four slices per 256-thread block.
+// Row of the calling thread: slice and lane.  B / 64 slices per block of B threads.
 struct RowPos {
     int64_t p;      // internal row
     int64_t slice;  // -1: past the last slice (the whole wavefront)
@@ -305,10 +305,10 @@ struct RowPos {
     bool live;
 };
 
-template <typename T>
+template <int B>
 __device__ __forceinline__ RowPos row_pos(const StageArgs& a) {
     RowPos rp;
-    const int64_t slice = (int64_t)xcd_block() * (BLK / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t slice = (int64_t)xcd_block() * (B / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     rp.lane = threadIdx.x & 63;
     rp.p = slice * 64 + rp.lane;
     rp.live = false;
@@ -575,7 +575,7 @@ __device__ __forceinline__ void laplacian_row(const StageArgs& a, const RowPos& 
                                               const T* __restrict__ w, const T* __restrict__ Y, const T (&yi)[2],
                                               T (&lap)[2]) {
     using V = typename Vec<T, S>::type;
-    __shared__ V ylds[BLK / 64][OP_HALO_MAX];
+    __shared__ V ylds[OP_HALO_MAX];
     const T* const ys[1] = {Y};
     RowAhead<T, S, 1, KEEP> ahead;
     ahead.load(a, rp, w, ys);
@@ -584,20 +584,23 @@ __device__ __forceinline__ void laplacian_row(const StageArgs& a, const RowPos& 
         if (rp.live) wd = ld<KEEP>(a.wd64 + rp.p);
     }
     if (rp.halo >= 0) {
-        ahead.finish(a, rp, w, ys, [](const V (&e)[1]) { return e[0]; }, ylds[threadIdx.x >> 6], yi, wd, lap);
+        ahead.finish(a, rp, w, ys, [](const V (&e)[1]) { return e[0]; }, ylds, yi, wd, lap);
         return;
     }
     if (rp.live) apply_row<T, S, KEEP>(rp, idx, w, Y, yi, wd, lap);
 }
 
-// RK4 stage `ST` (0..3).  Y: stage input; U: state at the start of the step;
+// RK4 stage `ST` (0..3), one wavefront per block: blocks of four, on a quarter
+// of the CUs, took 6.05 instead of 5.39 ms for 400 FP64 steps at N = 2500 and
+// 6.98 instead of 6.16 at N = 10242, two species; the same from N = 1e5 on.
+//  Y: stage input; U: state at the start of the step;
 // ACC: accumulator; YN: next stage input (stages 0-2) -- stage 3 updates U
 // (FP32: YN is then the compensation term of the update).
 template <typename T, int S, int R, int ST, bool FORCED, bool KEEP>
-__global__ __launch_bounds__(BLK) void k_rk4_stage(StageArgs a, const int32_t* __restrict__ idx,
+__global__ __launch_bounds__(64) void k_rk4_stage(StageArgs a, const int32_t* __restrict__ idx,
                                                    const T* __restrict__ w, const T* __restrict__ Y,
                                                    T* __restrict__ U, T* __restrict__ ACC, T* __restrict__ YN) {
-    const RowPos rp = row_pos<T>(a);
+    const RowPos rp = row_pos<64>(a);
     if (rp.slice < 0) return;  // the whole wavefront
     const int64_t p = rp.p;
     T yi[2] = {0, 0}, u[2], c[2], e[2], f[2], o[2];
@@ -668,9 +671,9 @@ __global__ void k_set_steps(int64_t* steps_done, int* nonfinite) {
 
 // one operator application (stage-free): out = L y (reaction-free, D = 1)
 template <typename T, bool KEEP>
-__global__ __launch_bounds__(BLK) void k_apply(StageArgs a, const int32_t* __restrict__ idx, const T* __restrict__ w,
+__global__ __launch_bounds__(64) void k_apply(StageArgs a, const int32_t* __restrict__ idx, const T* __restrict__ w,
                                                const T* __restrict__ Y, T* __restrict__ out) {
-    const RowPos rp = row_pos<T>(a);
+    const RowPos rp = row_pos<64>(a);
     if (rp.slice < 0) return;  // the whole wavefront
     T yi[2] = {0, 0};
     if (rp.live) vload<T, 1>(Y, rp.p, yi);
@@ -702,15 +705,15 @@ StageArgs stage_args(rbffd_op op, bool f64) {
     return a;
 }
 
-// Blocks of a stage launch: four slices each.
-inline dim3 stage_grid(int64_t nslices) { return dim3((unsigned)((nslices + BLK / 64 - 1) / (BLK / 64))); }
+// Blocks of a stage launch: one slice each.
+inline dim3 stage_grid(int64_t nslices) { return dim3((unsigned)nslices); }
 
 // One RK4 step, the i-th of its launch sequence; stage times t_n + c dt with
 // c = 0, 1/2, 1/2, 1.
 template <typename T, int S, int R, bool FORCED, bool KEEP>
 void enqueue_step(hipStream_t st, StageArgs a, int64_t i, const int32_t* idx, const T* w, T* U, T* ACC, T* Y1,
                   T* Y2, T* COMP) {
-    const dim3 g = stage_grid(a.nslices), b(BLK);
+    const dim3 g = stage_grid(a.nslices), b(64);
     a.toff = (double)i;
     hipLaunchKernelGGL((k_rk4_stage<T, S, R, 0, FORCED, KEEP>), g, b, 0, st, a, idx, w, U, U, ACC, Y1);
     a.toff = (double)i + 0.5;
@@ -749,7 +752,7 @@ void enqueue_steps_t(hipStream_t st, int S, int R, const StageArgs& a, const int
 
 template <typename T>
 void enqueue_apply(hipStream_t st, const StageArgs& a, const int32_t* idx, const T* w, const T* Y, T* out) {
-    const dim3 g = stage_grid(a.nslices), b(BLK);
+    const dim3 g = stage_grid(a.nslices), b(64);
     if (a.keep) hipLaunchKernelGGL((k_apply<T, true>), g, b, 0, st, a, idx, w, Y, out);
     else hipLaunchKernelGGL((k_apply<T, false>), g, b, 0, st, a, idx, w, Y, out);
 }
@@ -1275,7 +1278,10 @@ struct KrylovScalars {
 // the species' last solve took, and the kernels of iterations after
 // convergence (or a breakdown) return at once.
 constexpr int KRYLOV_BATCH = 8;
-// Block partials that a kernel sums by itself, two loads per thread; more are
+// Block partials that a kernel sums by itself, two loads per thread of a block
+// of four wavefronts; with as many slices or fewer the blocks are single
+// wavefronts, on four times as many CUs (five steps at N = 10242 6.3 -> 5.7 ms).
+// More are
 // first summed by a kernel of one block, whose launch (2 us) then costs less
 // than all of them read by every block of the next kernel.
 constexpr int PART_DIRECT = 512;
@@ -1300,7 +1306,7 @@ __global__ void k_reaction2(int64_t P, const double* __restrict__ u, const doubl
 // L y at row rp.p, neighbour values made by conv() from entries of NV vectors
 // (FP64, one species; in slot order).
 // load() first, then sum(); every lane of the wavefront takes part in both.
-template <int NV, bool KEEP>
+template <int NV, bool KEEP, int B>
 struct LaplacianOf {
     RowAhead<double, 1, NV, KEEP> ahead;
     double own[NV];
@@ -1319,7 +1325,7 @@ struct LaplacianOf {
     __device__ __forceinline__ double sum(const StageArgs& a, const RowPos& rp, const int32_t* __restrict__ idx,
                                           const double* __restrict__ w, const double* const (&Y)[NV], double yi,
                                           C&& conv) {
-        __shared__ double ylds[BLK / 64][OP_HALO_MAX];
+        __shared__ double ylds[B / 64][OP_HALO_MAX];
         const double y2[2] = {yi, 0.0};
         double lap[2] = {0.0, 0.0};
         if (rp.halo >= 0) {
@@ -1345,19 +1351,22 @@ __device__ __forceinline__ double wave_sum_block(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
-// Sums of two values over a block of 256, the same bits in every thread
-// (sh: 8 words; a barrier on entry, so that sh may be used again).
+// Sums of two values over a block of B = 64 or 256, the same bits in every
+// thread (sh: 8 words; a barrier on entry, so that sh may be used again).
+template <int B>
 __device__ __forceinline__ void block_sum2(double& v0, double& v1, double* sh) {
     v0 = wave_sum_block(v0);
     v1 = wave_sum_block(v1);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
-        sh[2 * (threadIdx.x >> 6)] = v0;
-        sh[2 * (threadIdx.x >> 6) + 1] = v1;
+    if constexpr (B > 64) {
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) {
+            sh[2 * (threadIdx.x >> 6)] = v0;
+            sh[2 * (threadIdx.x >> 6) + 1] = v1;
+        }
+        __syncthreads();
+        v0 = (sh[0] + sh[2]) + (sh[4] + sh[6]);
+        v1 = (sh[1] + sh[3]) + (sh[5] + sh[7]);
     }
-    __syncthreads();
-    v0 = (sh[0] + sh[2]) + (sh[4] + sh[6]);
-    v1 = (sh[1] + sh[3]) + (sh[5] + sh[7]);
 }
 // Block partials (pairs) summed in a fixed order: deterministic, and the same
 // in every block that does it.
@@ -1371,20 +1380,35 @@ struct Partials {
             d1 += v.y;
         }
     }
-    __device__ __forceinline__ void sum(double* sh) { block_sum2(d0, d1, sh); }
+    __device__ __forceinline__ void sum(double* sh) { block_sum2<256>(d0, d1, sh); }
 };
-// At most PART_DIRECT of them, both loads of a thread in flight at once.
+// At most PART_DIRECT of them, all loads of a thread in flight at once.
+template <int B>
 struct FewPartials {
-    double2 a, b;
+    static constexpr int M = PART_DIRECT / B;
+    double2 v[M];
+    int count;  // of this thread
     __device__ __forceinline__ FewPartials(const double2* __restrict__ part, int np)
-        : a(make_double2(0.0, 0.0)), b(make_double2(0.0, 0.0)) {
-        if ((int)threadIdx.x < np) a = part[threadIdx.x];
-        if ((int)threadIdx.x + 256 < np) b = part[threadIdx.x + 256];
+        : count((np - (int)threadIdx.x + B - 1) / B) {
+        if (np == 0) return;
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            if constexpr (B == 64) {  // no branches: 2 % of an iteration
+                v[i] = part[min((int)threadIdx.x + B * i, np - 1)];
+            } else {
+                v[i] = make_double2(0.0, 0.0);
+                if ((int)threadIdx.x + B * i < np) v[i] = part[threadIdx.x + B * i];
+            }
+        }
     }
     __device__ __forceinline__ void sum(double& d0, double& d1, double* sh) const {
-        d0 = a.x + b.x;
-        d1 = a.y + b.y;
-        block_sum2(d0, d1, sh);
+        d0 = d1 = 0.0;
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            d0 += B != 64 || i < count ? v[i].x : 0.0;
+            d1 += B != 64 || i < count ? v[i].y : 0.0;
+        }
+        block_sum2<B>(d0, d1, sh);
     }
 };
 __global__ __launch_bounds__(256) void k_sum_partials(const double2* __restrict__ part, int np, double2* out) {
@@ -1422,8 +1446,8 @@ __device__ __forceinline__ void end_iteration(KrylovScalars& k, double rr, doubl
 // hand side b = (-sum_{j>=1} a_j u^{n+1-j} + dt sum_j b_j R^{n+1-j} + dt ef F)
 // / a_0 and x = u^n.  Padding rows are written as
 // zero in every vector, here and below.
-template <bool FIRST, bool KEEP>
-__global__ __launch_bounds__(BLK) void k_kry_start(StageArgs a, const int32_t* __restrict__ idx,
+template <bool FIRST, bool KEEP, int B>
+__global__ __launch_bounds__(B) void k_kry_start(StageArgs a, const int32_t* __restrict__ idx,
                                                    const double* __restrict__ w, int nk, BdfCoef c, HistPtrs hp,
                                                    const double* __restrict__ F, double ef, double dt, double gamma,
                                                    double* __restrict__ b, double* __restrict__ x,
@@ -1431,11 +1455,11 @@ __global__ __launch_bounds__(BLK) void k_kry_start(StageArgs a, const int32_t* _
                                                    double* __restrict__ pv, double* __restrict__ v,
                                                    double2* __restrict__ part) {
     __shared__ double sh[8];
-    const RowPos rp = row_pos<double>(a);
+    const RowPos rp = row_pos<B>(a);
     const int64_t p = rp.p;
     const double* __restrict__ x0 = FIRST ? hp.u[0] : x;
     const double* const ys[1] = {x0};
-    LaplacianOf<1, KEEP> L;
+    LaplacianOf<1, KEEP, B> L;
     L.load(a, rp, w, ys);
     const double yi = rp.live ? L.own[0] : 0.0;
     const double lap = L.sum(a, rp, idx, w, ys, yi, [](const double (&e)[1]) { return e[0]; });
@@ -1462,7 +1486,7 @@ __global__ __launch_bounds__(BLK) void k_kry_start(StageArgs a, const int32_t* _
         bb = bv * bv;
         rr = rv * rv;
     }
-    block_sum2(bb, rr, sh);
+    block_sum2<B>(bb, rr, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = make_double2(bb, rr);
 }
 // bb, rr = rr0 = rho = r.r; alpha = omega = 1, tol and gamma stored; iters = 0
@@ -1471,7 +1495,7 @@ __global__ __launch_bounds__(256) void k_kry_begin(const double2* __restrict__ p
                                                    double tol, int first, double gamma) {
     __shared__ double sh[8];
     double d0, d1;
-    FewPartials(part, np).sum(d0, d1, sh);
+    FewPartials<256>(part, np).sum(d0, d1, sh);
     if (threadIdx.x != 0) return;
     ks->bb = d0;
     ks->rr = ks->rr0 = ks->rho = d1;
@@ -1497,8 +1521,8 @@ __global__ __launch_bounds__(256) void k_kry_begin(const double2* __restrict__ p
 //
 // k_kry_pv: the last iteration's end unless FIRST of a launch sequence (then ks_in is
 // final); p' = r + beta (p - omega v), v' = p' - gamma L p', partials rhat.v'
-template <bool FIRST, bool KEEP>
-__global__ __launch_bounds__(BLK) void k_kry_pv(StageArgs a, const int32_t* __restrict__ idx,
+template <bool FIRST, bool KEEP, int B>
+__global__ __launch_bounds__(B) void k_kry_pv(StageArgs a, const int32_t* __restrict__ idx,
                                                 const double* __restrict__ w, const double2* __restrict__ part_in,
                                                 int np, const KrylovScalars* ks_in, KrylovScalars* ks_out,
                                                 const double* __restrict__ r, const double* __restrict__ rh,
@@ -1508,10 +1532,10 @@ __global__ __launch_bounds__(BLK) void k_kry_pv(StageArgs a, const int32_t* __re
     __shared__ double sh[8];
     const bool writer = blockIdx.x == 0 && threadIdx.x == 0;
     KrylovScalars k = *ks_in;
-    const FewPartials sums(part_in, FIRST ? 0 : np);
-    const RowPos rp = row_pos<double>(a);
+    const FewPartials<B> sums(part_in, FIRST ? 0 : np);
+    const RowPos rp = row_pos<B>(a);
     const double* const ys[3] = {r, pv, v};
-    LaplacianOf<3, KEEP> L;
+    LaplacianOf<3, KEEP, B> L;
     L.load(a, rp, w, ys);
     if constexpr (!FIRST) {
         if (!k.done) {
@@ -1532,12 +1556,12 @@ __global__ __launch_bounds__(BLK) void k_kry_pv(StageArgs a, const int32_t* __re
         v_out[rp.p] = o;
         d = rh[rp.p] * o;
     }
-    block_sum2(d, z, sh);
+    block_sum2<B>(d, z, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = make_double2(d, 0.0);
 }
 // alpha = rho / rhat.v; s = r - alpha v, t = s - gamma L s, partials t.s and t.t
-template <bool KEEP>
-__global__ __launch_bounds__(BLK) void k_kry_st(StageArgs a, const int32_t* __restrict__ idx,
+template <bool KEEP, int B>
+__global__ __launch_bounds__(B) void k_kry_st(StageArgs a, const int32_t* __restrict__ idx,
                                                 const double* __restrict__ w, const double2* __restrict__ part_in,
                                                 int np, KrylovScalars* ks, const double* __restrict__ r,
                                                 const double* __restrict__ v, double* __restrict__ sv,
@@ -1545,10 +1569,10 @@ __global__ __launch_bounds__(BLK) void k_kry_st(StageArgs a, const int32_t* __re
     __shared__ double sh[8];
     const int done = ks->done;
     const double gamma = ks->gamma, rho = ks->rho;
-    const FewPartials sums(part_in, np);
-    const RowPos rp = row_pos<double>(a);
+    const FewPartials<B> sums(part_in, np);
+    const RowPos rp = row_pos<B>(a);
     const double* const ys[2] = {r, v};
-    LaplacianOf<2, KEEP> L;
+    LaplacianOf<2, KEEP, B> L;
     L.load(a, rp, w, ys);
     if (done) return;
     double d0, d1;
@@ -1570,11 +1594,12 @@ __global__ __launch_bounds__(BLK) void k_kry_st(StageArgs a, const int32_t* __re
         ts = o * yi;
         tt = o * o;
     }
-    block_sum2(ts, tt, sh);
+    block_sum2<B>(ts, tt, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = make_double2(ts, tt);
 }
 // omega = t.s / t.t; x += alpha p + omega s, r = s - omega t, partials r.r and rhat.r
-__global__ __launch_bounds__(256) void k_kry_xr(int64_t P, const double2* __restrict__ part_in, int np,
+template <int B>
+__global__ __launch_bounds__(B) void k_kry_xr(int64_t P, const double2* __restrict__ part_in, int np,
                                                 KrylovScalars* ks, const double* __restrict__ pv,
                                                 const double* __restrict__ sv, const double* __restrict__ tv,
                                                 const double* __restrict__ rh, double* __restrict__ x,
@@ -1582,8 +1607,8 @@ __global__ __launch_bounds__(256) void k_kry_xr(int64_t P, const double2* __rest
     __shared__ double sh[8];
     const int done = ks->done;
     const double alpha = ks->alpha;
-    const FewPartials sums(part_in, np);
-    const int64_t p = blockIdx.x * (int64_t)256 + threadIdx.x;
+    const FewPartials<B> sums(part_in, np);
+    const int64_t p = blockIdx.x * (int64_t)B + threadIdx.x;
     double s = 0.0, t = 0.0, pi = 0.0, xi = 0.0, h = 0.0;
     if (p < P) {
         s = sv[p];
@@ -1605,7 +1630,7 @@ __global__ __launch_bounds__(256) void k_kry_xr(int64_t P, const double2* __rest
         rr = q * q;
         hr = h * q;
     }
-    block_sum2(rr, hr, sh);
+    block_sum2<B>(rr, hr, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = make_double2(rr, hr);
 }
 // End of the last iteration of a launch sequence; the scalars move to *ks_out.
@@ -1613,7 +1638,7 @@ __global__ __launch_bounds__(256) void k_kry_end(const double2* __restrict__ par
                                                  KrylovScalars* ks_out) {
     __shared__ double sh[8];
     KrylovScalars k = *ks_in;
-    const FewPartials sums(part, np);
+    const FewPartials<256> sums(part, np);
     if (!k.done) {
         double d0, d1;
         sums.sum(d0, d1, sh);
@@ -1671,7 +1696,8 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
     // layout: scalars (two copies), summed partials, three sets of block partials;
     // U[s][order], R[s][order] (reaction), F[s], b, x, r, rh, p and v (two each), s, t
     const int nvec = S * order * (react ? 2 : 1) + S + 10;
-    const int nblk = (int)stage_grid(op->nslices).x;
+    const int kblk = op->nslices <= PART_DIRECT ? 64 : 256;  // threads per block of the solver's kernels
+    const int nblk = (int)((P + kblk - 1) / kblk);
     const size_t head = (1024 + 3 * (size_t)nblk * sizeof(double2) + 255) & ~(size_t)255;
     const size_t vbytes = (size_t)P * sizeof(double);
     int rc = ensure_impl(op, head + nvec * vbytes);
@@ -1735,7 +1761,19 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
     double worst = 0.0;
     int result = RBFFD_OK;
     int expect[2] = {1, 1};  // graphs of the species' last solve
-    const dim3 sg = stage_grid(a.nslices);
+    const dim3 sg(nblk), sb(kblk);
+    const bool one = kblk == 64;
+    const auto start_first = one ? (a.keep ? k_kry_start<true, true, 64> : k_kry_start<true, false, 64>)
+                                 : (a.keep ? k_kry_start<true, true, 256> : k_kry_start<true, false, 256>);
+    const auto start_again = one ? (a.keep ? k_kry_start<false, true, 64> : k_kry_start<false, false, 64>)
+                                 : (a.keep ? k_kry_start<false, true, 256> : k_kry_start<false, false, 256>);
+    const auto pv_first = one ? (a.keep ? k_kry_pv<true, true, 64> : k_kry_pv<true, false, 64>)
+                              : (a.keep ? k_kry_pv<true, true, 256> : k_kry_pv<true, false, 256>);
+    const auto pv_next = one ? (a.keep ? k_kry_pv<false, true, 64> : k_kry_pv<false, false, 64>)
+                             : (a.keep ? k_kry_pv<false, true, 256> : k_kry_pv<false, false, 256>);
+    const auto st_kernel = one ? (a.keep ? k_kry_st<true, 64> : k_kry_st<false, 64>)
+                               : (a.keep ? k_kry_st<true, 256> : k_kry_st<false, 256>);
+    const auto xr_kernel = one ? k_kry_xr<64> : k_kry_xr<256>;
     // what the next kernel sums: the block partials of set q, or their sum
     const int npart = nblk <= PART_DIRECT ? nblk : 1;
     auto summed = [&](int q) -> const double2* {
@@ -1761,11 +1799,11 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
             // (re)start from the true residual of x
             auto krylov_start = [&](int first) {
                 if (first)
-                    hipLaunchKernelGGL((a.keep ? k_kry_start<true, true> : k_kry_start<true, false>), sg, b, 0, st, a, op->idx32, op->w64, k, c, h,
+                    hipLaunchKernelGGL(start_first, sg, sb, 0, st, a, op->idx32, op->w64, k, c, h,
                                        forcing ? (const double*)Fi[s] : nullptr, ef, dt, gamma, bvec, x, r, rh, pv[0],
                                        v[0], part[0]);
                 else
-                    hipLaunchKernelGGL((a.keep ? k_kry_start<false, true> : k_kry_start<false, false>), sg, b, 0, st, a, op->idx32, op->w64, k, c, h, nullptr, ef, dt,
+                    hipLaunchKernelGGL(start_again, sg, sb, 0, st, a, op->idx32, op->w64, k, c, h, nullptr, ef, dt,
                                        gamma, bvec, x, r, rh, pv[0], v[0], part[0]);
                 const double2* ps = summed(0);
                 hipLaunchKernelGGL(k_kry_begin, dim3(1), dim3(256), 0, st, ps, npart, ks, tol, first, gamma);
@@ -1779,18 +1817,18 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
                 for (int q = 0; q < count; ++q) {
                     const int from = q & 1, to = 1 - from;
                     if (q == 0) {
-                        hipLaunchKernelGGL((a.keep ? k_kry_pv<true, true> : k_kry_pv<true, false>), sg, b, 0, st, a, op->idx32, op->w64, nullptr, 0, ks, ks, r,
+                        hipLaunchKernelGGL(pv_first, sg, sb, 0, st, a, op->idx32, op->w64, nullptr, 0, ks, ks, r,
                                            rh, pv[from], v[from], pv[to], v[to], part[0]);
                     } else {
-                        hipLaunchKernelGGL((a.keep ? k_kry_pv<false, true> : k_kry_pv<false, false>), sg, b, 0, st, a, op->idx32, op->w64, ps, npart, ks + cur,
+                        hipLaunchKernelGGL(pv_next, sg, sb, 0, st, a, op->idx32, op->w64, ps, npart, ks + cur,
                                            ks + 1 - cur, r, rh, pv[from], v[from], pv[to], v[to], part[0]);
                         cur = 1 - cur;
                     }
                     ps = summed(0);
-                    hipLaunchKernelGGL((a.keep ? k_kry_st<true> : k_kry_st<false>), sg, b, 0, st, a, op->idx32, op->w64, ps, npart, ks + cur, r, v[to], sv, tv,
+                    hipLaunchKernelGGL(st_kernel, sg, sb, 0, st, a, op->idx32, op->w64, ps, npart, ks + cur, r, v[to], sv, tv,
                                        part[1]);
                     ps = summed(1);
-                    hipLaunchKernelGGL(k_kry_xr, sg, b, 0, st, P, ps, npart, ks + cur, pv[to], sv, tv, rh, x, r,
+                    hipLaunchKernelGGL(xr_kernel, sg, sb, 0, st, P, ps, npart, ks + cur, pv[to], sv, tv, rh, x, r,
                                        part[2]);
                     ps = summed(2);
                 }
