@@ -22,6 +22,7 @@
 // D[4(l/16) + i][l%16], i = 0..3.
 #include "common.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace {
@@ -79,50 +80,21 @@ struct Bf16Params {
     const float* P;       // FP32 parameters (biases, w3, b3)
 };
 
-// Forward (and, when TRAIN, backward) over one tile of TB samples.
-// TRAIN false: forward only, writes y.  TRAIN true: forward + backward,
-// accumulates gradients into grad (FP32, atomics) and the summed squared
-// error into loss.  Sample s of the tile is row base + s of x, or a hashed
-// index when sampling.  The forward-only form keeps only the two row-major
-// tiles in LDS (32 KB instead of 128 KB: five workgroups per CU instead of
-// one); its arithmetic is the same, so y is the same bit for bit.
-template <bool TRAIN>
+// Forward over one tile of TB samples: y.
 __global__ __launch_bounds__(WG) void k_mlp(int64_t count, Bf16Params prm, const uint16_t* __restrict__ x,
-                                            const float* __restrict__ target, float* __restrict__ y,
-                                            float* __restrict__ grad, float* __restrict__ loss, float gscale,
-                                            uint64_t seed, int64_t step) {
+                                            float* __restrict__ y) {
     __shared__ __attribute__((aligned(16))) uint16_t Xs[TB * F];   // [b][k]
     __shared__ __attribute__((aligned(16))) uint16_t H1s[TB * H];  // [b][i]
-    // backward only
-    __shared__ __attribute__((aligned(16))) uint16_t XT[TRAIN ? F * TB : 8];   // [k][b]
-    __shared__ __attribute__((aligned(16))) uint16_t H1T[TRAIN ? H * TB : 8];  // [i][b]
-    __shared__ __attribute__((aligned(16))) uint16_t H2s[TRAIN ? TB * H : 8];  // [b][o]
-    __shared__ __attribute__((aligned(16))) uint16_t G2s[TRAIN ? TB * H : 8];  // dH2 [b][o]
-    __shared__ __attribute__((aligned(16))) uint16_t G2T[TRAIN ? H * TB : 8];  // dH2 [o][b]
-    __shared__ __attribute__((aligned(16))) uint16_t G1T[TRAIN ? H * TB : 8];  // dH1 [i][b]
-    __shared__ float ys[TB], dys[TB];
-    __shared__ int64_t rows[TB];
+    __shared__ float ys[TB];
     const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63;
     const int64_t base = (int64_t)blockIdx.x * TB;
-    if (tid < TB) {
-        int64_t rr = base + tid;
-        if (seed != 0) rr = (int64_t)(mix64(seed ^ mix64((uint64_t)step * 0x9e3779b97f4a7c15ull + (uint64_t)rr)) %
-                                      (uint64_t)count);
-        rows[tid] = rr;
-    }
-    __syncthreads();
     // ---- load the input tile (zeros beyond count)
     for (int e = tid; e < TB * F / 8; e += WG) {
         const int b = e / (F / 8), k8 = (e % (F / 8)) * 8;
-        const int64_t rr = rows[b];
+        const int64_t rr = base + b;
         uint4 v = make_uint4(0, 0, 0, 0);
         if (rr < count) v = *reinterpret_cast<const uint4*>(x + rr * F + k8);
         *reinterpret_cast<uint4*>(Xs + b * F + k8) = v;
-        if constexpr (TRAIN) {
-            const uint16_t* hv = reinterpret_cast<const uint16_t*>(&v);
-#pragma unroll
-            for (int t = 0; t < 8; ++t) XT[(k8 + t) * TB + b] = hv[t];
-        }
     }
     __syncthreads();
     const int r0 = wv * 16;              // this wave's 16 sample rows
@@ -134,12 +106,7 @@ __global__ __launch_bounds__(WG) void k_mlp(int64_t count, Bf16Params prm, const
         const int o = ct * 16 + col;
         const float bb = prm.P[OFF_B1 + o];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int b = r0 + rq + i;
-            const uint16_t h = f2bf(fmaxf(acc[i] + bb, 0.0f));
-            H1s[b * H + o] = h;
-            if constexpr (TRAIN) H1T[o * TB + b] = h;
-        }
+        for (int i = 0; i < 4; ++i) H1s[(r0 + rq + i) * H + o] = f2bf(fmaxf(acc[i] + bb, 0.0f));
     }
     __syncthreads();
     // ---- layer 2: H2 = relu(H1 W2^T + b2); layer 3: y = H2 . w3 + b3
@@ -150,12 +117,7 @@ __global__ __launch_bounds__(WG) void k_mlp(int64_t count, Bf16Params prm, const
         const int o = ct * 16 + col;
         const float bb = prm.P[OFF_B2 + o], w3 = prm.P[OFF_W3 + o];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int b = r0 + rq + i;
-            const uint16_t h = f2bf(fmaxf(acc[i] + bb, 0.0f));
-            if constexpr (TRAIN) H2s[b * H + o] = h;
-            part[i] = fmaf(bf2f(h), w3, part[i]);
-        }
+        for (int i = 0; i < 4; ++i) part[i] = fmaf(bf2f(f2bf(fmaxf(acc[i] + bb, 0.0f))), w3, part[i]);
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -167,85 +129,320 @@ __global__ __launch_bounds__(WG) void k_mlp(int64_t count, Bf16Params prm, const
         for (int i = 0; i < 4; ++i) ys[r0 + rq + i] = part[i] + prm.P[OFF_B3];
     }
     __syncthreads();
-    if constexpr (!TRAIN) {
-        if (tid < TB && base + tid < count) y[base + tid] = ys[tid];
-        return;
-    }
-    // ---- backward: L = gscale * sum_b (y_b - t_b)^2
-    if (tid < TB) {
-        const int64_t rr = rows[tid];
-        float d = 0.0f;
-        if (rr < count) {
-            const float e = ys[tid] - target[rr];
-            d = 2.0f * gscale * e;
-            atomicAdd(loss, gscale * e * e);
-        }
-        dys[tid] = d;
-    }
-    __syncthreads();
-    // dW3, db3 (one thread per output unit), dH2 = dy w3 [H2 > 0]
-    if (tid < H) {
-        float s = 0.0f;
-        for (int b = 0; b < TB; ++b) s = fmaf(dys[b], bf2f(H2s[b * H + tid]), s);
-        atomicAdd(grad + OFF_W3 + tid, s);
-    }
-    if (tid == H) {
-        float s = 0.0f;
-        for (int b = 0; b < TB; ++b) s += dys[b];
-        atomicAdd(grad + OFF_B3, s);
-    }
-    for (int e = tid; e < TB * H; e += WG) {
-        const int b = e / H, o = e % H;
-        const float g = H2s[e] != 0 ? dys[b] * prm.P[OFF_W3 + o] : 0.0f;
-        const uint16_t gh = f2bf(g);
-        G2s[e] = gh;
-        G2T[o * TB + b] = gh;
-    }
-    __syncthreads();
-    // db2 = sum_b dH2
-    if (tid < H) {
-        float s = 0.0f;
-        for (int b = 0; b < TB; ++b) s += bf2f(G2T[tid * TB + b]);
-        atomicAdd(grad + OFF_B2 + tid, s);
-    }
-    // dW2[o][i] = sum_b dH2[b][o] H1[b][i]: wave w owns output tile rows 2w, 2w+1
-    for (int rt = 2 * wv; rt < 2 * wv + 2; ++rt) {
-        for (int ct = 0; ct < H / 16; ++ct) {
-            floatx4 acc = {0, 0, 0, 0};
-            mma_tile(G2T + rt * 16 * TB, TB, H1T + ct * 16 * TB, TB, TB, acc);
+    if (tid < TB && base + tid < count) y[base + tid] = ys[tid];
+}
+
+// ---- training -------------------------------------------------------------
+// A step is two kernels.  k_mlp_backward takes 16 samples per workgroup through
+// forward and backward and stores what the weight gradients contract over,
+// sample-contiguous; k_mlp_update contracts it, one 16 x 16 block of a weight
+// matrix per workgroup, and applies Adam to the entries it owns.  At these
+// batches a step is bound by latency, so the first spreads over four times the
+// CUs that tiles of 64 reach and has every weight fragment in flight before the
+// first matrix product, and the second sums over the batch without atomics (one
+// kernel with 33 000 atomic adds per 64 samples, and a separate Adam, took
+// 42 us a step at a batch of 4096; these take 9.2 and 6.0 us, 17 us a step).
+constexpr int TT = 16;               // samples per workgroup
+constexpr int TLD = F + 8;           // row stride of the LDS tiles: rows start 4 banks apart
+constexpr int CHUNK = 1 << 15;       // samples per launch: 32 MB of workspace
+constexpr int STAT = H + 2;          // per workgroup: dw3, db3, loss
+
+// XT and so on: [tile][128][TT], sample-contiguous; a workgroup of the first
+// kernel writes 4 KB in a row of each, a fragment of the second reads two times
+// 512 bytes.
+struct Chunk {
+    uint16_t *XT, *H1T, *G1T, *G2T;
+    float* stat;                     // [tile][STAT]
+    int64_t ld;                      // samples of the launch, a multiple of 32
+};
+
+// One 16 x 16 tile over K = 128 with the B fragments in registers.
+__device__ __forceinline__ floatx4 mma_row(const uint16_t* a, const bf16x8 (&bf)[4]) {
+    const int l = threadIdx.x & 63;
+    floatx4 acc = {0, 0, 0, 0};
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                atomicAdd(grad + OFF_W2 + (rt * 16 + rq + i) * H + ct * 16 + col, acc[i]);
-        }
+    for (int q = 0; q < 4; ++q) {
+        const bf16x8 av = *reinterpret_cast<const bf16x8*>(a + (l & 15) * TLD + 32 * q + (l >> 4) * 8);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bf[q], acc, 0, 0, 0);
     }
-    // dH1 = (dH2 W2) [H1 > 0]  (B operand: W2^T rows)
-    for (int ct = 0; ct < H / 16; ++ct) {
-        floatx4 acc = {0, 0, 0, 0};
-        mma_tile(G2s + r0 * H, H, prm.W2T + ct * 16 * H, H, H, acc);
-        const int i_ = ct * 16 + col;
+    return acc;
+}
+__device__ __forceinline__ void load_fragments(const uint16_t* w, bf16x8 (&bf)[4]) {
+    const int l = threadIdx.x & 63;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        bf[q] = *reinterpret_cast<const bf16x8*>(w + (l & 15) * F + 32 * q + (l >> 4) * 8);
+}
+__device__ __forceinline__ uint2 pack4(const uint16_t (&h)[4]) {
+    return make_uint2((uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16);
+}
+
+// Samples first .. first + ld of the batch; sample s is row s of x, or with a
+// seed a hashed row.  Samples past `batch` (the last launch's padding) or rows
+// past count are zeros without error.  Wave w has columns 32 w .. 32 w + 31 of
+// every layer.
+__global__ __launch_bounds__(WG) void k_mlp_backward(int64_t count, int64_t first, int64_t batch, Bf16Params prm,
+                                                     const uint16_t* __restrict__ x, const float* __restrict__ target,
+                                                     Chunk c, float gscale, uint64_t seed, int64_t step) {
+    __shared__ __attribute__((aligned(16))) uint16_t Xs[TT * TLD], H1s[TT * TLD], G2s[TT * TLD];
+    __shared__ float ypart[WG / 64][TT], tgs[TT];
+    __shared__ bool ins[TT];
+    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63;
+    const int col = l & 15, rq = (l >> 4) * 4;
+    bf16x8 w1[2][4], w2[2][4], w2t[2][4];
+    float b1[2], b2[2], w3[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int o = 32 * wv + 16 * t;
+        load_fragments(prm.W1 + o * F, w1[t]);
+        b1[t] = prm.P[OFF_B1 + o + col];
+        b2[t] = prm.P[OFF_B2 + o + col];
+        w3[t] = prm.P[OFF_W3 + o + col];
+    }
+    const float b3 = prm.P[OFF_B3];
+    {
+        const int b = tid >> 4, k8 = (tid & 15) * 8;
+        const int64_t smp = first + (int64_t)blockIdx.x * TT + b;
+        int64_t rr = smp;
+        if (seed != 0)
+            rr = (int64_t)(mix64(seed ^ mix64((uint64_t)step * 0x9e3779b97f4a7c15ull + (uint64_t)smp)) %
+                           (uint64_t)count);
+        const bool in = smp < batch && rr < count;
+        uint4 v = make_uint4(0, 0, 0, 0);
+        float tg = 0.0f;
+        if (in) {
+            v = *reinterpret_cast<const uint4*>(x + rr * F + k8);
+            tg = target[rr];
+        }
+        // loads return in order: what is needed last is asked for last
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            load_fragments(prm.W2 + (32 * wv + 16 * t) * H, w2[t]);
+            load_fragments(prm.W2T + (32 * wv + 16 * t) * H, w2t[t]);
+        }
+        if (k8 == 0) {
+            tgs[b] = tg;
+            ins[b] = in;
+        }
+        *reinterpret_cast<uint4*>(Xs + b * TLD + k8) = v;
+    }
+    __syncthreads();
+    const int64_t t0 = (int64_t)blockIdx.x * TT * H;  // of the tile's arrays
+    // ---- layer 1: H1 = relu(X W1^T + b1)
+    uint16_t h1[2][4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const floatx4 acc = mma_row(Xs, w1[t]);
+        const int o = 32 * wv + 16 * t + col;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int b = r0 + rq + i;
-            const float g = H1s[b * H + i_] != 0 ? acc[i] : 0.0f;
-            G1T[i_ * TB + b] = f2bf(g);
+            h1[t][i] = f2bf(fmaxf(acc[i] + b1[t], 0.0f));
+            H1s[(rq + i) * TLD + o] = h1[t][i];
+        }
+        *reinterpret_cast<uint2*>(c.H1T + t0 + o * TT + rq) = pack4(h1[t]);
+    }
+    {   // X, sample-contiguous
+        const int k = tid >> 1, b0 = (tid & 1) * 8;
+        uint32_t v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            v[q] = (uint32_t)Xs[(b0 + 2 * q) * TLD + k] | (uint32_t)Xs[(b0 + 2 * q + 1) * TLD + k] << 16;
+        *reinterpret_cast<uint4*>(c.XT + t0 + k * TT + b0) = make_uint4(v[0], v[1], v[2], v[3]);
+    }
+    __syncthreads();
+    // ---- layer 2: H2 = relu(H1 W2^T + b2); layer 3: y = H2 . w3 + b3
+    float h2[2][4], part[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const floatx4 acc = mma_row(H1s, w2[t]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            h2[t][i] = bf2f(f2bf(fmaxf(acc[i] + b2[t], 0.0f)));
+            part[i] = fmaf(h2[t][i], w3[t], part[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int m = 1; m < 16; m <<= 1) part[i] += __shfl_xor(part[i], m, 64);
+        if (col == 0) ypart[wv][rq + i] = part[i];
+    }
+    __syncthreads();
+    // ---- backward: L = gscale * sum_b (y_b - t_b)^2
+    float dy[4], db3 = 0.0f, loss = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int b = rq + i;
+        const float y = ((ypart[0][b] + ypart[1][b]) + (ypart[2][b] + ypart[3][b])) + b3;
+        const float e = ins[b] ? y - tgs[b] : 0.0f;
+        dy[i] = 2.0f * gscale * e;
+        db3 += dy[i];
+        loss = fmaf(gscale * e, e, loss);
+    }
+    // dw3, db3 and the loss of the tile; dH2 = dy w3 [H2 > 0]
+    float* st = c.stat + (int64_t)blockIdx.x * STAT;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int o = 32 * wv + 16 * t + col;
+        float s = 0.0f;
+        uint16_t g[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s = fmaf(dy[i], h2[t][i], s);
+            g[i] = f2bf(h2[t][i] != 0.0f ? dy[i] * w3[t] : 0.0f);
+            G2s[(rq + i) * TLD + o] = g[i];
+        }
+        *reinterpret_cast<uint2*>(c.G2T + t0 + o * TT + rq) = pack4(g);
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (l < 16) st[o] = s;
+    }
+    if (wv == 0) {
+        db3 += __shfl_xor(db3, 16, 64);
+        db3 += __shfl_xor(db3, 32, 64);
+        loss += __shfl_xor(loss, 16, 64);
+        loss += __shfl_xor(loss, 32, 64);
+        if (l == 0) {
+            st[H] = db3;
+            st[H + 1] = loss;
         }
     }
     __syncthreads();
-    if (tid < H) {
-        float s = 0.0f;
-        for (int b = 0; b < TB; ++b) s += bf2f(G1T[tid * TB + b]);
-        atomicAdd(grad + OFF_B1 + tid, s);
-    }
-    // dW1[i][k] = sum_b dH1[b][i] X[b][k]
-    for (int rt = 2 * wv; rt < 2 * wv + 2; ++rt) {
-        for (int ct = 0; ct < F / 16; ++ct) {
-            floatx4 acc = {0, 0, 0, 0};
-            mma_tile(G1T + rt * 16 * TB, TB, XT + ct * 16 * TB, TB, TB, acc);
+    // ---- dH1 = (dH2 W2) [H1 > 0]
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                atomicAdd(grad + OFF_W1 + (rt * 16 + rq + i) * F + ct * 16 + col, acc[i]);
+    for (int t = 0; t < 2; ++t) {
+        const floatx4 acc = mma_row(G2s, w2t[t]);
+        uint16_t g[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) g[i] = f2bf(h1[t][i] != 0 ? acc[i] : 0.0f);
+        *reinterpret_cast<uint2*>(c.G1T + t0 + (32 * wv + 16 * t + col) * TT + rq) = pack4(g);
+    }
+}
+
+struct Adam {
+    float *P, *M, *V;
+    float lr, b1, b2, eps, c1, c2;
+    uint16_t *W1, *W2, *W2T;
+};
+// what becomes of an entry's gradient: + gin (of earlier launches), then
+// stored, or with gout null put through Adam
+struct Sink {
+    const float* gin;
+    float* gout;
+    Adam a;
+
+    // what take() needs of entry e, read before the sums
+    struct Entry {
+        float g, p, m, v;
+    };
+    __device__ __forceinline__ Entry entry(int e) const {
+        Entry n = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (gin) n.g = gin[e];
+        if (!gout) {
+            n.p = a.P[e];
+            n.m = a.M[e];
+            n.v = a.V[e];
+        }
+        return n;
+    }
+    __device__ __forceinline__ void take(int e, const Entry& n, float g) const {
+        if (gin) g += n.g;
+        if (gout) {
+            gout[e] = g;
+            return;
+        }
+        const float m = a.b1 * n.m + (1.0f - a.b1) * g;
+        const float v = a.b2 * n.v + (1.0f - a.b2) * g * g;
+        a.M[e] = m;
+        a.V[e] = v;
+        const float p = n.p - a.lr * (m * a.c1) / (sqrtf(v * a.c2) + a.eps);
+        a.P[e] = p;
+        if (e < OFF_B1) a.W1[e - OFF_W1] = f2bf(p);
+        if (e >= OFF_W2 && e < OFF_B2) {
+            const int q = e - OFF_W2;
+            const uint16_t h = f2bf(p);
+            a.W2[q] = h;
+            a.W2T[(q % H) * H + q / H] = h;
         }
     }
+};
+
+// Workgroups 0-63: tiles of dW1[i][k] = sum_b dH1[b][i] X[b][k]; 64-127: of
+// dW2[o][i] = sum_b dH2[b][o] H1[b][i]; those of column 0 also the biases, sums
+// of the same rows.  128: dw3, db3 and the loss from the tiles' sums.
+// Waves take 32 samples in turn, eight of these in flight.
+constexpr int UW = 16;               // waves
+constexpr int UPDATE_WGS = 2 * (H / 16) * (H / 16) + 1;
+__global__ __launch_bounds__(64 * UW) void k_mlp_update(Chunk c, int tiles, Sink sink, float* __restrict__ loss,
+                                                        int add_loss) {
+    __shared__ float red[UW][256];
+    __shared__ float bred[UW][16];
+    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63;
+    if (blockIdx.x == UPDATE_WGS - 1) {
+        // thread (g, o): tiles g, g + 7, ... of sum o; 7 x 130 threads
+        const int g = tid / STAT, o = tid % STAT;
+        const int e = tid < H ? OFF_W3 + tid : OFF_B3;
+        Sink::Entry n = {};
+        if (tid <= H) n = sink.entry(e);
+        float s = 0.0f;
+        if (g < 7) {
+#pragma unroll 8
+            for (int t = g; t < tiles; t += 7) s += c.stat[(int64_t)t * STAT + o];
+        }
+        float* r = &red[0][0];
+        if (g < 7) r[tid] = s;
+        __syncthreads();
+        if (tid >= STAT) return;
+        for (int q = 1; q < 7; ++q) s += r[q * STAT + tid];
+        if (tid <= H) sink.take(e, n, s);
+        else *loss = add_loss ? *loss + s : s;
+        return;
+    }
+    const int which = blockIdx.x >> 6, rt = (blockIdx.x >> 3) & 7, ct = blockIdx.x & 7;
+    const int at = ((l >> 5) * H + (l & 15)) * TT + ((l >> 4) & 1) * 8;
+    const uint16_t* A = (which ? c.G2T : c.G1T) + at + rt * 16 * TT;
+    const uint16_t* B = (which ? c.H1T : c.XT) + at + ct * 16 * TT;
+    int e = -1;  // the thread's entry
+    if (tid < 256) e = (which ? OFF_W2 : OFF_W1) + (rt * 16 + tid / 16) * H + ct * 16 + tid % 16;
+    else if (ct == 0 && tid < 256 + 16) e = (which ? OFF_B2 : OFF_B1) + rt * 16 + tid - 256;
+    Sink::Entry n = {};
+    if (e >= 0) n = sink.entry(e);
+    const int steps = (int)(c.ld / 32);
+    floatx4 acc = {0, 0, 0, 0};
+    float rows = 0.0f;
+    constexpr int U = 8;
+    for (int s0 = wv; s0 < steps; s0 += UW * U) {
+        bf16x8 av[U], bv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = min(s0 + UW * u, steps - 1);
+            av[u] = *reinterpret_cast<const bf16x8*>(A + 2 * TT * H * (int64_t)s);
+            bv[u] = *reinterpret_cast<const bf16x8*>(B + 2 * TT * H * (int64_t)s);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + UW * u < steps) {
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u], bv[u], acc, 0, 0, 0);
+                if (ct == 0) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) rows += (float)av[u][q];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) red[wv][(4 * (l >> 4) + i) * 16 + (l & 15)] = acc[i];
+    if (ct == 0) {
+        rows += __shfl_xor(rows, 16, 64);
+        rows += __shfl_xor(rows, 32, 64);
+        if (l < 16) bred[wv][l] = rows;
+    }
+    __syncthreads();
+    if (e < 0) return;
+    float s = 0.0f;
+#pragma unroll
+    for (int q = 0; q < UW; ++q) s += tid < 256 ? red[q][tid] : bred[q][tid - 256];
+    sink.take(e, n, s);
 }
 
 // BF16 copies of W1, W2 and W2^T from the FP32 parameters
@@ -257,29 +454,6 @@ __global__ void k_mlp_convert(const float* __restrict__ P, uint16_t* __restrict_
         const uint16_t v = f2bf(P[OFF_W2 + e]);
         W2[e] = v;
         W2T[(e % H) * H + e / H] = v;
-    }
-}
-
-// Adam on the FP32 parameters; clears the gradient; refreshes the BF16 copies.
-__global__ void k_adam(float* __restrict__ P, float* __restrict__ M, float* __restrict__ V, float* __restrict__ G,
-                       float lr, float b1, float b2, float eps, float c1, float c2, uint16_t* __restrict__ W1,
-                       uint16_t* __restrict__ W2, uint16_t* __restrict__ W2T) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= RBFFD_MLP_PARAMS) return;
-    const float g = G[e];
-    const float m = b1 * M[e] + (1.0f - b1) * g;
-    const float v = b2 * V[e] + (1.0f - b2) * g * g;
-    M[e] = m;
-    V[e] = v;
-    const float p = P[e] - lr * (m * c1) / (sqrtf(v * c2) + eps);
-    P[e] = p;
-    G[e] = 0.0f;
-    if (e < OFF_B1) W1[e - OFF_W1] = f2bf(p);
-    if (e >= OFF_W2 && e < OFF_B2) {
-        const int q = e - OFF_W2;
-        const uint16_t h = f2bf(p);
-        W2[q] = h;
-        W2T[(q % H) * H + q / H] = h;
     }
 }
 
@@ -377,6 +551,35 @@ int mlp_scratch(rbffd_ctx ctx, size_t extra, MlpScratch& ms, char** extra_ptr) {
     return RBFFD_OK;
 }
 
+size_t chunk_bytes(int64_t batch) {
+    const size_t ld = (size_t)((std::min<int64_t>(batch, CHUNK) + 31) & ~(int64_t)31);
+    return 4 * ld * H * sizeof(uint16_t) + ld / TT * STAT * sizeof(float);
+}
+
+// Gradient and loss of one batch, and with a.P set the Adam step (the
+// gradient is then only kept between the launches of a batch above CHUNK).
+void batch_step(hipStream_t st, int64_t count, int64_t batch, const Bf16Params& p, const uint16_t* feats,
+                const float* target, void* work, uint64_t seed, int64_t step, float* grad, float* loss, const Adam& a) {
+    for (int64_t first = 0; first < batch; first += CHUNK) {
+        const int64_t ns = std::min<int64_t>(batch - first, CHUNK);
+        Chunk c;
+        c.ld = (ns + 31) & ~(int64_t)31;
+        c.XT = (uint16_t*)work;
+        c.H1T = c.XT + c.ld * H;
+        c.G1T = c.H1T + c.ld * H;
+        c.G2T = c.G1T + c.ld * H;
+        c.stat = (float*)(c.G2T + c.ld * H);
+        const int tiles = (int)(c.ld / TT);
+        hipLaunchKernelGGL(k_mlp_backward, dim3(tiles), dim3(WG), 0, st, count, first, batch, p, feats, target, c,
+                           1.0f / (float)batch, seed, step);
+        Sink sink;
+        sink.gin = first ? grad : nullptr;
+        sink.gout = a.P && first + ns == batch ? nullptr : grad;
+        sink.a = a;
+        hipLaunchKernelGGL(k_mlp_update, dim3(UPDATE_WGS), dim3(64 * UW), 0, st, c, tiles, sink, loss, first != 0);
+    }
+}
+
 void convert(hipStream_t st, const float* P, const MlpScratch& ms) {
     hipLaunchKernelGGL(k_mlp_convert, dim3((H * F + 255) / 256), dim3(256), 0, st, P, ms.W1, ms.W2, ms.W2T);
 }
@@ -406,8 +609,7 @@ extern "C" int rbffd_mlp_forward(rbffd_ctx ctx, const float* params, int64_t B, 
     if (rc) return rc;
     convert(ctx->stream, params, ms);
     Bf16Params p{ms.W1, ms.W2, ms.W2T, params};
-    hipLaunchKernelGGL(k_mlp<false>, dim3((unsigned)((B + TB - 1) / TB)), dim3(WG), 0, ctx->stream, B, p, feats,
-                       nullptr, y, nullptr, nullptr, 0.0f, (uint64_t)0, (int64_t)0);
+    hipLaunchKernelGGL(k_mlp, dim3((unsigned)((B + TB - 1) / TB)), dim3(WG), 0, ctx->stream, B, p, feats, y);
     HIP_TRY(ctx, hipGetLastError());
     return RBFFD_OK;
 }
@@ -418,14 +620,12 @@ extern "C" int rbffd_mlp_grad(rbffd_ctx ctx, const float* params, int64_t B, con
     if (B <= 0) return set_error(ctx, RBFFD_E_ARG, "B must be > 0");
     if (!params || !feats || !target || !grad || !loss) return set_error(ctx, RBFFD_E_ARG, "null pointer");
     MlpScratch ms;
-    int rc = mlp_scratch(ctx, 0, ms, nullptr);
+    char* extra = nullptr;
+    int rc = mlp_scratch(ctx, chunk_bytes(B), ms, &extra);
     if (rc) return rc;
     convert(ctx->stream, params, ms);
-    HIP_TRY(ctx, hipMemsetAsync(grad, 0, RBFFD_MLP_PARAMS * sizeof(float), ctx->stream));
-    HIP_TRY(ctx, hipMemsetAsync(loss, 0, sizeof(float), ctx->stream));
     Bf16Params p{ms.W1, ms.W2, ms.W2T, params};
-    hipLaunchKernelGGL(k_mlp<true>, dim3((unsigned)((B + TB - 1) / TB)), dim3(WG), 0, ctx->stream, B, p, feats,
-                       target, nullptr, grad, loss, 1.0f / (float)B, (uint64_t)0, (int64_t)0);
+    batch_step(ctx->stream, B, B, p, feats, target, extra, 0, 0, grad, loss, Adam{});
     HIP_TRY(ctx, hipGetLastError());
     return RBFFD_OK;
 }
@@ -440,27 +640,29 @@ extern "C" int rbffd_mlp_train(rbffd_ctx ctx, float* params, float* adam_m, floa
     if (o->seed == 0) return set_error(ctx, RBFFD_E_ARG, "seed must be non-zero");
     MlpScratch ms;
     char* extra = nullptr;
-    const size_t gbytes = (RBFFD_MLP_PARAMS + 64) * sizeof(float);
-    int rc = mlp_scratch(ctx, gbytes + 256 * sizeof(float), ms, &extra);
+    const size_t gbytes = ((RBFFD_MLP_PARAMS + 1) * sizeof(float) + 255) & ~(size_t)255;  // a gradient and a loss
+    int rc = mlp_scratch(ctx, gbytes + chunk_bytes(o->batch), ms, &extra);
     if (rc) return rc;
     float* grad = (float*)extra;
-    float* loss_tmp = grad + RBFFD_MLP_PARAMS + 32;
     hipStream_t st = ctx->stream;
-    HIP_TRY(ctx, hipMemsetAsync(grad, 0, RBFFD_MLP_PARAMS * sizeof(float), st));
     convert(st, params, ms);
     Bf16Params p{ms.W1, ms.W2, ms.W2T, params};
-    const int nb = o->batch / TB;
     for (int64_t s = 0; s < o->steps; ++s) {
-        float* lp = loss_per_step ? loss_per_step + s : loss_tmp;
-        HIP_TRY(ctx, hipMemsetAsync(lp, 0, sizeof(float), st));
-        hipLaunchKernelGGL(k_mlp<true>, dim3(nb), dim3(WG), 0, st, count, p, feats, target, nullptr, grad, lp,
-                           1.0f / (float)o->batch, o->seed, o->step0 + s);
         const double t = (double)(o->step0 + s + 1);
-        const float c1 = (float)(1.0 / (1.0 - pow(o->beta1, t)));
-        const float c2 = (float)(1.0 / (1.0 - pow(o->beta2, t)));
-        hipLaunchKernelGGL(k_adam, dim3((RBFFD_MLP_PARAMS + 255) / 256), dim3(256), 0, st, params, adam_m, adam_v,
-                           grad, (float)o->lr, (float)o->beta1, (float)o->beta2, (float)o->adam_eps, c1, c2, ms.W1,
-                           ms.W2, ms.W2T);
+        const Adam a{params,
+                     adam_m,
+                     adam_v,
+                     (float)o->lr,
+                     (float)o->beta1,
+                     (float)o->beta2,
+                     (float)o->adam_eps,
+                     (float)(1.0 / (1.0 - pow(o->beta1, t))),
+                     (float)(1.0 / (1.0 - pow(o->beta2, t))),
+                     ms.W1,
+                     ms.W2,
+                     ms.W2T};
+        batch_step(st, count, o->batch, p, feats, target, extra + gbytes, o->seed, o->step0 + s, grad,
+                   loss_per_step ? loss_per_step + s : grad + RBFFD_MLP_PARAMS, a);
     }
     HIP_TRY(ctx, hipGetLastError());
     return RBFFD_OK;
@@ -487,8 +689,7 @@ extern "C" int rbffd_predict_eps(rbffd_ctx ctx, const float* params, int64_t N, 
                        idx, feats, rho);
     convert(st, params, ms);
     Bf16Params p{ms.W1, ms.W2, ms.W2T, params};
-    hipLaunchKernelGGL(k_mlp<false>, dim3((unsigned)((N + TB - 1) / TB)), dim3(WG), 0, st, N, p, feats, nullptr, y,
-                       nullptr, nullptr, 0.0f, (uint64_t)0, (int64_t)0);
+    hipLaunchKernelGGL(k_mlp, dim3((unsigned)((N + TB - 1) / TB)), dim3(WG), 0, st, N, p, feats, y);
     hipLaunchKernelGGL(k_eps_from_y, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, N, y, rho, eps);
     HIP_TRY(ctx, hipGetLastError());
     return RBFFD_OK;

@@ -128,3 +128,46 @@ def test_training_reduces_loss(lib, batch):
     assert np.all(np.isfinite(l))
     assert m1 < 0.2 * m0, (m0, m1)
     assert l[-20:].mean() < l[:20].mean()
+
+
+@pytest.mark.parametrize("B", [1, 15, 17, 33, 64, 1000, (1 << 15) + 5])
+def test_gradient_of_ragged_batches(lib, B):
+    """Part-filled tiles, the padding to the step of the contraction, and a
+    batch that needs a second launch: against the oracle at the tolerances of
+    the full batch above, and the same bits from a second call (every sum is
+    in a fixed order)."""
+    rng = np.random.default_rng(B)
+    X = omlp.bf16(rng.uniform(-1, 1, size=(B, omlp.F)))
+    t = rng.standard_normal(B)
+    p = lib.mlp_init(seed=5, bias_out=-0.6).astype(np.float64)
+    args = dev(p, torch.float32), to_bits(X), dev(t, torch.float32)
+    g, loss = lib.mlp_grad(*args)
+    g2, loss2 = lib.mlp_grad(*args)
+    torch.cuda.synchronize()
+    assert torch.equal(g, g2) and torch.equal(loss, loss2)
+    lo, go = omlp.loss_and_grad(p, X, t, quantize=True)
+    assert abs(loss.item() - lo) / lo < 1e-3
+    err = np.linalg.norm(g.cpu().numpy().astype(np.float64) - go) / np.linalg.norm(go)
+    print(f"[mlp] gradient of {B} samples: {err:.1e}", flush=True)
+    assert err < 1e-2
+
+
+def test_training_step_is_adam_on_the_gradient(lib):
+    """One step from zero moments moves every parameter by lr g / (|g| + eps)
+    up to the rounding of the bias corrections, and the loss returned is the
+    batch's."""
+    B = 128
+    rng = np.random.default_rng(3)
+    X = np.tile(omlp.bf16(rng.uniform(-1, 1, size=(1, omlp.F))), (B, 1))  # every draw is the same sample
+    p0 = dev(lib.mlp_init(seed=5, bias_out=-0.6), torch.float32)
+    feats, t = to_bits(X), dev(np.full(B, 0.3), torch.float32)
+    g, loss = lib.mlp_grad(p0, feats, t)
+    net = lib.MLP(p0.clone())
+    losses = net.train(feats, t, steps=1, batch=B, lr=1e-3, seed=7)
+    torch.cuda.synchronize()
+    assert abs(losses[0].item() - loss.item()) <= 1e-5 * loss.item()
+    d = (net.params - p0).cpu().numpy().astype(np.float64)
+    gg = g.cpu().numpy().astype(np.float64)
+    big = np.abs(gg) > 1e-4  # eps = 1e-8 and the FP32 rounding of p are far below lr there
+    assert big.sum() > 1000
+    assert np.max(np.abs(d[big] + 1e-3 * np.sign(gg[big]))) < 1e-6
