@@ -171,3 +171,20 @@ def test_training_step_is_adam_on_the_gradient(lib):
     big = np.abs(gg) > 1e-4  # eps = 1e-8 and the FP32 rounding of p are far below lr there
     assert big.sum() > 1000
     assert np.max(np.abs(d[big] + 1e-3 * np.sign(gg[big]))) < 1e-6
+
+
+@pytest.mark.parametrize("N,n", [(2000, 2), (1999, 9), (2031, 33), (2033, 63), (2001, 64)])
+def test_fused_prediction_is_features_then_network(lib, N, n):
+    """Part-filled wavefronts and the narrowest and widest stencils: eps from
+    one kernel is exp(y) / rho of the separate features and forward calls, up
+    to the rounding of exp and the quotient (2 ulp each)."""
+    X, nrm = blob(N, seed=N)[:2]
+    idx = oracle_knn(X, n)
+    p = dev(lib.mlp_init(seed=5, bias_out=-0.6), torch.float32)
+    xyz, nv, ix = dev(X), dev(nrm), dev(idx, torch.int32)
+    feats, rho = lib.mlp_features(xyz, nv, ix)
+    y = lib.mlp_forward(p, feats)
+    eps = lib.MLP(p).predict_eps(xyz, nv, ix)
+    torch.cuda.synchronize()
+    want = np.exp(y.cpu().numpy().astype(np.float64)) / rho.cpu().numpy()
+    assert np.max(np.abs(eps.cpu().numpy() / want - 1)) < 4 * 2.3e-16
