@@ -219,76 +219,130 @@ __device__ __forceinline__ bool key_less(double da, int ia, double db, int ib) {
     return da < db || (da == db && ia < ib);
 }
 
-// Bitonic sort of the first S (power of two) entries of the wave's buffer.
-// Up to 128 entries: entries lane and lane + 64 in registers, exchanged across
-// the lanes (no barrier between the stages); up to 64 only the first half.
-// Entries S.. of the network are padding (+inf, INT_MAX) that sorts last, and
-// only the first S are written back.
-__device__ __forceinline__ void lane_exchange(double& v, int& x, int pos, int j, int k) {
-    const double ov = __shfl_xor(v, j, 64);
-    const int ox = __shfl_xor(x, j, 64);
-    const bool keep_min = ((pos & j) == 0) == ((pos & k) == 0);
-    const bool take = keep_min ? key_less(ov, ox, v, x) : key_less(v, x, ov, ox);
-    if (take) {
-        v = ov;
-        x = ox;
+// v of lane ^ M in registers (DPP within 16 lanes, the row swaps above), where
+// a shuffle is a trip through the LDS pipe.
+template <int M>
+__device__ __forceinline__ int lane_xor(int v) {
+    if constexpr (M == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);   // quad 1 0 3 2
+    else if constexpr (M == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);  // quad 2 3 0 1
+    else if constexpr (M == 4)  // mirror of 8, then of 4: 7 - (3 - ..)
+        return __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true), 0x1B, 0xf, 0xf,
+                                           true);
+    else if constexpr (M == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, true);  // row rotated by 8
+    else if constexpr (M == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return threadIdx.x & 16 ? r[0] : r[1];
+    } else {
+        static_assert(M == 32, "one bit");
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return threadIdx.x & 32 ? r[0] : r[1];
     }
 }
+template <int M>
+__device__ __forceinline__ double lane_xor(double v) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)lane_xor<M>((int)(uint32_t)u), hi = (uint32_t)lane_xor<M>((int)(u >> 32));
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// One step (pairs J apart, ascending where position & K is 0) of the sort below
+// on the entry at position lane + OFF.
+template <int J, int K, int OFF>
+__device__ __forceinline__ void lane_exchange(double& v, int& x) {
+    const double ov = lane_xor<J>(v);
+    const int ox = lane_xor<J>(x);
+    const int pos = threadIdx.x + OFF;
+    const bool keep_max = ((pos & J) == 0) != ((pos & K) == 0);
+    // equal entries (padding) may be taken either way
+    const bool take = ((ov < v) | ((ov == v) & (ox < x))) != keep_max;
+    v = take ? ov : v;
+    x = take ? ox : x;
+}
+template <int J, int K>
+__device__ __forceinline__ void merge64(double& v, int& x) {
+    lane_exchange<J, K, 0>(v, x);
+    if constexpr (J > 1) merge64<J / 2, K>(v, x);
+}
+// (distance, index) of the 64 lanes in ascending order
+template <int K = 2>
+__device__ __forceinline__ void sort64(double& v, int& x) {
+    merge64<K / 2, K>(v, x);
+    if constexpr (K < 64) sort64<2 * K>(v, x);
+}
+template <int J, int K>
+__device__ __forceinline__ void merge128(double& v0, int& x0, double& v1, int& x1) {
+    if constexpr (J == 64) {  // the pair (lane, lane + 64) is in one lane
+        if (key_less(v1, x1, v0, x0)) {
+            const double tv = v0;
+            const int tx = x0;
+            v0 = v1; x0 = x1;
+            v1 = tv; x1 = tx;
+        }
+    } else {
+        lane_exchange<J, K, 0>(v0, x0);
+        lane_exchange<J, K, 64>(v1, x1);
+    }
+    if constexpr (J > 1) merge128<J / 2, K>(v0, x0, v1, x1);
+}
+// 128 entries, lane and lane + 64
+template <int K = 2>
+__device__ __forceinline__ void sort128(double& v0, int& x0, double& v1, int& x1) {
+    merge128<K / 2, K>(v0, x0, v1, x1);
+    if constexpr (K < 128) sort128<2 * K>(v0, x0, v1, x1);
+}
+
+template <int J, int K>
+__device__ __forceinline__ void merge64(uint32_t& v) {
+    const uint32_t o = (uint32_t)lane_xor<J>((int)v);
+    const bool keep_max = ((threadIdx.x & J) == 0) != ((threadIdx.x & K) == 0);
+    v = keep_max ? max(v, o) : min(v, o);
+    if constexpr (J > 1) merge64<J / 2, K>(v);
+}
+template <int K = 2>
+__device__ __forceinline__ void sort64(uint32_t& v) {
+    merge64<K / 2, K>(v);
+    if constexpr (K < 64) sort64<2 * K>(v);
+}
+// The first `count` (<= 64) entries sorted, distances at most `top`.  Sorts
+// 26-bit steps of the distance with the lane below them, a quarter of the
+// instructions of the exact sort, and puts the entries in that order; only if
+// two entries share a step (or top is not a positive finite number) the exact
+// sort decides.
+__device__ __forceinline__ void sort_entries(double& v, int& x, int count, double top) {
+    const int lane = threadIdx.x;
+    const double scale = (double)((1 << 26) - 4) / top;
+    uint32_t k = lane < count ? (uint32_t)(v * scale) << 6 | (uint32_t)lane : 0xffffffffu;
+    sort64(k);
+    const uint32_t below = (uint32_t)__shfl_up((int)k, 1, 64);
+    const bool tie = lane > 0 && lane < count && (k >> 6) == (below >> 6);
+    if (__ballot(tie) != 0 || !(top > 0.0 && top < 1e300 && scale < 1e300)) {
+        sort64(v, x);
+        return;
+    }
+    const double sv = __shfl(v, (int)(k & 63), 64);
+    const int sx = __shfl(x, (int)(k & 63), 64);
+    v = lane < count ? sv : INFINITY;
+    x = lane < count ? sx : 0x7fffffff;
+}
+
+// Bitonic sort of the first S (power of two) entries of the wave's buffer, up
+// to 128 of them in registers.  Entries S.. of the network are padding (+inf,
+// INT_MAX) that sorts last, and only the first S are written back.
 __device__ void wave_bitonic(double* d2, int* id, int S) {
     const int lane = threadIdx.x;
-    if (S > 64 && S <= 128) {
-        double v0 = d2[lane], v1 = lane + 64 < S ? d2[lane + 64] : INFINITY;
-        int x0 = id[lane], x1 = lane + 64 < S ? id[lane + 64] : 0x7fffffff;
-#pragma unroll
-        for (int k = 2; k <= 128; k <<= 1) {
-#pragma unroll
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                if (j == 64) {  // the pair (lane, lane + 64) is in one lane
-                    const bool asc = (lane & k) == 0;
-                    const bool sw = asc ? key_less(v1, x1, v0, x0) : key_less(v0, x0, v1, x1);
-                    if (sw) {
-                        const double tv = v0;
-                        const int tx = x0;
-                        v0 = v1; x0 = x1;
-                        v1 = tv; x1 = tx;
-                    }
-                } else {
-                    lane_exchange(v0, x0, lane, j, k);
-                    lane_exchange(v1, x1, lane + 64, j, k);
-                }
-            }
-        }
+    if (S <= 128) {
+        double v0 = lane < S ? d2[lane] : INFINITY, v1 = lane + 64 < S ? d2[lane + 64] : INFINITY;
+        int x0 = lane < S ? id[lane] : 0x7fffffff, x1 = lane + 64 < S ? id[lane + 64] : 0x7fffffff;
+        if (S <= 64) sort64(v0, x0);
+        else sort128(v0, x0, v1, x1);
         __syncthreads();  // every lane has read its entries
-        d2[lane] = v0;
-        id[lane] = x0;
+        if (lane < S) {
+            d2[lane] = v0;
+            id[lane] = x0;
+        }
         if (lane + 64 < S) {
             d2[lane + 64] = v1;
             id[lane + 64] = x1;
-        }
-        __syncthreads();
-        return;
-    }
-    if (S <= 64) {
-        double v = lane < S ? d2[lane] : INFINITY;
-        int x = lane < S ? id[lane] : 0x7fffffff;
-#pragma unroll
-        for (int k = 2; k <= 64; k <<= 1) {
-#pragma unroll
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                const double ov = __shfl_xor(v, j, 64);
-                const int ox = __shfl_xor(x, j, 64);
-                const bool keep_min = ((lane & j) == 0) == ((lane & k) == 0);
-                const bool take = keep_min ? key_less(ov, ox, v, x) : key_less(v, x, ov, ox);
-                if (take) {
-                    v = ov;
-                    x = ox;
-                }
-            }
-        }
-        __syncthreads();  // every lane has read its entry
-        if (lane < S) {
-            d2[lane] = v;
-            id[lane] = x;
         }
         __syncthreads();
         return;
@@ -403,15 +457,61 @@ __device__ int prefilter(double* cd, int* cid, int cnt, int need) {
     return kept;
 }
 
-// One 64-lane workgroup per query position p (spatial order).
+// d rounded up to float, as bits (d >= 0: they compare like the numbers)
+__device__ __forceinline__ uint32_t round_up_bits(double d) {
+    const float f = (float)d;
+    return __float_as_uint(f) + ((double)f < d ? 1u : 0u);
+}
+
+// A threshold T with `need` <= count(key <= T) for keys that hold positive
+// floats, and count <= limit unless equal keys forbid it.  On a surface the
+// count grows about in proportion to the squared distance, so guesses follow
+// the last count (two or three as a rule); after eight, bisection of the bits.
+template <int NC>
+__device__ __forceinline__ uint32_t select_bits(const uint32_t (&key)[NC], float guess, int need, int limit, int cnt,
+                                                int& kept) {
+    uint32_t lo = 0, hi = 0x7f800000u;  // the answer is in (lo, hi]
+    kept = cnt;
+    float t = guess;
+    for (int it = 0; hi - lo > 1 && kept > limit; ++it) {
+        uint32_t b = __builtin_amdgcn_readfirstlane(__float_as_uint(t));
+        if (it >= 8 || b <= lo || b >= hi) b = lo + ((hi - lo) >> 1);
+        int c = 0;
+#pragma unroll
+        for (int q = 0; q < NC; ++q) c += __popcll(__ballot(key[q] <= b));
+        if (c < need) {
+            lo = b;
+        } else {
+            hi = b;
+            kept = c;
+        }
+        t = __uint_as_float(b) * ((0.5f * (float)(need + limit)) / (float)(c > 0 ? c : 1));
+    }
+    return hi;
+}
+
+template <int CTRL>
+__device__ __forceinline__ int dpp_or_zero(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
+}
+
+// One wavefront per query position p (spatial order; each XCD takes one
+// contiguous range).  The candidates of the 27 cells around the query are
+// taken at once when they are at most 64 NC: keys of all of them in registers,
+// a threshold that leaves few more than are needed, and only those are sorted.
+// More candidates, and shells further out, go through a list in LDS.
+template <int NC>
 __global__ __launch_bounds__(64) void k_knn(int64_t N, int n, Grid G, const double* __restrict__ xs,
                                              const double* __restrict__ ys, const double* __restrict__ zs,
                                              const int32_t* __restrict__ order, const int32_t* __restrict__ start,
                                              int32_t* __restrict__ idx_out) {
     __shared__ double cd[KNN_CAP];
     __shared__ int cid[KNN_CAP];
+    __shared__ int cstart[27], cexcl[27], delta[27];
+    __shared__ uint64_t mark[NC];
     const int lane = threadIdx.x;
-    const int64_t p = blockIdx.x;
+    const int64_t nb = gridDim.x, bx = blockIdx.x & 7, rem = nb & 7;
+    const int64_t p = bx * (nb >> 3) + (bx < rem ? bx : rem) + (blockIdx.x >> 3);
     if (p >= N) return;
     const double qx = xs[p], qy = ys[p], qz = zs[p];
     const int q = order[p];
@@ -461,11 +561,24 @@ __global__ __launch_bounds__(64) void k_knn(int64_t N, int n, Grid G, const doub
         cnt += add;
         __syncthreads();
     };
-    // After the shells up to R: sort, bound, and stop once the searched box
-    // provably holds the `need` nearest (or covers the whole grid).
+    auto covers = [&](int R) {
+        return (cx - R <= 0) && (cy - R <= 0) && (cz - R <= 0) && (cx + R >= G.g[0] - 1) && (cy + R >= G.g[1] - 1) &&
+               (cz + R >= G.g[2] - 1);
+    };
+    // With the need-th best distance known: stop once the box of the shells up
+    // to R provably holds the `need` nearest (or covers the whole grid).
+    auto finish = [&](int R) {
+        double r_safe = INFINITY;
+        const double q3[3] = {qx, qy, qz};
+        const int c3[3] = {cx, cy, cz};
+        for (int d = 0; d < 3; ++d) {
+            if (c3[d] - R > 0) r_safe = fmin(r_safe, q3[d] - (G.lo[d] + (c3[d] - R) * G.h));
+            if (c3[d] + R < G.g[d] - 1) r_safe = fmin(r_safe, (G.lo[d] + (c3[d] + R + 1) * G.h) - q3[d]);
+        }
+        if (covers(R) || (r_safe > 0 && bound < r_safe * r_safe * (1.0 - 1e-12))) done = true;
+    };
+    // After the shells up to R: sort and bound.
     auto settle = [&](int R) {
-        bool covers = (cx - R <= 0) && (cy - R <= 0) && (cz - R <= 0) && (cx + R >= G.g[0] - 1) &&
-                      (cy + R >= G.g[1] - 1) && (cz + R >= G.g[2] - 1);
         if (cnt >= need) {
             if (need <= 64 && cnt > 128) cnt = prefilter<1>(cd, cid, cnt, need);
             else if (need <= 128 && cnt > 256) cnt = prefilter<2>(cd, cid, cnt, need);
@@ -473,24 +586,30 @@ __global__ __launch_bounds__(64) void k_knn(int64_t N, int n, Grid G, const doub
             // leaves at most 64 (128) to sort
             if (need <= 64 && cnt > 64) cnt = prefilter<1>(cd, cid, cnt, need);
             else if (need <= 128 && cnt > 128) cnt = prefilter<2>(cd, cid, cnt, need);
-            int S = next_pow2(cnt);
-            for (int t = cnt + lane; t < S; t += 64) {
-                cd[t] = INFINITY;
-                cid[t] = 0x7fffffff;
+            if (cnt <= 64) {
+                __syncthreads();
+                double v = lane < cnt ? cd[lane] : INFINITY;
+                int x = lane < cnt ? cid[lane] : 0x7fffffff;
+                sort_entries(v, x, cnt, bound);  // none is above a finite bound
+                __syncthreads();
+                if (lane < need) {
+                    cd[lane] = v;
+                    cid[lane] = x;
+                }
+                __syncthreads();
+            } else {
+                int S = next_pow2(cnt);
+                for (int t = cnt + lane; t < S; t += 64) {
+                    cd[t] = INFINITY;
+                    cid[t] = 0x7fffffff;
+                }
+                __syncthreads();
+                wave_bitonic(cd, cid, S);
             }
-            __syncthreads();
-            wave_bitonic(cd, cid, S);
             cnt = need;
             bound = cd[need - 1];
-            double r_safe = INFINITY;
-            const double q3[3] = {qx, qy, qz};
-            const int c3[3] = {cx, cy, cz};
-            for (int d = 0; d < 3; ++d) {
-                if (c3[d] - R > 0) r_safe = fmin(r_safe, q3[d] - (G.lo[d] + (c3[d] - R) * G.h));
-                if (c3[d] + R < G.g[d] - 1) r_safe = fmin(r_safe, (G.lo[d] + (c3[d] + R + 1) * G.h) - q3[d]);
-            }
-            if (covers || (r_safe > 0 && bound < r_safe * r_safe * (1.0 - 1e-12))) done = true;
-        } else if (covers) {
+            finish(R);
+        } else if (covers(R)) {
             done = true;  // cannot happen when n <= N
         }
     };
@@ -507,53 +626,171 @@ __global__ __launch_bounds__(64) void k_knn(int64_t N, int n, Grid G, const doub
                 c0 = start[k + 1] - s0;
             }
         }
-        // inclusive prefix sum of the counts over the wave
+        // inclusive prefix sum of the counts (lanes 27.. hold none)
         int incl = c0;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += v;
-        }
-        const int total = __shfl(incl, 63, 64);
-        __shared__ int cstart[27], cexcl[28];
-        if (lane < 27) {
-            cstart[lane] = s0;
-            cexcl[lane] = incl - c0;
-        }
-        if (lane == 0) cexcl[27] = total;
+        incl += dpp_or_zero<0x111>(incl);  // from 1, 2, 4 and 8 lanes below in the row of 16
+        incl += dpp_or_zero<0x112>(incl);
+        incl += dpp_or_zero<0x114>(incl);
+        incl += dpp_or_zero<0x118>(incl);
+        const int row0 = __builtin_amdgcn_readlane(incl, 15);
+        if (lane & 16) incl += row0;
+        const int total = __builtin_amdgcn_readlane(incl, 31), excl = incl - c0;
+        // position t of the list is point t + delta[r] of the r-th cell that is
+        // not empty; r follows from the bits set where the cells begin
+        const uint64_t used = __ballot(c0 > 0);
+        if (lane < NC) mark[lane] = 0;
         __syncthreads();
-        for (int b = 0; b < total; b += 64) {
-            const int t = b + lane;
-            int j = 0;
-            if (t < total) {
-                int lo = 0, hi = 26;  // the cell whose exclusive prefix is the last <= t
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (cexcl[mid] <= t) lo = mid;
-                    else hi = mid - 1;
-                }
-                j = cstart[lo] + (t - cexcl[lo]);
-            }
-            consider(j, t < total);
+        if (c0 > 0) {
+            delta[__builtin_amdgcn_mbcnt_hi((uint32_t)(used >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)used, 0))] =
+                s0 - excl;
+            if (excl < 64 * NC) atomicOr((unsigned long long*)&mark[excl >> 6], 1ull << (excl & 63));
         }
-        settle(1);
-    }
-    for (int R = 2; !done; ++R) {
-        // the shell of cells at Chebyshev distance R from the query's cell
-        for (int dx = -R; dx <= R; ++dx) {
-            int ix = cx + dx;
-            if (ix < 0 || ix >= G.g[0]) continue;
-            for (int dy = -R; dy <= R; ++dy) {
-                int iy = cy + dy;
-                if (iy < 0 || iy >= G.g[1]) continue;
-                bool edge_xy = (dx == -R || dx == R || dy == -R || dy == R);
-                for (int dz = -R; dz <= R; dz += (edge_xy ? 1 : 2 * R)) {
-                    int iz = cz + dz;
-                    if (iz >= 0 && iz < G.g[2]) {
-                        uint32_t k = morton3(ix, iy, iz);
-                        int s = start[k], e = start[k + 1];
-                        for (int b = s; b < e; b += 64) consider(b + lane, b + lane < e);
+        __syncthreads();
+        bool taken = false;
+        if (total <= 64 * NC && total > need) {
+            const int chunks = (total + 63) >> 6, found = total - 1, limit = need <= 64 ? 64 : 128;
+            uint32_t key[NC];
+            int at[NC], before = -1;
+            double x[NC], y[NC], z[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                if (c < chunks) {
+                    const uint64_t m = mark[c];
+                    const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)m);
+                    const uint32_t m1 = __builtin_amdgcn_readfirstlane((uint32_t)(m >> 32));
+                    const uint64_t w = (uint64_t)m1 << 32 | m0, v = w >> 1;
+                    // cells that begin at or before the lane's position
+                    const int r = before + (int)(w & 1) +
+                                  (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(v >> 32),
+                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)v, 0));
+                    before += __popcll(w);
+                    const int t = 64 * c + lane;
+                    at[c] = (t < total ? t : total - 1) + delta[r];
+                    x[c] = xs[at[c]];
+                    y[c] = ys[at[c]];
+                    z[c] = zs[at[c]];
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                key[c] = 0xffffffffu;
+                if (c < chunks) {
+                    const double ddx = x[c] - qx, ddy = y[c] - qy, ddz = z[c] - qz;
+                    const uint32_t u = round_up_bits((ddx * ddx + ddy * ddy) + ddz * ddz);
+                    if (64 * c + lane < total && at[c] != (int)p) key[c] = u;
+                }
+            }
+            int kept;
+            // about the area of the block over its candidates, times the number wanted
+            const float guess = (float)(G.h * G.h) * (9.0f / 3.1416f) * 0.5f * (float)(need + limit) / (float)found;
+            const uint32_t T = select_bits<NC>(key, guess, need, limit, found, kept);
+            if (kept <= limit) {
+                taken = true;
+                int base = 0;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    if (c < chunks) {
+                        const bool keep = key[c] <= T;
+                        const uint64_t m = __ballot(keep);
+                        if (keep)
+                            cid[base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] = at[c];
+                        base += __popcll(m);
                     }
                 }
+                __syncthreads();
+                double v[2] = {INFINITY, INFINITY};
+                int id[2] = {0x7fffffff, 0x7fffffff};
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (64 * h + lane < kept) {
+                        const int j = cid[64 * h + lane];
+                        const double ddx = xs[j] - qx, ddy = ys[j] - qy, ddz = zs[j] - qz;
+                        v[h] = (ddx * ddx + ddy * ddy) + ddz * ddz;
+                        id[h] = order[j];
+                    }
+                }
+                if (kept <= 64) sort_entries(v[0], id[0], kept, (double)__uint_as_float(T));
+                else sort128(v[0], id[0], v[1], id[1]);
+                __syncthreads();
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (64 * h + lane < need) {
+                        cd[64 * h + lane] = v[h];
+                        cid[64 * h + lane] = id[h];
+                    }
+                }
+                cnt = need;
+                __syncthreads();
+                bound = cd[need - 1];
+                finish(1);
+            }
+        }
+        if (!taken) {
+            if (lane < 27) {
+                cstart[lane] = s0;
+                cexcl[lane] = excl;
+            }
+            __syncthreads();
+            for (int b = 0; b < total; b += 64) {
+                const int t = b + lane;
+                int j = 0;
+                if (t < total) {
+                    int lo = 0, hi = 26;  // the cell whose exclusive prefix is the last <= t
+                    while (lo < hi) {
+                        const int mid = (lo + hi + 1) >> 1;
+                        if (cexcl[mid] <= t) lo = mid;
+                        else hi = mid - 1;
+                    }
+                    j = cstart[lo] + (t - cexcl[lo]);
+                }
+                consider(j, t < total);
+            }
+            settle(1);
+        }
+    }
+    for (int R = 2; !done; ++R) {
+        // the shell of cells at Chebyshev distance R from the query's cell, one
+        // per lane: the faces z = -R and R, then the rings between them.  Cells
+        // further away than the bound are left out (distances relative to the
+        // grid's origin, as the cells were assigned; slack for their rounding).
+        const int side = 2 * R + 1, face = side * side, shell = 2 * face + (side - 2) * 8 * R;
+        for (int b = 0; b < shell; b += 64) {
+            int t = b + lane, dx, dy, dz;
+            const bool in_shell = t < shell;
+            if (t < 2 * face) {
+                dz = t < face ? -R : R;
+                t -= t < face ? 0 : face;
+                dx = t % side - R;
+                dy = t / side - R;
+            } else {
+                t -= 2 * face;
+                dz = t / (8 * R) - (R - 1);
+                t %= 8 * R;
+                const int edge = t / (2 * R), v = t % (2 * R);
+                dx = edge == 0 ? v - R : (edge == 2 ? R - v : (edge == 1 ? R : -R));
+                dy = edge == 1 ? v - R : (edge == 3 ? R - v : (edge == 2 ? R : -R));
+            }
+            const int ix = cx + dx, iy = cy + dy, iz = cz + dz;
+            int s0 = 0, c0 = 0;
+            if (in_shell && ix >= 0 && ix < G.g[0] && iy >= 0 && iy < G.g[1] && iz >= 0 && iz < G.g[2]) {
+                auto gap = [&](double q, double lo, int c, int g) {
+                    const double u = q - lo;
+                    const double d = fmax(c * G.h - u, c < g - 1 ? u - (c + 1) * G.h : 0.0) - 1e-9 * G.h;
+                    return fmax(d, 0.0);
+                };
+                const double gx = gap(qx, G.lo[0], ix, G.g[0]), gy = gap(qy, G.lo[1], iy, G.g[1]),
+                             gz = gap(qz, G.lo[2], iz, G.g[2]);
+                if ((gx * gx + gy * gy + gz * gz) * (1.0 - 1e-12) <= bound) {
+                    const uint32_t k = morton3(ix, iy, iz);
+                    s0 = start[k];
+                    c0 = start[k + 1] - s0;
+                }
+            }
+            for (uint64_t left = __ballot(c0 > 0); left; left &= left - 1) {
+                const int from = __builtin_ctzll(left);
+                const int s = __builtin_amdgcn_readlane(s0, from), e = s + __builtin_amdgcn_readlane(c0, from);
+                for (int a = s; a < e; a += 64) consider(a + lane, a + lane < e);
             }
         }
         settle(R);
@@ -645,7 +882,9 @@ int knn_internal(rbffd_ctx ctx, int64_t N, const double* xyz, int32_t n, int32_t
     hipLaunchKernelGGL(k_cell_sort, dim3(gN), dim3(B), 0, st, N, key, start, order);
     hipLaunchKernelGGL(k_gather_sorted, dim3(gN), dim3(B), 0, st, N, xyz, order, xs, ys, zs);
     if (idx) {
-        hipLaunchKernelGGL(k_knn, dim3((unsigned)N), dim3(64), 0, st, N, n, G, xs, ys, zs, order, start, idx);
+        // the 27 cells hold about 8.6 n candidates
+        const auto kernel = n <= 56 ? k_knn<8> : (n <= 84 ? k_knn<12> : k_knn<18>);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)N), dim3(64), 0, st, N, n, G, xs, ys, zs, order, start, idx);
     }
     HIP_TRY(ctx, hipGetLastError());
     return RBFFD_OK;
