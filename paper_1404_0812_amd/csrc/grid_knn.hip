@@ -6,8 +6,9 @@
 //      of their integer coordinates,
 //   3. counting sort of nodes by cell key (stable within a cell by node index),
 //      which also yields the spatial order used by the sparse operator,
-//   4. one wavefront per query: expanding shells of cells, candidates in LDS,
-//      bitonic sort by (squared distance, index), stop once the n-1-th best
+//   4. one wavefront per query: the candidates of the 27 cells around it in
+//      registers, cut to few more than n - 1 by a threshold and sorted by
+//      (squared distance, index); then shells of cells until the n-1-th best
 //      distance is inside the searched box.
 // Squared distances are ((dx*dx + dy*dy) + dz*dz) in FP64 with contraction
 // disabled, so the order (and ties, broken by node index) is exact.
@@ -24,13 +25,11 @@ namespace {
 #ifndef KNN_CELL_SCALE
 #define KNN_CELL_SCALE 1.0  // cell edge relative to the expected stencil radius
 #endif
-// Candidate buffer per query (entries; a power of two for the bitonic sort).
-// At least need + 64 = 191 for n <= 128, so that a chunk fits after a cut.
-// 512 holds the ~430 candidates of the 27 cells at n = 50 without a cut and
-// keeps the LDS per query at 6 KB: the search is latency-bound, and 1024
-// entries (12 KB) let half as many queries run per CU (7.5 vs 4.9 ms at
-// N = 1e6, n = 50; 17.5 vs 10.9 ms at n = 101); 256 cuts every n = 101 query
-// at least once (14.4 ms).
+// Candidate list per query in LDS (entries; a power of two for the bitonic
+// sort), for shells past the first block and blocks with more candidates than
+// the registers take.  At least need + 64 = 191 for n <= 128, so that a chunk
+// fits after a cut.  512 leaves room for 24 queries per CU; their registers
+// allow 28.
 constexpr int KNN_CAP = 512;
 static_assert(KNN_CAP >= 127 + 64 && (KNN_CAP & (KNN_CAP - 1)) == 0, "candidate buffer");
 constexpr int MAX_BITS = 9;    // Morton bits per axis (2^27 cells at most)
@@ -88,16 +87,20 @@ __global__ void k_bbox_partial(int64_t N, const double* __restrict__ xyz, double
     if (threadIdx.x < 6) part[blockIdx.x * 6 + threadIdx.x] = s[threadIdx.x][0];
 }
 
-__global__ void k_bbox_final(int nblk, const double* __restrict__ part, double* __restrict__ out) {
-    if (threadIdx.x < 6) {
-        int d = threadIdx.x;
-        double v = d < 3 ? INFINITY : -INFINITY;
-        for (int b = 0; b < nblk; ++b) {
-            double p = part[b * 6 + d];
-            v = d < 3 ? fmin(v, p) : fmax(v, p);
-        }
-        out[d] = v;
+// One wavefront per bound (a serial pass over 256 partials took 36 us).
+__global__ __launch_bounds__(384) void k_bbox_final(int nblk, const double* __restrict__ part,
+                                                    double* __restrict__ out) {
+    const int d = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double v = d < 3 ? INFINITY : -INFINITY;
+    for (int b = lane; b < nblk; b += 64) {
+        const double p = part[b * 6 + d];
+        v = d < 3 ? fmin(v, p) : fmax(v, p);
     }
+    for (int o = 32; o > 0; o >>= 1) {
+        const double p = __shfl_xor(v, o, 64);
+        v = d < 3 ? fmin(v, p) : fmax(v, p);
+    }
+    if (lane == 0) out[d] = v;
 }
 
 __global__ void k_cell_keys(int64_t N, const double* __restrict__ xyz, Grid G, uint32_t* __restrict__ key,
@@ -117,102 +120,132 @@ constexpr int SCAN_BLOCK = 256;
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_TILE = SCAN_BLOCK * SCAN_ITEMS;
 
+// sh: SCAN_BLOCK / 64 words
 __device__ int block_exclusive_scan(int v, int* sh, int* total) {
-    int lane = threadIdx.x;
-    sh[lane] = v;
-    __syncthreads();
-    for (int off = 1; off < SCAN_BLOCK; off <<= 1) {
-        int t = lane >= off ? sh[lane - off] : 0;
-        __syncthreads();
-        sh[lane] += t;
-        __syncthreads();
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int incl = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += t;
     }
-    int incl = sh[lane];
-    *total = sh[SCAN_BLOCK - 1];
+    if (lane == 63) sh[wv] = incl;
     __syncthreads();
-    return incl - v;
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < SCAN_BLOCK / 64; ++w) {
+        before += w < wv ? sh[w] : 0;
+        all += sh[w];
+    }
+    *total = all;
+    __syncthreads();
+    return before + incl - v;
 }
 
 __global__ void k_scan_tiles(int64_t K, const int32_t* __restrict__ in, int32_t* __restrict__ out,
                              int32_t* __restrict__ tile_sums) {
-    __shared__ int sh[SCAN_BLOCK];
-    int64_t base = blockIdx.x * (int64_t)SCAN_TILE + threadIdx.x * SCAN_ITEMS;
+    __shared__ int sh[SCAN_BLOCK / 64];
+    static_assert(SCAN_ITEMS == 8, "two vectors");
+    const int64_t base = blockIdx.x * (int64_t)SCAN_TILE + threadIdx.x * SCAN_ITEMS;
+    const bool whole = base + SCAN_ITEMS <= K;
     int v[SCAN_ITEMS];
-    int s = 0;
-    for (int t = 0; t < SCAN_ITEMS; ++t) {
-        int64_t i = base + t;
-        v[t] = i < K ? in[i] : 0;
-        s += v[t];
+    if (whole) {
+        *reinterpret_cast<int4*>(v) = *reinterpret_cast<const int4*>(in + base);
+        *reinterpret_cast<int4*>(v + 4) = *reinterpret_cast<const int4*>(in + base + 4);
+    } else {
+#pragma unroll
+        for (int t = 0; t < SCAN_ITEMS; ++t) v[t] = base + t < K ? in[base + t] : 0;
     }
+    int s = 0;
+#pragma unroll
+    for (int t = 0; t < SCAN_ITEMS; ++t) s += v[t];
     int tot;
     int ex = block_exclusive_scan(s, sh, &tot);
+#pragma unroll
     for (int t = 0; t < SCAN_ITEMS; ++t) {
-        int64_t i = base + t;
-        if (i < K) out[i] = ex;
-        ex += v[t];
+        const int c = v[t];
+        v[t] = ex;
+        ex += c;
+    }
+    if (whole) {
+        *reinterpret_cast<int4*>(out + base) = *reinterpret_cast<const int4*>(v);
+        *reinterpret_cast<int4*>(out + base + 4) = *reinterpret_cast<const int4*>(v + 4);
+    } else {
+#pragma unroll
+        for (int t = 0; t < SCAN_ITEMS; ++t)
+            if (base + t < K) out[base + t] = v[t];
     }
     if (threadIdx.x == 0) tile_sums[blockIdx.x] = tot;
 }
 
-// single block: exclusive scan of the tile sums (sequential chunks of 256)
+// single block: exclusive scan of the tile sums (sequential chunks of SCAN_TILE)
 __global__ void k_scan_sums(int ntiles, int32_t* __restrict__ sums, int32_t* __restrict__ grand) {
-    __shared__ int sh[SCAN_BLOCK];
+    __shared__ int sh[SCAN_BLOCK / 64];
     int carry = 0;
-    for (int b = 0; b < ntiles; b += SCAN_BLOCK) {
-        int i = b + threadIdx.x;
-        int v = i < ntiles ? sums[i] : 0;
+    for (int b = 0; b < ntiles; b += SCAN_TILE) {
+        const int i0 = b + (int)threadIdx.x * SCAN_ITEMS;
+        int v[SCAN_ITEMS], sum = 0;
+#pragma unroll
+        for (int t = 0; t < SCAN_ITEMS; ++t) {
+            v[t] = i0 + t < ntiles ? sums[i0 + t] : 0;
+            sum += v[t];
+        }
         int tot;
-        int ex = block_exclusive_scan(v, sh, &tot);
-        if (i < ntiles) sums[i] = ex + carry;
+        int ex = block_exclusive_scan(sum, sh, &tot) + carry;
+#pragma unroll
+        for (int t = 0; t < SCAN_ITEMS; ++t) {
+            if (i0 + t < ntiles) sums[i0 + t] = ex;
+            ex += v[t];
+        }
         carry += tot;
+        __syncthreads();
     }
     if (threadIdx.x == 0) *grand = carry;
 }
 
 __global__ void k_scan_add(int64_t K, int32_t* __restrict__ out, const int32_t* __restrict__ sums) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < K) out[i] += sums[i / SCAN_TILE];
-}
-
-__global__ void k_scatter(int64_t N, const uint32_t* __restrict__ key, const int32_t* __restrict__ start,
-                          int32_t* __restrict__ fill, int32_t* __restrict__ order) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    uint32_t k = key[i];
-    int pos = start[k] + atomicAdd(&fill[k], 1);
-    order[pos] = (int32_t)i;
-}
-
-// Sort each cell's nodes by index (insertion sort; cells hold a few dozen nodes).
-// One thread per sorted position; the first position of each cell does the work.
-__global__ void k_cell_sort(int64_t N, const uint32_t* __restrict__ key, const int32_t* __restrict__ start,
-                            int32_t* __restrict__ order) {
-    int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (p >= N) return;
-    uint32_t k = key[order[p]];
-    // `order` is being permuted within cells only, so the key of any member of
-    // the cell is k; the cell begins at start[k]
-    if (start[k] != p) return;
-    int e = start[k + 1];
-    for (int a = (int)p + 1; a < e; ++a) {
-        int v = order[a];
-        int b = a - 1;
-        while (b >= (int)p && order[b] > v) {
-            order[b + 1] = order[b];
-            --b;
-        }
-        order[b + 1] = v;
+    const int64_t base = blockIdx.x * (int64_t)SCAN_TILE + threadIdx.x * SCAN_ITEMS;
+    const int32_t s = sums[blockIdx.x];
+    if (base + SCAN_ITEMS <= K) {
+        int4* o = reinterpret_cast<int4*>(out + base);
+        const int4 a = o[0], b = o[1];
+        o[0] = make_int4(a.x + s, a.y + s, a.z + s, a.w + s);
+        o[1] = make_int4(b.x + s, b.y + s, b.z + s, b.w + s);
+    } else {
+        for (int64_t i = base; i < K; ++i) out[i] += s;
     }
 }
 
-__global__ void k_gather_sorted(int64_t N, const double* __restrict__ xyz, const int32_t* __restrict__ order,
-                                double* __restrict__ xs, double* __restrict__ ys, double* __restrict__ zs) {
+// Each node into some place of its cell; uses up the counts.
+__global__ void k_scatter(int64_t N, const uint32_t* __restrict__ key, const int32_t* __restrict__ start,
+                          int32_t* __restrict__ cnt, int32_t* __restrict__ placed) {
+    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= N) return;
+    uint32_t k = key[i];
+    placed[start[k] + atomicSub(&cnt[k], 1) - 1] = (int32_t)i;
+}
+
+// The nodes of a cell in index order: a node's place is the number of smaller
+// indices in its cell (cells hold a few dozen nodes; one thread per cell
+// sorting by insertion took 19 us at N = 1e5 and 45 at 1e6, and the
+// coordinates another kernel).
+__global__ void k_place(int64_t N, const uint32_t* __restrict__ key, const int32_t* __restrict__ start,
+                        const int32_t* __restrict__ placed, const double* __restrict__ xyz,
+                        int32_t* __restrict__ order, double* __restrict__ xs, double* __restrict__ ys,
+                        double* __restrict__ zs) {
     int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (p >= N) return;
-    int i = order[p];
-    xs[p] = xyz[3 * (int64_t)i + 0];
-    ys[p] = xyz[3 * (int64_t)i + 1];
-    zs[p] = xyz[3 * (int64_t)i + 2];
+    const int i = placed[p];
+    const uint32_t k = key[i];
+    const double x = xyz[3 * (int64_t)i], y = xyz[3 * (int64_t)i + 1], z = xyz[3 * (int64_t)i + 2];
+    const int s = start[k], e = start[k + 1];
+    int at = s;
+#pragma unroll 4
+    for (int q = s; q < e; ++q) at += placed[q] < i;
+    order[at] = i;
+    xs[at] = x;
+    ys[at] = y;
+    zs[at] = z;
 }
 
 __device__ __forceinline__ bool key_less(double da, int ia, double db, int ib) {
@@ -496,7 +529,8 @@ __device__ __forceinline__ int dpp_or_zero(int v) {
 }
 
 // One wavefront per query position p (spatial order; each XCD takes one
-// contiguous range).  The candidates of the 27 cells around the query are
+// contiguous range).  Bound by vector instructions: 950 per query at N = 1e6, n =
+// 50 keep the units busy for 86 % of 1.8 ms.  The candidates of the 27 cells around the query are
 // taken at once when they are at most 64 NC: keys of all of them in registers,
 // a threshold that leaves few more than are needed, and only those are sorted.
 // More candidates, and shells further out, go through a list in LDS.
@@ -811,7 +845,7 @@ int knn_internal(rbffd_ctx ctx, int64_t N, const double* xyz, int32_t n, int32_t
     double* part = (double*)ctx->scratch;
     double* bb = part + nblk_bbox * 6;
     hipLaunchKernelGGL(k_bbox_partial, dim3(nblk_bbox), dim3(256), 0, st, N, xyz, part);
-    hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(64), 0, st, nblk_bbox, part, bb);
+    hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(384), 0, st, nblk_bbox, part, bb);
     double hb[6];
     HIP_TRY(ctx, hipMemcpyAsync(hb, bb, sizeof(hb), hipMemcpyDeviceToHost, st));
     HIP_TRY(ctx, hipStreamSynchronize(st));
@@ -851,7 +885,7 @@ int knn_internal(rbffd_ctx ctx, int64_t N, const double* xyz, int32_t n, int32_t
     size_t o_key = take(N * sizeof(uint32_t));
     size_t o_cnt = take((K + 1) * sizeof(int32_t));
     size_t o_start = take((K + 1) * sizeof(int32_t));
-    size_t o_fill = take((K + 1) * sizeof(int32_t));
+    size_t o_placed = take(N * sizeof(int32_t));
     size_t o_sums = take((ntiles + 1) * sizeof(int32_t));
     size_t o_order = take(N * sizeof(int32_t));
     size_t o_xs = take(N * sizeof(double));
@@ -863,7 +897,7 @@ int knn_internal(rbffd_ctx ctx, int64_t N, const double* xyz, int32_t n, int32_t
     uint32_t* key = (uint32_t*)(base + o_key);
     int32_t* cnt = (int32_t*)(base + o_cnt);
     int32_t* start = (int32_t*)(base + o_start);
-    int32_t* fill = (int32_t*)(base + o_fill);
+    int32_t* placed = (int32_t*)(base + o_placed);
     int32_t* sums = (int32_t*)(base + o_sums);
     int32_t* order = perm ? perm : (int32_t*)(base + o_order);
     double* xs = (double*)(base + o_xs);
@@ -871,16 +905,14 @@ int knn_internal(rbffd_ctx ctx, int64_t N, const double* xyz, int32_t n, int32_t
     double* zs = (double*)(base + o_zs);
 
     HIP_TRY(ctx, hipMemsetAsync(cnt, 0, (K + 1) * sizeof(int32_t), st));
-    HIP_TRY(ctx, hipMemsetAsync(fill, 0, (K + 1) * sizeof(int32_t), st));
     const int B = 256;
     int gN = (int)((N + B - 1) / B);
     hipLaunchKernelGGL(k_cell_keys, dim3(gN), dim3(B), 0, st, N, xyz, G, key, cnt);
     hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)ntiles), dim3(SCAN_BLOCK), 0, st, K + 1, cnt, start, sums);
     hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(SCAN_BLOCK), 0, st, (int)ntiles, sums, sums + ntiles);
-    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((K + 1 + B - 1) / B)), dim3(B), 0, st, K + 1, start, sums);
-    hipLaunchKernelGGL(k_scatter, dim3(gN), dim3(B), 0, st, N, key, start, fill, order);
-    hipLaunchKernelGGL(k_cell_sort, dim3(gN), dim3(B), 0, st, N, key, start, order);
-    hipLaunchKernelGGL(k_gather_sorted, dim3(gN), dim3(B), 0, st, N, xyz, order, xs, ys, zs);
+    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)ntiles), dim3(SCAN_BLOCK), 0, st, K + 1, start, sums);
+    hipLaunchKernelGGL(k_scatter, dim3(gN), dim3(B), 0, st, N, key, start, cnt, placed);
+    hipLaunchKernelGGL(k_place, dim3(gN), dim3(B), 0, st, N, key, start, placed, xyz, order, xs, ys, zs);
     if (idx) {
         // the 27 cells hold about 8.6 n candidates
         const auto kernel = n <= 56 ? k_knn<8> : (n <= 84 ? k_knn<12> : k_knn<18>);
