@@ -1281,9 +1281,8 @@ constexpr int KRYLOV_BATCH = 8;
 // Block partials that a kernel sums by itself, two loads per thread of a block
 // of four wavefronts; with as many slices or fewer the blocks are single
 // wavefronts, on four times as many CUs (five steps at N = 10242 6.3 -> 5.7 ms).
-// More are
-// first summed by a kernel of one block, whose launch (2 us) then costs less
-// than all of them read by every block of the next kernel.
+// More are first summed by a kernel of one block, whose launch (2 us) then
+// costs less than all of them read by every block of the next kernel.
 constexpr int PART_DIRECT = 512;
 
 struct HistPtrs {
@@ -1512,12 +1511,11 @@ __global__ __launch_bounds__(256) void k_kry_begin(const double2* __restrict__ p
 // from the vectors of the kernel before while it is gathered, so neither is a
 // pass of its own; scalars are formed from the block partials by every block
 // alike and stored by block 0, in the other of two copies where other blocks
-// still read the old one.  What bounds it is the latency of a launch
-// and of its dependent loads (7.6, 7.0 and 3.7 us at N = 10242, n = 31), and
-// above N = 1e5 the operator's bytes, read twice.  Against eleven kernels an
-// iteration: ten steps at N = 10242 26.1 -> 13.4 ms, five at N = 2500 9.1 ->
-// 4.5 ms, five at N = 1e5, n = 50 21.8 -> 14.7 ms, three at N = 6e5 37.0 ->
-// 35.7 ms.
+// still read the old one.  What bounds it is the latency of a launch and of its
+// dependent loads, and above N = 1e5 the operator's bytes, read twice.  Against
+// eleven kernels an iteration and the stage kernels' earlier order of loads: ten
+// steps at N = 10242, n = 31 26.4 -> 10.4 ms, five at N = 2500 10.9 -> 4.3 ms,
+// five at N = 1e5, n = 50 21.8 -> 11.8 ms, three at N = 6e5 36.8 -> 35.5 ms.
 //
 // k_kry_pv: the last iteration's end unless FIRST of a launch sequence (then ks_in is
 // final); p' = r + beta (p - omega v), v' = p' - gamma L p', partials rhat.v'
