@@ -1281,9 +1281,17 @@ constexpr int KRYLOV_BATCH = 8;
 // Block partials that a kernel sums by itself, two loads per thread of a block
 // of four wavefronts; with as many slices or fewer the blocks are single
 // wavefronts, on four times as many CUs (five steps at N = 10242 6.3 -> 5.7 ms).
-// More are first summed by a kernel of one block, whose launch (2 us) then
-// costs less than all of them read by every block of the next kernel.
+// More are first summed to PART_SUMS by a kernel of as many blocks, whose launch
+// (2 us) costs less than all of them read by every block of the next kernel
+// (summed by one block they cost 5 % of an iteration at N = 1e6).
 constexpr int PART_DIRECT = 512;
+constexpr int PART_SUMS = 32;
+// Slot bytes up to which p and s are formed while they are gathered.  Ten SBDF2
+// steps, fused against p and s as passes of their own: 294 MB 89.4 and 90.9 ms,
+// 490 MB 146.4 and 144.4 (torus), 153.7 and 151.5 (ellipsoid), 600 MB 203.8 and
+// 198.6: an operator that streams from memory drives the vectors out of the
+// caches, and the fused kernels gather up to three of them.
+constexpr int64_t KRY_FUSED = (int64_t)384 << 20;
 
 struct HistPtrs {
     const double* u[4];   // u^n, u^{n-1}, ... (one species)
@@ -1369,18 +1377,6 @@ __device__ __forceinline__ void block_sum2(double& v0, double& v1, double* sh) {
 }
 // Block partials (pairs) summed in a fixed order: deterministic, and the same
 // in every block that does it.
-struct Partials {
-    double d0, d1;
-    // the loads; few of them in every kernel but k_sum_partials
-    __device__ __forceinline__ Partials(const double2* __restrict__ part, int np) : d0(0.0), d1(0.0) {
-        for (int i = threadIdx.x; i < np; i += 256) {
-            const double2 v = part[i];
-            d0 += v.x;
-            d1 += v.y;
-        }
-    }
-    __device__ __forceinline__ void sum(double* sh) { block_sum2<256>(d0, d1, sh); }
-};
 // At most PART_DIRECT of them, all loads of a thread in flight at once.
 template <int B>
 struct FewPartials {
@@ -1410,11 +1406,19 @@ struct FewPartials {
         block_sum2<B>(d0, d1, sh);
     }
 };
-__global__ __launch_bounds__(256) void k_sum_partials(const double2* __restrict__ part, int np, double2* out) {
+// More of them into PART_SUMS, one range per block.
+__global__ __launch_bounds__(256) void k_sum_partials(const double2* __restrict__ part, int np,
+                                                      double2* __restrict__ out) {
     __shared__ double sh[8];
-    Partials d(part, np);
-    d.sum(sh);
-    if (threadIdx.x == 0) *out = make_double2(d.d0, d.d1);
+    const int per = (np + PART_SUMS - 1) / PART_SUMS, first = blockIdx.x * per, last = min(first + per, np);
+    double d0 = 0.0, d1 = 0.0;
+    for (int i = first + threadIdx.x; i < last; i += 256) {
+        const double2 v = part[i];
+        d0 += v.x;
+        d1 += v.y;
+    }
+    block_sum2<256>(d0, d1, sh);
+    if (threadIdx.x == 0) out[blockIdx.x] = make_double2(d0, d1);
 }
 
 __device__ __forceinline__ int residual_state(const KrylovScalars& k, double rr) {
@@ -1595,6 +1599,72 @@ __global__ __launch_bounds__(B) void k_kry_st(StageArgs a, const int32_t* __rest
     block_sum2<B>(ts, tt, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = make_double2(ts, tt);
 }
+// The two operator kernels above for an operator that streams from memory
+// (past KRY_FUSED bytes), where p and s are passes of their own.
+template <bool FIRST>
+__global__ __launch_bounds__(256) void k_kry_p(int64_t P, const double2* __restrict__ part_in, int np,
+                                               const KrylovScalars* ks_in, KrylovScalars* ks_out,
+                                               const double* __restrict__ r, const double* __restrict__ pv,
+                                               const double* __restrict__ v, double* __restrict__ p_out) {
+    __shared__ double sh[8];
+    KrylovScalars k = *ks_in;
+    if constexpr (!FIRST) {
+        const FewPartials<256> sums(part_in, np);
+        if (!k.done) {
+            double d0, d1;
+            sums.sum(d0, d1, sh);
+            end_iteration(k, d0, d1);
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) *ks_out = k;
+    }
+    const int64_t p = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (k.done || p >= P) return;
+    p_out[p] = fma(k.beta, fma(-k.omega, v[p], pv[p]), r[p]);
+}
+__global__ __launch_bounds__(256) void k_kry_s(int64_t P, const double2* __restrict__ part_in, int np,
+                                               KrylovScalars* ks, const double* __restrict__ r,
+                                               const double* __restrict__ v, double* __restrict__ sv) {
+    __shared__ double sh[8];
+    if (ks->done) return;
+    const double rho = ks->rho;
+    const FewPartials<256> sums(part_in, np);
+    double d0, d1;
+    sums.sum(d0, d1, sh);
+    const bool broken = d0 == 0.0;
+    const double alpha = broken ? 0.0 : rho / d0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {  // no block reads these two here
+        ks->alpha = alpha;
+        if (broken) ks->breakdown = 1;
+    }
+    const int64_t p = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (p < P) sv[p] = fma(-alpha, v[p], r[p]);
+}
+// out = y - gamma L y, partials of rhat.out (rh given) or of out.y and out.out
+template <bool KEEP>
+__global__ __launch_bounds__(256) void k_kry_av(StageArgs a, const int32_t* __restrict__ idx,
+                                                const double* __restrict__ w, const KrylovScalars* ks,
+                                                const double* __restrict__ y, const double* __restrict__ rh,
+                                                double* __restrict__ out, double2* __restrict__ part) {
+    __shared__ double sh[8];
+    if (ks->done) return;
+    const double gamma = ks->gamma;
+    const RowPos rp = row_pos<256>(a);
+    const double* const ys[1] = {y};
+    LaplacianOf<1, KEEP, 256> L;
+    L.load(a, rp, w, ys);
+    const double yi = rp.live ? L.own[0] : 0.0;
+    const double lap = L.sum(a, rp, idx, w, ys, yi, [](const double (&e)[1]) { return e[0]; });
+    double d0 = 0.0, d1 = 0.0;
+    if (rp.slice >= 0) {
+        const double o = fma(-gamma, lap, yi);
+        out[rp.p] = o;
+        d0 = o * (rh ? rh[rp.p] : yi);
+        d1 = rh ? 0.0 : o * o;
+    }
+    block_sum2<256>(d0, d1, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = make_double2(d0, d1);
+}
+
 // omega = t.s / t.t; x += alpha p + omega s, r = s - omega t, partials r.r and rhat.r
 template <int B>
 __global__ __launch_bounds__(B) void k_kry_xr(int64_t P, const double2* __restrict__ part_in, int np,
@@ -1696,16 +1766,17 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
     const int nvec = S * order * (react ? 2 : 1) + S + 10;
     const int kblk = op->nslices <= PART_DIRECT ? 64 : 256;  // threads per block of the solver's kernels
     const int nblk = (int)((P + kblk - 1) / kblk);
-    const size_t head = (1024 + 3 * (size_t)nblk * sizeof(double2) + 255) & ~(size_t)255;
+    constexpr size_t sums_at = 512, parts_at = sums_at + 3 * PART_SUMS * sizeof(double2);
+    const size_t head = (parts_at + 3 * (size_t)nblk * sizeof(double2) + 255) & ~(size_t)255;
     const size_t vbytes = (size_t)P * sizeof(double);
     int rc = ensure_impl(op, head + nvec * vbytes);
     if (rc) return rc;
     hipStream_t st = ctx->stream;
-    static_assert(2 * sizeof(KrylovScalars) <= 512, "scalars");
+    static_assert(2 * sizeof(KrylovScalars) <= sums_at, "scalars");
     KrylovScalars* ks = (KrylovScalars*)op->impl;
-    double2* psum = (double2*)((char*)op->impl + 512);
+    double2* psum = (double2*)((char*)op->impl + sums_at);
     double2* part[3];
-    for (int q = 0; q < 3; ++q) part[q] = (double2*)((char*)op->impl + 1024) + (size_t)q * nblk;
+    for (int q = 0; q < 3; ++q) part[q] = (double2*)((char*)op->impl + parts_at) + (size_t)q * nblk;
     double* base = (double*)((char*)op->impl + head);
     auto vec = [&](int i) { return base + (size_t)i * P; };
     int vi = 0;
@@ -1760,7 +1831,7 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
     int result = RBFFD_OK;
     int expect[2] = {1, 1};  // graphs of the species' last solve
     const dim3 sg(nblk), sb(kblk);
-    const bool one = kblk == 64;
+    const bool one = kblk == 64, fused = op->slots * 10 <= KRY_FUSED;
     const auto start_first = one ? (a.keep ? k_kry_start<true, true, 64> : k_kry_start<true, false, 64>)
                                  : (a.keep ? k_kry_start<true, true, 256> : k_kry_start<true, false, 256>);
     const auto start_again = one ? (a.keep ? k_kry_start<false, true, 64> : k_kry_start<false, false, 64>)
@@ -1771,13 +1842,14 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
                              : (a.keep ? k_kry_pv<false, true, 256> : k_kry_pv<false, false, 256>);
     const auto st_kernel = one ? (a.keep ? k_kry_st<true, 64> : k_kry_st<false, 64>)
                                : (a.keep ? k_kry_st<true, 256> : k_kry_st<false, 256>);
+    const auto av_kernel = a.keep ? k_kry_av<true> : k_kry_av<false>;
     const auto xr_kernel = one ? k_kry_xr<64> : k_kry_xr<256>;
     // what the next kernel sums: the block partials of set q, or their sum
-    const int npart = nblk <= PART_DIRECT ? nblk : 1;
+    const int npart = nblk <= PART_DIRECT ? nblk : PART_SUMS;
     auto summed = [&](int q) -> const double2* {
         if (npart == nblk) return part[q];
-        hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, st, part[q], nblk, psum + q);
-        return psum + q;
+        hipLaunchKernelGGL(k_sum_partials, dim3(PART_SUMS), dim3(256), 0, st, part[q], nblk, psum + q * PART_SUMS);
+        return psum + q * PART_SUMS;
     };
     for (int64_t n = 0; n < nsteps && result == RBFFD_OK; ++n) {
         const int k = std::min(order, have);
@@ -1814,6 +1886,27 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
                 const double2* ps = nullptr;
                 for (int q = 0; q < count; ++q) {
                     const int from = q & 1, to = 1 - from;
+                    if (!fused) {
+                        if (q == 0) {
+                            hipLaunchKernelGGL(k_kry_p<true>, sg, sb, 0, st, P, nullptr, 0, ks, ks, r, pv[from], v[from],
+                                               pv[to]);
+                        } else {
+                            hipLaunchKernelGGL(k_kry_p<false>, sg, sb, 0, st, P, ps, npart, ks + cur, ks + 1 - cur, r,
+                                               pv[from], v[from], pv[to]);
+                            cur = 1 - cur;
+                        }
+                        hipLaunchKernelGGL(av_kernel, sg, sb, 0, st, a, op->idx32, op->w64, ks + cur, pv[to], rh, v[to],
+                                           part[0]);
+                        ps = summed(0);
+                        hipLaunchKernelGGL(k_kry_s, sg, sb, 0, st, P, ps, npart, ks + cur, r, v[to], sv);
+                        hipLaunchKernelGGL(av_kernel, sg, sb, 0, st, a, op->idx32, op->w64, ks + cur, sv, nullptr, tv,
+                                           part[1]);
+                        ps = summed(1);
+                        hipLaunchKernelGGL(xr_kernel, sg, sb, 0, st, P, ps, npart, ks + cur, pv[to], sv, tv, rh, x, r,
+                                           part[2]);
+                        ps = summed(2);
+                        continue;
+                    }
                     if (q == 0) {
                         hipLaunchKernelGGL(pv_first, sg, sb, 0, st, a, op->idx32, op->w64, nullptr, 0, ks, ks, r,
                                            rh, pv[from], v[from], pv[to], v[to], part[0]);

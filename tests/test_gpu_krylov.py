@@ -1,5 +1,6 @@
 """The fused BiCGSTAB kernels of the implicit steps where they can go wrong:
-part-filled slices, more block partials than a kernel sums by itself, slices
+part-filled slices, more block partials than a kernel sums by itself, an
+operator too large for the kernels that form p and s as they gather, slices
 whose neighbours do not fit the staged list, and a workspace that an earlier
 call with another layout has left behind.
 
@@ -35,7 +36,8 @@ def graph_operator(lib, N, n, far, seed):
 
 
 @pytest.mark.parametrize("N,n,far", [(65, 11, False), (257, 12, False), (2049, 19, False), (20000, 64, True),
-                                     (131072, 11, False), (131073, 11, False), (140001, 14, False)])
+                                     (131072, 11, False), (131073, 11, False), (140001, 14, False),
+                                     (640001, 66, False)])
 def test_first_order_step_solves_its_system(lib, N, n, far):
     idx, w, op = graph_operator(lib, N, n, far, N)
     u0 = np.random.default_rng(1).standard_normal(N)
