@@ -248,7 +248,7 @@ struct StageArgs {
     const void* F;
     double lam, t0, toff;   // toff = (step_in_launch + c_stage), set per launch
     const int64_t* steps_done;
-    bool keep;              // host: the KEEP kernels (keep_slots)
+    int mode;               // host: the kernels to use (stage_mode)
 };
 
 // Blocks are dispatched round-robin over the 8 XCDs; remap them so that each
@@ -333,26 +333,28 @@ typedef double d2v __attribute__((ext_vector_type(2)));
 // The operator's slots are read once per stage.  KEEP: ordinary loads, which
 // leave them in the caches (256 MB behind the L2s) for the next stage; else
 // non-temporal ones, so that an operator which cannot stay there at least does
-// not drive out the state.
-template <bool KEEP, typename V>
+// not drive out the state.  STREAM_WIDE: also without reading ahead, for the
+// wavefronts that fewer registers allow (stage_mode).
+enum { KEEP, STREAM, STREAM_WIDE };
+template <int MODE, typename V>
 __device__ __forceinline__ V ld(const V* p) {
-    if constexpr (KEEP) return *p;
+    if constexpr (MODE == KEEP) return *p;
     else return __builtin_nontemporal_load(p);
 }
 
 // four consecutive slots of one lane
-template <bool KEEP>
+template <int MODE>
 __device__ __forceinline__ void load4(const int32_t* ix, const float* wx, int (&j)[4], float (&w)[4]) {
-    const i4v jv = ld<KEEP>(reinterpret_cast<const i4v*>(ix));
-    const f4v wv = ld<KEEP>(reinterpret_cast<const f4v*>(wx));
+    const i4v jv = ld<MODE>(reinterpret_cast<const i4v*>(ix));
+    const f4v wv = ld<MODE>(reinterpret_cast<const f4v*>(wx));
     j[0] = jv.x; j[1] = jv.y; j[2] = jv.z; j[3] = jv.w;
     w[0] = wv.x; w[1] = wv.y; w[2] = wv.z; w[3] = wv.w;
 }
-template <bool KEEP>
+template <int MODE>
 __device__ __forceinline__ void load4(const int32_t* ix, const double* wx, int (&j)[4], double (&w)[4]) {
-    const i4v jv = ld<KEEP>(reinterpret_cast<const i4v*>(ix));
-    const d2v w0 = ld<KEEP>(reinterpret_cast<const d2v*>(wx));
-    const d2v w1 = ld<KEEP>(reinterpret_cast<const d2v*>(wx) + 1);
+    const i4v jv = ld<MODE>(reinterpret_cast<const i4v*>(ix));
+    const d2v w0 = ld<MODE>(reinterpret_cast<const d2v*>(wx));
+    const d2v w1 = ld<MODE>(reinterpret_cast<const d2v*>(wx) + 1);
     j[0] = jv.x; j[1] = jv.y; j[2] = jv.z; j[3] = jv.w;
     w[0] = w0.x; w[1] = w0.y; w[2] = w1.x; w[3] = w1.y;
 }
@@ -374,7 +376,7 @@ __device__ __forceinline__ void accumulate(const T* __restrict__ Y, int j, T wk,
 // L applied to the stage input of row rp.p by direct gathers, in slot order.
 // FP32: difference form over the n-1 off-diagonal slots; FP64: the diagonal
 // term wd u_i, then the off-diagonal slots (plain form).
-template <typename T, int S, bool KEEP>
+template <typename T, int S, int MODE>
 __device__ __forceinline__ void apply_row(const RowPos& rp, const int32_t* __restrict__ idx,
                                           const T* __restrict__ w, const T* __restrict__ Y, const T (&yi)[2],
                                           T wd, T (&acc)[2]) {
@@ -387,8 +389,8 @@ __device__ __forceinline__ void apply_row(const RowPos& rp, const int32_t* __res
     for (; g + 2 <= G; g += 2) {  // eight slots in flight
         int j[8];
         T wk[8];
-        load4<KEEP>(ix + 256 * g, wx + 256 * g, *reinterpret_cast<int(*)[4]>(j), *reinterpret_cast<T(*)[4]>(wk));
-        load4<KEEP>(ix + 256 * (g + 1), wx + 256 * (g + 1), *reinterpret_cast<int(*)[4]>(j + 4),
+        load4<MODE>(ix + 256 * g, wx + 256 * g, *reinterpret_cast<int(*)[4]>(j), *reinterpret_cast<T(*)[4]>(wk));
+        load4<MODE>(ix + 256 * (g + 1), wx + 256 * (g + 1), *reinterpret_cast<int(*)[4]>(j + 4),
               *reinterpret_cast<T(*)[4]>(wk + 4));
 #pragma unroll
         for (int t = 0; t < 8; ++t) accumulate<T, S>(Y, j[t], wk[t], yi, s0, s1);
@@ -396,14 +398,14 @@ __device__ __forceinline__ void apply_row(const RowPos& rp, const int32_t* __res
     if (g < G) {
         int j[4];
         T wk[4];
-        load4<KEEP>(ix + 256 * g, wx + 256 * g, j, wk);
+        load4<MODE>(ix + 256 * g, wx + 256 * g, j, wk);
 #pragma unroll
         for (int t = 0; t < 4; ++t) accumulate<T, S>(Y, j[t], wk[t], yi, s0, s1);
     }
     const int32_t* ir = idx + rp.base + 256 * G + rp.lane;
     const T* wr = w + rp.base + 256 * G + rp.lane;
     for (int t = 0; t < ns - 4 * G; ++t)
-        accumulate<T, S>(Y, ld<KEEP>(ir + 64 * t), ld<KEEP>(wr + 64 * t), yi,
+        accumulate<T, S>(Y, ld<MODE>(ir + 64 * t), ld<MODE>(wr + 64 * t), yi,
                          s0, s1);
     acc[0] = s0;
     acc[1] = s1;
@@ -424,27 +426,28 @@ __device__ __forceinline__ void halo_value(const typename Vec<T, S>::type* ylds,
 }
 
 // four consecutive weights of one lane
-template <bool KEEP>
+template <int MODE>
 __device__ __forceinline__ void loadw4(const float* wx, float (&w)[4]) {
-    const f4v wv = ld<KEEP>(reinterpret_cast<const f4v*>(wx));
+    const f4v wv = ld<MODE>(reinterpret_cast<const f4v*>(wx));
     w[0] = wv.x; w[1] = wv.y; w[2] = wv.z; w[3] = wv.w;
 }
-template <bool KEEP>
+template <int MODE>
 __device__ __forceinline__ void loadw4(const double* wx, double (&w)[4]) {
-    const d2v w0 = ld<KEEP>(reinterpret_cast<const d2v*>(wx));
-    const d2v w1 = ld<KEEP>(reinterpret_cast<const d2v*>(wx) + 1);
+    const d2v w0 = ld<MODE>(reinterpret_cast<const d2v*>(wx));
+    const d2v w1 = ld<MODE>(reinterpret_cast<const d2v*>(wx) + 1);
     w[0] = w0.x; w[1] = w0.y; w[2] = w1.x; w[3] = w1.y;
 }
 
 // The n-1 off-diagonal slots with neighbour values from the staged halo, in
 // slot order as apply_row.  Up to some 1e5 rows a stage is bound by its chain of
 // dependent loads (slice -> halo list -> neighbour values, 0.5-0.8 us each).  So
-// the first 256 entries of the halo list are read without waiting for the
+// the first 384 entries of the halo list are read without waiting for the
 // slice; neighbour values, the first sixteen slots and the tail are all in
 // flight before the first of them is used; and sixteen slots are read ahead of
 // those being summed.  Against reading the halo first and then sixteen slots at
-// a time, 1000 FP64 steps at N = 2500, n = 31 took 20.4 -> 15.1 ms.
-constexpr int HALO_AHEAD = 4;  // halo entries per lane
+// a time, 1000 FP64 steps at N = 2500, n = 31 took 20.4 -> 15.1 ms (256 entries;
+// 384 take 5-10 % less from N = 1e4 to 1e5, where lists are longer than 256).
+constexpr int HALO_AHEAD = 6;  // halo entries per lane
 static_assert(64 * HALO_AHEAD <= OP_HALO_MAX, "halo lists are OP_HALO_MAX long");
 template <typename T>
 struct Slots {
@@ -453,18 +456,18 @@ struct Slots {
 };
 // Groups past the last are read as the last: a load under a condition would
 // make the compiler wait for every load after it as well.
-template <typename T, bool KEEP>
+template <typename T, int MODE>
 __device__ __forceinline__ void load_slots(const uint16_t* lx, const T* wx, int g, int G, Slots<T>& b) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int at = 256 * (g + q < G ? g + q : G - 1);
-        b.l[q] = ld<KEEP>(reinterpret_cast<const u4v*>(lx + at));
-        loadw4<KEEP>(wx + at, b.w[q]);
+        b.l[q] = ld<MODE>(reinterpret_cast<const u4v*>(lx + at));
+        loadw4<MODE>(wx + at, b.w[q]);
     }
 }
 
 // Y: NV state vectors; conv() makes a neighbour's value of their entries.
-template <typename T, int S, int NV, bool KEEP>
+template <typename T, int S, int NV, int MODE>
 struct RowAhead {
     using V = typename Vec<T, S>::type;
     V y[NV][HALO_AHEAD];
@@ -474,7 +477,7 @@ struct RowAhead {
 
     __device__ __forceinline__ void load(const StageArgs& arg, const RowPos& rp, const T* __restrict__ w,
                                          const T* const (&Y)[NV]) {
-        if (rp.slice < 0) return;
+        if (MODE == STREAM_WIDE || rp.slice < 0) return;
         const int32_t* h = arg.halo + rp.slice * OP_HALO_MAX + rp.lane;
         int j[HALO_AHEAD];
 #pragma unroll
@@ -485,10 +488,10 @@ struct RowAhead {
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
             const int64_t k = at + 64 * (t < tail ? t : 0);
-            lt[t] = ld<KEEP>(arg.lidx + k);
-            wt[t] = ld<KEEP>(w + k);
+            lt[t] = ld<MODE>(arg.lidx + k);
+            wt[t] = ld<MODE>(w + k);
         }
-        if (G) load_slots<T, KEEP>(arg.lidx + rp.base + 4 * rp.lane, w + rp.base + 4 * rp.lane, 0, G, a);
+        if (G) load_slots<T, MODE>(arg.lidx + rp.base + 4 * rp.lane, w + rp.base + 4 * rp.lane, 0, G, a);
 #pragma unroll
         for (int q = 0; q < HALO_AHEAD; ++q) {
             const int64_t k = rp.lane + 64 * q < rp.halo ? j[q] : rp.p;
@@ -501,8 +504,9 @@ struct RowAhead {
     __device__ __forceinline__ void finish(const StageArgs& arg, const RowPos& rp, const T* __restrict__ w,
                                            const T* const (&Y)[NV], C&& conv, V* yl, const T (&yi)[2], T wd,
                                            T (&acc)[2]) {
+        constexpr int first = MODE == STREAM_WIDE ? 0 : HALO_AHEAD;
 #pragma unroll
-        for (int q = 0; q < HALO_AHEAD; ++q) {
+        for (int q = 0; q < first; ++q) {
             if (rp.lane + 64 * q < rp.halo) {
                 V e[NV];
 #pragma unroll
@@ -510,7 +514,7 @@ struct RowAhead {
                 yl[rp.lane + 64 * q] = conv(e);
             }
         }
-        for (int t = rp.lane + 64 * HALO_AHEAD; t < rp.halo; t += 64) {
+        for (int t = rp.lane + 64 * first; t < rp.halo; t += 64) {
             const int64_t j = arg.halo[rp.slice * OP_HALO_MAX + t];
             V e[NV];
 #pragma unroll
@@ -543,17 +547,32 @@ struct RowAhead {
         };
         const uint16_t* lx = arg.lidx + rp.base + 4 * rp.lane;
         const T* wx = w + rp.base + 4 * rp.lane;
-        Slots<T> b;
         int g = 0;
+        if constexpr (MODE == STREAM_WIDE) {
+            for (; g + 4 <= G; g += 4) {
+                load_slots<T, MODE>(lx, wx, g, G, a);
+                sum(a, 4);
+            }
+            if (g < G) {
+                load_slots<T, MODE>(lx, wx, g, G, a);
+                sum(a, G - g);
+            }
+            const int64_t at = rp.base + 256 * G + rp.lane;
+            for (int t = 0; t < tail; ++t) acc1(ld<MODE>(arg.lidx + at + 64 * t), ld<MODE>(w + at + 64 * t));
+            acc[0] = s0;
+            acc[1] = s1;
+            return;
+        }
+        Slots<T> b;
         while (g + 8 < G) {
-            load_slots<T, KEEP>(lx, wx, g + 4, G, b);
+            load_slots<T, MODE>(lx, wx, g + 4, G, b);
             sum(a, 4);
-            load_slots<T, KEEP>(lx, wx, g + 8, G, a);
+            load_slots<T, MODE>(lx, wx, g + 8, G, a);
             sum(b, 4);
             g += 8;
         }
         if (g + 4 < G) {
-            load_slots<T, KEEP>(lx, wx, g + 4, G, b);
+            load_slots<T, MODE>(lx, wx, g + 4, G, b);
             sum(a, 4);
             sum(b, G - g - 4);
         } else {
@@ -570,24 +589,24 @@ struct RowAhead {
 // L applied to the stage input of row rp.p: through the staged halo when the
 // slice has one, otherwise by direct gathers.  Every lane of the wavefront
 // must call this (the halo is loaded cooperatively).
-template <typename T, int S, bool KEEP>
+template <typename T, int S, int MODE>
 __device__ __forceinline__ void laplacian_row(const StageArgs& a, const RowPos& rp, const int32_t* __restrict__ idx,
                                               const T* __restrict__ w, const T* __restrict__ Y, const T (&yi)[2],
                                               T (&lap)[2]) {
     using V = typename Vec<T, S>::type;
     __shared__ V ylds[OP_HALO_MAX];
     const T* const ys[1] = {Y};
-    RowAhead<T, S, 1, KEEP> ahead;
+    RowAhead<T, S, 1, MODE> ahead;
     ahead.load(a, rp, w, ys);
     T wd = (T)0;
     if constexpr (sizeof(T) == 8) {
-        if (rp.live) wd = ld<KEEP>(a.wd64 + rp.p);
+        if (rp.live) wd = ld<MODE>(a.wd64 + rp.p);
     }
     if (rp.halo >= 0) {
         ahead.finish(a, rp, w, ys, [](const V (&e)[1]) { return e[0]; }, ylds, yi, wd, lap);
         return;
     }
-    if (rp.live) apply_row<T, S, KEEP>(rp, idx, w, Y, yi, wd, lap);
+    if (rp.live) apply_row<T, S, MODE>(rp, idx, w, Y, yi, wd, lap);
 }
 
 // RK4 stage `ST` (0..3), one wavefront per block: blocks of four, on a quarter
@@ -596,7 +615,7 @@ __device__ __forceinline__ void laplacian_row(const StageArgs& a, const RowPos& 
 //  Y: stage input; U: state at the start of the step;
 // ACC: accumulator; YN: next stage input (stages 0-2) -- stage 3 updates U
 // (FP32: YN is then the compensation term of the update).
-template <typename T, int S, int R, int ST, bool FORCED, bool KEEP>
+template <typename T, int S, int R, int ST, bool FORCED, int MODE>
 __global__ __launch_bounds__(64) void k_rk4_stage(StageArgs a, const int32_t* __restrict__ idx,
                                                    const T* __restrict__ w, const T* __restrict__ Y,
                                                    T* __restrict__ U, T* __restrict__ ACC, T* __restrict__ YN) {
@@ -612,7 +631,7 @@ __global__ __launch_bounds__(64) void k_rk4_stage(StageArgs a, const int32_t* __
         if constexpr (FORCED) vload<T, S>(reinterpret_cast<const T*>(a.F), p, f);
     }
     T lap[2];
-    laplacian_row<T, S, KEEP>(a, rp, idx, w, Y, yi, lap);
+    laplacian_row<T, S, MODE>(a, rp, idx, w, Y, yi, lap);
     if (!rp.live) return;
     T r[2];
     reaction<T, R>(yi, r, a.rp);
@@ -670,7 +689,7 @@ __global__ void k_set_steps(int64_t* steps_done, int* nonfinite) {
 }
 
 // one operator application (stage-free): out = L y (reaction-free, D = 1)
-template <typename T, bool KEEP>
+template <typename T, int MODE>
 __global__ __launch_bounds__(64) void k_apply(StageArgs a, const int32_t* __restrict__ idx, const T* __restrict__ w,
                                                const T* __restrict__ Y, T* __restrict__ out) {
     const RowPos rp = row_pos<64>(a);
@@ -678,7 +697,7 @@ __global__ __launch_bounds__(64) void k_apply(StageArgs a, const int32_t* __rest
     T yi[2] = {0, 0};
     if (rp.live) vload<T, 1>(Y, rp.p, yi);
     T lap[2];
-    laplacian_row<T, 1, KEEP>(a, rp, idx, w, Y, yi, lap);
+    laplacian_row<T, 1, MODE>(a, rp, idx, w, Y, yi, lap);
     if (rp.live) out[rp.p] = lap[0];
 }
 
@@ -688,9 +707,13 @@ __global__ __launch_bounds__(64) void k_apply(StageArgs a, const int32_t* __rest
 // 10.64, 588 MB 17.6 -> 19.8.  FP64 moves more besides the slots and loses
 // later: 98 MB 2.73 -> 2.18 ms, 217 MB 8.32 -> 5.99, 294 MB 11.8 -> 10.8, 490 MB
 // 18.5 -> 18.2, 600 MB 24.2 -> 24.5.
+// Above that, reading ahead pays for FP32 up to n = 64 (N = 1e6, n = 50: 1-2 %)
+// and costs FP32 3 % at n = 101 and FP64 up to 8 % (N = 1e6, n = 70: 22.8 -> 24.6
+// ms): more registers, fewer wavefronts, on a launch that memory bounds.
 template <typename T>
-bool keep_slots(int64_t slots) {
-    return slots * (int64_t)(sizeof(T) + sizeof(uint16_t)) <= (int64_t)(sizeof(T) == 4 ? 256 : 512) << 20;
+int stage_mode(int64_t slots, int n) {
+    if (slots * (int64_t)(sizeof(T) + sizeof(uint16_t)) <= (int64_t)(sizeof(T) == 4 ? 256 : 512) << 20) return KEEP;
+    return sizeof(T) == 4 && n <= 64 ? STREAM : STREAM_WIDE;
 }
 
 StageArgs stage_args(rbffd_op op, bool f64) {
@@ -701,7 +724,7 @@ StageArgs stage_args(rbffd_op op, bool f64) {
     a.lidx = op->lidx;
     a.halo = op->halo;
     a.wd64 = op->wd64;
-    a.keep = f64 ? keep_slots<double>(op->slots) : keep_slots<float>(op->slots);
+    a.mode = f64 ? stage_mode<double>(op->slots, op->n) : stage_mode<float>(op->slots, op->n);
     return a;
 }
 
@@ -710,51 +733,58 @@ inline dim3 stage_grid(int64_t nslices) { return dim3((unsigned)nslices); }
 
 // One RK4 step, the i-th of its launch sequence; stage times t_n + c dt with
 // c = 0, 1/2, 1/2, 1.
-template <typename T, int S, int R, bool FORCED, bool KEEP>
+template <typename T, int S, int R, bool FORCED, int MODE>
 void enqueue_step(hipStream_t st, StageArgs a, int64_t i, const int32_t* idx, const T* w, T* U, T* ACC, T* Y1,
                   T* Y2, T* COMP) {
     const dim3 g = stage_grid(a.nslices), b(64);
     a.toff = (double)i;
-    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 0, FORCED, KEEP>), g, b, 0, st, a, idx, w, U, U, ACC, Y1);
+    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 0, FORCED, MODE>), g, b, 0, st, a, idx, w, U, U, ACC, Y1);
     a.toff = (double)i + 0.5;
-    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 1, FORCED, KEEP>), g, b, 0, st, a, idx, w, Y1, U, ACC, Y2);
-    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 2, FORCED, KEEP>), g, b, 0, st, a, idx, w, Y2, U, ACC, Y1);
+    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 1, FORCED, MODE>), g, b, 0, st, a, idx, w, Y1, U, ACC, Y2);
+    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 2, FORCED, MODE>), g, b, 0, st, a, idx, w, Y2, U, ACC, Y1);
     a.toff = (double)i + 1.0;
-    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 3, FORCED, KEEP>), g, b, 0, st, a, idx, w, Y1, U, ACC, COMP);
+    hipLaunchKernelGGL((k_rk4_stage<T, S, R, 3, FORCED, MODE>), g, b, 0, st, a, idx, w, Y1, U, ACC, COMP);
 }
 
-template <typename T, bool FORCED, bool KEEP>
+template <typename T, bool FORCED, int MODE>
 void enqueue_steps_f(hipStream_t st, int S, int R, const StageArgs& a, const int32_t* idx, const T* w, T* U, T* ACC,
                      T* COMP, T* Y1, T* Y2, int64_t steps) {
     for (int64_t i = 0; i < steps; ++i) {
         if (S == 1) {
-            enqueue_step<T, 1, RBFFD_REACT_NONE, FORCED, KEEP>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
+            enqueue_step<T, 1, RBFFD_REACT_NONE, FORCED, MODE>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
         } else if (R == RBFFD_REACT_SCHNAKENBERG) {
-            enqueue_step<T, 2, RBFFD_REACT_SCHNAKENBERG, FORCED, KEEP>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
+            enqueue_step<T, 2, RBFFD_REACT_SCHNAKENBERG, FORCED, MODE>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
         } else if (R == RBFFD_REACT_TURING) {
-            enqueue_step<T, 2, RBFFD_REACT_TURING, FORCED, KEEP>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
+            enqueue_step<T, 2, RBFFD_REACT_TURING, FORCED, MODE>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
         } else {
-            enqueue_step<T, 2, RBFFD_REACT_NONE, FORCED, KEEP>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
+            enqueue_step<T, 2, RBFFD_REACT_NONE, FORCED, MODE>(st, a, i, idx, w, U, ACC, Y1, Y2, COMP);
         }
     }
     // forced stages read the step counter: advance it past this sequence
     if (FORCED) hipLaunchKernelGGL(k_advance_steps, dim3(1), dim3(1), 0, st, const_cast<int64_t*>(a.steps_done), steps);
 }
 
+template <typename T, int MODE>
+void enqueue_steps_m(hipStream_t st, int S, int R, const StageArgs& a, const int32_t* idx, const T* w, T* U, T* ACC,
+                     T* COMP, T* Y1, T* Y2, int64_t steps) {
+    if (a.F) enqueue_steps_f<T, true, MODE>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
+    else enqueue_steps_f<T, false, MODE>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
+}
+
 template <typename T>
 void enqueue_steps_t(hipStream_t st, int S, int R, const StageArgs& a, const int32_t* idx, const T* w, T* U, T* ACC,
                      T* COMP, T* Y1, T* Y2, int64_t steps) {
-    if (a.F && a.keep) enqueue_steps_f<T, true, true>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
-    else if (a.F) enqueue_steps_f<T, true, false>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
-    else if (a.keep) enqueue_steps_f<T, false, true>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
-    else enqueue_steps_f<T, false, false>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
+    if (a.mode == KEEP) enqueue_steps_m<T, KEEP>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
+    else if (sizeof(T) == 4 && a.mode == STREAM)
+        enqueue_steps_m<T, sizeof(T) == 4 ? STREAM : KEEP>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
+    else enqueue_steps_m<T, STREAM_WIDE>(st, S, R, a, idx, w, U, ACC, COMP, Y1, Y2, steps);
 }
 
 template <typename T>
 void enqueue_apply(hipStream_t st, const StageArgs& a, const int32_t* idx, const T* w, const T* Y, T* out) {
     const dim3 g = stage_grid(a.nslices), b(64);
-    if (a.keep) hipLaunchKernelGGL((k_apply<T, true>), g, b, 0, st, a, idx, w, Y, out);
-    else hipLaunchKernelGGL((k_apply<T, false>), g, b, 0, st, a, idx, w, Y, out);
+    if (a.mode == KEEP) hipLaunchKernelGGL((k_apply<T, KEEP>), g, b, 0, st, a, idx, w, Y, out);
+    else hipLaunchKernelGGL((k_apply<T, STREAM_WIDE>), g, b, 0, st, a, idx, w, Y, out);
 }
 
 // The flag of the stepper's last stage on the host side, allocated on first use.
@@ -1313,9 +1343,9 @@ __global__ void k_reaction2(int64_t P, const double* __restrict__ u, const doubl
 // L y at row rp.p, neighbour values made by conv() from entries of NV vectors
 // (FP64, one species; in slot order).
 // load() first, then sum(); every lane of the wavefront takes part in both.
-template <int NV, bool KEEP, int B>
+template <int NV, int MODE, int B>
 struct LaplacianOf {
-    RowAhead<double, 1, NV, KEEP> ahead;
+    RowAhead<double, 1, NV, MODE> ahead;
     double own[NV];
     double wd;
 
@@ -1324,7 +1354,7 @@ struct LaplacianOf {
         if (rp.live) {
 #pragma unroll
             for (int v = 0; v < NV; ++v) own[v] = Y[v][rp.p];
-            wd = ld<KEEP>(a.wd64 + rp.p);
+            wd = ld<MODE>(a.wd64 + rp.p);
         }
         ahead.load(a, rp, w, Y);
     }
@@ -1449,7 +1479,7 @@ __device__ __forceinline__ void end_iteration(KrylovScalars& k, double rr, doubl
 // hand side b = (-sum_{j>=1} a_j u^{n+1-j} + dt sum_j b_j R^{n+1-j} + dt ef F)
 // / a_0 and x = u^n.  Padding rows are written as
 // zero in every vector, here and below.
-template <bool FIRST, bool KEEP, int B>
+template <bool FIRST, int MODE, int B>
 __global__ __launch_bounds__(B) void k_kry_start(StageArgs a, const int32_t* __restrict__ idx,
                                                    const double* __restrict__ w, int nk, BdfCoef c, HistPtrs hp,
                                                    const double* __restrict__ F, double ef, double dt, double gamma,
@@ -1462,7 +1492,7 @@ __global__ __launch_bounds__(B) void k_kry_start(StageArgs a, const int32_t* __r
     const int64_t p = rp.p;
     const double* __restrict__ x0 = FIRST ? hp.u[0] : x;
     const double* const ys[1] = {x0};
-    LaplacianOf<1, KEEP, B> L;
+    LaplacianOf<1, MODE, B> L;
     L.load(a, rp, w, ys);
     const double yi = rp.live ? L.own[0] : 0.0;
     const double lap = L.sum(a, rp, idx, w, ys, yi, [](const double (&e)[1]) { return e[0]; });
@@ -1518,12 +1548,12 @@ __global__ __launch_bounds__(256) void k_kry_begin(const double2* __restrict__ p
 // still read the old one.  What bounds it is the latency of a launch and of its
 // dependent loads, and above N = 1e5 the operator's bytes, read twice.  Against
 // eleven kernels an iteration and the stage kernels' earlier order of loads: ten
-// steps at N = 10242, n = 31 26.4 -> 10.4 ms, five at N = 2500 10.9 -> 4.3 ms,
-// five at N = 1e5, n = 50 21.8 -> 11.8 ms, three at N = 6e5 36.8 -> 35.5 ms.
+// steps at N = 10242, n = 31 26.4 -> 10.0 ms, five at N = 2500 10.9 -> 4.3 ms,
+// five at N = 1e5, n = 50 21.8 -> 11.4 ms, ten at N = 6e5 99.0 -> 89.9 ms.
 //
 // k_kry_pv: the last iteration's end unless FIRST of a launch sequence (then ks_in is
 // final); p' = r + beta (p - omega v), v' = p' - gamma L p', partials rhat.v'
-template <bool FIRST, bool KEEP, int B>
+template <bool FIRST, int MODE, int B>
 __global__ __launch_bounds__(B) void k_kry_pv(StageArgs a, const int32_t* __restrict__ idx,
                                                 const double* __restrict__ w, const double2* __restrict__ part_in,
                                                 int np, const KrylovScalars* ks_in, KrylovScalars* ks_out,
@@ -1537,7 +1567,7 @@ __global__ __launch_bounds__(B) void k_kry_pv(StageArgs a, const int32_t* __rest
     const FewPartials<B> sums(part_in, FIRST ? 0 : np);
     const RowPos rp = row_pos<B>(a);
     const double* const ys[3] = {r, pv, v};
-    LaplacianOf<3, KEEP, B> L;
+    LaplacianOf<3, MODE, B> L;
     L.load(a, rp, w, ys);
     if constexpr (!FIRST) {
         if (!k.done) {
@@ -1562,7 +1592,7 @@ __global__ __launch_bounds__(B) void k_kry_pv(StageArgs a, const int32_t* __rest
     if (threadIdx.x == 0) part[blockIdx.x] = make_double2(d, 0.0);
 }
 // alpha = rho / rhat.v; s = r - alpha v, t = s - gamma L s, partials t.s and t.t
-template <bool KEEP, int B>
+template <int MODE, int B>
 __global__ __launch_bounds__(B) void k_kry_st(StageArgs a, const int32_t* __restrict__ idx,
                                                 const double* __restrict__ w, const double2* __restrict__ part_in,
                                                 int np, KrylovScalars* ks, const double* __restrict__ r,
@@ -1574,7 +1604,7 @@ __global__ __launch_bounds__(B) void k_kry_st(StageArgs a, const int32_t* __rest
     const FewPartials<B> sums(part_in, np);
     const RowPos rp = row_pos<B>(a);
     const double* const ys[2] = {r, v};
-    LaplacianOf<2, KEEP, B> L;
+    LaplacianOf<2, MODE, B> L;
     L.load(a, rp, w, ys);
     if (done) return;
     double d0, d1;
@@ -1640,7 +1670,7 @@ __global__ __launch_bounds__(256) void k_kry_s(int64_t P, const double2* __restr
     if (p < P) sv[p] = fma(-alpha, v[p], r[p]);
 }
 // out = y - gamma L y, partials of rhat.out (rh given) or of out.y and out.out
-template <bool KEEP>
+template <int MODE>
 __global__ __launch_bounds__(256) void k_kry_av(StageArgs a, const int32_t* __restrict__ idx,
                                                 const double* __restrict__ w, const KrylovScalars* ks,
                                                 const double* __restrict__ y, const double* __restrict__ rh,
@@ -1650,7 +1680,7 @@ __global__ __launch_bounds__(256) void k_kry_av(StageArgs a, const int32_t* __re
     const double gamma = ks->gamma;
     const RowPos rp = row_pos<256>(a);
     const double* const ys[1] = {y};
-    LaplacianOf<1, KEEP, 256> L;
+    LaplacianOf<1, MODE, 256> L;
     L.load(a, rp, w, ys);
     const double yi = rp.live ? L.own[0] : 0.0;
     const double lap = L.sum(a, rp, idx, w, ys, yi, [](const double (&e)[1]) { return e[0]; });
@@ -1832,17 +1862,16 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
     int expect[2] = {1, 1};  // graphs of the species' last solve
     const dim3 sg(nblk), sb(kblk);
     const bool one = kblk == 64, fused = op->slots * 10 <= KRY_FUSED;
-    const auto start_first = one ? (a.keep ? k_kry_start<true, true, 64> : k_kry_start<true, false, 64>)
-                                 : (a.keep ? k_kry_start<true, true, 256> : k_kry_start<true, false, 256>);
-    const auto start_again = one ? (a.keep ? k_kry_start<false, true, 64> : k_kry_start<false, false, 64>)
-                                 : (a.keep ? k_kry_start<false, true, 256> : k_kry_start<false, false, 256>);
-    const auto pv_first = one ? (a.keep ? k_kry_pv<true, true, 64> : k_kry_pv<true, false, 64>)
-                              : (a.keep ? k_kry_pv<true, true, 256> : k_kry_pv<true, false, 256>);
-    const auto pv_next = one ? (a.keep ? k_kry_pv<false, true, 64> : k_kry_pv<false, false, 64>)
-                             : (a.keep ? k_kry_pv<false, true, 256> : k_kry_pv<false, false, 256>);
-    const auto st_kernel = one ? (a.keep ? k_kry_st<true, 64> : k_kry_st<false, 64>)
-                               : (a.keep ? k_kry_st<true, 256> : k_kry_st<false, 256>);
-    const auto av_kernel = a.keep ? k_kry_av<true> : k_kry_av<false>;
+    // up to 512 slices, and up to KRY_FUSED bytes, the slots are kept
+    const bool keep = a.mode == KEEP;
+    const auto start_first = one ? k_kry_start<true, KEEP, 64>
+                                 : (keep ? k_kry_start<true, KEEP, 256> : k_kry_start<true, STREAM_WIDE, 256>);
+    const auto start_again = one ? k_kry_start<false, KEEP, 64>
+                                 : (keep ? k_kry_start<false, KEEP, 256> : k_kry_start<false, STREAM_WIDE, 256>);
+    const auto pv_first = one ? k_kry_pv<true, KEEP, 64> : k_kry_pv<true, KEEP, 256>;
+    const auto pv_next = one ? k_kry_pv<false, KEEP, 64> : k_kry_pv<false, KEEP, 256>;
+    const auto st_kernel = one ? k_kry_st<KEEP, 64> : k_kry_st<KEEP, 256>;
+    const auto av_kernel = keep ? k_kry_av<KEEP> : k_kry_av<STREAM_WIDE>;
     const auto xr_kernel = one ? k_kry_xr<64> : k_kry_xr<256>;
     // what the next kernel sums: the block partials of set q, or their sum
     const int npart = nblk <= PART_DIRECT ? nblk : PART_SUMS;

@@ -37,7 +37,7 @@ def graph_operator(lib, N, n, far, seed):
 
 @pytest.mark.parametrize("N,n,far", [(65, 11, False), (257, 12, False), (2049, 19, False), (20000, 64, True),
                                      (131072, 11, False), (131073, 11, False), (140001, 14, False),
-                                     (640001, 66, False)])
+                                     (640001, 66, False), (840001, 66, False)])
 def test_first_order_step_solves_its_system(lib, N, n, far):
     idx, w, op = graph_operator(lib, N, n, far, N)
     u0 = np.random.default_rng(1).standard_normal(N)
@@ -61,3 +61,20 @@ def test_workspace_of_another_layout_leaves_nothing_behind(lib):
     op.step_imex(0.1 * u0, 1e-3, 6, order=4, D=(1.0, 10.0), reaction="schnakenberg", params=(0.1, 0.9, 5.0))
     got, _, _ = op.step_imex(u0[:1], 0.02, 4, order=2)
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("N,n", [(1000, 3), (1000, 30), (4097, 66), (840001, 50), (840001, 66)])
+def test_apply_in_every_slot_mode(lib, N, n):
+    """L u where the slots stay in the caches, where they stream, and where
+    they stream without reading ahead (FP32 above 256 MB and n = 64, FP64 above
+    512 MB).  Per row, FP64 and FP32 rounding of n terms: (n + 2) u sum |w| (|u_j| + |u_i|)."""
+    idx, w, op = graph_operator(lib, N, n, False, N + n)
+    u = np.random.default_rng(4).standard_normal(N)
+    du = u[idx] - u[:, None]
+    want = np.einsum("ij,ij->i", w, du)
+    scale = np.einsum("ij,ij->i", np.abs(w), np.abs(u[idx]) + np.abs(u)[:, None])
+    for prec, eps in (("f64", 2.0 ** -53), ("f32", 2.0 ** -24)):
+        got = op.apply(torch.as_tensor(u).cuda(), prec=prec).cpu().numpy().reshape(-1)
+        worst = np.max(np.abs(got - want) / scale)
+        print(f"[apply] N={N} n={n} {prec}: {worst:.1e}", flush=True)
+        assert worst <= (n + 2) * eps
