@@ -702,10 +702,10 @@ __global__ __launch_bounds__(64) void k_apply(StageArgs a, const int32_t* __rest
 }
 
 // KEEP up to about what the 256 MB cache holds: (slot + index) bytes against
-// non-temporal loads, 40 steps each.  FP32: 118 MB 2.38 -> 2.22 ms, 176 MB
+// non-temporal loads, 40 steps each.  FP32: 59 MB 2.38 -> 2.22 ms, 176 MB
 // 6.21 -> 5.17, 235 MB 8.06 -> 6.91, 265 MB 9.11 -> 8.59, but 294 MB 9.87 ->
 // 10.64, 588 MB 17.6 -> 19.8.  FP64 moves more besides the slots and loses
-// later: 98 MB 2.73 -> 2.18 ms, 217 MB 8.32 -> 5.99, 294 MB 11.8 -> 10.8, 490 MB
+// later: 49 MB 2.73 -> 2.18 ms, 210 MB 8.32 -> 5.99, 294 MB 11.8 -> 10.8, 490 MB
 // 18.5 -> 18.2, 600 MB 24.2 -> 24.5.
 // Above that, reading ahead pays for FP32 up to n = 64 (N = 1e6, n = 50: 1-2 %)
 // and costs FP32 3 % at n = 101 and FP64 up to 8 % (N = 1e6, n = 70: 22.8 -> 24.6
