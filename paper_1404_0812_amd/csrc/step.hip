@@ -1670,7 +1670,6 @@ __global__ __launch_bounds__(256) void k_kry_s(int64_t P, const double2* __restr
     if (p < P) sv[p] = fma(-alpha, v[p], r[p]);
 }
 // out = y - gamma L y, partials of rhat.out (rh given) or of out.y and out.out
-template <int MODE>
 __global__ __launch_bounds__(256) void k_kry_av(StageArgs a, const int32_t* __restrict__ idx,
                                                 const double* __restrict__ w, const KrylovScalars* ks,
                                                 const double* __restrict__ y, const double* __restrict__ rh,
@@ -1680,7 +1679,7 @@ __global__ __launch_bounds__(256) void k_kry_av(StageArgs a, const int32_t* __re
     const double gamma = ks->gamma;
     const RowPos rp = row_pos<256>(a);
     const double* const ys[1] = {y};
-    LaplacianOf<1, MODE, 256> L;
+    LaplacianOf<1, STREAM_WIDE, 256> L;
     L.load(a, rp, w, ys);
     const double yi = rp.live ? L.own[0] : 0.0;
     const double lap = L.sum(a, rp, idx, w, ys, yi, [](const double (&e)[1]) { return e[0]; });
@@ -1862,16 +1861,16 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
     int expect[2] = {1, 1};  // graphs of the species' last solve
     const dim3 sg(nblk), sb(kblk);
     const bool one = kblk == 64, fused = op->slots * 10 <= KRY_FUSED;
-    // up to 512 slices, and up to KRY_FUSED bytes, the slots are kept
-    const bool keep = a.mode == KEEP;
+    // the fused kernels keep the slots (512 slices are far below KRY_FUSED), the
+    // others do not (ten steps, 490 MB: kept 143.8, not 140.6 ms; ellipsoid 152.7
+    // and 144.9)
     const auto start_first = one ? k_kry_start<true, KEEP, 64>
-                                 : (keep ? k_kry_start<true, KEEP, 256> : k_kry_start<true, STREAM_WIDE, 256>);
+                                 : (fused ? k_kry_start<true, KEEP, 256> : k_kry_start<true, STREAM_WIDE, 256>);
     const auto start_again = one ? k_kry_start<false, KEEP, 64>
-                                 : (keep ? k_kry_start<false, KEEP, 256> : k_kry_start<false, STREAM_WIDE, 256>);
+                                 : (fused ? k_kry_start<false, KEEP, 256> : k_kry_start<false, STREAM_WIDE, 256>);
     const auto pv_first = one ? k_kry_pv<true, KEEP, 64> : k_kry_pv<true, KEEP, 256>;
     const auto pv_next = one ? k_kry_pv<false, KEEP, 64> : k_kry_pv<false, KEEP, 256>;
     const auto st_kernel = one ? k_kry_st<KEEP, 64> : k_kry_st<KEEP, 256>;
-    const auto av_kernel = keep ? k_kry_av<KEEP> : k_kry_av<STREAM_WIDE>;
     const auto xr_kernel = one ? k_kry_xr<64> : k_kry_xr<256>;
     // what the next kernel sums: the block partials of set q, or their sum
     const int npart = nblk <= PART_DIRECT ? nblk : PART_SUMS;
@@ -1924,11 +1923,11 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
                                                pv[from], v[from], pv[to]);
                             cur = 1 - cur;
                         }
-                        hipLaunchKernelGGL(av_kernel, sg, sb, 0, st, a, op->idx32, op->w64, ks + cur, pv[to], rh, v[to],
+                        hipLaunchKernelGGL(k_kry_av, sg, sb, 0, st, a, op->idx32, op->w64, ks + cur, pv[to], rh, v[to],
                                            part[0]);
                         ps = summed(0);
                         hipLaunchKernelGGL(k_kry_s, sg, sb, 0, st, P, ps, npart, ks + cur, r, v[to], sv);
-                        hipLaunchKernelGGL(av_kernel, sg, sb, 0, st, a, op->idx32, op->w64, ks + cur, sv, nullptr, tv,
+                        hipLaunchKernelGGL(k_kry_av, sg, sb, 0, st, a, op->idx32, op->w64, ks + cur, sv, nullptr, tv,
                                            part[1]);
                         ps = summed(1);
                         hipLaunchKernelGGL(xr_kernel, sg, sb, 0, st, P, ps, npart, ks + cur, pv[to], sv, tv, rh, x, r,
