@@ -115,7 +115,11 @@ const char* rbffd_last_error(rbffd_ctx ctx);
  * xyz: N x 3 FP64.  idx: N x n int32 output in the layout described above.
  * perm (nullable): N int32 output, the library's spatial order, perm[p] =
  * caller index of the node at position p (cell-sorted, Morton order of cells).
- * Errors: n < 1, n > N, n > 128, N > 2^31 - 1.
+ * A node with a NaN coordinate is nobody's neighbour; its own row, and every
+ * row where fewer than n nodes are left, is filled up with -1 (which the other
+ * calls report as an index outside [0, N)).
+ * Errors: n < 1, n > N, n > 128, N > 2^31 - 1, infinite coordinates, no
+ * coordinate that is a number.
  */
 int rbffd_knn(rbffd_ctx ctx, int64_t N, const double* xyz, int32_t n, int32_t* idx, int32_t* perm);
 

@@ -555,7 +555,7 @@ __global__ __launch_bounds__(64) void k_knn(int64_t N, int n, Grid G, const doub
     const int need = n - 1;  // neighbours besides the centre
     int cnt = 0;
     double bound = INFINITY;  // current need-th best squared distance once known
-    bool done = need == 0;
+    bool done = need == 0 || qx != qx || qy != qy || qz != qz;  // a NaN is near nothing
     // One chunk of up to 64 candidates (point index j in cell order, valid
     // when in range): squared distances, those within the bound appended to
     // the LDS list; on overflow the list is cut to its best `need` first.
@@ -644,7 +644,7 @@ __global__ __launch_bounds__(64) void k_knn(int64_t N, int n, Grid G, const doub
             bound = cd[need - 1];
             finish(R);
         } else if (covers(R)) {
-            done = true;  // cannot happen when n <= N
+            done = true;  // only where NaN coordinates leave fewer than n nodes
         }
     };
     if (!done) {
@@ -714,25 +714,30 @@ __global__ __launch_bounds__(64) void k_knn(int64_t N, int n, Grid G, const doub
                     if (64 * c + lane < total && at[c] != (int)p) key[c] = u;
                 }
             }
-            int kept;
+            int most;
             // about the area of the block over its candidates, times the number wanted
             const float guess = (float)(G.h * G.h) * (9.0f / 3.1416f) * 0.5f * (float)(need + limit) / (float)found;
-            const uint32_t T = select_bits<NC>(key, guess, need, limit, found, kept);
-            if (kept <= limit) {
-                taken = true;
-                int base = 0;
+            const uint32_t T = select_bits<NC>(key, guess, need, limit, found, most);
+            // what is written below is what may be read: candidates at no
+            // distance (a NaN coordinate) have keys above every T, so with
+            // all `found` <= limit taken there can be fewer than `most`
+            int kept = 0;
+            if (most <= limit) {
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
                     if (c < chunks) {
                         const bool keep = key[c] <= T;
                         const uint64_t m = __ballot(keep);
                         if (keep)
-                            cid[base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                            cid[kept + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] = at[c];
-                        base += __popcll(m);
+                        kept += __popcll(m);
                     }
                 }
                 __syncthreads();
+            }
+            if (kept >= need) {
+                taken = true;
                 double v[2] = {INFINITY, INFINITY};
                 int id[2] = {0x7fffffff, 0x7fffffff};
 #pragma unroll
@@ -831,7 +836,8 @@ __global__ __launch_bounds__(64) void k_knn(int64_t N, int n, Grid G, const doub
     }
     int32_t* row = idx_out + (int64_t)q * n;
     if (lane == 0) row[0] = q;
-    for (int t = lane; t < need; t += 64) row[1 + t] = cid[t];
+    // short of neighbours (a node or too many others with a NaN coordinate): no index
+    for (int t = lane; t < need; t += 64) row[1 + t] = t < cnt ? cid[t] : -1;
 }
 
 }  // namespace

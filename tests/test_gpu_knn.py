@@ -53,3 +53,27 @@ def test_every_node_of_a_small_cloud(lib, N):
     idx, _ = lib.knn(torch.as_tensor(X).cuda(), n)
     torch.cuda.synchronize()
     assert np.array_equal(idx.cpu().numpy(), oracle_knn(X, n))
+
+
+@pytest.mark.parametrize("N,n,nans", [(12, 11, (3,)), (40, 11, (0, 39)), (70, 31, (5, 6, 7)), (200, 31, range(0, 200, 3)),
+                                      (64, 64, (1,)), (1500, 50, (0, 700, 1499)), (130, 128, range(60))])
+def test_nan_coordinates_are_nobodys_neighbours(lib, N, n, nans):
+    """Whole blocks of candidates at or below the search's limit, some of them
+    at no distance: the others' neighbours are exact, a node without
+    coordinates has none, and where too few nodes are left the row ends in -1."""
+    X = cloud("sphere", N)
+    nans = np.array(list(nans))
+    for t, i in enumerate(nans):
+        X[i, t % 3] = np.nan
+    good = np.setdiff1d(np.arange(N), nans)
+    idx, _ = lib.knn(torch.as_tensor(X).cuda(), n)
+    torch.cuda.synchronize()
+    idx = idx.cpu().numpy()
+    assert np.array_equal(idx[:, 0], np.arange(N))
+    assert (idx[nans, 1:] == -1).all()
+    k = min(n, len(good))
+    want = good[oracle_knn(X[good], k)]
+    if k == n:
+        assert np.array_equal(idx[good], want)
+    else:
+        assert np.array_equal(np.sort(idx[good][:, 1:k]), np.sort(want[:, 1:])) and (idx[good][:, k:] == -1).all()
