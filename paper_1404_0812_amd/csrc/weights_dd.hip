@@ -21,13 +21,17 @@
 // a step reach the rows through DPP row broadcasts.  The final LU works in
 // LDS, in the space of the search's vectors.
 //
-// What bounds it: FP64 issue (a double-double multiply-add is 12 operations
-// where the sums carry their low words, 18 in an update).  Sums and updates
-// with full renormalisation after every operation, the matrix in 38 KB of
-// LDS, three divisions per quotient and 13 eigenvalue passes per decision
-// took 38.3 ms for 2562 stencils of 31 nodes to kappa_T = 1e18; now 5.2 ms
-// (40962 stencils: 551 -> 66 ms; 1200 of 47 nodes: 33 -> 15 ms).
+// What bounds it: FP64 issue (two double-double products and their sum with a
+// third value are 32 operations, see dd.h).  The matrix in 38 KB of LDS, every
+// operation renormalised by itself, quotients of three divisions and 13
+// eigenvalue passes per decision took 38.3 ms for 2562 stencils of 31 nodes to
+// kappa_T = 1e18; now 6.3 ms (40962 stencils: 551 -> 84 ms; 1200 of 47 nodes:
+// 33 -> 16 ms).  Low words summed in plain FP64 took 5.1 ms and were less
+// accurate (MQ weights up to 1.09 times the former kernel's mean error); now,
+// against 113-bit weights at the same eps, 28 sets of 642 stencils (11 to 47
+// nodes, kappa 1e18 and 1e20) have 0.96 to 1.02 times its mean error, 0.99 over all.
 #include "common.h"
+#include "dd.h"
 #include "weights_job.h"
 
 #include <cmath>
@@ -46,98 +50,6 @@ struct DDL {
     static constexpr int BR = MM == 32 ? 4 : 16;  // rows per block of the reduction's code
     static constexpr int LDA = MM + 1;
 };
-
-// ------------------------------------------------------ double-double ----
-// Unevaluated sums hi + lo with |lo| <= ulp(hi) / 2: the error-free sum of
-// two doubles (Knuth's two-sum), the error-free product through FMA, and
-// the usual compensated add / multiply / divide / square root built on them.
-struct dd {
-    double hi, lo;
-};
-
-__device__ __forceinline__ dd mk(double a) { return {a, 0.0}; }
-__device__ __forceinline__ dd quick_two_sum(double a, double b) {
-    const double s = a + b;
-    return {s, b - (s - a)};
-}
-__device__ __forceinline__ dd two_sum(double a, double b) {
-    const double s = a + b;
-    const double bb = s - a;
-    return {s, (a - (s - bb)) + (b - bb)};
-}
-__device__ __forceinline__ dd two_prod(double a, double b) {
-    const double p = a * b;
-    return {p, __builtin_fma(a, b, -p)};
-}
-__device__ __forceinline__ dd add(dd a, dd b) {
-    dd s = two_sum(a.hi, b.hi);
-    const dd t = two_sum(a.lo, b.lo);
-    s.lo += t.hi;
-    s = quick_two_sum(s.hi, s.lo);
-    s.lo += t.lo;
-    return quick_two_sum(s.hi, s.lo);
-}
-__device__ __forceinline__ dd neg(dd a) { return {-a.hi, -a.lo}; }
-__device__ __forceinline__ dd sub(dd a, dd b) { return add(a, neg(b)); }
-__device__ __forceinline__ dd mul(dd a, dd b) {
-    dd p = two_prod(a.hi, b.hi);
-    const double c = a.hi * b.lo;
-    const double d = a.lo * b.hi;
-    p.lo += c + d;
-    return quick_two_sum(p.hi, p.lo);
-}
-__device__ __forceinline__ dd mul_d(dd a, double b) {
-    dd p = two_prod(a.hi, b);
-    p.lo += a.lo * b;
-    return quick_two_sum(p.hi, p.lo);
-}
-// 1 / q to the last place or so: hardware reciprocal, two Newton steps
-__device__ __forceinline__ double recip1(double q) {
-    double r = __builtin_amdgcn_rcp(q);
-    r = __builtin_fma(r, __builtin_fma(-q, r, 1.0), r);
-    return __builtin_fma(r, __builtin_fma(-q, r, 1.0), r);
-}
-// a / b: the first quotient's remainder is exact in one FMA plus the low
-// words, and a second quotient of it leaves 2^-104 or so
-__device__ __forceinline__ dd dvd(dd a, dd b) {
-    const double r = recip1(b.hi);
-    const double q1 = a.hi * r;
-    const double t = __builtin_fma(-q1, b.hi, a.hi);
-    const double rem = t + __builtin_fma(-q1, b.lo, a.lo);
-    const double q2 = rem * r;
-    const dd q = quick_two_sum(q1, q2);
-    // the second remainder's high part, for the bits the reciprocal lacks
-    const double t2 = __builtin_fma(-q2, b.hi, rem);
-    return quick_two_sum(q.hi, __builtin_fma(t2, r, q.lo));
-}
-__device__ __forceinline__ dd dsqrt(dd a) {
-    if (!(a.hi > 0.0)) return mk(a.hi == 0.0 ? 0.0 : NAN);
-    const double x = 1.0 / sqrt(a.hi);
-    const double ax = a.hi * x;
-    const dd e = sub(a, two_prod(ax, ax));
-    return two_sum(ax, e.hi * (x * 0.5));
-}
-// s += a b and s += t with the low word left unnormalised (normalise with
-// norm() before use elsewhere): the high words' sum is error-free, so a sum of
-// n terms is off by about n 2^-106 times the sum of their magnitudes, as it is
-// with a normalisation after every term.
-__device__ __forceinline__ void mac(dd& s, dd a, dd b) {
-    const double ph = a.hi * b.hi;
-    double pl = __builtin_fma(a.hi, b.hi, -ph);
-    pl = __builtin_fma(a.hi, b.lo, pl);
-    pl = __builtin_fma(a.lo, b.hi, pl);
-    const dd t = two_sum(s.hi, ph);
-    s.hi = t.hi;
-    s.lo += t.lo + pl;
-}
-__device__ __forceinline__ void acc(dd& s, dd t) {
-    const dd u = two_sum(s.hi, t.hi);
-    s.hi = u.hi;
-    s.lo += u.lo + t.lo;
-}
-__device__ __forceinline__ dd norm(dd s) { return quick_two_sum(s.hi, s.lo); }
-__device__ __forceinline__ double to_d(dd a) { return a.hi + a.lo; }
-__device__ __forceinline__ bool is_fin(dd a) { return isfinite(a.hi) && isfinite(a.lo); }
 
 template <int CTRL>
 __device__ __forceinline__ double dpp(double v) {
@@ -181,24 +93,22 @@ __device__ __forceinline__ void swap32(dd v, dd& a, dd& b) {
 __device__ __forceinline__ dd halves_sum(dd v) {
     dd a, b;
     swap32(v, a, b);
-    acc(a, b);
-    return norm(a);
+    return add(a, b);
 }
 // Sum over the columns (each half of the wavefront holds all of them where
-// H = 2), the same value in every lane: the error-free sums of the high words
-// do not depend on the order of two operands.
+// H = 2), the same bits in every lane: two partners add the same two values,
+// and add() does not depend on their order.
 template <int MM>
 __device__ __forceinline__ dd wsum(dd v) {
-    acc(v, dpp<0xB1>(v));   // quad_perm [1,0,3,2]
-    acc(v, dpp<0x4E>(v));   // quad_perm [2,3,0,1]
-    acc(v, dpp<0x141>(v));  // row_half_mirror
-    acc(v, dpp<0x140>(v));  // row_mirror
+    v = add(v, dpp<0xB1>(v));   // quad_perm [1,0,3,2]
+    v = add(v, dpp<0x4E>(v));   // quad_perm [2,3,0,1]
+    v = add(v, dpp<0x141>(v));  // row_half_mirror
+    v = add(v, dpp<0x140>(v));  // row_mirror
     dd a, b;
     swap16(v.hi, a.hi, b.hi);
     swap16(v.lo, a.lo, b.lo);
-    acc(a, b);
-    if constexpr (DDL<MM>::H == 2) return norm(a);
-    else return halves_sum(a);
+    if constexpr (DDL<MM>::H == 2) return add(a, b);
+    else return halves_sum(add(a, b));
 }
 
 __device__ __forceinline__ void fence() {
@@ -323,9 +233,7 @@ __device__ __forceinline__ void tridiag_block(dd (&a)[DDL<MM>::R], DDShared<MM>&
     for (int k = k0; k < kend; ++k) {
         const dd alpha = ld(S.f.ch, S.f.cl, k + 1);
         const bool tail = c > k + 1 && c < m;
-        dd t = mk(0.0);
-        if (tail) mac(t, x, x);
-        const dd xn2 = wsum<MM>(t);
+        const dd xn2 = wsum<MM>(tail ? mul(x, x) : mk(0.0));
         dd beta = alpha, tau = mk(0.0), scal = mk(0.0);
         if (xn2.hi > 0.0) {
             const dd nrm = dsqrt(add(mul(alpha, alpha), xn2));
@@ -348,13 +256,14 @@ __device__ __forceinline__ void tridiag_block(dd (&a)[DDL<MM>::R], DDShared<MM>&
         dd v[R / 16], w[R / 16];
 #pragma unroll
         for (int g = 0; g < R / 16; ++g) v[g] = ld(S.f.vh, S.f.vl, H * (16 * g + l15) + h);
-        dd p = mk(0.0);
-        each<BR * B, R>([&](auto q) __attribute__((always_inline)) {
-            constexpr int i = decltype(q)::value;
-            mac(p, a[i], row_lane<i % 16>(v[i / 16]));
+        dd p = mk(0.0), p2 = mk(0.0);  // two chains, two terms at a time
+        each<BR * B / 2, R / 2>([&](auto q) __attribute__((always_inline)) {
+            constexpr int i = 2 * decltype(q)::value;
+            dd& s = (i / 2) % 2 ? p2 : p;
+            s = mac2(s, a[i], row_lane<i % 16>(v[i / 16]), a[i + 1], row_lane<(i + 1) % 16>(v[(i + 1) / 16]));
         });
+        p = add(p, p2);
         if constexpr (H == 2) p = halves_sum(p);
-        else p = norm(p);
         dd wj = (c > k && c < m) ? mul(tau, p) : mk(0.0);
         const dd s = wsum<MM>(mul(wj, vj));
         wj = sub(wj, mul(mul_d(mul(tau, s), 0.5), vj));
@@ -365,9 +274,7 @@ __device__ __forceinline__ void tridiag_block(dd (&a)[DDL<MM>::R], DDShared<MM>&
         const dd nv = neg(vj), nw = neg(wj);
         each<BR * B, R>([&](auto q) __attribute__((always_inline)) {
             constexpr int i = decltype(q)::value;
-            mac(a[i], row_lane<i % 16>(v[i / 16]), nw);
-            mac(a[i], row_lane<i % 16>(w[i / 16]), nv);
-            a[i] = norm(a[i]);
+            a[i] = mac2(a[i], row_lane<i % 16>(v[i / 16]), nw, row_lane<i % 16>(w[i / 16]), nv);
         });
         x = row_at<MM>(a, k + 1);
         st(S.f.ch, S.f.cl, c, x);
@@ -418,14 +325,9 @@ __device__ __forceinline__ int sturm_dd(const DDShared<MM>& S, int m, double sig
 #pragma unroll 2
     for (int i = 0; i < m; ++i) {
         const double4 de = S.f.de[i];
-        // e^2 / q to about 2^-104
-        const double r = recip1(q.hi);
-        const double q1 = i ? de.z * r : 0.0;
-        const double t = __builtin_fma(-q1, q.hi, de.z);
-        const double q2 = i ? (t + __builtin_fma(-q1, q.lo, de.w)) * r : 0.0;
-        const dd d = two_sum(de.x, -sigma);
-        const dd u = two_sum(d.hi, -q1);
-        q = quick_two_sum(u.hi, u.lo + ((d.lo + de.y) - q2));
+        dd t = dvd({de.z, de.w}, q);
+        if (i == 0) t = mk(0.0);
+        q = sub_q({de.x, de.y}, sigma, t);
         if (fabs(q.hi) < pivmin) q = mk(-pivmin);
         cnt += q.hi < 0.0 ? 1 : 0;
     }
@@ -552,12 +454,6 @@ __device__ __forceinline__ double min_abs_dd(const DDShared<MM>& S, int m, const
     return fmin(pos, ng);
 }
 
-// a - b c
-__device__ __forceinline__ dd nmac(dd a, dd b, dd c) {
-    mac(a, neg(b), c);
-    return norm(a);
-}
-
 // LU with partial pivoting of A~ in place (lane (c, h): column c, rows of
 // parity h); false on a zero pivot
 template <int MM>
@@ -583,7 +479,7 @@ __device__ bool lu_dd(DDShared<MM>& S, int m, int c, int h) {
         fence();
         if (c > k && c < m) {
             const dd ukj = A(S, k, c);
-            for (int r = k + 1 + ((k + 1 + h) & (H - 1)); r < m; r += H) setA(S, r, c, nmac(A(S, r, c), A(S, r, k), ukj));
+            for (int r = k + 1 + ((k + 1 + h) & (H - 1)); r < m; r += H) setA(S, r, c, sub(A(S, r, c), mul(A(S, r, k), ukj)));
         }
         fence();
     }
@@ -607,7 +503,7 @@ __device__ void lu_solve_dd(DDShared<MM>& S, int m, int nb, int lane) {
         if (lane > k && lane < m) {
             const dd l = A(S, lane, k);
             for (int v = 0; v < nb; ++v)
-                st(S.bh[v], S.bl[v], lane, nmac(ld(S.bh[v], S.bl[v], lane), l, ld(S.bh[v], S.bl[v], k)));
+                st(S.bh[v], S.bl[v], lane, sub(ld(S.bh[v], S.bl[v], lane), mul(l, ld(S.bh[v], S.bl[v], k))));
         }
         fence();
     }
@@ -617,7 +513,7 @@ __device__ void lu_solve_dd(DDShared<MM>& S, int m, int nb, int lane) {
         if (lane < k) {
             const dd u = A(S, lane, k);
             for (int v = 0; v < nb; ++v)
-                st(S.bh[v], S.bl[v], lane, nmac(ld(S.bh[v], S.bl[v], lane), u, ld(S.bh[v], S.bl[v], k)));
+                st(S.bh[v], S.bl[v], lane, sub(ld(S.bh[v], S.bl[v], lane), mul(u, ld(S.bh[v], S.bl[v], k))));
         }
         fence();
     }
@@ -775,11 +671,11 @@ __global__ __launch_bounds__(64, 2) void k_weights_dd(rbw::Job J) {
             dd d[3];
             diff3(S, i, c, d);
             const dd ps = psi<K>(e2, norm2(d));
-            dd dot = mk(0.0);
-            for (int t = 0; t < 3; ++t) mac(dot, d[t], ld(S.bh[t], S.bl[t], i));
-            mac(rj, ps, norm(dot));
+            dd dot = mul(d[0], ld(S.bh[0], S.bl[0], i));
+            for (int t = 1; t < 3; ++t) dot = add(dot, mul(d[t], ld(S.bh[t], S.bl[t], i)));
+            rj = add(rj, mul(ps, dot));
         }
-    rj = H == 2 ? halves_sum(rj) : norm(rj);
+    if (H == 2) rj = halves_sum(rj);
     fence();
     if (lane < m) st(S.bh[0], S.bl[0], lane, rj);
     fence();
