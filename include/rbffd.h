@@ -272,7 +272,8 @@ typedef struct {
  * Errors: nsurf < 1 or any surface invalid as in rbffd_op_create. */
 int rbffd_op_create_batched(rbffd_ctx ctx, int32_t nsurf, const rbffd_op_surface* surf, rbffd_op* out);
 /* The context keeps the device memory of its last destroyed operator (up to
- * 2 GiB) for the next one; rbffd_destroy frees it. */
+ * 2 GiB) for the next one; rbffd_destroy frees it, and so does any allocation
+ * of the library on that context that fails (which is then tried again). */
 int rbffd_op_destroy(rbffd_op op);
 
 /* Layout statistics of an operator (HOST outputs, each nullable): slices of

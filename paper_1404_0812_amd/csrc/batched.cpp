@@ -151,8 +151,7 @@ int ensure_batch(rbffd_ctx ctx, size_t bytes) {
         ctx->batch_bytes = 0;
     }
     const size_t want = bytes + bytes / 2 + 4096;
-    if (hipMalloc(&ctx->batch, want) != hipSuccess) {
-        ctx->batch = nullptr;
+    if (device_alloc(ctx->spare, &ctx->batch, want) != hipSuccess) {
         return set_error(ctx, RBFFD_E_NOMEM, "cannot allocate %zu bytes for the batch work list", want);
     }
     ctx->batch_bytes = want;

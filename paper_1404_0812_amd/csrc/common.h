@@ -11,6 +11,24 @@
 
 #include "rbffd.h"
 
+// Device memory of the context's last destroyed operator, kept for the next one
+// of a similar size (SPARE_MAX bytes at most).
+// Given back when the context is destroyed and whenever an allocation of the
+// library fails.  Shared by the context and its operators, which may be
+// destroyed later and by other threads.
+struct SpareMemory {
+    struct Block {
+        void* p = nullptr;
+        size_t bytes = 0;
+    };
+    std::mutex mu;
+    int owners = 1;
+    int device = 0;
+    bool open = true;  // the context is alive
+    Block block[2];
+};
+constexpr size_t SPARE_MAX = (size_t)2 << 30;
+
 struct rbffd_ctx_s {
     hipStream_t stream = nullptr;
     int device = 0;
@@ -18,12 +36,7 @@ struct rbffd_ctx_s {
     // growable scratch owned by the context
     void* scratch = nullptr;
     size_t scratch_bytes = 0;
-    // the last destroyed operator's device memory, for the next one (see
-    // slab_take in step.hip); the mutex is for operators destroyed by another
-    // thread than the context's
-    std::mutex spare_mu;
-    void* spare = nullptr;
-    size_t spare_bytes = 0;
+    SpareMemory* spare = nullptr;
     // work list of the batched weights launch (kept apart from scratch, which kNN uses)
     void* batch = nullptr;
     size_t batch_bytes = 0;
@@ -58,8 +71,8 @@ struct rbffd_op_s {
     int32_t* halo = nullptr;      // OP_HALO_MAX sorted distinct neighbour rows per slice
     int32_t* perm = nullptr;      // internal row -> caller row (-1 for padding), P entries
     void* work = nullptr;         // state workspace (internal order)
-    void* slab = nullptr;         // the one device allocation that holds the arrays above and the counters
-    size_t slab_bytes = 0;
+    SpareMemory::Block slab;      // the one device allocation that holds the arrays above and the counters
+    SpareMemory* spare = nullptr; // of the context that built it
     rbffd_ctx home = nullptr;     // the context that built it
     bool roamed = false;          // used on another context's stream
     // vectors of the implicit (BDF) stepper, allocated on first use
@@ -88,6 +101,15 @@ int set_error(rbffd_ctx ctx, int code, const char* fmt, ...);
 int noalloc_scratch_setup(rbffd_ctx ctx, int device);
 // Ensure ctx->scratch holds at least `bytes`; returns 0 or an error code.
 int ensure_scratch(rbffd_ctx ctx, size_t bytes);
+// hipMalloc; when it fails, once more without the spare memory.
+hipError_t device_alloc(SpareMemory* spare, void** p, size_t bytes);
+// A spare block of bytes .. 4 bytes, or a new one; false: out of memory.
+bool spare_take(SpareMemory* spare, size_t bytes, SpareMemory::Block& out);
+// The blocks of a destroyed operator, idle on the device, in place of those
+// kept so far; freed instead with `keep` false or the context gone.
+void spare_give(SpareMemory* spare, const SpareMemory::Block (&blocks)[2], bool keep);
+// One owner less; the last deletes it.
+void spare_leave(SpareMemory* spare, bool context);
 
 #define HIP_TRY(ctx, call)                                                                   \
     do {                                                                                     \

@@ -4,6 +4,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <utility>
 
 int set_error(rbffd_ctx ctx, int code, const char* fmt, ...) {
     if (ctx) {
@@ -13,6 +14,70 @@ int set_error(rbffd_ctx ctx, int code, const char* fmt, ...) {
         va_end(ap);
     }
     return code;
+}
+
+namespace {
+void free_blocks(SpareMemory::Block (&b)[2]) {
+    for (SpareMemory::Block& q : b) {
+        if (q.p) (void)hipFree(q.p);
+        q = SpareMemory::Block{};
+    }
+}
+}  // namespace
+
+hipError_t device_alloc(SpareMemory* spare, void** p, size_t bytes) {
+    *p = nullptr;
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess) return e;
+    {
+        std::lock_guard<std::mutex> lock(spare->mu);
+        if (!spare->block[0].p && !spare->block[1].p) return e;
+        (void)hipGetLastError();
+        free_blocks(spare->block);
+    }
+    e = hipMalloc(p, bytes);
+    if (e != hipSuccess) *p = nullptr;
+    return e;
+}
+
+bool spare_take(SpareMemory* spare, size_t bytes, SpareMemory::Block& out) {
+    {
+        std::lock_guard<std::mutex> lock(spare->mu);
+        SpareMemory::Block* best = nullptr;
+        for (SpareMemory::Block& b : spare->block)
+            if (b.p && b.bytes >= bytes && b.bytes / 4 <= bytes && (!best || b.bytes < best->bytes)) best = &b;
+        if (best) {
+            out = *best;
+            *best = SpareMemory::Block{};
+            return true;
+        }
+    }
+    out.bytes = bytes;
+    return device_alloc(spare, &out.p, bytes) == hipSuccess;
+}
+
+void spare_give(SpareMemory* spare, const SpareMemory::Block (&blocks)[2], bool keep) {
+    SpareMemory::Block drop[2] = {blocks[0], blocks[1]};
+    if (!drop[0].p) return;  // an operator that got no memory
+    if (keep && blocks[0].bytes + blocks[1].bytes <= SPARE_MAX) {
+        std::lock_guard<std::mutex> lock(spare->mu);
+        if (spare->open)
+            for (int q = 0; q < 2; ++q) std::swap(spare->block[q], drop[q]);
+    }
+    free_blocks(drop);
+}
+
+void spare_leave(SpareMemory* spare, bool context) {
+    bool last;
+    {
+        std::lock_guard<std::mutex> lock(spare->mu);
+        if (context) {
+            spare->open = false;
+            free_blocks(spare->block);
+        }
+        last = --spare->owners == 0;
+    }
+    if (last) delete spare;
 }
 
 int ensure_scratch(rbffd_ctx ctx, size_t bytes) {
@@ -25,8 +90,7 @@ int ensure_scratch(rbffd_ctx ctx, size_t bytes) {
         ctx->scratch_bytes = 0;
     }
     size_t want = bytes + bytes / 4 + (1u << 20);
-    if (hipMalloc(&ctx->scratch, want) != hipSuccess) {
-        ctx->scratch = nullptr;
+    if (device_alloc(ctx->spare, &ctx->scratch, want) != hipSuccess) {
         return set_error(ctx, RBFFD_E_NOMEM, "cannot allocate %zu bytes of scratch", want);
     }
     ctx->scratch_bytes = want;
@@ -65,6 +129,12 @@ extern "C" int rbffd_create(rbffd_ctx* out, void* stream) {
         delete c;
         return RBFFD_E_HIP;
     }
+    c->spare = new (std::nothrow) SpareMemory();
+    if (!c->spare) {
+        delete c;
+        return RBFFD_E_NOMEM;
+    }
+    c->spare->device = c->device;
     *out = c;
     return RBFFD_OK;
 }
@@ -75,14 +145,11 @@ extern "C" int rbffd_destroy(rbffd_ctx ctx) {
         (void)hipStreamSynchronize(ctx->stream);
         (void)hipFree(ctx->scratch);
     }
-    if (ctx->spare) {
-        (void)hipStreamSynchronize(ctx->stream);
-        (void)hipFree(ctx->spare);
-    }
     if (ctx->batch) {
         (void)hipStreamSynchronize(ctx->stream);
         (void)hipFree(ctx->batch);
     }
+    spare_leave(ctx->spare, true);
     delete ctx;
     return RBFFD_OK;
 }

@@ -813,40 +813,6 @@ void reset_kgraph(rbffd_op op) {
     op->kgraph_key = nullptr;
 }
 
-// Device memory of one operator.  A context keeps the last destroyed
-// operator's, up to SPARE_MAX bytes, for the next one of a similar size:
-// freeing and allocating 230 MB (2e5 rows, n = 50) took 5 ms, ten times the
-// build.  Given back when the context is destroyed or an allocation fails.
-constexpr size_t SPARE_MAX = (size_t)2 << 30;
-
-void* slab_take(rbffd_ctx ctx, size_t bytes, size_t& got) {
-    std::lock_guard<std::mutex> lock(ctx->spare_mu);
-    void* p = nullptr;
-    if (ctx->spare && ctx->spare_bytes >= bytes && ctx->spare_bytes / 4 <= bytes) {
-        p = ctx->spare;
-        got = ctx->spare_bytes;
-        ctx->spare = nullptr;
-        return p;
-    }
-    got = bytes;
-    if (hipMalloc(&p, bytes) == hipSuccess) return p;
-    if (!ctx->spare) return nullptr;
-    (void)hipGetLastError();
-    (void)hipFree(ctx->spare);
-    ctx->spare = nullptr;
-    return hipMalloc(&p, bytes) == hipSuccess ? p : nullptr;
-}
-// The caller has waited for the context's stream; hipFree itself waits for the
-// whole device, which an operator used on other streams needs.
-void slab_give(rbffd_ctx ctx, void* p, size_t bytes, bool keep) {
-    if (keep && bytes <= SPARE_MAX) {
-        std::lock_guard<std::mutex> lock(ctx->spare_mu);
-        std::swap(ctx->spare, p);
-        ctx->spare_bytes = bytes;
-    }
-    if (p) (void)hipFree(p);
-}
-
 // Every call on an operator names its context.
 void use_on(rbffd_op op, rbffd_ctx ctx) {
     op->ctx = ctx;
@@ -855,9 +821,11 @@ void use_on(rbffd_op op, rbffd_ctx ctx) {
 
 // Build the sliced operator of nsurf surfaces (validated by the callers).  All
 // device arrays of the operator, the state workspace included, are one
-// allocation; the inverse permutation is in the context's scratch.  Build,
-// two FP64 applications and release at N = 2e5, n = 50: 2.73 -> 0.39 ms, of
-// which 1.5 ms were the two kernels above and the rest 13 allocations.
+// allocation; the inverse permutation is in the context's scratch.  Build, two FP64
+// applications and release at N = 2e5, n = 50: 2.9 -> 0.41 ms with the memory of
+// an operator destroyed before, 3.6 -> 1.1 ms for the first of a context, 0.74
+// ms where nothing is kept (hipMalloc and hipFree take 0.25 ms at 64 MB to 1
+// GB, 0.5 ms above; the former 13 allocations took 1 ms).
 int create_op(rbffd_ctx ctx, int nsurf, const rbffd_op_surface* surf, rbffd_op* out) {
     int64_t P = 0, N = 0, slots = 0, maxN = 0, nslices = 0;
     int32_t nmax = 0;
@@ -878,6 +846,11 @@ int create_op(rbffd_ctx ctx, int nsurf, const rbffd_op_surface* surf, rbffd_op* 
     rbffd_op op = new (std::nothrow) rbffd_op_s();
     if (!op) return set_error(ctx, RBFFD_E_NOMEM, "host allocation failed");
     op->ctx = op->home = ctx;
+    op->spare = ctx->spare;
+    {
+        std::lock_guard<std::mutex> lock(op->spare->mu);
+        ++op->spare->owners;
+    }
     op->N = N;
     op->P = P;
     op->n = nmax;
@@ -897,12 +870,11 @@ int create_op(rbffd_ctx ctx, int nsurf, const rbffd_op_surface* surf, rbffd_op* 
     const size_t o_cnt = take(sizeof(int64_t) + sizeof(int));
     // 4 state buffers (U, ACC, Y1, Y2) x 2 species x FP64, and the forcing (2 species)
     const size_t o_work = take(5 * 2 * (size_t)P * sizeof(double));
-    op->slab = slab_take(ctx, bytes, op->slab_bytes);
-    if (!op->slab) {
+    if (!spare_take(op->spare, bytes, op->slab)) {
         rbffd_op_destroy(op);
         return set_error(ctx, RBFFD_E_NOMEM, "operator allocation failed");
     }
-    char* base = (char*)op->slab;
+    char* base = (char*)op->slab.p;
     op->slices = (OpSlice*)(base + o_sl);
     op->wd64 = (double*)(base + o_wd);
     op->w64 = (double*)(base + o_w64);
@@ -987,9 +959,13 @@ extern "C" int rbffd_op_destroy(rbffd_op op) {
     if (op->ctx) (void)hipStreamSynchronize(op->ctx->stream);
     reset_graph(op);
     reset_kgraph(op);
-    if (op->slab) slab_give(op->ctx, op->slab, op->slab_bytes, !op->roamed);
+    // kept blocks have waited for the context's stream; hipFree itself waits for
+    // the whole device, which an operator used on other streams needs
+    const SpareMemory::Block blocks[2] = {op->slab, SpareMemory::Block{}};
+    spare_give(op->spare, blocks, !op->roamed);
     if (op->impl) (void)hipFree(op->impl);
     if (op->nonfinite_host) (void)hipHostFree(op->nonfinite_host);
+    spare_leave(op->spare, false);
     delete op;
     return RBFFD_OK;
 }
@@ -1759,8 +1735,7 @@ int ensure_impl(rbffd_op op, size_t bytes) {
         op->impl = nullptr;
         op->impl_bytes = 0;
     }
-    if (hipMalloc(&op->impl, bytes) != hipSuccess) {
-        op->impl = nullptr;
+    if (device_alloc(op->spare, &op->impl, bytes) != hipSuccess) {
         return set_error(op->ctx, RBFFD_E_NOMEM, "cannot allocate %zu bytes for the implicit stepper", bytes);
     }
     op->impl_bytes = bytes;

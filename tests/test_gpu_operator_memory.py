@@ -1,0 +1,56 @@
+"""Operators that follow one another in the memory of destroyed ones: other
+sizes, several alive at once, other contexts; every result is that of a plain
+sum over the stencils."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def problem(N, n, seed):
+    """Caller stencils, weights and a state on the GPU, and L u from them."""
+    rng = np.random.default_rng(seed)
+    off = np.stack([1 + rng.choice(min(N - 1, 150), n - 1, replace=False) for _ in range(1)])[0]
+    idx = np.concatenate([np.arange(N)[:, None], (np.arange(N)[:, None] + off[None]) % N], axis=1).astype(np.int32)
+    w = rng.standard_normal((N, n))
+    w[:, 0] = -w[:, 1:].sum(1)
+    u = rng.standard_normal(N)
+    return [torch.as_tensor(a).cuda() for a in (idx, w, u)] + [(w * u[idx]).sum(1), (np.abs(w) * np.abs(u[idx])).sum(1)]
+
+
+def check(op, p):
+    got = op.apply(p[2]).cpu().numpy()
+    assert np.all(np.abs(got - p[3]) <= 2 * p[0].shape[1] * 2.0 ** -53 * p[4])
+
+
+def test_sizes_in_turn(lib):
+    """Equal, smaller, much smaller (not served by the kept memory) and larger operators, one after another."""
+    ctx = lib.Context()
+    for q, (N, n) in enumerate([(3000, 31), (3000, 31), (2000, 31), (200, 9), (9000, 50), (9000, 33), (64, 2), (70000, 60),
+                                (65, 64)]):
+        p = problem(N, n, q)
+        op = lib.Operator(p[0], p[1], ctx=ctx)
+        check(op, p)
+        op.close()
+    ctx.close()
+
+
+def test_several_alive(lib):
+    ctx = lib.Context()
+    ps = [problem(N, 31, N) for N in (2000, 2000, 2500)]
+    ops = []
+    for turn in range(3):
+        ops += [lib.Operator(p[0], p[1], ctx=ctx) for p in ps]
+        for op, p in zip(ops, ps):
+            check(op, p)
+        ops.pop(turn).close()
+        ps = ps[:turn] + ps[turn + 1:] + [ps[turn]]
+        for op, p in zip(ops, ps[:2]):
+            check(op, p)
+        for op in ops:
+            op.close()
+        ops = []
+    ctx.close()
