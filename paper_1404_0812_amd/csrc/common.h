@@ -73,8 +73,6 @@ struct rbffd_op_s {
     void* work = nullptr;         // state workspace (internal order)
     SpareMemory::Block slab;      // the one device allocation that holds the arrays above and the counters
     SpareMemory* spare = nullptr; // of the context that built it
-    rbffd_ctx home = nullptr;     // the context that built it
-    bool roamed = false;          // used on another context's stream
     // vectors of the implicit (BDF) stepper, allocated on first use
     void* impl = nullptr;
     size_t impl_bytes = 0;

@@ -813,12 +813,6 @@ void reset_kgraph(rbffd_op op) {
     op->kgraph_key = nullptr;
 }
 
-// Every call on an operator names its context.
-void use_on(rbffd_op op, rbffd_ctx ctx) {
-    op->ctx = ctx;
-    if (ctx != op->home) op->roamed = true;
-}
-
 // Build the sliced operator of nsurf surfaces (validated by the callers).  All
 // device arrays of the operator, the state workspace included, are one
 // allocation; the inverse permutation is in the context's scratch.  Build, two FP64
@@ -845,7 +839,7 @@ int create_op(rbffd_ctx ctx, int nsurf, const rbffd_op_surface* surf, rbffd_op* 
     int32_t* iperm = (int32_t*)((char*)ctx->scratch + 256);
     rbffd_op op = new (std::nothrow) rbffd_op_s();
     if (!op) return set_error(ctx, RBFFD_E_NOMEM, "host allocation failed");
-    op->ctx = op->home = ctx;
+    op->ctx = ctx;
     op->spare = ctx->spare;
     {
         std::lock_guard<std::mutex> lock(op->spare->mu);
@@ -954,17 +948,22 @@ extern "C" int rbffd_op_create_batched(rbffd_ctx ctx, int32_t nsurf, const rbffd
     return create_op(ctx, nsurf, surf, out);
 }
 
+// The whole device is waited for, as by the hipFree of memory that is not kept:
+// the operator may have been used on other contexts' streams, or recorded in a
+// graph that the caller launched on a stream of its own.
 extern "C" int rbffd_op_destroy(rbffd_op op) {
     if (!op) return RBFFD_E_ARG;
-    if (op->ctx) (void)hipStreamSynchronize(op->ctx->stream);
+    int dev = op->spare->device;
+    (void)hipGetDevice(&dev);
+    if (dev != op->spare->device) (void)hipSetDevice(op->spare->device);
+    const bool idle = hipDeviceSynchronize() == hipSuccess;
     reset_graph(op);
     reset_kgraph(op);
-    // kept blocks have waited for the context's stream; hipFree itself waits for
-    // the whole device, which an operator used on other streams needs
     const SpareMemory::Block blocks[2] = {op->slab, SpareMemory::Block{}};
-    spare_give(op->spare, blocks, !op->roamed);
+    spare_give(op->spare, blocks, idle);
     if (op->impl) (void)hipFree(op->impl);
     if (op->nonfinite_host) (void)hipHostFree(op->nonfinite_host);
+    if (dev != op->spare->device) (void)hipSetDevice(dev);
     spare_leave(op->spare, false);
     delete op;
     return RBFFD_OK;
@@ -1033,7 +1032,6 @@ extern "C" int rbffd_apply_noalloc(rbffd_ctx ctx, rbffd_op op, int32_t prec, con
         if (ctx->device >= 0 && ctx->device < MAX_DEVICES) base = g_scratch_ptr[ctx->device];
     }
     if (!base) return set_error(ctx, RBFFD_E_HIP, "no scratch address for device %d", ctx->device);
-    if (ctx != op->home) op->roamed = true;
     hipStream_t st = ctx->stream;
     const dim3 g((unsigned)((P + BLK - 1) / BLK)), b(BLK);
     StageArgs a = stage_args(op, prec == RBFFD_F64);
@@ -1057,7 +1055,7 @@ extern "C" int rbffd_apply_noalloc(rbffd_ctx ctx, rbffd_op op, int32_t prec, con
 extern "C" int rbffd_apply(rbffd_ctx ctx, rbffd_op op, int32_t prec, const double* u, double* Lu) {
     if (!ctx || !op || !u || !Lu) return set_error(ctx, RBFFD_E_ARG, "null argument");
     if (prec != RBFFD_F64 && prec != RBFFD_F32) return set_error(ctx, RBFFD_E_ARG, "prec must be F64 or F32");
-    use_on(op, ctx);
+    op->ctx = ctx;
     hipStream_t st = ctx->stream;
     const int64_t N = op->N, P = op->P;
     const dim3 g((unsigned)((P + BLK - 1) / BLK)), b(BLK);
@@ -1096,7 +1094,7 @@ int step_impl(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, double* state, int32
     if (graph_steps < 0) return set_error(ctx, RBFFD_E_ARG, "graph_steps must be >= 0");
     if (forcing && !(std::isfinite(t0) && std::isfinite(lam)))
         return set_error(ctx, RBFFD_E_ARG, "t0 and lambda must be finite");
-    use_on(op, ctx);
+    op->ctx = ctx;
     int rc = ensure_flag(op);
     if (rc) return rc;
     hipStream_t st = ctx->stream;
@@ -1761,7 +1759,7 @@ extern "C" int rbffd_step_imex(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, dou
     if (!(tol > 0.0) || maxit < 1) return set_error(ctx, RBFFD_E_ARG, "tol must be > 0 and maxit >= 1");
     if (forcing && !(std::isfinite(t0) && std::isfinite(lambda)))
         return set_error(ctx, RBFFD_E_ARG, "t0 and lambda must be finite");
-    use_on(op, ctx);
+    op->ctx = ctx;
     const int64_t N = op->N, P = op->P;
     const int S = nspecies;
     const bool react = reaction != RBFFD_REACT_NONE;

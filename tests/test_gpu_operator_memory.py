@@ -54,3 +54,49 @@ def test_several_alive(lib):
             op.close()
         ops = []
     ctx.close()
+
+
+def test_on_another_context(lib):
+    """An operator applied on a second context's stream, destroyed and followed
+    by one in its memory while that stream may still be busy."""
+    a, b = lib.Context(), lib.Context()
+    p, q = problem(200000, 31, 1), problem(200000, 31, 2)
+    for turn in range(3):
+        op = lib.Operator(p[0], p[1], ctx=a)
+        op.ctx = b
+        outs = [op.apply(p[2]) for _ in range(20)]
+        op.close()
+        op = lib.Operator(q[0], q[1], ctx=a)
+        check(op, q)
+        assert all(torch.equal(o, outs[0]) for o in outs)
+        assert np.all(np.abs(outs[0].cpu().numpy() - p[3]) <= 62 * 2.0 ** -53 * p[4])
+        op.close()
+    a.close()
+    b.close()
+
+
+def test_recorded_application_outlives_nothing(lib):
+    """A graph of applications launched on a stream the library does not know:
+    destroying the operator waits for it before the memory serves another."""
+    ctx = lib.Context()
+    p, q = problem(200000, 31, 3), problem(200000, 31, 4)
+    side = torch.cuda.Stream()
+    for turn in range(3):
+        op = lib.Operator(p[0], p[1], ctx=ctx)
+        out = torch.zeros_like(p[2])
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=ctx.stream):
+            for _ in range(60):
+                rc = ctx.lib.rbffd_apply_noalloc(ctx.h, op.h, 0, ctypes.c_void_p(p[2].data_ptr()),
+                                                 ctypes.c_void_p(out.data_ptr()))
+                assert rc == 0
+        with torch.cuda.stream(side):
+            g.replay()
+        op.close()
+        op = lib.Operator(q[0], q[1], ctx=ctx)
+        check(op, q)
+        torch.cuda.synchronize()
+        assert np.all(np.abs(out.cpu().numpy() - p[3]) <= 62 * 2.0 ** -53 * p[4])
+        op.close()
+    ctx.close()
