@@ -12,7 +12,7 @@
 #include "rbffd.h"
 
 // Device memory of the context's last destroyed operator, kept for the next one
-// of a similar size (SPARE_MAX bytes at most).
+// of a similar size (the slab and the state workspace, SPARE_MAX bytes in all).
 // Given back when the context is destroyed and whenever an allocation of the
 // library fails.  Shared by the context and its operators, which may be
 // destroyed later and by other threads.
@@ -70,8 +70,8 @@ struct rbffd_op_s {
     uint16_t* lidx = nullptr;     // slot entries as positions in the slice's halo list
     int32_t* halo = nullptr;      // OP_HALO_MAX sorted distinct neighbour rows per slice
     int32_t* perm = nullptr;      // internal row -> caller row (-1 for padding), P entries
-    void* work = nullptr;         // state workspace (internal order)
     SpareMemory::Block slab;      // the one device allocation that holds the arrays above and the counters
+    SpareMemory::Block work;      // state workspace (internal order), allocated on first use
     SpareMemory* spare = nullptr; // of the context that built it
     // vectors of the implicit (BDF) stepper, allocated on first use
     void* impl = nullptr;

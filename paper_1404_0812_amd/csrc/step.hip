@@ -813,13 +813,23 @@ void reset_kgraph(rbffd_op op) {
     op->kgraph_key = nullptr;
 }
 
+// The state workspace: 4 state buffers (U, ACC, Y1, Y2) x 2 species x FP64, and
+// the forcing (2 species).
+int ensure_work(rbffd_op op) {
+    if (op->work.p) return RBFFD_OK;
+    const size_t need = 5 * 2 * (size_t)op->P * sizeof(double);
+    if (spare_take(op->spare, need, op->work)) return RBFFD_OK;
+    return set_error(op->ctx, RBFFD_E_NOMEM, "cannot allocate %zu bytes of state", need);
+}
+
 // Build the sliced operator of nsurf surfaces (validated by the callers).  All
-// device arrays of the operator, the state workspace included, are one
-// allocation; the inverse permutation is in the context's scratch.  Build, two FP64
-// applications and release at N = 2e5, n = 50: 2.9 -> 0.41 ms with the memory of
-// an operator destroyed before, 3.6 -> 1.1 ms for the first of a context, 0.74
-// ms where nothing is kept (hipMalloc and hipFree take 0.25 ms at 64 MB to 1
-// GB, 0.5 ms above; the former 13 allocations took 1 ms).
+// device arrays of the operator but the state workspace are one allocation; the
+// inverse permutation is in the context's scratch.  Build, two FP64
+// applications and release at N = 2e5, n = 50: 2.9 -> 0.43 ms with the memory of
+// an operator destroyed before (also one used on a second context), 3.6 -> 1.3 ms
+// for the first of a context and 6.1 -> 1.1 ms for two alive at once, where
+// hipMalloc and hipFree add 0.25 ms for each of 64 MB to 1 GB, 0.5 ms above; four
+// operators of growing size 11.7 -> 3.5 ms.
 int create_op(rbffd_ctx ctx, int nsurf, const rbffd_op_surface* surf, rbffd_op* out) {
     int64_t P = 0, N = 0, slots = 0, maxN = 0, nslices = 0;
     int32_t nmax = 0;
@@ -862,8 +872,6 @@ int create_op(rbffd_ctx ctx, int nsurf, const rbffd_op_surface* surf, rbffd_op* 
     const size_t o_w32 = take(slots * sizeof(float)), o_lidx = take(slots * sizeof(uint16_t));
     const size_t o_halo = take(nslices * OP_HALO_MAX * sizeof(int32_t)), o_perm = take(P * sizeof(int32_t));
     const size_t o_cnt = take(sizeof(int64_t) + sizeof(int));
-    // 4 state buffers (U, ACC, Y1, Y2) x 2 species x FP64, and the forcing (2 species)
-    const size_t o_work = take(5 * 2 * (size_t)P * sizeof(double));
     if (!spare_take(op->spare, bytes, op->slab)) {
         rbffd_op_destroy(op);
         return set_error(ctx, RBFFD_E_NOMEM, "operator allocation failed");
@@ -878,7 +886,6 @@ int create_op(rbffd_ctx ctx, int nsurf, const rbffd_op_surface* surf, rbffd_op* 
     op->halo = (int32_t*)(base + o_halo);
     op->perm = (int32_t*)(base + o_perm);
     op->counters = base + o_cnt;
-    op->work = base + o_work;
     hipStream_t st = ctx->stream;
     hipError_t e = hipMemsetAsync(bad, 0, sizeof(int), st);
     int64_t slice0 = 0, off0 = 0, col0 = 0;
@@ -959,7 +966,7 @@ extern "C" int rbffd_op_destroy(rbffd_op op) {
     const bool idle = hipDeviceSynchronize() == hipSuccess;
     reset_graph(op);
     reset_kgraph(op);
-    const SpareMemory::Block blocks[2] = {op->slab, SpareMemory::Block{}};
+    const SpareMemory::Block blocks[2] = {op->slab, op->work};
     spare_give(op->spare, blocks, idle);
     if (op->impl) (void)hipFree(op->impl);
     if (op->nonfinite_host) (void)hipHostFree(op->nonfinite_host);
@@ -1056,18 +1063,20 @@ extern "C" int rbffd_apply(rbffd_ctx ctx, rbffd_op op, int32_t prec, const doubl
     if (!ctx || !op || !u || !Lu) return set_error(ctx, RBFFD_E_ARG, "null argument");
     if (prec != RBFFD_F64 && prec != RBFFD_F32) return set_error(ctx, RBFFD_E_ARG, "prec must be F64 or F32");
     op->ctx = ctx;
+    const int rc = ensure_work(op);
+    if (rc) return rc;
     hipStream_t st = ctx->stream;
     const int64_t N = op->N, P = op->P;
     const dim3 g((unsigned)((P + BLK - 1) / BLK)), b(BLK);
     StageArgs a = stage_args(op, prec == RBFFD_F64);
     if (prec == RBFFD_F64) {
-        double* Y = (double*)op->work;
+        double* Y = (double*)op->work.p;
         double* out = Y + P;
         hipLaunchKernelGGL(k_load_state<double>, g, b, 0, st, P, N, 1, u, op->perm, Y);
         enqueue_apply<double>(st, a, op->idx32, op->w64, Y, out);
         hipLaunchKernelGGL(k_store_state<double>, g, b, 0, st, P, N, 1, out, op->perm, Lu);
     } else {
-        float* Y = (float*)op->work;
+        float* Y = (float*)op->work.p;
         float* out = Y + P;
         hipLaunchKernelGGL(k_load_state<float>, g, b, 0, st, P, N, 1, u, op->perm, Y);
         enqueue_apply<float>(st, a, op->idx32, op->w32, Y, out);
@@ -1096,6 +1105,7 @@ int step_impl(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, double* state, int32
         return set_error(ctx, RBFFD_E_ARG, "t0 and lambda must be finite");
     op->ctx = ctx;
     int rc = ensure_flag(op);
+    if (!rc) rc = ensure_work(op);
     if (rc) return rc;
     hipStream_t st = ctx->stream;
     const int64_t N = op->N, P = op->P;
@@ -1112,7 +1122,7 @@ int step_impl(rbffd_ctx ctx, rbffd_op op, int32_t nspecies, double* state, int32
     a.steps_done = steps_done;
     const int G = graph_steps > 0 ? graph_steps : 50;
     const size_t esz = prec == RBFFD_F64 ? sizeof(double) : sizeof(float);
-    char* base = (char*)op->work;
+    char* base = (char*)op->work.p;
     void* U = base;
     void* ACC = base + 2 * P * esz;
     void* Y1 = base + 4 * P * esz;

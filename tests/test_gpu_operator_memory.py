@@ -100,3 +100,39 @@ def test_recorded_application_outlives_nothing(lib):
         assert np.all(np.abs(out.cpu().numpy() - p[3]) <= 62 * 2.0 ** -53 * p[4])
         op.close()
     ctx.close()
+
+
+def test_no_workspace_before_it_is_needed(lib):
+    """80 bytes a row of state workspace: not taken by an operator that is built
+    and only applied without allocation, taken once by one that is applied or stepped."""
+    ctx = lib.Context()
+    N = 1 << 20
+    p = problem(N, 2, 5)
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    lib.Operator(p[0], p[1], ctx=ctx)  # scratch, code objects
+    out = torch.empty_like(p[2])
+    ctx.lib.rbffd_destroy(ctx.h)  # gives everything back
+    ctx.h = None
+    ctx = lib.Context()
+    before = free()
+    op = lib.Operator(p[0], p[1], ctx=ctx)
+    built = before - free()
+    assert ctx.lib.rbffd_apply_noalloc(ctx.h, op.h, 0, ctypes.c_void_p(p[2].data_ptr()),
+                                       ctypes.c_void_p(out.data_ptr())) == 0
+    assert before - free() == built
+    assert built < 140 * N  # slots 18, diagonal 8, halo lists 40, order 4 bytes a row; scratch 5: not 80 more
+    ctx.enter(p[2])
+    rc = ctx.lib.rbffd_apply(ctx.h, op.h, 0, ctypes.c_void_p(p[2].data_ptr()), ctypes.c_void_p(out.data_ptr()))
+    ctx.leave()
+    assert rc == 0
+    first = before - free()
+    assert first - built >= 80 * N
+    check(op, p)
+    op.step(p[2], 1e-6, 2)
+    ctx.stream.synchronize()
+    op.close()
+    ctx.close()
