@@ -1678,13 +1678,18 @@ __device__ __forceinline__ void process_stencil(const Job& J, int64_t s, Shared<
     } else {
         // m differs between the halves only where one of them dropped a border
         // column: then they run one after the other, so that m bounds the
-        // loops as a scalar.  The loop runs on the mask of the lanes left, a
-        // scalar: a loop on a lane's own flag gets merged into one pass.
+        // loops as a scalar.  What is left and whose turn it is are scalar
+        // masks, formed before the first pass: a loop on a lane's own flag
+        // gets merged into one pass, and a value kept in a vector register
+        // across the passes may come back wrong (the compiler reloads such a
+        // spilled value where the branches meet, before it restores the mask
+        // of active lanes, and with none active nothing is read).
         const int m = S.m;
-        for (uint64_t left = __ballot(true); left;) {
-            const int mu = __builtin_amdgcn_readlane(m, __builtin_ctzll(left));
-            if (m == mu) solve_stencil<K, MM>(J, s, S, t, G);
-            left &= ~__ballot(m == mu);
+        uint64_t left = __ballot(true);
+        const uint64_t first = __ballot(m == __builtin_amdgcn_readlane(m, __builtin_ctzll(left)));
+        for (uint64_t turn = first; left; turn = left) {
+            if (__builtin_amdgcn_inverse_ballot_w64(turn)) solve_stencil<K, MM>(J, s, S, t, G);
+            left &= ~turn;
         }
     }
 }

@@ -40,8 +40,13 @@ inline int tiling(const WOpts& o) {
     const int m = o.n + border_cols(o.degree);
     return m <= 32 ? 32 : (m <= 48 ? 48 : (m <= 64 ? 64 : 128));
 }
-// The persistent launches have no half-wavefront form (its first run ended
-// with a GPU fault whose cause was not found): m <= 32 runs there as m <= 48.
+// The persistent launches have no half-wavefront form: m <= 32 runs there as
+// m <= 48.  The halves leave a loop over an item's stencils at different turns,
+// so its counter is a vector register, live across the whole of
+// process_stencil, and spilled; the compiler reloaded it where branches meet,
+// ahead of the instruction that restores the mask of active lanes.  With no
+// lane active there nothing was reloaded, and the loop went on from whatever
+// the register held, to stencils that do not exist (a GPU fault).
 inline int batch_tiling(const WOpts& o) { return tiling(o) < 48 ? 48 : tiling(o); }
 
 }  // namespace rbw
