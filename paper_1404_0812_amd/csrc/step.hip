@@ -1746,9 +1746,11 @@ int ensure_impl(rbffd_op op, size_t bytes) {
     if (device_alloc(op->spare, &op->impl, bytes) != hipSuccess) {
         return set_error(op->ctx, RBFFD_E_NOMEM, "cannot allocate %zu bytes for the implicit stepper", bytes);
     }
+    // Left as it comes: every vector and partial sum is written in full before it
+    // is read.  Padding rows of the reaction terms hold R(0, 0), which need not be
+    // zero; the solver kernels write them as zero in every vector of a solve and
+    // take nothing else from them (rp.live).
     op->impl_bytes = bytes;
-    // every vector starts at zero (padding rows are never written again)
-    HIP_TRY(op->ctx, hipMemsetAsync(op->impl, 0, bytes, op->ctx->stream));
     return RBFFD_OK;
 }
 
