@@ -1074,27 +1074,23 @@ __device__ __forceinline__ void tri_solve(const Shared<MM>& S, double* b) {
     }
 }
 
-// y <- Q^T y (FWD) or y <- Q y, for NV = 1 or 3 vectors (thread holds component
-// t.c).  The reflector v_k is register row k (one wave) or is published through
-// LDS by the row block that holds row k (four waves).
+// Four waves: y <- Q^T y (FWD) or y <- Q y, for NV = 1 or 3 vectors (thread holds
+// component t.c).  The reflector v_k is published through LDS by the row block
+// that holds row k.
 template <int MM, int NV, bool FWD>
 __device__ __forceinline__ void apply_q(const double (&a)[Lay<MM>::R], Shared<MM>& S, const Tid& t, double (&y)[3]) {
+    static_assert(MM > 64, "four-wave tiling only");
     const int m = stencil_m<MM>(S);
     #pragma unroll
     for (int kk = 0; kk < MM - 2; ++kk) {
         const int k = FWD ? kk : MM - 3 - kk;  // a compile-time constant after unrolling
         if (k < m - 2) {
-            double v;
-            if constexpr (MM <= 64) {
-                v = a[k];
-            } else {
-                if (t.rb == k / 64) S.g.vb[t.c] = a[k % 64];
-                bsync<MM>();
-                v = S.g.vb[t.c];
-            }
+            if (t.rb == k / 64) S.g.vb[t.c] = a[k % 64];
+            bsync<MM>();
+            const double v = S.g.vb[t.c];
             if constexpr (NV == 3) {
                 double s0 = v * y[0], s1 = v * y[1], s2 = v * y[2];
-                sum_cols3<MM>(s0, s1, s2, S, t);  // ends with a barrier with four waves
+                sum_cols3<MM>(s0, s1, s2, S, t);  // ends with a barrier
                 const double ta = S.tau[k];
                 y[0] = fma(-ta * s0, v, y[0]);
                 y[1] = fma(-ta * s1, v, y[1]);
