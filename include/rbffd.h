@@ -200,7 +200,9 @@ typedef struct {
 typedef struct {
     int32_t stencils_per_item; /* stencils taken per counter increment, 1..4096 */
     int32_t groups_per_cu;     /* persistent workgroups (four wavefronts) per compute unit, 1 or 2 */
-    int32_t order;             /* 0: surfaces by decreasing n, ties as given; 1: as given */
+    int32_t order;             /* 0: surfaces by decreasing n, ties as given; 1: as given
+                                  (among the surfaces of one register tiling: tilings are
+                                  separate launches, the largest first) */
     int32_t reserved;
     double us_per_stencil;     /* set by rbffd_autotune_batched: measured time per sampled stencil */
 } rbffd_batch_tuning;
