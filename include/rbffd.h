@@ -406,7 +406,9 @@ int rbffd_mlp_features(rbffd_ctx ctx, int64_t N, const double* xyz, const double
 /* y[B] (FP32) = network(feats[B x 128]). */
 int rbffd_mlp_forward(rbffd_ctx ctx, const float* params, int64_t B, const uint16_t* feats, float* y);
 /* Gradient of the mean squared error over all B samples: grad[RBFFD_MLP_PARAMS]
- * (FP32, overwritten) and loss[1] (FP32, overwritten). */
+ * (FP32, overwritten) and loss[1] (FP32, overwritten).  This call and
+ * rbffd_mlp_train take up to 33 MB of the context's scratch (32768 samples at a
+ * time); a call that finds it large enough allocates nothing. */
 int rbffd_mlp_grad(rbffd_ctx ctx, const float* params, int64_t B, const uint16_t* feats, const float* target,
                    float* grad, float* loss);
 /* Adam training on (feats, target) pairs (count samples); params, adam_m and
