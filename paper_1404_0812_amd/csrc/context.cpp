@@ -26,18 +26,16 @@ void free_blocks(SpareMemory::Block (&b)[2]) {
 }  // namespace
 
 hipError_t device_alloc(SpareMemory* spare, void** p, size_t bytes) {
-    *p = nullptr;
-    hipError_t e = hipMalloc(p, bytes);
-    if (e == hipSuccess) return e;
-    {
+    for (;;) {
+        *p = nullptr;
+        const hipError_t e = hipMalloc(p, bytes);
+        if (e == hipSuccess) return e;
+        *p = nullptr;
+        (void)hipGetLastError();  // not for the next call to find
         std::lock_guard<std::mutex> lock(spare->mu);
         if (!spare->block[0].p && !spare->block[1].p) return e;
-        (void)hipGetLastError();
         free_blocks(spare->block);
     }
-    e = hipMalloc(p, bytes);
-    if (e != hipSuccess) *p = nullptr;
-    return e;
 }
 
 bool spare_take(SpareMemory* spare, size_t bytes, SpareMemory::Block& out) {

@@ -21,9 +21,10 @@ SOURCE = r"""
 static std::map<void*, size_t> held;
 static size_t capacity = 1000, used = 0;
 static int waits = 0;
+static hipError_t last = hipSuccess;
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
-    if (used + n > capacity) return hipErrorOutOfMemory;
+    if (used + n > capacity) return last = hipErrorOutOfMemory;
     *p = std::malloc(1);
     held[*p] = n;
     used += n;
@@ -36,7 +37,11 @@ hipError_t hipFree(void* p) {
     std::free(p);
     return hipSuccess;
 }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() {
+    const hipError_t e = last;
+    last = hipSuccess;
+    return e;
+}
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { ++waits; return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "?"; }
@@ -67,6 +72,7 @@ int main() {
     CHECK(hipFree(big) == hipSuccess);
     void* much = &ctx;
     CHECK(device_alloc(sp, &much, 1001) != hipSuccess && much == nullptr);
+    CHECK(last == hipSuccess);  // a failure that was reported is not left for the next call
     // scratch: 4/3 of a megabyte at least
     capacity = (size_t)3 << 20;
     Block d;
@@ -74,7 +80,7 @@ int main() {
     spare_give(sp, {d, c}, true);
     CHECK(ensure_scratch(ctx, (size_t)1 << 20) == RBFFD_OK);
     CHECK(ensure_scratch(ctx, (size_t)1 << 20) == RBFFD_OK);
-    CHECK(ensure_scratch(ctx, (size_t)3 << 20) == RBFFD_E_NOMEM);
+    CHECK(ensure_scratch(ctx, (size_t)3 << 20) == RBFFD_E_NOMEM && last == hipSuccess);
     CHECK(used == 0 && ensure_scratch(ctx, 1) == RBFFD_OK);
     // the next operator's blocks replace the kept ones; none at all replace nothing
     capacity = (size_t)8 << 30;
