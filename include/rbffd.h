@@ -289,6 +289,8 @@ int rbffd_op_stats(rbffd_op op, int64_t* nslices, int64_t* halo_slices, int64_t*
 /*
  * One operator application Lu = L_X u (caller order, FP64 in and out),
  * computed in FP64 (plain form sum_j w_ij u_j) or FP32 (difference form).
+ * The operator's state workspace is allocated by the first call that needs it
+ * (this one or a stepper), so that call cannot be under graph capture.
  */
 int rbffd_apply(rbffd_ctx ctx, rbffd_op op, int32_t prec, const double* u, double* Lu);
 
